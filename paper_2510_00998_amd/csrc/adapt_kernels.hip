@@ -58,7 +58,7 @@ __global__ __launch_bounds__(REMAP_THREADS) void k_remap(T* tr, long long tstrid
   for (int e = tid; e < (m + 1) * TL; e += REMAP_THREADS) {
     const int j = e / TL, o = e % TL;
     const size_t slot = j < m ? (size_t)(fB ^ 1) * ncell + row[2 + j] : (size_t)fB * ncell + B;
-    sSrc[e] = (C)t[slot * TL + o];
+    sSrc[j * TL + (o & 1) * L + (o >> 1)] = (C)t[slot * TL + o];  // pairs (g, q) -> [g | q]
   }
   for (int e = tid; e < 2 * r * NN; e += REMAP_THREADS) sMat[e] = mort[e];
   __syncthreads();
@@ -69,7 +69,7 @@ __global__ __launch_bounds__(REMAP_THREADS) void k_remap(T* tr, long long tstrid
   if constexpr (D == 2) {
     // fine slot j: I_j g_B; coarse slot: sum_j P_j g_j
     for (int e = tid; e < (m + 1) * TL; e += REMAP_THREADS) {
-      const int j = e / TL, o = e % TL, f = o / L, a = o % L;
+      const int j = e / TL, o = e % TL, f = o & 1, a = o >> 1;
       C acc = 0;
       if (j < m) {
         const C* src = sSrc + m * TL + f * L;
@@ -104,7 +104,7 @@ __global__ __launch_bounds__(REMAP_THREADS) void k_remap(T* tr, long long tstrid
     // second axis: fine slot j = (sa, sb): sum_y I_sb[b][y] tmp[sa][f][a][y];
     // coarse slot: sum_s sum_y P_{sb(s)}[b][y] tmp[r + s][f][a][y]
     for (int e = tid; e < (m + 1) * TL; e += REMAP_THREADS) {
-      const int j = e / TL, o = e % TL, f = o / L, l = o % L, a = l % N, b = l / N;
+      const int j = e / TL, o = e % TL, f = o & 1, l = o >> 1, a = l % N, b = l / N;
       C acc = 0;
       if (j < m) {
         const int sa = j % r, sb = j / r;

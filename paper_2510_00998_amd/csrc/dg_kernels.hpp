@@ -67,12 +67,19 @@ using DGShape = DGShapeV<D, N, 0>;
 //   [N^2+N, N^2+2N)     ep1: same at x=1
 //   [N^2+2N, N^2+3N)    ev0: value functional at x=0 (used with gl)
 //   [N^2+3N, N^2+4N)    ev1: value functional at x=1
-//   [N^2+4N, ...)       E: interpolation to the fine nodes from the next
+//   [N^2+4N, N^2+5N)    al0: lift of a neighbour's normal derivative q' across
+//                       the facet at x=0, nodal (see nodal_lifts); mirrored at x=1
+//   [N^2+5N, N^2+6N)    be0: the same of its value g'
+//   then four compact even-odd tables (EO<N>::SIZE each): Mhat, Mhat^-1, and
+//   for constant kappa S and Si^T of the interior class
+//   [E, ...)            interpolation to the fine nodes from the next
 //                       coarser nodes, E[a*NC + j] (only when NC > 0)
 template <int N>
 struct RefOff {
+  static constexpr int Q = ((N + 1) / 2) * ((N + 1) / 2) + (N / 2) * (N / 2);
   static constexpr int M = 0, EP0 = N * N, EP1 = N * N + N, EV0 = N * N + 2 * N, EV1 = N * N + 3 * N,
-                       E = N * N + 4 * N;
+                       AL0 = N * N + 4 * N, BE0 = N * N + 5 * N, MC = N * N + 6 * N, MIC = MC + Q, SC = MC + 2 * Q,
+                       SIC = MC + 3 * Q, E = MC + 4 * Q;
 };
 
 // Storage type T of the cell vectors and traces, compute type CT<T> of the

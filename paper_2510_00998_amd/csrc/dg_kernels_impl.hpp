@@ -1,17 +1,23 @@
 // Kernel bodies for dg_kernels.hpp (included by the per-instantiation .hip
 // files).  See dg_kernels.hpp for the mathematics.
 //
-// Block structure of the fused sweep (3D, constant kappa):
-//   P1  u, b lines -> registers; neighbour traces -> flux fields, first
-//       tangential transform fused into the load -> LDS
-//   P2  second tangential transform of the flux fields
-//   P3..P5 forward transforms along x, y, z (lifts subtracted per axis),
-//       diagonal scaling, first inverse transform
-//   P6, P7 inverse transforms along y, x; update, store of u and of the
-//       x-facet traces straight from registers
-//   P8  y- and z-facet traces from the updated cell in LDS
-// Seven barriers; the facet traces are written by each cell for its own
-// interior facets and read once by the neighbour in the next sweep.
+// Every thread owns the line of a cell along the last axis (z in 3D): its
+// global loads and stores of u, b and the traces are consecutive across
+// lanes.  The lifts of all facets are added where the state holds nodal
+// values along every axis (b multiplied by Mhat^-1 along each axis), where a
+// facet field needs no tangential transform (see nodal_lifts).  Steps of the
+// fused sweep, one barrier after each (3D):
+//   z  u, b lines and the neighbour traces -> registers; traces -> LDS;
+//      Mhat^-1 b along z
+//   y  Mhat^-1
+//   x  Mhat^-1, minus the lifts of all facets, Si = S^T Mhat
+//   z  Si
+//   y  Si, division by the eigenvalue sums, S
+//   x  S
+//   z  S, update, store of u and of the z-facet traces
+//   x, y facet traces from the updated cell in LDS
+// The facet traces are written by each cell for its own interior facets and
+// read once by the neighbour in the next sweep.
 #pragma once
 #include <type_traits>
 
@@ -77,20 +83,21 @@ __device__ __forceinline__ void mv(P G, const T (&in)[N], T (&out)[N]) {
   }
 }
 
-// Even-odd forms of the products with the interior-class matrices, whose
-// columns (S) or rows (Si = S^T Mhat) are mirror-even for the first
-// (N+1)/2 and mirror-odd for the last N/2 indices: entry A(i, c) is G[i N + c]
-// (S) or G[c N + i] (SI, i.e. Si accessed transposed), and
-// A(N-1-i, c) = +-A(i, c).  Forward: out[c] = sum_i A(i, c) in[i], from the
-// mirror sums and differences of in.  Inverse: out[i] = sum_c A(i, c) in[c],
-// as even part +- odd part.  About half the multiply-adds of mv.
-template <int N, bool SI, typename T, typename P>
-__device__ __forceinline__ T eo_at(P G, int i, int c) {
-  return SI ? G[c * N + i] : G[i * N + c];
-}
-template <int N, bool SI, typename T, typename P>
-__device__ __forceinline__ void mv_fwd_eo(P G, const T (&in)[N], T (&out)[N]) {
-  constexpr int H = N / 2, NE = (N + 1) / 2;
+// Even-odd products with matrices of mirror symmetry, from compact tables
+// (EO<N>::SIZE entries, fetched with scalar loads): about half the
+// multiply-adds and half the scalar registers of mv.
+//
+// S of the interior class holds mirror-even columns c < NE, then mirror-odd
+// ones: table [i][c] = S(i, c) for i, c < NE, then [i][c] = S(i, NE + c) for
+// i, c < H.  eo_fwd: out = S^T in (with the table of Si^T: out = Si in);
+// eo_inv: out = S in.
+template <int N>
+struct EO {
+  static constexpr int H = N / 2, NE = (N + 1) / 2, SIZE = NE * NE + H * H;
+};
+template <int N, typename T, typename P>
+__device__ __forceinline__ void eo_fwd(P G, const T (&in)[N], T (&out)[N]) {
+  constexpr int H = EO<N>::H, NE = EO<N>::NE;
   T e[H], o[H];
 #pragma unroll
   for (int i = 0; i < H; ++i) {
@@ -99,39 +106,70 @@ __device__ __forceinline__ void mv_fwd_eo(P G, const T (&in)[N], T (&out)[N]) {
   }
 #pragma unroll
   for (int c = 0; c < NE; ++c) {
-    T s = (N & 1) ? eo_at<N, SI, T>(G, H, c) * in[H] : T(0);
+    T s = (N & 1) ? G[H * NE + c] * in[H] : T(0);
 #pragma unroll
-    for (int i = 0; i < H; ++i) s += eo_at<N, SI, T>(G, i, c) * e[i];
+    for (int i = 0; i < H; ++i) s += G[i * NE + c] * e[i];
     out[c] = s;
   }
 #pragma unroll
-  for (int c = NE; c < N; ++c) {
+  for (int c = 0; c < H; ++c) {
     T s = 0;
 #pragma unroll
-    for (int i = 0; i < H; ++i) s += eo_at<N, SI, T>(G, i, c) * o[i];
-    out[c] = s;
+    for (int i = 0; i < H; ++i) s += G[NE * NE + i * H + c] * o[i];
+    out[NE + c] = s;
   }
 }
-template <int N, bool SI, typename T, typename P>
-__device__ __forceinline__ void mv_inv_eo(P G, const T (&in)[N], T (&out)[N]) {
-  constexpr int H = N / 2, NE = (N + 1) / 2;
-  T ev[NE], od[H > 0 ? H : 1];
+template <int N, typename T, typename P>
+__device__ __forceinline__ void eo_inv(P G, const T (&in)[N], T (&out)[N]) {
+  constexpr int H = EO<N>::H, NE = EO<N>::NE;
+  T ev[NE], od[H];
 #pragma unroll
   for (int i = 0; i < NE; ++i) {
     ev[i] = 0;
 #pragma unroll
-    for (int c = 0; c < NE; ++c) ev[i] += eo_at<N, SI, T>(G, i, c) * in[c];
+    for (int c = 0; c < NE; ++c) ev[i] += G[i * NE + c] * in[c];
   }
 #pragma unroll
   for (int i = 0; i < H; ++i) {
     od[i] = 0;
 #pragma unroll
-    for (int c = NE; c < N; ++c) od[i] += eo_at<N, SI, T>(G, i, c) * in[c];
+    for (int c = 0; c < H; ++c) od[i] += G[NE * NE + i * H + c] * in[NE + c];
   }
   // out written in ascending order (as mv does), so that the stores of the
-  // alternative paths of stage_mv coincide index by index
+  // alternative paths of block_mv coincide index by index (no scratch)
 #pragma unroll
-  for (int i = 0; i < N; ++i) out[i] = i < H ? ev[i] + od[i] : (i == H && (N & 1) ? ev[H] : ev[N - 1 - i] - od[N - 1 - i]);
+  for (int i = 0; i < N; ++i)
+    out[i] = i < H ? ev[i] + od[i] : (i == H && (N & 1) ? ev[H] : ev[N - 1 - i] - od[N - 1 - i]);
+}
+// x = G x for a matrix with G(N-1-i, N-1-j) = G(i, j) (Mhat and its inverse):
+// table [i][j] = (G(i, j) + G(i, N-1-j)) / 2 for i, j < NE (G(i, H) in the
+// middle column of odd N), then the halved differences for i, j < H.
+template <int N, typename T, typename P>
+__device__ __forceinline__ void cs_mv(P G, T (&x)[N]) {
+  constexpr int H = EO<N>::H, NE = EO<N>::NE;
+  T e[NE], o[H];
+#pragma unroll
+  for (int i = 0; i < H; ++i) {
+    e[i] = x[i] + x[N - 1 - i];
+    o[i] = x[i] - x[N - 1 - i];
+  }
+  if (N & 1) e[NE - 1] = x[H];
+#pragma unroll
+  for (int i = 0; i < H; ++i) {
+    T ev = 0, od = 0;
+#pragma unroll
+    for (int j = 0; j < NE; ++j) ev += G[i * NE + j] * e[j];
+#pragma unroll
+    for (int j = 0; j < H; ++j) od += G[NE * NE + i * H + j] * o[j];
+    x[i] = ev + od;
+    x[N - 1 - i] = ev - od;
+  }
+  if (N & 1) {
+    T ev = 0;
+#pragma unroll
+    for (int j = 0; j < NE; ++j) ev += G[H * NE + j] * e[j];
+    x[H] = ev;
+  }
 }
 
 template <int D>
@@ -150,16 +188,6 @@ __device__ __forceinline__ double recip(double d) {
 __device__ __forceinline__ float recip(float d) {
   float r = __builtin_amdgcn_rcpf(d);
   return __builtin_fmaf(__builtin_fmaf(-d, r, 1.0f), r, r);
-}
-
-// Load scheme of the neighbour traces in the constant-kappa sweep: every
-// load of a thread issued at once with the first tangential transform fused
-// (facet_pass0_const), except for the 3D FP64 degree-1 and degree-4 sweeps,
-// which measured faster with each (facet, cell) record first copied into LDS
-// as whole 16-byte vectors (the apply kernels always use the fused loads).
-template <typename T, int D, int N>
-constexpr bool sweep_copies_traces() {
-  return D == 3 && sizeof(T) == 8 && (N == 2 || N == 5);
 }
 
 // Thread index within the block's NT working threads; threads beyond NT
@@ -205,12 +233,16 @@ struct EigLDS {
 };
 
 // LDS after the staged eigendata: kappa_F per (cell, facet) (variable
-// kappa; one unused entry otherwise), kappa_K per cell (variable kappa),
-// then the boundary masks of the block's cells (read by the facet passes
-// that follow a barrier).
+// kappa; none otherwise), kappa_K per cell (variable kappa), the lift
+// coefficients AL0 | BE0 (2N), then the boundary masks of the block's cells
+// (matrix-core sweep).
 template <int D, int N, bool VARK>
 constexpr int kappa_lds_entries() {
-  return VARK ? DGShape<D, N>::CPB * (DGShape<D, N>::NF + 1) : 1;
+  return (VARK ? DGShape<D, N>::CPB * (DGShape<D, N>::NF + 1) : 0) + 2 * N;
+}
+template <int D, int N, bool VARK, typename C>
+__device__ __forceinline__ C* lift_lds(C* sKF) {
+  return sKF + kappa_lds_entries<D, N, VARK>() - 2 * N;
 }
 template <int D, int N, bool VARK, typename C>
 __device__ __forceinline__ int* mask_lds(C* sKF) {
@@ -230,7 +262,13 @@ __device__ __forceinline__ void load_eig(const DGArgs<T>& a, int c0, int nc, CT<
   constexpr int NN = N * N;
   const int tid = work_tid<D, N>();
   if constexpr (!VARK) {
-    for (int i = tid; i < n_classes<AD>() * Sh::EGS; i += Sh::NT) sE[i] = a.eig[i];
+    constexpr int NE = n_classes<AD>() * Sh::EGS, IE = (NE + Sh::NT - 1) / Sh::NT;
+    C ev[IE];
+#pragma unroll
+    for (int m = 0; m < IE; ++m) ev[m] = a.eig[min(tid + m * Sh::NT, NE - 1)];
+#pragma unroll
+    for (int m = 0; m < IE; ++m)
+      if (tid + m * Sh::NT < NE) sE[tid + m * Sh::NT] = ev[m];
   } else {
     // every load of the thread is issued before the first LDS store (no
     // load waits on another): eigendata, then kappa of the cell and of its
@@ -551,380 +589,162 @@ __device__ __forceinline__ void make_si(const DGArgs<T>& a, int nc, CT<T>* sE) {
   }
 }
 
-// Matrix of (cell, axis k) at offset `off` within its S | Si | lambda record,
-// applied to a line (TR: transposed).  Constant kappa: when every active
-// lane of the wave needs the same boundary class the record is read from
-// the global class table with scalar loads; otherwise from the LDS copy
-// (LDS = true, after the block staged it) or per lane from global memory.
-template <typename T, int D, int N, bool VARK, bool TR, bool SIM, bool LDS = true, bool AD = false>
-__device__ __forceinline__ void stage_mv(const DGArgs<T>& a, const CT<T>* sE, int cl, int mask, int k,
+// Matrix of (cell, axis k) applied to a line: S^T (OP_ST), Si = S^T Mhat
+// (OP_SI), Si^T (OP_SIT) or S (OP_S) of its S | Si | lambda record.  Constant kappa: when
+// every lane of the wave needs the interior class, the even-odd form from
+// the compact tables; otherwise the record's LDS copy.
+enum BlockOp { OP_ST = 0, OP_SI = 1, OP_S = 2, OP_SIT = 3 };
+template <typename T, int D, int N, bool VARK, bool IVAR, bool AD, int OP>
+__device__ __forceinline__ void block_mv(const DGArgs<T>& a, const CT<T>* sE, int cl, int mask, int k,
                                          const CT<T> (&in)[N], CT<T> (&out)[N]) {
   using C = CT<T>;
   using Sh = DGShape<D, N>;
-  constexpr int off = SIM ? N * N : 0;  // S or Si within the S | Si | lambda record
-  // matrices that fit in about 72 SGPRs take the scalar path
-  constexpr bool SCALAR_OK = N * N * (int)sizeof(C) / 4 <= 72;
+  constexpr bool si = OP == OP_SI || OP == OP_SIT, tr = OP == OP_ST || OP == OP_SIT;
+  constexpr int off = si ? N * N : 0;
   if constexpr (VARK) {
-    mv<N, TR>(sE + (cl * D + k) * Sh::EGS + off, in, out);
+    mv<N, tr>(sE + (cl * D + k) * Sh::EGS + off, in, out);
   } else {
-    const int cls = axis_cls<AD>(mask, k);
-    bool uni = false;
-    int c0 = cls;
-    if constexpr (SCALAR_OK) {
-      c0 = __builtin_amdgcn_readfirstlane(cls);
-      uni = __all(cls == c0);
-    }
-    // interior class in FP32 arithmetic (bound by vector-ALU issue): even-odd
-    // forms; FP64 (bound by memory latency) keeps the plain products
-    if (uni && sizeof(C) == 4 && c0 == 0) {
-      const cptr<C> G = as_const(a.eig) + off;
-      if constexpr (TR != SIM)
-        mv_fwd_eo<N, SIM>(G, in, out);
+    const int cls = IVAR ? 0 : axis_cls<AD>(mask, k);
+    // 2D degree 8 in FP32 keeps the plain product: the fixed point of its
+    // cycle is the rounded operator's (see dual_form)
+    constexpr bool eo = D == 3 || sizeof(C) == 8 || N <= 8;
+    if (eo && (IVAR || __all(cls == 0))) {
+      const cptr<C> G = as_const(a.ref) + (si ? RefOff<N>::SIC : RefOff<N>::SC);
+      if constexpr (OP == OP_S || OP == OP_SIT)
+        eo_inv<N>(G, in, out);
       else
-        mv_inv_eo<N, SIM>(G, in, out);
-    } else if (uni)
-      mv<N, TR>(as_const(a.eig) + c0 * Sh::EGS + off, in, out);
-    else if constexpr (LDS)
-      mv<N, TR>(sE + cls * Sh::EGS + off, in, out);
-    else
-      mv<N, TR>(a.eig + cls * Sh::EGS + off, in, out);
+        eo_fwd<N>(G, in, out);
+    } else {
+      mv<N, tr>(sE + cls * Sh::EGS + off, in, out);
+    }
   }
 }
 
-// Tangential axis of pass `pass` of the facet transform of facets normal to k.
-template <int D>
-__device__ __forceinline__ int tangential(int k, int pass) {
+// Eigenvalue sums of the line along axis k of thread line ln: out[j] =
+// lambda_k[j] + the two (one) tangential eigenvalues.
+template <int D, int N, bool VARK, bool IVAR, bool AD, typename C>
+__device__ __forceinline__ void eig_sums(const C* sE, int cl, int mask, int k, int ln, C (&out)[N]) {
+  using Sh = DGShape<D, N>;
+  constexpr int NN = N * N;
+  auto lam = [&](int m) -> const C* {
+    return sE + (VARK ? cl * D + m : (IVAR ? 0 : axis_cls<AD>(mask, m))) * Sh::EGS + 2 * NN;
+  };
+  C ls;
   if constexpr (D == 2)
-    return 1 - k;
+    ls = lam(1 - k)[ln];
   else
-    return pass == 0 ? ((k == 0) ? 1 : 0) : ((k == 2) ? 1 : 2);
+    ls = lam(k == 0 ? 1 : 0)[ln % N] + lam(k == 2 ? 1 : 2)[ln / N];
+  const C* lk = lam(k);
+#pragma unroll
+  for (int j = 0; j < N; ++j) out[j] = ls + lk[j];
 }
 
-// Facet flux fields.  From the neighbour's traces (g', q') across facet f
-//   F1 = T_f (kappa_F (q'/2 - sigma_hat g')),  F2 = T_f (kappa_F g'/2),
-// T_f = G_t1 x G_t2 over the tangential axes with G_t = Si_t for t < k
-// (axes already transformed when facet k is processed) and Mhat otherwise.
-// sNB[cl][f][F1|F2][L].  Pass 0 reads the neighbour traces (FROM_GLOBAL:
-// straight from the trace buffer, item after item; else from the plain LDS
-// copy) and transforms along t1; pass 1 transforms along t2 (3D).  Work items are
-// ordered (facet, cell, line) so that a wave mostly sees one facet
-// direction and therefore one matrix.
-template <typename T, int D, int N, bool VARK, bool FROM_GLOBAL = false, bool IVAR = false, bool AD = false>
-__device__ __forceinline__ void facet_pass(const DGArgs<T>& a, const T* tr, int c0, int nc, int pass, CT<T>* sNB,
-                                           const CT<T>* sE, const CT<T>* sKF) {
-  using C = CT<T>;
-  using Sh = DGShape<D, N>;
-  constexpr int NN = N * N;
-  constexpr int L = Sh::L;
-  constexpr int TL = 2 * L;
-  constexpr int LINES = (D == 2) ? 1 : N;
-  const cptr<C> Mh = as_const(a.ref) + RefOff<N>::M;
-  for (int i = work_tid<D, N>(); i < Sh::CPB * Sh::NF * LINES; i += Sh::NT) {
-    const int f = i / (Sh::CPB * LINES), rem = i % (Sh::CPB * LINES);
-    const int cl = rem / LINES, li = rem % LINES;
-    if (cl >= nc) continue;
-    const int c = c0 + cl;
-    const int k = f >> 1;
-    const int t = tangential<D>(k, pass);
-    const int st = pass == 0 ? 1 : N;  // node stride along t within the facet
-    const int lo = pass == 0 ? N * li : li;
-    C* g = sNB + (cl * Sh::NF + f) * TL + lo;
-    const int mask = FROM_GLOBAL ? a.bmask[c] : mask_lds<D, N, VARK>(sKF)[cl];
-    const int smask = IVAR ? 0 : mask;  // boundary classes of the block solve
-    C x1[N], x2[N], o1[N], o2[N];
-    if (pass == 0) {
-      const bool bdy = (mask >> f) & 1;
-      if (bdy && !(FROM_GLOBAL && IVAR)) {  // boundary facet: no neighbour, zero flux fields
-#pragma unroll
-        for (int j = 0; j < N; ++j) {
-          g[j] = C(0);
-          g[L + j] = C(0);
-        }
-        continue;
-      }
-      C gv[N], qv[N];
-      if constexpr (FROM_GLOBAL) {
-        const int s = f & 1;
-        const int stc = ipow<D>(a.n, k);
-        if constexpr (IVAR) {
-          // interior-block smoother: a boundary facet reads the cell's own
-          // traces, negated
-          const T* src = bdy ? tr + ((size_t)f * a.ncell + c) * TL + lo
-                             : tr + ((size_t)(f ^ 1) * a.ncell + (s ? c + stc : c - stc)) * TL + lo;
-          const C sg = bdy ? C(-1) : C(1);
-#pragma unroll
-          for (int j = 0; j < N; ++j) {
-            gv[j] = sg * (C)src[j];
-            qv[j] = sg * (C)src[L + j];
-          }
-        } else {
-          const T* src = tr + ((size_t)(f ^ 1) * a.ncell + (s ? c + stc : c - stc)) * TL + lo;
-#pragma unroll
-          for (int j = 0; j < N; ++j) {
-            gv[j] = src[j];
-            qv[j] = src[L + j];
-          }
-        }
-      } else {
-#pragma unroll
-        for (int j = 0; j < N; ++j) {
-          gv[j] = g[j];
-          qv[j] = g[L + j];
-        }
-      }
-      C kf;
-      if constexpr (VARK)
-        kf = sKF[cl * Sh::NF + f];
-      else
-        kf = a.kappa_const;
-#pragma unroll
-      for (int j = 0; j < N; ++j) {
-        x1[j] = kf * (C(0.5) * qv[j] - a.sigma_hat * gv[j]);
-        x2[j] = C(0.5) * kf * gv[j];
-      }
-    } else {
-#pragma unroll
-      for (int j = 0; j < N; ++j) {
-        x1[j] = g[st * j];
-        x2[j] = g[L + st * j];
-      }
-    }
-    if (t < k) {
-      stage_mv<T, D, N, VARK, false, true, !FROM_GLOBAL, AD>(a, sE, cl, smask, t, x1, o1);
-      stage_mv<T, D, N, VARK, false, true, !FROM_GLOBAL, AD>(a, sE, cl, smask, t, x2, o2);
-    } else {
-      mv<N, false>(Mh, x1, o1);
-      mv<N, false>(Mh, x2, o2);
-    }
-#pragma unroll
-    for (int j = 0; j < N; ++j) {
-      g[st * j] = o1[j];
-      g[L + st * j] = o2[j];
-    }
-  }
-}
+// Trace record of a (facet, cell): L pairs (value g, reference outward
+// normal derivative q), one per facet node.
+template <typename T>
+struct alignas(2 * sizeof(T)) TrPair {
+  T g, q;
+};
 
-// Pass 0 for constant kappa with every global load of the thread issued
-// before the first use of any of them: the class tables, the boundary masks
-// of its items' cells and the neighbour traces (neighbour index clamped into
-// the mesh, boundary facets zeroed by a select afterwards), so that the
-// block waits for memory once.  Stages the class tables in sE.  AD
-// (adaptive meshes): the neighbour-side traces of (cell, facet) come from
-// slot nbslot[f ncell + c], and the coarse side of a hanging facet takes
-// the penalty sig_hang.
-template <typename T, int D, int N, bool AD = false>
-__device__ __forceinline__ void facet_pass0_const(const DGArgs<T>& a, const T* tr, int c0, int nc, CT<T>* sNB,
-                                                  CT<T>* sE, int* sMask) {
-  using C = CT<T>;
-  using Sh = DGShape<D, N>;
-  constexpr int NN = N * N;
-  constexpr int L = Sh::L;
-  constexpr int TL = 2 * L;
-  constexpr int LINES = (D == 2) ? 1 : N;
-  constexpr int ITEMS = Sh::CPB * Sh::NF * LINES;
-  constexpr int IT = (ITEMS + Sh::NT - 1) / Sh::NT;
-  constexpr int NE = n_classes<AD>() * Sh::EGS;
-  constexpr int IE = (NE + Sh::NT - 1) / Sh::NT;
-  const int tid = work_tid<D, N>();
-  const cptr<C> Mh = as_const(a.ref) + RefOff<N>::M;
-  C ev[IE];
+// Neighbour-side traces of the 2D facets of cell c at facet node ln.
+// Boundary facets have none: the caller zeroes them (finish_pair).  AD
+// (adaptive meshes): the slot table names the record.  IVAR (interior-block
+// smoother): a boundary facet takes the cell's own traces, negated.
+template <typename T, int D, int N, bool IVAR, bool AD>
+__device__ __forceinline__ void load_pairs(const DGArgs<T>& a, const T* tr, int c, int mask, int ln,
+                                           TrPair<T> (&p)[2 * D]) {
+  constexpr int L = DGShape<D, N>::L;
 #pragma unroll
-  for (int m = 0; m < IE; ++m) {
-    const int i = tid + m * Sh::NT;
-    ev[m] = i < NE ? a.eig[i] : C(0);
-  }
-  // no branches around the loads: an item past the block's work reads the
-  // first word of the trace buffer (one cache line for all such lanes)
-  C gv[IT][N], qv[IT][N];
-  int msk[IT];
-#pragma unroll
-  for (int m = 0; m < IT; ++m) {
-    const int i = tid + m * Sh::NT;
-    const int f = min(i / (Sh::CPB * LINES), Sh::NF - 1), rem = i % (Sh::CPB * LINES);
-    const int cl = rem / LINES, li = rem % LINES;
-    const bool valid = i < ITEMS && cl < nc;
-    const int c = c0 + (valid ? cl : 0);
+  for (int f = 0; f < 2 * D; ++f) {
     size_t slot;
     if constexpr (AD) {
       slot = (size_t)a.nbslot[(size_t)f * a.ncell + c];
     } else {
-      const int stc = ipow<D>(a.n, f >> 1);
-      const int nb = min(max((f & 1) ? c + stc : c - stc, 0), a.ncell - 1);
+      const int st = ipow<D>(a.n, f >> 1);
+      const int nb = min(max((f & 1) ? c + st : c - st, 0), a.ncell - 1);
       slot = (size_t)(f ^ 1) * a.ncell + nb;
+      if (IVAR && ((mask >> f) & 1)) slot = (size_t)f * a.ncell + c;
     }
-    const T* src = valid ? tr + slot * TL + N * li : tr;
-#pragma unroll
-    for (int j = 0; j < N; ++j) {
-      gv[m][j] = src[j];
-      qv[m][j] = src[L + j];
-    }
-    msk[m] = cell_mask<AD>(a, c);
-  }
-  const int cmask = cell_mask<AD>(a, c0 + min(tid, nc - 1));
-  // keep every use of the loaded values below this point, so that the
-  // compiler does not wait for one item's data before issuing the next loads
-  __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-  for (int m = 0; m < IE; ++m) {
-    const int i = tid + m * Sh::NT;
-    if (i < NE) sE[i] = ev[m];
-  }
-  if (tid < nc) sMask[tid] = cmask;
-#pragma unroll
-  for (int m = 0; m < IT; ++m) {
-    const int i = tid + m * Sh::NT;
-    const int f = i / (Sh::CPB * LINES), rem = i % (Sh::CPB * LINES);
-    const int cl = rem / LINES, li = rem % LINES;
-    if (!(i < ITEMS && cl < nc)) continue;
-    const int k = f >> 1;
-    const int t = tangential<D>(k, 0);
-    const bool bdy = (msk[m] >> f) & 1;
-    const C kf = a.kappa_const;
-    C sh = a.sigma_hat;
-    if constexpr (AD) sh = ((msk[m] >> (8 + f)) & 1) ? a.sig_hang : a.sigma_hat;
-    C x1[N], x2[N], o1[N], o2[N];
-#pragma unroll
-    for (int j = 0; j < N; ++j) {
-      const C g = bdy ? C(0) : gv[m][j];
-      const C q = bdy ? C(0) : qv[m][j];
-      x1[j] = kf * (C(0.5) * q - sh * g);
-      x2[j] = C(0.5) * kf * g;
-    }
-    if (t < k) {
-      stage_mv<T, D, N, false, false, true, false, AD>(a, sE, cl, msk[m], t, x1, o1);
-      stage_mv<T, D, N, false, false, true, false, AD>(a, sE, cl, msk[m], t, x2, o2);
-    } else {
-      mv<N, false>(Mh, x1, o1);
-      mv<N, false>(Mh, x2, o2);
-    }
-    C* g = sNB + (cl * Sh::NF + f) * TL + N * li;
-#pragma unroll
-    for (int j = 0; j < N; ++j) {
-      g[j] = o1[j];
-      g[L + j] = o2[j];
-    }
+    p[f] = *reinterpret_cast<const TrPair<T>*>(tr + (slot * L + ln) * 2);
   }
 }
-
-// Plain copy of the neighbour traces into sNB (variable kappa path, whose
-// facet transform needs the staged per-cell eigendata).  The 2L trace
-// entries of a (facet, cell) record are contiguous in the trace buffer and
-// in sNB, so the copy moves whole vectors of VB bytes (16 where the record
-// size allows; trace buffers are 256-byte aligned and each right-hand side
-// column starts at a multiple of the record size).  Item i of the block is
-// (facet f, cell cl, vector v), i = (f CPB + cl) NVEC + v; all loads of a
-// thread are issued before its LDS stores, from neighbour indices clamped
-// into the mesh (boundary facets take zeros).
-template <typename T, int D, int N>
-__device__ __forceinline__ void copy_neighbour_traces(const DGArgs<T>& a, const T* tr, int c0, int nc, CT<T>* sNB) {
+// The pair as the lifts read it: zero (IVAR: negated) on a boundary facet;
+// on the coarse side of a hanging facet, whose penalty is sig_hang,
+// alpha q + beta g with the conforming coefficients needs
+// q - 2 (sig_hang - sigma_hat) g.
+template <typename T, bool IVAR, bool AD>
+__device__ __forceinline__ TrPair<CT<T>> finish_pair(const DGArgs<T>& a, const TrPair<T>& p, int mask, int f) {
   using C = CT<T>;
-  using Sh = DGShape<D, N>;
-  constexpr int TL = 2 * Sh::L;
-  constexpr int RB = TL * (int)sizeof(T);
-  constexpr int VB = RB % 16 == 0 ? 16 : (RB % 8 == 0 ? 8 : (RB % 4 == 0 ? 4 : (int)sizeof(T)));
-  constexpr int VE = VB / (int)sizeof(T);
-  constexpr int NVEC = TL / VE;
-  constexpr int NE = Sh::NF * Sh::CPB * NVEC;
-  constexpr int IT = (NE + Sh::NT - 1) / Sh::NT;
-  struct alignas(VB) Vec {
-    T e[VE];
-  };
-  const int tid = work_tid<D, N>();
-  Vec v[IT];
-#pragma unroll
-  for (int m = 0; m < IT; ++m) {
-    const int i = min(tid + m * Sh::NT, NE - 1);
-    const int r = i / NVEC, e = (i % NVEC) * VE;
-    const int f = r / Sh::CPB, cl = min(r % Sh::CPB, nc - 1);
-    const int c = c0 + cl;
-    const int st = ipow<D>(a.n, f >> 1);
-    const int nb = min(max((f & 1) ? c + st : c - st, 0), a.ncell - 1);
-    const bool bdy = (a.bmask[c] >> f) & 1;
-    v[m] = *reinterpret_cast<const Vec*>(tr + ((size_t)(f ^ 1) * a.ncell + nb) * TL + e);
-    if (bdy) {
-#pragma unroll
-      for (int j = 0; j < VE; ++j) v[m].e[j] = T(0);
-    }
+  const bool bdy = (mask >> f) & 1;
+  TrPair<C> r;
+  r.g = (C)p.g;
+  r.q = (C)p.q;
+  if (bdy) {
+    r.g = IVAR ? -r.g : C(0);
+    r.q = IVAR ? -r.q : C(0);
   }
-#pragma unroll
-  for (int m = 0; m < IT; ++m) {
-    const int i = tid + m * Sh::NT;
-    const int r = i / NVEC, e = (i % NVEC) * VE;
-    const int f = r / Sh::CPB, cl = r % Sh::CPB;
-    if (i < NE && cl < nc) {
-      C* dst = sNB + (cl * Sh::NF + f) * TL + e;
-#pragma unroll
-      for (int j = 0; j < VE; ++j) dst[j] = (C)v[m].e[j];
-    }
+  if constexpr (AD) {
+    if ((mask >> (8 + f)) & 1) r.q -= C(2) * (a.sig_hang - a.sigma_hat) * r.g;
   }
+  return r;
 }
 
-// All facet flux fields of the block in sNB, the eigendata in sE and the
-// boundary masks of the block's cells in LDS; ends with a barrier.
-template <typename T, int D, int N, bool VARK, bool COPY_FIRST = false, bool IVAR = false, bool AD = false>
-__device__ __forceinline__ void flux_fields(const DGArgs<T>& a, const T* tr, int c0, int nc, CT<T>* sNB, CT<T>* sE, CT<T>* sKF) {
-  static_assert(!AD || (!VARK && !COPY_FIRST && !IVAR), "adaptive meshes: constant kappa, exact blocks, fused loads");
-  int* sMask = mask_lds<D, N, VARK>(sKF);
-  const int tid = work_tid<D, N>();
-  if constexpr (!VARK) {
-    if constexpr (IVAR) {  // interior-block smoother: item after item (boundary facets read own traces)
-      facet_pass<T, D, N, false, true, true>(a, tr, c0, nc, 0, sNB, sE, sKF);
-      load_eig<T, D, N, false>(a, c0, nc, sE, sKF);
-      if (tid < nc) sMask[tid] = a.bmask[c0 + tid];
-    } else if constexpr (COPY_FIRST) {  // records copied, then the first transform from LDS
-      copy_neighbour_traces<T, D, N>(a, tr, c0, nc, sNB);
-      load_eig<T, D, N, false>(a, c0, nc, sE, sKF);
-      if (tid < nc) sMask[tid] = a.bmask[c0 + tid];
-      __syncthreads();
-      facet_pass<T, D, N, false>(a, tr, c0, nc, 0, sNB, sE, sKF);
-    } else {
-      facet_pass0_const<T, D, N, AD>(a, tr, c0, nc, sNB, sE, sMask);
-    }
-    __syncthreads();
-  } else {
-    copy_neighbour_traces<T, D, N>(a, tr, c0, nc, sNB);
-    load_eig<T, D, N, true>(a, c0, nc, sE, sKF);
-    if (tid < nc) sMask[tid] = a.bmask[c0 + tid];
-    __syncthreads();
-    if (a.rk) {
-      recompute_eig<T, D, N>(a, nc, sE, sKF);
-      __syncthreads();
-    }
-    make_si<T, D, N>(a, nc, sE);
-    __syncthreads();
-    facet_pass<T, D, N, true>(a, tr, c0, nc, 0, sNB, sE, sKF);
-    __syncthreads();
-  }
-  if constexpr (D == 3) {
-    facet_pass<T, D, N, VARK, false, IVAR, AD>(a, tr, c0, nc, 1, sNB, sE, sKF);
-    __syncthreads();
-  }
-}
-
-// r -= lift of facets (k,0) and (k,1): value part at the facet node, normal
-// derivative part along the line (sweep, SIGN = -1) or r += (apply, +1).
-template <typename T, int D, int N, int SIGN>
-__device__ __forceinline__ void add_lifts(const DGArgs<T>& a, int cl, int k, int ln, const CT<T>* sNB, CT<T> (&r)[N]) {
+// r += SIGN x the lifts of all facets at the nodes of the line along axis k
+// of thread line ln, in nodal values (the dual lift of facet (m, s) is the
+// facet mass times kappa_F (q'/2 - sigma_hat g') e_s + kappa_F g'/2 ep_s along
+// its axis; multiplied by Mhat^-1 along every axis the mass cancels and the
+// lift at a node is alpha_s q' + beta_s g' of the facet node it projects to,
+//   alpha_s = kappa_F/2 Mhat^-1 e_s,
+//   beta_s = kappa_F (Mhat^-1 ep_s / 2 - sigma_hat Mhat^-1 e_s),
+// tables AL0, BE0 for s = 0 (kappa_F = 1 when it varies), mirrored for s = 1.
+template <typename T, int D, int N, bool VARK, int SIGN>
+__device__ __forceinline__ void nodal_lifts(const DGArgs<T>& a, int cl, int k, int ln, const CT<T>* sNB,
+                                            const CT<T>* sKF, CT<T> (&r)[N]) {
   using C = CT<T>;
   using Sh = DGShape<D, N>;
   constexpr int L = Sh::L;
-  const cptr<C> ep0 = as_const(a.ref) + RefOff<N>::EP0;
-  const cptr<C> ep1 = as_const(a.ref) + RefOff<N>::EP1;
-  const C* f0 = sNB + (cl * Sh::NF + 2 * k) * 2 * L;
-  const C* f1 = f0 + 2 * L;
-  const C v0 = f0[ln], d0 = f0[L + ln], v1 = f1[ln], d1 = f1[L + ln];
-  constexpr C sg = SIGN < 0 ? C(-1) : C(1);
-  if (a.gl) {  // value functionals are dense (Gauss-Legendre nodes)
-    const cptr<C> ev0 = as_const(a.ref) + RefOff<N>::EV0;
-    const cptr<C> ev1 = as_const(a.ref) + RefOff<N>::EV1;
+  constexpr C sg = C(SIGN);
+  using P = TrPair<C>;
+  const P* nb = reinterpret_cast<const P*>(sNB) + cl * Sh::NF * L;
+  const C* kf = sKF + cl * Sh::NF;  // VARK only
+  {
+    const cptr<C> al = as_const(a.ref) + RefOff<N>::AL0;
+    const cptr<C> be = as_const(a.ref) + RefOff<N>::BE0;
+    P p0 = nb[(2 * k) * L + ln], p1 = nb[(2 * k + 1) * L + ln];
+    const C f0 = VARK ? sg * kf[2 * k] : sg, f1 = VARK ? sg * kf[2 * k + 1] : sg;
+    p0.g *= f0;
+    p0.q *= f0;
+    p1.g *= f1;
+    p1.q *= f1;
 #pragma unroll
-    for (int j = 0; j < N; ++j) r[j] += sg * (ev0[j] * v0 + ev1[j] * v1);
-  } else {
-    r[0] += sg * v0;
-    r[N - 1] += sg * v1;
+    for (int j = 0; j < N; ++j) {
+      r[j] += al[j] * p0.q + be[j] * p0.g;
+      r[j] += al[N - 1 - j] * p1.q + be[N - 1 - j] * p1.g;
+    }
   }
+  const C* sAB = sKF + kappa_lds_entries<D, N, VARK>() - 2 * N;
+  static_assert(D == 3, "nodal form: 3D");
+  const int i0 = ln % N, i1 = ln / N;
 #pragma unroll
-  for (int j = 0; j < N; ++j) r[j] += sg * (ep0[j] * d0 + ep1[j] * d1);
+  for (int mm = 1; mm < D; ++mm) {
+    // m: the other axes in increasing order; x = the line's index along m,
+    // y = its index along the remaining axis
+    const int m = mm - 1 < k ? mm - 1 : mm;
+    const int x = mm == 1 ? i0 : i1, y = mm == 1 ? i1 : i0;
+    // facet nodes of the line on the facets normal to m: the tangential axes
+    // are k and the remaining one, lower axis first
+    const int rest = 3 - k - m;
+    const int base = k < rest ? N * y : y, st = k < rest ? 1 : N;
+    const C f0 = VARK ? sg * kf[2 * m] : sg, f1 = VARK ? sg * kf[2 * m + 1] : sg;
+    const C a0 = f0 * sAB[x], b0 = f0 * sAB[N + x], a1 = f1 * sAB[N - 1 - x], b1 = f1 * sAB[2 * N - 1 - x];
+    const P* q0 = nb + (2 * m) * L + base;
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+      const P p0 = q0[j * st], p1 = q0[L + j * st];
+      r[j] += a0 * p0.q + b0 * p0.g;
+      r[j] += a1 * p1.q + b1 * p1.g;
+    }
+  }
 }
 
 // Traces (value, outward normal derivative) of a line along axis k, stored
@@ -933,9 +753,7 @@ template <typename T, int D, int N, bool IVAR = false>
 __device__ __forceinline__ void store_line_traces(const DGArgs<T>& a, T* trout, int c, int mask, int k, int ln,
                                                   const CT<T> (&u)[N]) {
   using C = CT<T>;
-  using Sh = DGShape<D, N>;
-  constexpr int L = Sh::L;
-  constexpr int TL = 2 * L;
+  constexpr int L = DGShape<D, N>::L;
   const cptr<C> ep0 = as_const(a.ref) + RefOff<N>::EP0;
   const cptr<C> ep1 = as_const(a.ref) + RefOff<N>::EP1;
   C d0 = 0, d1 = 0, g0 = u[0], g1 = u[N - 1];
@@ -955,32 +773,184 @@ __device__ __forceinline__ void store_line_traces(const DGArgs<T>& a, T* trout, 
       g1 += ev1[j] * u[j];
     }
   }
-  if (IVAR || !((mask >> (2 * k)) & 1)) {
-    T* t0 = trout + ((size_t)(2 * k) * a.ncell + c) * TL;
-    t0[ln] = g0;
-    t0[L + ln] = d0;
-  }
-  if (IVAR || !((mask >> (2 * k + 1)) & 1)) {
-    T* t1 = trout + ((size_t)(2 * k + 1) * a.ncell + c) * TL;
-    t1[ln] = g1;
-    t1[L + ln] = d1;
-  }
+  if (IVAR || !((mask >> (2 * k)) & 1))
+    *reinterpret_cast<TrPair<T>*>(trout + (((size_t)(2 * k) * a.ncell + c) * L + ln) * 2) = {(T)g0, (T)d0};
+  if (IVAR || !((mask >> (2 * k + 1)) & 1))
+    *reinterpret_cast<TrPair<T>*>(trout + (((size_t)(2 * k + 1) * a.ncell + c) * L + ln) * 2) = {(T)g1, (T)d1};
 }
 
-// Traces of the y (and z) lines of the cell vector staged in sU.
-template <typename T, int D, int N, bool IVAR = false>
-__device__ __forceinline__ void store_yz_traces(const DGArgs<T>& a, T* trout, const CT<T>* sU, int cl, int c, int mask,
-                                                int ln) {
+// Traces along every axis but F of the cell vector staged in sU.
+template <typename T, int D, int N, int F, bool IVAR = false>
+__device__ __forceinline__ void store_other_traces(const DGArgs<T>& a, T* trout, const CT<T>* sU, int cl, int c,
+                                                   int mask, int ln) {
   using C = CT<T>;
   using Sh = DGShape<D, N>;
 #pragma unroll
-  for (int k = 1; k < D; ++k) {
+  for (int k = 0; k < D; ++k) {
+    if (k == F) continue;
     const int base = cl * Sh::NV + line_base<D, N>(k, ln);
     C u[N];
 #pragma unroll
     for (int j = 0; j < N; ++j) u[j] = sU[base + j * line_stride<N>(k)];
     store_line_traces<T, D, N, IVAR>(a, trout, c, mask, k, ln, u);
   }
+}
+
+// Stages what a traversal of one block needs in LDS: the neighbour traces,
+// the eigendata and the lift coefficients (a barrier must follow before they
+// are read).  The class tables' and traces' loads of a thread are all issued
+// before the first LDS store.  SPLIT (dual form): the facet record as [g | q] instead
+// of pairs.
+template <typename T, int D, int N, bool VARK, bool IVAR, bool AD, bool TRACES, bool SPLIT = false>
+__device__ __forceinline__ void stage_block(const DGArgs<T>& a, const T* tr, int c0, int nc, int cl, int c, int ln,
+                                            bool act, int mask, CT<T>* sNB, CT<T>* sE, CT<T>* sKF) {
+  using C = CT<T>;
+  using Sh = DGShape<D, N>;
+  constexpr int L = Sh::L;
+  const int tid = work_tid<D, N>();
+  TrPair<T> p[2 * D];
+  if constexpr (TRACES) load_pairs<T, D, N, IVAR, AD>(a, tr, c, mask, ln, p);
+  C* sAB = lift_lds<D, N, VARK>(sKF);
+  const C ab = tid < 2 * N ? a.ref[RefOff<N>::AL0 + tid] : C(0);
+  static_assert(2 * N <= Sh::NT, "the lift table is staged in one pass");
+  load_eig<T, D, N, VARK, AD>(a, c0, nc, sE, sKF);
+  if (tid < 2 * N) sAB[tid] = ab;
+  if constexpr (TRACES) {
+    if (act) {
+#pragma unroll
+      for (int f = 0; f < 2 * D; ++f) {
+        const TrPair<C> v = finish_pair<T, IVAR, AD>(a, p[f], mask, f);
+        if constexpr (SPLIT) {
+          C* g = sNB + (cl * Sh::NF + f) * 2 * L + ln;
+          g[0] = v.g;
+          g[L] = v.q;
+        } else {
+          reinterpret_cast<TrPair<C>*>(sNB)[(cl * Sh::NF + f) * L + ln] = v;
+        }
+      }
+    }
+  }
+  if constexpr (VARK) {
+    __syncthreads();
+    if (a.rk) {
+      recompute_eig<T, D, N>(a, nc, sE, sKF);
+      __syncthreads();
+    }
+    make_si<T, D, N>(a, nc, sE);
+  }
+}
+
+// Form of a traversal: nodal (sweep_body, apply_body) or dual
+// (sweep_dual_body, apply_dual_body).
+// 2D is dual: its facets take one tangential transform of a single line, so
+// that the nodal form's extra products with Mhat^-1 buy nothing (Q2 16^2
+// V-cycle 41 us in both).
+// The FP32 residual is dual too: the fixed point of an FP32 cycle is that of
+// this operator as its rounded tables give it, and nothing after it corrects
+// it.  On Q4, 32^3 a cycle repeated to stagnation ends 4.9e-5 from the FP64
+// solution with the dual form's tables and 1.7e-4 with the nodal form's
+// (products with Mhat, S and Si each rounded), for 25 against 19 us per
+// residual.  The sweeps, whose rounding a cycle does correct, FP64 and the
+// 16-bit formats, whose stored u is coarser than either, are nodal.
+template <typename T, int D, bool RESID>
+constexpr bool dual_form() {
+  return D == 2 || (std::is_same<T, float>::value && RESID);
+}
+
+// ---- dual form: facet transforms and lifts (also of the matrix-core sweep)
+
+// Tangential axis of pass `pass` of the facet transform of facets normal to k.
+template <int D>
+__device__ __forceinline__ int tangential(int k, int pass) {
+  if constexpr (D == 2)
+    return 1 - k;
+  else
+    return pass == 0 ? ((k == 0) ? 1 : 0) : ((k == 2) ? 1 : 2);
+}
+
+// Facet flux fields.  From the neighbour's traces (g', q') across facet f
+//   F1 = T_f (kappa_F (q'/2 - sigma_hat g')),  F2 = T_f (kappa_F g'/2),
+// T_f = G_t1 x G_t2 over the tangential axes with G_t = Si_t for t < k
+// (axes already transformed when facet k is processed) and Mhat otherwise.
+// sNB[cl][f][F1|F2][L].  Pass 0 reads the traces staged as [g | q] and
+// transforms along t1; pass 1 transforms along t2 (3D).  Work items are
+// ordered (facet, cell, line) so that a wave mostly sees one facet
+// direction and therefore one matrix.
+template <typename T, int D, int N, bool VARK, bool IVAR, bool AD = false>
+__device__ __forceinline__ void facet_pass(const DGArgs<T>& a, int nc, int pass, CT<T>* sNB, const CT<T>* sE,
+                                           const CT<T>* sKF) {
+  using C = CT<T>;
+  using Sh = DGShape<D, N>;
+  constexpr int L = Sh::L;
+  constexpr int TL = 2 * L;
+  constexpr int LINES = (D == 2) ? 1 : N;
+  const cptr<C> Mh = as_const(a.ref) + RefOff<N>::M;
+  for (int i = work_tid<D, N>(); i < Sh::CPB * Sh::NF * LINES; i += Sh::NT) {
+    const int f = i / (Sh::CPB * LINES), rem = i % (Sh::CPB * LINES);
+    const int cl = rem / LINES, li = rem % LINES;
+    if (cl >= nc) continue;
+    const int k = f >> 1;
+    const int t = tangential<D>(k, pass);
+    const int st = pass == 0 ? 1 : N;  // node stride along t within the facet
+    const int lo = pass == 0 ? N * li : li;
+    C* g = sNB + (cl * Sh::NF + f) * TL + lo;
+    const int smask = IVAR ? 0 : mask_lds<D, N, VARK>(sKF)[cl];  // boundary classes of the block solve
+    C x1[N], x2[N], o1[N], o2[N];
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+      x1[j] = g[st * j];
+      x2[j] = g[L + st * j];
+    }
+    if (pass == 0) {
+      const C kf = VARK ? sKF[cl * Sh::NF + f] : a.kappa_const;
+#pragma unroll
+      for (int j = 0; j < N; ++j) {
+        const C gv = x1[j], qv = x2[j];
+        // one rounding: sigma_hat g' and q'/2 cancel for a smooth u
+        x1[j] = kf * fma(-a.sigma_hat, gv, C(0.5) * qv);
+        x2[j] = C(0.5) * kf * gv;
+      }
+    }
+    if (t < k) {
+      block_mv<T, D, N, VARK, IVAR, AD, OP_SI>(a, sE, cl, smask, t, x1, o1);
+      block_mv<T, D, N, VARK, IVAR, AD, OP_SI>(a, sE, cl, smask, t, x2, o2);
+    } else {
+      mv<N, false>(Mh, x1, o1);
+      mv<N, false>(Mh, x2, o2);
+    }
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+      g[st * j] = o1[j];
+      g[L + st * j] = o2[j];
+    }
+  }
+}
+
+// r += SIGN x the dual lift of facets (k,0) and (k,1): value part at the
+// facet node, normal derivative part along the line.
+template <typename T, int D, int N, int SIGN>
+__device__ __forceinline__ void dual_lifts(const DGArgs<T>& a, int cl, int k, int ln, const CT<T>* sNB,
+                                               CT<T> (&r)[N]) {
+  using C = CT<T>;
+  using Sh = DGShape<D, N>;
+  constexpr int L = Sh::L;
+  const cptr<C> ep0 = as_const(a.ref) + RefOff<N>::EP0;
+  const cptr<C> ep1 = as_const(a.ref) + RefOff<N>::EP1;
+  const C* f0 = sNB + (cl * Sh::NF + 2 * k) * 2 * L;
+  const C* f1 = f0 + 2 * L;
+  const C v0 = f0[ln], d0 = f0[L + ln], v1 = f1[ln], d1 = f1[L + ln];
+  constexpr C sg = C(SIGN);
+  if (a.gl) {  // value functionals are dense (Gauss-Legendre nodes)
+    const cptr<C> ev0 = as_const(a.ref) + RefOff<N>::EV0;
+    const cptr<C> ev1 = as_const(a.ref) + RefOff<N>::EV1;
+#pragma unroll
+    for (int j = 0; j < N; ++j) r[j] += sg * (ev0[j] * v0 + ev1[j] * v1);
+  } else {
+    r[0] += sg * v0;
+    r[N - 1] += sg * v1;
+  }
+#pragma unroll
+  for (int j = 0; j < N; ++j) r[j] += sg * (ep0[j] * d0 + ep1[j] * d1);
 }
 
 // z_j of the Krylov projection (see DGArgs::kry), read by its storage type.
@@ -1007,10 +977,20 @@ __device__ __forceinline__ void block_partial(double v, double* sh, double* out)
 }
 
 // ---------------------------------------------------------------------------
+// Bound and measurements of the nodal traversals: the LDS round trips between
+// the axes and the trace traffic.  In dual form each facet field took two
+// tangential transforms (24 N^3 multiply-adds per cell beside the volume's
+// 6 N^4); in nodal form b takes Mhat^-1 along each axis (3 N^4, about half of
+// that in even-odd form) and a facet field enters with one multiply-add per
+// node, trace and facet.  Four instead of three waves per SIMD need no
+// register cap (74 VGPRs at degree 4 in FP64, 125 before).  Measured sweep,
+// dual -> nodal: FP64 Q4 32^3 57 -> 41.7 us, variable kappa Q3 64^3 FP32
+// 190 -> 135 us, FP16 Q5 48^3 99 -> 82 us; FP64 apply Q7 25^3 80 -> 55 us.
+//
 // Fused block-Jacobi sweep.  UZERO: u is identically zero on entry (first
 // sweep of a coarse-level smoothing with zero initial guess): u and the
-// neighbour traces are not read.  The x-line of u and b of each thread
-// stay in registers from the load to the update.
+// neighbour traces are not read.  The thread's line of u stays in registers
+// from the load to the update.
 // LDS bytes of the sweep / apply bodies.
 template <typename T, int D, int N, bool VARK, bool AD = false>
 constexpr int cell_lds_bytes() {
@@ -1027,11 +1007,152 @@ template <typename T, int D, int N, bool UZERO, bool VARK, bool IVAR = false, bo
 __device__ __forceinline__ void sweep_body(const DGArgs<T>& a, int bx, int by, char* lds) {
   using C = CT<T>;
   using Sh = DGShape<D, N>;
-  constexpr int NN = N * N;
+  static_assert(D == 3, "nodal form: 3D");
   constexpr int L = Sh::L;
-  C* sW = (C*)lds;
-  C* sNB = sW + Sh::CPB * Sh::NV;
-  C* sE = sNB + Sh::CPB * Sh::NF * 2 * L;
+  constexpr int A = D - 1;  // axis of the thread's own line
+  C* sNB = (C*)lds;  // pairs: first, for their alignment
+  C* sW = sNB + Sh::CPB * Sh::NF * 2 * L;
+  C* sE = sW + Sh::CPB * Sh::NV;
+  C* sKF = sE + EigLDS<D, N, VARK, AD>::SIZE;
+
+  const int c0 = bx * Sh::CPB;
+  const int nc = min(Sh::CPB, a.ncell - c0);
+  const size_t rv = (size_t)by * a.vstride, rt = (size_t)by * a.tstride;
+  const int tid = work_tid<D, N>();
+  const int cl = tid / L, ln = tid % L;
+  const bool act = tid < Sh::NT && cl < nc;
+  const int c = c0 + (act ? cl : 0);
+  const int mask = cell_mask<AD>(a, c);
+  const int smask = IVAR ? 0 : mask;  // boundary classes of the block solve
+  C hf = a.h_fwd;
+  if constexpr (AD) {
+    if (a.hscale) hf *= a.hscale[c];
+  }
+  auto get = [&](int k, C(&r)[N]) {
+    const int base = cl * Sh::NV + line_base<D, N>(k, ln);
+#pragma unroll
+    for (int j = 0; j < N; ++j) r[j] = sW[base + j * line_stride<N>(k)];
+  };
+  auto put = [&](int k, const C(&r)[N]) {
+    const int base = cl * Sh::NV + line_base<D, N>(k, ln);
+#pragma unroll
+    for (int j = 0; j < N; ++j) sW[base + j * line_stride<N>(k)] = r[j];
+  };
+  const size_t own = rv + (size_t)c * Sh::NV + ln;  // first node of the thread's line, stride L
+
+  C ul[N], r[N], t[N];
+#pragma unroll
+  for (int j = 0; j < N; ++j) r[j] = a.b[own + j * L];
+  if constexpr (!UZERO) {
+#pragma unroll
+    for (int j = 0; j < N; ++j) ul[j] = a.u_in[own + j * L];
+  }
+  stage_block<T, D, N, VARK, IVAR, AD, !UZERO>(a, a.tr_in + rt, c0, nc, cl, c, ln, act, mask, sNB, sE, sKF);
+#pragma unroll
+  for (int j = 0; j < N; ++j) r[j] *= hf;
+
+  // forward to the eigenvector basis along every axis; the last forward
+  // axis also divides by the eigenvalue sums and transforms back
+  auto middle = [&](int k) {
+    C ls[N];
+    eig_sums<D, N, VARK, IVAR, AD>(sE, cl, smask, k, ln, ls);
+#pragma unroll
+    for (int j = 0; j < N; ++j) t[j] *= recip(ls[j]);
+    block_mv<T, D, N, VARK, IVAR, AD, OP_S>(a, sE, cl, smask, k, t, r);
+  };
+  if constexpr (UZERO) {
+    __syncthreads();  // eigendata staged
+#pragma unroll
+    for (int k = A; k >= 0; --k) {
+      if (act) {
+        if (k != A) get(k, r);
+        block_mv<T, D, N, VARK, IVAR, AD, OP_ST>(a, sE, cl, smask, k, r, t);
+        if (k == 0) {
+          middle(0);
+          put(0, r);
+        } else {
+          put(k, t);
+        }
+      }
+      __syncthreads();
+    }
+    if (act) {
+      get(1, r);
+      block_mv<T, D, N, VARK, IVAR, AD, OP_S>(a, sE, cl, smask, 1, r, t);
+      put(1, t);
+    }
+    __syncthreads();
+  } else {
+    const cptr<C> Mi = as_const(a.ref) + RefOff<N>::MIC;
+    if (act) {
+      cs_mv<N>(Mi, r);
+      put(A, r);
+    }
+    __syncthreads();
+    if (act) {
+      get(1, r);
+      cs_mv<N>(Mi, r);
+      put(1, r);
+    }
+    __syncthreads();
+    // x: b in nodal values along every axis, minus the lifts
+    if (act) {
+      get(0, r);
+      cs_mv<N>(Mi, r);
+      nodal_lifts<T, D, N, VARK, -1>(a, cl, 0, ln, sNB, sKF, r);
+      block_mv<T, D, N, VARK, IVAR, AD, OP_SI>(a, sE, cl, smask, 0, r, t);
+      put(0, t);
+    }
+    __syncthreads();
+    if (act) {
+      get(A, r);
+      block_mv<T, D, N, VARK, IVAR, AD, OP_SI>(a, sE, cl, smask, A, r, t);
+      put(A, t);
+    }
+    __syncthreads();
+    if (act) {
+      get(1, r);
+      block_mv<T, D, N, VARK, IVAR, AD, OP_SI>(a, sE, cl, smask, 1, r, t);
+      middle(1);
+      put(1, r);
+    }
+    __syncthreads();
+    if (act) {
+      get(0, r);
+      block_mv<T, D, N, VARK, IVAR, AD, OP_S>(a, sE, cl, smask, 0, r, t);
+      put(0, t);
+    }
+    __syncthreads();
+  }
+  // last inverse transform, update, store of u and of the traces
+  T* trout = a.tr_out + rt;
+  if (act) {
+    get(A, r);
+    block_mv<T, D, N, VARK, IVAR, AD, OP_S>(a, sE, cl, smask, A, r, t);
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+      const C uo0 = UZERO ? C(0) : ul[j];
+      t[j] = (C(1) - a.omega) * uo0 + a.omega * t[j];
+      a.u_out[own + j * L] = t[j];
+    }
+    put(A, t);
+    store_line_traces<T, D, N, IVAR>(a, trout, c, mask, A, ln, t);
+  }
+  __syncthreads();
+  if (act) store_other_traces<T, D, N, A, IVAR>(a, trout, sW, cl, c, mask, ln);
+}
+
+// The sweep in dual form (see dual_form): S^T along every axis with the
+// facet lifts, transformed along their tangential axes, subtracted before
+// each; the x-lines of u and b stay in registers from load to update.
+template <typename T, int D, int N, bool UZERO, bool VARK, bool IVAR = false, bool AD = false>
+__device__ __forceinline__ void sweep_dual_body(const DGArgs<T>& a, int bx, int by, char* lds) {
+  using C = CT<T>;
+  using Sh = DGShape<D, N>;
+  constexpr int L = Sh::L;
+  C* sNB = (C*)lds;
+  C* sW = sNB + Sh::CPB * Sh::NF * 2 * L;
+  C* sE = sW + Sh::CPB * Sh::NV;
   C* sKF = sE + EigLDS<D, N, VARK, AD>::SIZE;
 
   const int c0 = bx * Sh::CPB;
@@ -1060,17 +1181,13 @@ __device__ __forceinline__ void sweep_body(const DGArgs<T>& a, int bx, int by, c
       for (int j = 0; j < N; ++j) ul[j] = us[j];
     }
   }
-  if (!UZERO) {
-    flux_fields<T, D, N, VARK, !AD && sweep_copies_traces<T, D, N>(), IVAR, AD>(a, a.tr_in + rt, c0, nc, sNB, sE, sKF);
-  } else {
-    load_eig<T, D, N, VARK, AD>(a, c0, nc, sE, sKF);
-    __syncthreads();
-    if constexpr (VARK) {
-      if (a.rk) {
-        recompute_eig<T, D, N>(a, nc, sE, sKF);
-        __syncthreads();
-      }
-      make_si<T, D, N>(a, nc, sE);
+  stage_block<T, D, N, VARK, IVAR, AD, !UZERO, true>(a, a.tr_in + rt, c0, nc, cl, c, ln, act, mask, sNB, sE, sKF);
+  if (act && ln == 0) mask_lds<D, N, VARK>(sKF)[cl] = mask;
+  __syncthreads();
+  if constexpr (!UZERO) {
+#pragma unroll
+    for (int pass = 0; pass < D - 1; ++pass) {
+      facet_pass<T, D, N, VARK, IVAR, AD>(a, nc, pass, sNB, sE, sKF);
       __syncthreads();
     }
   }
@@ -1089,23 +1206,15 @@ __device__ __forceinline__ void sweep_body(const DGArgs<T>& a, int bx, int by, c
 #pragma unroll
         for (int j = 0; j < N; ++j) r[j] = sW[base + j * line_stride<N>(k)];
       }
-      if (!UZERO) add_lifts<T, D, N, -1>(a, cl, k, ln, sNB, r);
-      stage_mv<T, D, N, VARK, true, false, true, AD>(a, sE, cl, smask, k, r, t);  // S^T
+      if (!UZERO) dual_lifts<T, D, N, -1>(a, cl, k, ln, sNB, r);
+      block_mv<T, D, N, VARK, IVAR, AD, OP_ST>(a, sE, cl, smask, k, r, t);
       if (k == D - 1) {
         // diagonal scaling and the first inverse transform along the last axis
-        const C* E0 = VARK ? sE + (cl * D + 0) * Sh::EGS : sE + axis_cls<AD>(smask, 0) * Sh::EGS;
-        const C* E1 = VARK ? sE + (cl * D + 1) * Sh::EGS : sE + axis_cls<AD>(smask, 1) * Sh::EGS;
-        if constexpr (D == 2) {
-          const C ls = E0[2 * NN + ln];
+        C ls[N];
+        eig_sums<D, N, VARK, IVAR, AD>(sE, cl, smask, k, ln, ls);
 #pragma unroll
-          for (int j = 0; j < N; ++j) t[j] *= recip(ls + E1[2 * NN + j]);
-        } else {
-          const C* E2 = VARK ? sE + (cl * D + 2) * Sh::EGS : sE + axis_cls<AD>(smask, 2) * Sh::EGS;
-          const C ls = E0[2 * NN + ln % N] + E1[2 * NN + ln / N];
-#pragma unroll
-          for (int j = 0; j < N; ++j) t[j] *= recip(ls + E2[2 * NN + j]);
-        }
-        stage_mv<T, D, N, VARK, false, false, true, AD>(a, sE, cl, smask, k, t, r);  // S
+        for (int j = 0; j < N; ++j) t[j] *= recip(ls[j]);
+        block_mv<T, D, N, VARK, IVAR, AD, OP_S>(a, sE, cl, smask, k, t, r);
 #pragma unroll
         for (int j = 0; j < N; ++j) t[j] = r[j];
       }
@@ -1124,7 +1233,7 @@ __device__ __forceinline__ void sweep_body(const DGArgs<T>& a, int bx, int by, c
       C r[N], t[N];
 #pragma unroll
       for (int j = 0; j < N; ++j) r[j] = sW[base + j * line_stride<N>(k)];
-      stage_mv<T, D, N, VARK, false, false, true, AD>(a, sE, cl, smask, k, r, t);
+      block_mv<T, D, N, VARK, IVAR, AD, OP_S>(a, sE, cl, smask, k, r, t);
       if (k == 0) {
         T* uo = a.u_out + rv + (size_t)c0 * Sh::NV + base0;
 #pragma unroll
@@ -1142,7 +1251,7 @@ __device__ __forceinline__ void sweep_body(const DGArgs<T>& a, int bx, int by, c
     }
     __syncthreads();
   }
-  if (act) store_yz_traces<T, D, N, IVAR>(a, trout, sW, cl, c, mask, ln);
+  if (act) store_other_traces<T, D, N, 0, IVAR>(a, trout, sW, cl, c, mask, ln);
 }
 
 // ---------------------------------------------------------------------------
@@ -1305,16 +1414,16 @@ __device__ __forceinline__ void mfma_stage(float* sW, const float* sE, const int
 
 // Fused sweep of a 16-bit storage type with the volume contractions on the
 // matrix cores (mfma_stage); facet flux fields, lifts, update and traces as
-// in sweep_body.  Launched with whole waves (DGShape::BLOCK threads).
+// in dual form (facet_pass, dual_lifts).  Launched with whole waves (DGShape::BLOCK threads).
 template <typename T, int D, int N, bool UZERO, bool VARK, bool IVAR>
 __device__ __forceinline__ void sweep_body_mfma(const DGArgs<T>& a, int bx, int by, char* lds) {
   using C = CT<T>;
   static_assert(sizeof(C) == 4, "matrix-core sweep: 16-bit storage, FP32 compute");
   using Sh = DGShape<D, N>;
   constexpr int L = Sh::L;
-  C* sW = (C*)lds;
-  C* sNB = sW + Sh::CPB * Sh::NV;
-  C* sE = sNB + Sh::CPB * Sh::NF * 2 * L;
+  C* sNB = (C*)lds;  // pairs: first, for their alignment
+  C* sW = sNB + Sh::CPB * Sh::NF * 2 * L;
+  C* sE = sW + Sh::CPB * Sh::NV;
   C* sKF = sE + EigLDS<D, N, VARK>::SIZE;
   int* sMask = mask_lds<D, N, VARK>(sKF);
 
@@ -1339,18 +1448,13 @@ __device__ __forceinline__ void sweep_body_mfma(const DGArgs<T>& a, int bx, int 
       for (int j = 0; j < N; ++j) ul[j] = us[j];
     }
   }
-  if (!UZERO) {
-    flux_fields<T, D, N, VARK, sweep_copies_traces<T, D, N>(), IVAR>(a, a.tr_in + rt, c0, nc, sNB, sE, sKF);
-  } else {
-    load_eig<T, D, N, VARK>(a, c0, nc, sE, sKF);
-    if (tid < nc) sMask[tid] = a.bmask[c0 + tid];
-    __syncthreads();
-    if constexpr (VARK) {
-      if (a.rk) {
-        recompute_eig<T, D, N>(a, nc, sE, sKF);
-        __syncthreads();
-      }
-      make_si<T, D, N>(a, nc, sE);
+  if (tid < nc) sMask[tid] = a.bmask[c0 + tid];
+  stage_block<T, D, N, VARK, IVAR, false, !UZERO, true>(a, a.tr_in + rt, c0, nc, cl, c, ln, act, mask, sNB, sE, sKF);
+  __syncthreads();
+  if constexpr (!UZERO) {
+#pragma unroll
+    for (int pass = 0; pass < D - 1; ++pass) {
+      facet_pass<T, D, N, VARK, IVAR>(a, nc, pass, sNB, sE, sKF);
       __syncthreads();
     }
   }
@@ -1369,7 +1473,7 @@ __device__ __forceinline__ void sweep_body_mfma(const DGArgs<T>& a, int bx, int 
 #pragma unroll
         for (int j = 0; j < N; ++j) r[j] = sW[base + j * line_stride<N>(k)];
       }
-      if (!UZERO) add_lifts<T, D, N, -1>(a, cl, k, ln, sNB, r);
+      if (!UZERO) dual_lifts<T, D, N, -1>(a, cl, k, ln, sNB, r);
 #pragma unroll
       for (int j = 0; j < N; ++j) sW[base + j * line_stride<N>(k)] = r[j];
     }
@@ -1401,7 +1505,7 @@ __device__ __forceinline__ void sweep_body_mfma(const DGArgs<T>& a, int bx, int 
     store_line_traces<T, D, N, IVAR>(a, trout, c, mask, 0, ln, t);
   }
   __syncthreads();
-  if (act) store_yz_traces<T, D, N, IVAR>(a, trout, sW, cl, c, mask, ln);
+  if (act) store_other_traces<T, D, N, 0, IVAR>(a, trout, sW, cl, c, mask, ln);
 }
 
 // At least two waves per SIMD for the 3D FP64 degree 7 and 8 sweeps: left to
@@ -1419,25 +1523,125 @@ __attribute__((amdgpu_waves_per_eu(sweep_waves_per_eu<T, D, N>()))) void k_sweep
   __shared__ __attribute__((aligned(16))) char lds[cell_lds_bytes<T, D, N, VARK, AD>()];
   if constexpr (MF)
     sweep_body_mfma<T, D, N, UZERO, VARK, IVAR>(a, blockIdx.x, blockIdx.y, lds);
+  else if constexpr (dual_form<T, D, false>())
+    sweep_dual_body<T, D, N, UZERO, VARK, IVAR, AD>(a, blockIdx.x, blockIdx.y, lds);
   else
     sweep_body<T, D, N, UZERO, VARK, IVAR, AD>(a, blockIdx.x, blockIdx.y, lds);
 }
 
 // ---------------------------------------------------------------------------
-// y = A u (RESID: r = b - A u), optionally restricted to the next coarser
-// level: NC > 0 gives per cell (E^C x E^C x E^C) r with E the interpolation
-// from the coarse nodes (DG_q: a coarse cell vector; Q1: the 2^d corner
-// contributions of each cell, summed over cells by the gather kernel).
-// Needs the traces of u in tr_in.
-template <typename T, int D, int N, int NC, bool RESID, bool VARK, bool IVAR = false, bool AD = false>
-__device__ __forceinline__ void apply_body(const DGArgs<T>& a, int bx, int by, char* lds) {
+// Restriction (E^T)^(x d) of the cell residuals in sW, one axis per pass,
+// through sNB (every lift has been read) into a.out: a coarse DG cell
+// vector, or the 2^d Q1 corner contributions of each cell.
+template <typename T, int D, int N, int NC>
+__device__ __forceinline__ void restrict_body(const DGArgs<T>& a, int c0, int nc, int by, CT<T>* sNB, CT<T>* sW) {
   using C = CT<T>;
   using Sh = DGShape<D, N>;
-  constexpr int NN = N * N;
   constexpr int L = Sh::L;
-  C* sW = (C*)lds;
-  C* sNB = sW + Sh::CPB * Sh::NV;
-  C* sE = sNB + Sh::CPB * Sh::NF * 2 * L;
+  const int tid = work_tid<D, N>();
+  // NC < 0: the coarse node count ncr comes at run time (a.ncd <= N), loops
+  // run to N.
+  constexpr int NCB = NC > 0 ? NC : N;
+  const int ncr = NC > 0 ? NC : a.ncd;
+  const cptr<C> E = as_const(a.ref) + RefOff<N>::E;
+  const int NCD = (D == 2) ? ncr * ncr : ncr * ncr * ncr;
+  constexpr int NBS = Sh::NF * 2 * L;  // per-cell stride of sNB
+  C* dst = a.out + (size_t)by * a.cstride + (size_t)c0 * NCD;
+  // x: sW[cl][..][a] -> sNB[cl][ln][a'] (a' + ncr*ln)
+  for (int i = tid; i < nc * L; i += Sh::NT) {
+    const int c2 = i / L, l2 = i % L;
+    C x[N];
+#pragma unroll
+    for (int j = 0; j < N; ++j) x[j] = sW[c2 * Sh::NV + j + N * l2];
+#pragma unroll
+    for (int jc = 0; jc < NCB; ++jc) {
+      if (jc < ncr) {
+        C s = 0;
+#pragma unroll
+        for (int j = 0; j < N; ++j) s += E[j * ncr + jc] * x[j];
+        sNB[c2 * NBS + jc + ncr * l2] = s;
+      }
+    }
+  }
+  __syncthreads();
+  if constexpr (D == 2) {
+    // y: sNB[cl][b][a'] -> dst[a' + ncr b']
+    for (int i = tid; i < nc * ncr; i += Sh::NT) {
+      const int c2 = i / ncr, ac = i % ncr;
+      C x[N];
+#pragma unroll
+      for (int j = 0; j < N; ++j) x[j] = sNB[c2 * NBS + ac + ncr * j];
+#pragma unroll
+      for (int bc = 0; bc < NCB; ++bc) {
+        if (bc < ncr) {
+          C s = 0;
+#pragma unroll
+          for (int j = 0; j < N; ++j) s += E[j * ncr + bc] * x[j];
+          dst[(size_t)c2 * NCD + ac + ncr * bc] = s;
+        }
+      }
+    }
+  } else {
+    // y: sNB[cl][c][b][a'] (a' + ncr(b + N c)) -> sW[cl][c][b'][a'] (a' + ncr(b' + ncr c))
+    for (int i = tid; i < nc * ncr * N; i += Sh::NT) {
+      const int c2 = i / (ncr * N), rem = i % (ncr * N);
+      const int ac = rem % ncr, cz = rem / ncr;
+      C x[N];
+#pragma unroll
+      for (int j = 0; j < N; ++j) x[j] = sNB[c2 * NBS + ac + ncr * (j + N * cz)];
+#pragma unroll
+      for (int bc = 0; bc < NCB; ++bc) {
+        if (bc < ncr) {
+          C s = 0;
+#pragma unroll
+          for (int j = 0; j < N; ++j) s += E[j * ncr + bc] * x[j];
+          sW[c2 * Sh::NV + ac + ncr * (bc + ncr * cz)] = s;
+        }
+      }
+    }
+    __syncthreads();
+    // z: sW[cl][c][b'][a'] -> dst[a' + ncr b' + ncr^2 c']
+    for (int i = tid; i < nc * ncr * ncr; i += Sh::NT) {
+      const int c2 = i / (ncr * ncr), rem = i % (ncr * ncr);
+      C x[N];
+#pragma unroll
+      for (int j = 0; j < N; ++j) x[j] = sW[c2 * Sh::NV + rem + ncr * ncr * j];
+#pragma unroll
+      for (int ccz = 0; ccz < NCB; ++ccz) {
+        if (ccz < ncr) {
+          C s = 0;
+#pragma unroll
+          for (int j = 0; j < N; ++j) s += E[j * ncr + ccz] * x[j];
+          dst[(size_t)c2 * NCD + rem + ncr * ncr * ccz] = s;
+        }
+      }
+    }
+  }
+}
+
+// The block's share of p.(A p) in the outer FP64 iteration (kdot).
+template <typename T, int NC, bool RESID>
+__device__ __forceinline__ void apply_partial(const DGArgs<T>& a, double pdot, int bx) {
+  if constexpr (std::is_same<T, double>::value && NC == 0 && !RESID) {
+    if (a.kdot) {
+      __shared__ double sh[16];
+      block_partial(pdot, sh, a.kpartial + bx);
+    }
+  }
+}
+
+// apply_body in dual form: Si along every axis, the eigenvalue sums, Si^T
+// back, with the facet lifts transformed along their tangential axes
+// (facet_pass) and added right after each axis.  See dual_form for where it
+// is used.
+template <typename T, int D, int N, int NC, bool RESID, bool VARK, bool IVAR = false, bool AD = false>
+__device__ __forceinline__ void apply_dual_body(const DGArgs<T>& a, int bx, int by, char* lds) {
+  using C = CT<T>;
+  using Sh = DGShape<D, N>;
+  constexpr int L = Sh::L;
+  C* sNB = (C*)lds;  // as in sweep_body
+  C* sW = sNB + Sh::CPB * Sh::NF * 2 * L;
+  C* sE = sW + Sh::CPB * Sh::NV;
   C* sKF = sE + EigLDS<D, N, VARK, AD>::SIZE;
 
   const int c0 = bx * Sh::CPB;
@@ -1460,14 +1664,21 @@ __device__ __forceinline__ void apply_body(const DGArgs<T>& a, int bx, int by, c
     const T* us = a.u_in + rv + (size_t)c0 * Sh::NV + base0;
 #pragma unroll
     for (int j = 0; j < N; ++j) ul[j] = us[j];
-    if (RESID) {
+    if constexpr (RESID) {
       const T* bs = a.b + rv + (size_t)c0 * Sh::NV + base0;
 #pragma unroll
       for (int j = 0; j < N; ++j) bl[j] = bs[j];
     }
   }
-  flux_fields<T, D, N, VARK, false, IVAR, AD>(a, a.tr_in + rt, c0, nc, sNB, sE, sKF);
   double pdot = 0.0;  // share of p.(A p) (kdot)
+  stage_block<T, D, N, VARK, IVAR, AD, true, true>(a, a.tr_in + rt, c0, nc, cl, c, ln, act, mask, sNB, sE, sKF);
+  if (act && ln == 0) mask_lds<D, N, VARK>(sKF)[cl] = mask;
+  __syncthreads();
+#pragma unroll
+  for (int pass = 0; pass < D - 1; ++pass) {
+    facet_pass<T, D, N, VARK, IVAR, AD>(a, nc, pass, sNB, sE, sKF);
+    __syncthreads();
+  }
 
   // Si along every axis, diagonal scaling, then Si^T (= M S) back with the
   // lifts added right after each axis is transformed back.
@@ -1483,22 +1694,14 @@ __device__ __forceinline__ void apply_body(const DGArgs<T>& a, int bx, int by, c
 #pragma unroll
         for (int j = 0; j < N; ++j) r[j] = sW[base + j * line_stride<N>(k)];
       }
-      stage_mv<T, D, N, VARK, false, true, true, AD>(a, sE, cl, smask, k, r, t);  // Si
+      block_mv<T, D, N, VARK, IVAR, AD, OP_SI>(a, sE, cl, smask, k, r, t);
       if (k == D - 1) {
-        const C* E0 = VARK ? sE + (cl * D + 0) * Sh::EGS : sE + axis_cls<AD>(smask, 0) * Sh::EGS;
-        const C* E1 = VARK ? sE + (cl * D + 1) * Sh::EGS : sE + axis_cls<AD>(smask, 1) * Sh::EGS;
-        if constexpr (D == 2) {
-          const C ls = E0[2 * NN + ln];
+        C ls[N];
+        eig_sums<D, N, VARK, IVAR, AD>(sE, cl, smask, k, ln, ls);
 #pragma unroll
-          for (int j = 0; j < N; ++j) t[j] *= (ls + E1[2 * NN + j]);
-        } else {
-          const C* E2 = VARK ? sE + (cl * D + 2) * Sh::EGS : sE + axis_cls<AD>(smask, 2) * Sh::EGS;
-          const C ls = E0[2 * NN + ln % N] + E1[2 * NN + ln / N];
-#pragma unroll
-          for (int j = 0; j < N; ++j) t[j] *= (ls + E2[2 * NN + j]);
-        }
-        stage_mv<T, D, N, VARK, true, true, true, AD>(a, sE, cl, smask, k, t, r);  // Si^T
-        add_lifts<T, D, N, +1>(a, cl, k, ln, sNB, r);
+        for (int j = 0; j < N; ++j) t[j] *= ls[j];
+        block_mv<T, D, N, VARK, IVAR, AD, OP_SIT>(a, sE, cl, smask, k, t, r);
+        dual_lifts<T, D, N, 1>(a, cl, k, ln, sNB, r);
 #pragma unroll
         for (int j = 0; j < N; ++j) t[j] = r[j];
       }
@@ -1514,120 +1717,151 @@ __device__ __forceinline__ void apply_body(const DGArgs<T>& a, int bx, int by, c
       C r[N], t[N];
 #pragma unroll
       for (int j = 0; j < N; ++j) r[j] = sW[base + j * line_stride<N>(k)];
-      stage_mv<T, D, N, VARK, true, true, true, AD>(a, sE, cl, smask, k, r, t);
-      add_lifts<T, D, N, +1>(a, cl, k, ln, sNB, t);
+      block_mv<T, D, N, VARK, IVAR, AD, OP_SIT>(a, sE, cl, smask, k, r, t);
+      dual_lifts<T, D, N, 1>(a, cl, k, ln, sNB, t);
       if (k == 0) {
 #pragma unroll
         for (int j = 0; j < N; ++j) {
           t[j] *= ha;
-          if (RESID) t[j] = bl[j] - t[j];
-        }
-        if constexpr (NC == 0) {
-          C* dst = a.out + rv + (size_t)c0 * Sh::NV + base0;
-#pragma unroll
-          for (int j = 0; j < N; ++j) dst[j] = t[j];
-          if constexpr (std::is_same<T, double>::value && !RESID) {
-#pragma unroll
-            for (int j = 0; j < N; ++j) pdot += ul[j] * t[j];
-          }
-        } else {
-#pragma unroll
-          for (int j = 0; j < N; ++j) sW[base + j] = t[j];
+          if constexpr (RESID) t[j] = bl[j] - t[j];
+          if constexpr (NC == 0)
+            a.out[rv + (size_t)c0 * Sh::NV + base0 + j] = t[j];
+          else
+            sW[base + j] = t[j];
+          if constexpr (std::is_same<T, double>::value && NC == 0 && !RESID) pdot += ul[j] * t[j];
         }
       } else {
 #pragma unroll
         for (int j = 0; j < N; ++j) sW[base + j * line_stride<N>(k)] = t[j];
       }
     }
-    if (k > 0 || NC != 0) __syncthreads();
+    __syncthreads();
   }
-  if constexpr (std::is_same<T, double>::value && NC == 0 && !RESID) {
-    if (a.kdot) {
-      __shared__ double sh[16];
-      block_partial(pdot, sh, a.kpartial + bx);
-    }
+  apply_partial<T, NC, RESID>(a, pdot, bx);
+  if constexpr (NC != 0) restrict_body<T, D, N, NC>(a, c0, nc, by, sNB, sW);
+}
+
+// y = A u (RESID: r = b - A u), optionally restricted to the next coarser
+// level: NC > 0 gives per cell (E^C x E^C x E^C) r with E the interpolation
+// from the coarse nodes (DG_q: a coarse cell vector; Q1: the 2^d corner
+// contributions of each cell, summed over cells by the gather kernel).
+// Needs the traces of u in tr_in.
+template <typename T, int D, int N, int NC, bool RESID, bool VARK, bool IVAR = false, bool AD = false>
+__device__ __forceinline__ void apply_body(const DGArgs<T>& a, int bx, int by, char* lds) {
+  using C = CT<T>;
+  using Sh = DGShape<D, N>;
+  static_assert(D == 3, "nodal form: 3D");
+  constexpr int L = Sh::L;
+  constexpr int A = D - 1;  // axis of the thread's own line
+  C* sNB = (C*)lds;  // pairs: first, for their alignment
+  C* sW = sNB + Sh::CPB * Sh::NF * 2 * L;
+  C* sE = sW + Sh::CPB * Sh::NV;
+  C* sKF = sE + EigLDS<D, N, VARK, AD>::SIZE;
+
+  const int c0 = bx * Sh::CPB;
+  const int nc = min(Sh::CPB, a.ncell - c0);
+  const size_t rv = (size_t)by * a.vstride, rt = (size_t)by * a.tstride;
+  const int tid = work_tid<D, N>();
+  const int cl = tid / L, ln = tid % L;
+  const bool act = tid < Sh::NT && cl < nc;
+  const int c = c0 + (act ? cl : 0);
+  const int mask = cell_mask<AD>(a, c);
+  const int smask = IVAR ? 0 : mask;  // boundary classes of the block solve
+  C ha = a.h_apply;
+  if constexpr (AD) {
+    if (a.hscale) ha /= a.hscale[c];
   }
-  if constexpr (NC != 0) {
-    // restriction (E^T)^(x d) of the cell residual, one axis per pass; sNB
-    // is free once every lift has been read (barrier above).  NC < 0: the
-    // coarse node count ncr comes at run time (a.ncd <= N), loops run to N.
-    constexpr int NCB = NC > 0 ? NC : N;
-    const int ncr = NC > 0 ? NC : a.ncd;
-    const cptr<C> E = as_const(a.ref) + RefOff<N>::E;
-    const int NCD = (D == 2) ? ncr * ncr : ncr * ncr * ncr;
-    constexpr int NBS = Sh::NF * 2 * L;  // per-cell stride of sNB
-    C* dst = a.out + (size_t)by * a.cstride + (size_t)c0 * NCD;
-    // x: sW[cl][..][a] -> sNB[cl][ln][a'] (a' + ncr*ln)
-    for (int i = tid; i < nc * L; i += Sh::NT) {
-      const int c2 = i / L, l2 = i % L;
-      C x[N];
+
+  auto get = [&](int k, C(&r)[N]) {
+    const int base = cl * Sh::NV + line_base<D, N>(k, ln);
 #pragma unroll
-      for (int j = 0; j < N; ++j) x[j] = sW[c2 * Sh::NV + j + N * l2];
+    for (int j = 0; j < N; ++j) r[j] = sW[base + j * line_stride<N>(k)];
+  };
+  auto put = [&](int k, const C(&r)[N]) {
+    const int base = cl * Sh::NV + line_base<D, N>(k, ln);
 #pragma unroll
-      for (int jc = 0; jc < NCB; ++jc) {
-        if (jc < ncr) {
-          C s = 0;
+    for (int j = 0; j < N; ++j) sW[base + j * line_stride<N>(k)] = r[j];
+  };
+  const size_t own = rv + (size_t)c * Sh::NV + ln;  // first node of the thread's line, stride L
+
+  C ul[N], bl[N], r[N], t[N];
 #pragma unroll
-          for (int j = 0; j < N; ++j) s += E[j * ncr + jc] * x[j];
-          sNB[c2 * NBS + jc + ncr * l2] = s;
-        }
+  for (int j = 0; j < N; ++j) ul[j] = a.u_in[own + j * L];
+  if constexpr (RESID) {
+#pragma unroll
+    for (int j = 0; j < N; ++j) bl[j] = a.b[own + j * L];
+  }
+  stage_block<T, D, N, VARK, IVAR, AD, true>(a, a.tr_in + rt, c0, nc, cl, c, ln, act, mask, sNB, sE, sKF);
+  __syncthreads();
+  double pdot = 0.0;  // share of p.(A p) (kdot)
+
+  // S Lambda Si u: nodal values of Mhat^-1 (A_{K<-K} u) along every axis
+#pragma unroll
+  for (int k = A; k >= 0; --k) {
+    if (act) {
+      if (k == A) {
+        block_mv<T, D, N, VARK, IVAR, AD, OP_SI>(a, sE, cl, smask, k, ul, t);
+      } else {
+        get(k, r);
+        block_mv<T, D, N, VARK, IVAR, AD, OP_SI>(a, sE, cl, smask, k, r, t);
+      }
+      if (k == 0) {
+        C ls[N];
+        eig_sums<D, N, VARK, IVAR, AD>(sE, cl, smask, 0, ln, ls);
+#pragma unroll
+        for (int j = 0; j < N; ++j) t[j] *= ls[j];
+        block_mv<T, D, N, VARK, IVAR, AD, OP_S>(a, sE, cl, smask, 0, t, r);
+        put(0, r);
+      } else {
+        put(k, t);
       }
     }
     __syncthreads();
-    if constexpr (D == 2) {
-      // y: sNB[cl][b][a'] -> dst[a' + ncr b']
-      for (int i = tid; i < nc * ncr; i += Sh::NT) {
-        const int c2 = i / ncr, ac = i % ncr;
-        C x[N];
+  }
+  if (act) {
+    get(A, r);
+    block_mv<T, D, N, VARK, IVAR, AD, OP_S>(a, sE, cl, smask, A, r, t);
+    put(A, t);
+  }
+  __syncthreads();
+  // plus the lifts (in the y-lines), times the mass along every axis
+  const cptr<C> Mc = as_const(a.ref) + RefOff<N>::MC;
+  if (act) {
+    get(1, r);
+    block_mv<T, D, N, VARK, IVAR, AD, OP_S>(a, sE, cl, smask, 1, r, t);
+    nodal_lifts<T, D, N, VARK, 1>(a, cl, 1, ln, sNB, sKF, t);
+    cs_mv<N>(Mc, t);
+    put(1, t);
+  }
+  __syncthreads();
+  if (act) {
+    get(0, r);
+    cs_mv<N>(Mc, r);
+    put(0, r);
+  }
+  __syncthreads();
+  if (act) {
+    get(A, t);
+    cs_mv<N>(Mc, t);
 #pragma unroll
-        for (int j = 0; j < N; ++j) x[j] = sNB[c2 * NBS + ac + ncr * j];
+    for (int j = 0; j < N; ++j) {
+      t[j] *= ha;
+      if (RESID) t[j] = bl[j] - t[j];
+    }
+    if constexpr (NC == 0) {
 #pragma unroll
-        for (int bc = 0; bc < NCB; ++bc) {
-          if (bc < ncr) {
-            C s = 0;
+      for (int j = 0; j < N; ++j) a.out[own + j * L] = t[j];
+      if constexpr (std::is_same<T, double>::value && !RESID) {
 #pragma unroll
-            for (int j = 0; j < N; ++j) s += E[j * ncr + bc] * x[j];
-            dst[(size_t)c2 * NCD + ac + ncr * bc] = s;
-          }
-        }
+        for (int j = 0; j < N; ++j) pdot += ul[j] * t[j];
       }
     } else {
-      // y: sNB[cl][c][b][a'] (a' + ncr(b + N c)) -> sW[cl][c][b'][a'] (a' + ncr(b' + ncr c))
-      for (int i = tid; i < nc * ncr * N; i += Sh::NT) {
-        const int c2 = i / (ncr * N), rem = i % (ncr * N);
-        const int ac = rem % ncr, cz = rem / ncr;
-        C x[N];
-#pragma unroll
-        for (int j = 0; j < N; ++j) x[j] = sNB[c2 * NBS + ac + ncr * (j + N * cz)];
-#pragma unroll
-        for (int bc = 0; bc < NCB; ++bc) {
-          if (bc < ncr) {
-            C s = 0;
-#pragma unroll
-            for (int j = 0; j < N; ++j) s += E[j * ncr + bc] * x[j];
-            sW[c2 * Sh::NV + ac + ncr * (bc + ncr * cz)] = s;
-          }
-        }
-      }
-      __syncthreads();
-      // z: sW[cl][c][b'][a'] -> dst[a' + ncr b' + ncr^2 c']
-      for (int i = tid; i < nc * ncr * ncr; i += Sh::NT) {
-        const int c2 = i / (ncr * ncr), rem = i % (ncr * ncr);
-        C x[N];
-#pragma unroll
-        for (int j = 0; j < N; ++j) x[j] = sW[c2 * Sh::NV + rem + ncr * ncr * j];
-#pragma unroll
-        for (int ccz = 0; ccz < NCB; ++ccz) {
-          if (ccz < ncr) {
-            C s = 0;
-#pragma unroll
-            for (int j = 0; j < N; ++j) s += E[j * ncr + ccz] * x[j];
-            dst[(size_t)c2 * NCD + rem + ncr * ncr * ccz] = s;
-          }
-        }
-      }
+      put(A, t);
     }
   }
+  if constexpr (NC != 0) __syncthreads();
+  apply_partial<T, NC, RESID>(a, pdot, bx);
+  if constexpr (NC != 0) restrict_body<T, D, N, NC>(a, c0, nc, by, sNB, sW);
 }
 
 // Apply holds u, b and the neighbour traces in registers at once; for the
@@ -1640,7 +1874,10 @@ template <typename T, int D, int N, int NC, bool RESID, bool VARK, bool IVAR, bo
 __global__ __launch_bounds__((DGShape<D, N>::BLOCK))
 __attribute__((amdgpu_waves_per_eu(apply_waves_per_eu<T, N>()))) void k_apply(DGArgs<T> a) {
   __shared__ __attribute__((aligned(16))) char lds[cell_lds_bytes<T, D, N, VARK, AD>()];
-  apply_body<T, D, N, NC, RESID, VARK, IVAR, AD>(a, blockIdx.x, blockIdx.y, lds);
+  if constexpr (dual_form<T, D, RESID>())
+    apply_dual_body<T, D, N, NC, RESID, VARK, IVAR, AD>(a, blockIdx.x, blockIdx.y, lds);
+  else
+    apply_body<T, D, N, NC, RESID, VARK, IVAR, AD>(a, blockIdx.x, blockIdx.y, lds);
 }
 
 // ---------------------------------------------------------------------------
@@ -1678,25 +1915,25 @@ __device__ __forceinline__ void prolong_body(const DGArgs<T>& a, int bx, int by,
   const int ncr = NC >= 0 ? NC : a.ncd;
   const int NCD = (NC == 0) ? 0 : ((D == 2) ? ncr * ncr : ncr * ncr * ncr);
 
+  // the thread's own line: along the last axis in 3D (as in the nodal
+  // traversals), along x in 2D (as in the dual ones)
+  constexpr int F = D == 3 ? 2 : 0, ST = line_stride<N>(F);
+  const int lb = line_base<D, N>(F, ln);
   C u[N];
-  if (act) {
-    const size_t off = rv + (size_t)c0 * Sh::NV + cl * Sh::NV + line_base<D, N>(0, ln);
-    const T* us = a.u_in + off;
+  const size_t own = rv + (size_t)c * Sh::NV + lb;
 #pragma unroll
-    for (int j = 0; j < N; ++j) u[j] = us[j];
-    if constexpr (std::is_same<T, double>::value && NC == 0) {
-      if (a.kry) {  // p = z + beta p, in place
-        const double beta = a.kscal[3];
-        const double sc = a.zscaled ? a.kscal[8] / a.kmul : 1.0;
+  for (int j = 0; j < N; ++j) u[j] = a.u_in[own + j * ST];
+  if constexpr (std::is_same<T, double>::value && NC == 0) {
+    if (a.kry && act) {  // p = z + beta p, in place
+      const double beta = a.kscal[3];
+      const double sc = a.zscaled ? a.kscal[8] / a.kmul : 1.0;
 #pragma unroll
-        for (int j = 0; j < N; ++j) {
-          const double zj = krylov_z(a, off + j, sc);
-          u[j] = beta == 0.0 ? zj : zj + beta * u[j];
-        }
-        T* uo = a.u_out + off;
-#pragma unroll
-        for (int j = 0; j < N; ++j) uo[j] = u[j];
+      for (int j = 0; j < N; ++j) {
+        const double zj = krylov_z(a, own + j * ST, sc);
+        u[j] = beta == 0.0 ? zj : zj + beta * u[j];
       }
+#pragma unroll
+      for (int j = 0; j < N; ++j) a.u_out[own + j * ST] = u[j];
     }
   }
   if constexpr (NC != 0) {
@@ -1730,39 +1967,39 @@ __device__ __forceinline__ void prolong_body(const DGArgs<T>& a, int bx, int by,
     __syncthreads();
     const cptr<C> E = as_const(a.ref) + RefOff<N>::E;
     if constexpr (D == 3) {
-      // z: [c'][b'][a'] -> sNB[cl][c][b'][a'] (a' + NC b' + NC^2 c)
+      // x: [c'][b'][a'] -> sNB[cl][c'][b'][a] (a + N (b' + NC c'))
       for (int i = tid; i < nc * ncr * ncr; i += Sh::NT) {
         const int c2 = i / (ncr * ncr), rem = i % (ncr * ncr);
         C x[NCB];
 #pragma unroll
-        for (int j = 0; j < NCB; ++j) x[j] = j >= ncr ? C(0) : sW[c2 * Sh::NV + rem + ncr * ncr * min(j, ncr - 1)];
+        for (int j = 0; j < NCB; ++j) x[j] = j >= ncr ? C(0) : sW[c2 * Sh::NV + ncr * rem + min(j, ncr - 1)];
 #pragma unroll
-        for (int cz = 0; cz < N; ++cz) {
+        for (int ax = 0; ax < N; ++ax) {
           C s = 0;
 #pragma unroll
-          for (int j = 0; j < NCB; ++j) s += E[cz * ncr + min(j, ncr - 1)] * x[j];  // x[j] = 0 past ncr
-          sNB[c2 * Sh::NF * 2 * L + rem + ncr * ncr * cz] = s;
+          for (int j = 0; j < NCB; ++j) s += E[ax * ncr + min(j, ncr - 1)] * x[j];  // x[j] = 0 past ncr
+          sNB[c2 * Sh::NF * 2 * L + N * rem + ax] = s;
         }
       }
       __syncthreads();
-      // y: sNB[c][b'][a'] -> sW[cl][c][b][a'] (a' + NC b + NC N c)
+      // y: sNB[c'][b'][a] -> sW[cl][c'][b][a] (a + N b + N^2 c')
       for (int i = tid; i < nc * ncr * N; i += Sh::NT) {
         const int c2 = i / (ncr * N), rem = i % (ncr * N);
-        const int ac = rem % ncr, cz = rem / ncr;
+        const int ax = rem % N, cz = rem / N;
         C x[NCB];
 #pragma unroll
-        for (int j = 0; j < NCB; ++j) x[j] = j >= ncr ? C(0) : sNB[c2 * Sh::NF * 2 * L + ac + ncr * min(j, ncr - 1) + ncr * ncr * cz];
+        for (int j = 0; j < NCB; ++j)
+          x[j] = j >= ncr ? C(0) : sNB[c2 * Sh::NF * 2 * L + ax + N * (min(j, ncr - 1) + ncr * cz)];
 #pragma unroll
         for (int by = 0; by < N; ++by) {
           C s = 0;
 #pragma unroll
           for (int j = 0; j < NCB; ++j) s += E[by * ncr + min(j, ncr - 1)] * x[j];  // x[j] = 0 past ncr
-          sW[c2 * Sh::NV + ac + ncr * (by + N * cz)] = s;
+          sW[c2 * Sh::NV + ax + N * by + N * N * cz] = s;
         }
       }
-      __syncthreads();
     } else {
-      // y: [b'][a'] -> sNB[cl][b][a'] -> copy back into sW layout (a' + NC b)
+      // y: [b'][a'] -> sNB[cl][b][a'] (a' + NC b)
       for (int i = tid; i < nc * ncr; i += Sh::NT) {
         const int c2 = i / ncr, ac = i % ncr;
         C x[NCB];
@@ -1776,41 +2013,35 @@ __device__ __forceinline__ void prolong_body(const DGArgs<T>& a, int bx, int by,
           sNB[c2 * Sh::NF * 2 * L + ac + ncr * by] = s;
         }
       }
-      __syncthreads();
-      for (int i = tid; i < nc * ncr * N; i += Sh::NT) {
-        const int c2 = i / (ncr * N), rem = i % (ncr * N);
-        sW[c2 * Sh::NV + rem] = sNB[c2 * Sh::NF * 2 * L + rem];
-      }
-      __syncthreads();
     }
+    __syncthreads();
   }
-  // x: line of thread ln (facet index = (b[,c])): add the prolongated
-  // correction, store u and the x-facet traces, stage u for the y/z traces
+  // the thread's own line: add the prolongated correction, store u and the
+  // traces of that axis, stage u for the others
   T* trout = a.tr_out + rt;
   if (act) {
-    const int base = cl * Sh::NV + line_base<D, N>(0, ln);
     if constexpr (NC != 0) {
       const cptr<C> E = as_const(a.ref) + RefOff<N>::E;
+      const C* src = D == 3 ? sW + cl * Sh::NV + ln : sNB + cl * Sh::NF * 2 * L + ncr * ln;
       C x[NCB];
 #pragma unroll
-      for (int j = 0; j < NCB; ++j) x[j] = j >= ncr ? C(0) : sW[cl * Sh::NV + min(j, ncr - 1) + ncr * ln];
+      for (int j = 0; j < NCB; ++j) x[j] = j >= ncr ? C(0) : src[min(j, ncr - 1) * ST];
 #pragma unroll
-      for (int ax = 0; ax < N; ++ax) {
+      for (int az = 0; az < N; ++az) {
         C s = 0;
 #pragma unroll
-        for (int j = 0; j < NCB; ++j) s += E[ax * ncr + min(j, ncr - 1)] * x[j];  // x[j] = 0 past ncr
-        u[ax] += s;
+        for (int j = 0; j < NCB; ++j) s += E[az * ncr + min(j, ncr - 1)] * x[j];  // x[j] = 0 past ncr
+        u[az] += s;
       }
-      T* uo = a.u_out + rv + (size_t)c0 * Sh::NV + base;
 #pragma unroll
-      for (int j = 0; j < N; ++j) uo[j] = u[j];
+      for (int j = 0; j < N; ++j) a.u_out[own + j * ST] = u[j];
     }
 #pragma unroll
-    for (int j = 0; j < N; ++j) sU[base + j] = u[j];
-    store_line_traces<T, D, N, IVAR>(a, trout, c, mask, 0, ln, u);
+    for (int j = 0; j < N; ++j) sU[cl * Sh::NV + lb + j * ST] = u[j];
+    store_line_traces<T, D, N, IVAR>(a, trout, c, mask, F, ln, u);
   }
   __syncthreads();
-  if (act) store_yz_traces<T, D, N, IVAR>(a, trout, sU, cl, c, mask, ln);
+  if (act) store_other_traces<T, D, N, F, IVAR>(a, trout, sU, cl, c, mask, ln);
 }
 
 template <typename T, int D, int N, int NC, bool IVAR, bool AD = false>

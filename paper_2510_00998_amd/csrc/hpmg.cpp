@@ -207,6 +207,31 @@ std::vector<double> remap_tables(const hpmg::Basis1D& B, int r) {
   return out;
 }
 
+// Compact even-odd table of a matrix with G(N-1-i, N-1-j) = G(i, j) (cs_mv).
+std::vector<double> compact_centro(const std::vector<double>& G, int N) {
+  const int H = N / 2, NE = (N + 1) / 2;
+  std::vector<double> t;
+  for (int i = 0; i < NE; ++i)
+    for (int j = 0; j < NE; ++j)
+      t.push_back(j < H ? 0.5 * (G[(size_t)i * N + j] + G[(size_t)i * N + N - 1 - j]) : G[(size_t)i * N + j]);
+  for (int i = 0; i < H; ++i)
+    for (int j = 0; j < H; ++j) t.push_back(0.5 * (G[(size_t)i * N + j] - G[(size_t)i * N + N - 1 - j]));
+  return t;
+}
+
+// Compact table of a matrix whose first (N+1)/2 columns are mirror-even and
+// whose last N/2 are mirror-odd (eo_fwd, eo_inv); entry (i, c) by at(i, c).
+template <class F>
+std::vector<double> compact_parity(int N, F at) {
+  const int H = N / 2, NE = (N + 1) / 2;
+  std::vector<double> t;
+  for (int i = 0; i < NE; ++i)
+    for (int c = 0; c < NE; ++c) t.push_back(at(i, c));
+  for (int i = 0; i < H; ++i)
+    for (int c = 0; c < H; ++c) t.push_back(at(i, NE + c));
+  return t;
+}
+
 void build_dg_level(hpmg_ctx* h, DGLevel& L, const hpmg::Basis1D& B, const hpmg::Basis1D* Bnext,
                     hipStream_t s) {
   const int N = B.N, NN = N * N, D = h->dim;
@@ -214,26 +239,11 @@ void build_dg_level(hpmg_ctx* h, DGLevel& L, const hpmg::Basis1D& B, const hpmg:
   const size_t nif = h->adapt ? (size_t)h->amesh[L.am].nif : 0;
   L.ndof = ncell * ipow(N, D);
   L.trsize = ((size_t)2 * D * ncell + nif * (h->mif + 1)) * 2 * ipow(N, D - 1);
-  // reference data
-  std::vector<double> ref;
-  ref.insert(ref.end(), B.M.begin(), B.M.end());
-  ref.insert(ref.end(), B.ep0.begin(), B.ep0.end());
-  ref.insert(ref.end(), B.ep1.begin(), B.ep1.end());
-  ref.insert(ref.end(), B.e0.begin(), B.e0.end());
-  ref.insert(ref.end(), B.e1.begin(), B.e1.end());
-  if (Bnext) {
-    std::vector<double> E = hpmg::interp_matrix(B.xi, Bnext->xi);
-    ref.insert(ref.end(), E.begin(), E.end());
-  } else {
-    for (int a = 0; a < N; ++a) {
-      ref.push_back(1.0 - B.xi[a]);
-      ref.push_back(B.xi[a]);
-    }
-  }
-  L.d.ref = h->mem.upload(ref, s);
-  L.f.ref = h->mem.upload(cast_vec<float>(ref), s);
   // eigendata of the cell blocks
   const int EGS = 2 * NN + N;
+  // compact even-odd tables of S and Si^T of the interior class (constant kappa)
+  const size_t nq = (size_t)((N + 1) / 2) * ((N + 1) / 2) + (size_t)(N / 2) * (N / 2);
+  std::vector<double> sc(nq, 0.0), sic(nq, 0.0);
   std::vector<double> Lm;
   if (!h->vark) {
     // classes: bit 0 / 1 lower / upper facet on the boundary; adaptive
@@ -275,12 +285,53 @@ void build_dg_level(hpmg_ctx* h, DGLevel& L, const hpmg::Basis1D& B, const hpmg:
     }
     L.d.eig = h->mem.upload(tab, s);
     L.f.eig = h->mem.upload(cast_vec<float>(tab), s);
+    sc = compact_parity(N, [&](int i, int c) { return tab[(size_t)i * N + c]; });
+    sic = compact_parity(N, [&](int i, int c) { return tab[(size_t)NN + c * N + i]; });
     if (h->adapt) {
       const std::vector<double> mt = remap_tables(B, h->rfac);
       L.d.mort = h->mem.upload(mt, s);
       L.f.mort = h->mem.upload(cast_vec<float>(mt), s);
     }
+  }
+  // reference data (RefOff)
+  std::vector<double> ref;
+  auto append = [&](const std::vector<double>& v) { ref.insert(ref.end(), v.begin(), v.end()); };
+  append(B.M);
+  append(B.ep0);
+  append(B.ep1);
+  append(B.e0);
+  append(B.e1);
+  std::vector<double> id((size_t)NN, 0.0);
+  for (int i = 0; i < N; ++i) id[(size_t)i * N + i] = 1.0;
+  const std::vector<double> Mi = mass_solve(B, id);
+  const double kl = h->vark ? 1.0 : h->kappa_const;  // kappa_F of the lift tables
+  std::vector<double> al(N), be(N);
+  for (int i = 0; i < N; ++i) {
+    double me = 0.0, mep = 0.0;
+    for (int j = 0; j < N; ++j) {
+      me += Mi[(size_t)i * N + j] * B.e0[j];
+      mep += Mi[(size_t)i * N + j] * B.ep0[j];
+    }
+    al[i] = 0.5 * kl * me;
+    be[i] = kl * (0.5 * mep - L.sigma_hat * me);
+  }
+  append(al);
+  append(be);
+  append(compact_centro(B.M, N));
+  append(compact_centro(Mi, N));
+  append(sc);
+  append(sic);
+  if (Bnext) {
+    append(hpmg::interp_matrix(B.xi, Bnext->xi));
   } else {
+    for (int a = 0; a < N; ++a) {
+      ref.push_back(1.0 - B.xi[a]);
+      ref.push_back(B.xi[a]);
+    }
+  }
+  L.d.ref = h->mem.upload(ref, s);
+  L.f.ref = h->mem.upload(cast_vec<float>(ref), s);
+  if (h->vark) {
     // the kernels rebuild S, lambda per cell and axis from kappa
     // (block_recompute) or read them from per-cell records built here on the
     // device by the same eigensolve: both need Khat and W = C^-1 with
