@@ -133,8 +133,6 @@ struct Table {
   std::vector<hpmg::WorkItem> items1;  // of tile variant 1 (DG only)
 };
 
-int cpb_of(int N, int V) { return hpmg::cells_per_block_v(3, N, V); }
-
 // Launch builder: collects per-problem arguments and work items, uploads.
 struct Builder {
   BatchPlan* b;
@@ -160,9 +158,13 @@ void add_dg_items(Table<hpmg::DGArgs<T>>& t, const hpmg::DGArgs<T>& a, int N, in
   const int idx = (int)t.args.size();
   t.args.push_back(a);
   for (int V = 0; V < hpmg::kTileVariants; ++V) {
-    const int nb = (a.ncell + cpb_of(N, V) - 1) / cpb_of(N, V);
+    const hpmg::Brick b = hpmg::brick(N, V);
+    std::vector<hpmg::WorkItem>& items = V == 0 ? t.items : t.items1;
     for (int r = 0; r < nrhs; ++r)
-      for (int blk = 0; blk < nb; ++blk) (V == 0 ? t.items : t.items1).push_back(hpmg::WorkItem{idx, blk, r, N});
+      for (int z = 0; z < hpmg::brick_layers(a.n, b.z); ++z)
+        for (int y = 0; y < hpmg::brick_layers(a.n, b.y); ++y)
+          for (int x = 0; x < hpmg::brick_layers(a.n, b.x); ++x)
+            items.push_back(hpmg::WorkItem{idx, hpmg::brick_id(x, y, z), r, N});
   }
 }
 

@@ -14,8 +14,13 @@ constexpr int batch_lds() {
               item_lds<T, 6, OP>());
 }
 
+// threads of a block that takes items of any degree
+constexpr int BATCH_BLOCK = cmax(cmax(cmax(DGShapeV<3, 2, 0>::BLOCK, DGShapeV<3, 3, 0>::BLOCK),
+                                      cmax(DGShapeV<3, 4, 0>::BLOCK, DGShapeV<3, 5, 0>::BLOCK)),
+                                 DGShapeV<3, 6, 0>::BLOCK);
+
 template <typename T, int OP>
-__global__ __launch_bounds__(256) void k_dg_batch(const DGArgs<T>* __restrict__ args,
+__global__ __launch_bounds__(BATCH_BLOCK) void k_dg_batch(const DGArgs<T>* __restrict__ args,
                                                   const WorkItem* __restrict__ items, int nitems) {
   __shared__ __attribute__((aligned(16))) char lds[batch_lds<T, OP>()];
   for (int it = blockIdx.x; it < nitems; it += gridDim.x) {
@@ -411,7 +416,7 @@ inline unsigned grid_for(int n, int cap) { return (unsigned)(n < cap ? (n > 0 ? 
 
 template <typename T>
 void batch_dg(int op, const DGArgs<T>* args, const WorkItem* items, int nitems, int grid, hipStream_t s) {
-  const dim3 g(grid_for(nitems, grid)), b(256);
+  const dim3 g(grid_for(nitems, grid)), b(BATCH_BLOCK);
   switch (op) {
     case BOP_SWEEP: hipLaunchKernelGGL((k_dg_batch<T, BOP_SWEEP>), g, b, 0, s, args, items, nitems); break;
     case BOP_SWEEP0: hipLaunchKernelGGL((k_dg_batch<T, BOP_SWEEP0>), g, b, 0, s, args, items, nitems); break;

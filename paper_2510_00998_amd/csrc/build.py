@@ -32,7 +32,11 @@ SOURCES = [
     "dg_inst_2d_f16.hip",
     "dg_inst_2d_bf16.hip",
     "dg_inst_3d_float.hip",
+    "dg_inst_3d_float_vark.hip",
+    "dg_inst_3d_float_runs.hip",
     "dg_inst_3d_double.hip",
+    "dg_inst_3d_double_vark.hip",
+    "dg_inst_3d_double_runs.hip",
     "dg_inst_3d_f16.hip",
     "dg_inst_3d_bf16.hip",
 ]

@@ -1,50 +1,51 @@
-// Shared body of the per-(type, dimension) instantiation files: dispatch of
-// a DG operation to the kernel of degree N - 1.
+// Shared body of the per-(type, dimension, block shape) instantiation files:
+// dispatch of a DG operation to the kernel of degree N - 1.
 #pragma once
 #include "dg_kernels_impl.hpp"
 #include "kernels.hpp"
 
 namespace hpmg {
-namespace inst {
+namespace HPMG_DGK {
 
 template <typename T, int D, int N>
-void run(int op, const DGArgs<T>& a, int nrhs, int flag, hipStream_t s) {
+bool run(int op, const DGArgs<T>& a, int nrhs, int flag, hipStream_t s) {
   constexpr int NC = nc_next(N);
   switch (op) {
-    case OP_SWEEP: launch_sweep<T, D, N>(a, nrhs, flag != 0, s); break;
-    case OP_APPLY: launch_apply<T, D, N, 0>(a, nrhs, flag != 0, s); break;
-    case OP_RESTRICT: launch_apply<T, D, N, NC>(a, nrhs, true, s); break;
-    case OP_PROJECT: launch_prolong<T, D, N, 0>(a, nrhs, s); break;
-    case OP_PROLONG: launch_prolong<T, D, N, NC>(a, nrhs, s); break;
-    case OP_RESTRICT_Q1: launch_apply<T, D, N, 2>(a, nrhs, true, s); break;
-    case OP_PROLONG_Q1: launch_prolong<T, D, N, 2>(a, nrhs, s); break;
+    case OP_SWEEP: return launch_sweep<T, D, N>(a, nrhs, flag != 0, s);
+    case OP_APPLY: return launch_apply<T, D, N, 0>(a, nrhs, flag != 0, s);
+    case OP_RESTRICT: return launch_apply_r<T, D, N, NC, true>(a, nrhs, s);
+    case OP_PROJECT: return launch_prolong<T, D, N, 0>(a, nrhs, s);
+    case OP_PROLONG: return launch_prolong<T, D, N, NC>(a, nrhs, s);
+    case OP_RESTRICT_Q1: return launch_apply_r<T, D, N, 2, true>(a, nrhs, s);
+    case OP_PROLONG_Q1: return launch_prolong<T, D, N, 2>(a, nrhs, s);
     case OP_RESTRICT_DYN:
-      if constexpr (N >= 4) launch_apply<T, D, N, -1>(a, nrhs, true, s);
-      break;
+      if constexpr (N >= 4) return launch_apply_r<T, D, N, -1, true>(a, nrhs, s);
+      return false;
     case OP_PROLONG_DYN:
-      if constexpr (N >= 4) launch_prolong<T, D, N, -1>(a, nrhs, s);
-      break;
+      if constexpr (N >= 4) return launch_prolong<T, D, N, -1>(a, nrhs, s);
+      return false;
     case OP_BUILD_EIG:
-      if constexpr (std::is_same<T, double>::value || std::is_same<T, float>::value) launch_build_eig<T, D, N>(a, s);
-      break;
-    default: break;
+      if constexpr (std::is_same<T, double>::value || std::is_same<T, float>::value)
+        return launch_build_eig<T, D, N>(a, s);
+      return false;
+    default: return false;
   }
 }
 
 template <typename T, int D>
 bool dispatch(int N, int op, const DGArgs<T>& a, int nrhs, int flag, hipStream_t s) {
   switch (N) {
-    case 2: run<T, D, 2>(op, a, nrhs, flag, s); return true;
-    case 3: run<T, D, 3>(op, a, nrhs, flag, s); return true;
-    case 4: run<T, D, 4>(op, a, nrhs, flag, s); return true;
-    case 5: run<T, D, 5>(op, a, nrhs, flag, s); return true;
-    case 6: run<T, D, 6>(op, a, nrhs, flag, s); return true;
-    case 7: run<T, D, 7>(op, a, nrhs, flag, s); return true;
-    case 8: run<T, D, 8>(op, a, nrhs, flag, s); return true;
-    case 9: run<T, D, 9>(op, a, nrhs, flag, s); return true;
+    case 2: return run<T, D, 2>(op, a, nrhs, flag, s);
+    case 3: return run<T, D, 3>(op, a, nrhs, flag, s);
+    case 4: return run<T, D, 4>(op, a, nrhs, flag, s);
+    case 5: return run<T, D, 5>(op, a, nrhs, flag, s);
+    case 6: return run<T, D, 6>(op, a, nrhs, flag, s);
+    case 7: return run<T, D, 7>(op, a, nrhs, flag, s);
+    case 8: return run<T, D, 8>(op, a, nrhs, flag, s);
+    case 9: return run<T, D, 9>(op, a, nrhs, flag, s);
     default: return false;
   }
 }
 
-}  // namespace inst
+}  // namespace HPMG_DGK
 }  // namespace hpmg

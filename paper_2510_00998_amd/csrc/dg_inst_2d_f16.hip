@@ -3,6 +3,6 @@
 
 namespace hpmg {
 bool dg_dispatch2(int N, int op, const DGArgs<_Float16>& a, int nrhs, int flag, hipStream_t s) {
-  return inst::dispatch<_Float16, 2>(N, op, a, nrhs, flag, s);
+  return dgk::dispatch<_Float16, 2>(N, op, a, nrhs, flag, s);
 }
 }  // namespace hpmg

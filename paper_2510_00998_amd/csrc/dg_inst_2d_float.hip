@@ -3,6 +3,6 @@
 
 namespace hpmg {
 bool dg_dispatch2(int N, int op, const DGArgs<float>& a, int nrhs, int flag, hipStream_t s) {
-  return inst::dispatch<float, 2>(N, op, a, nrhs, flag, s);
+  return dgk::dispatch<float, 2>(N, op, a, nrhs, flag, s);
 }
 }  // namespace hpmg

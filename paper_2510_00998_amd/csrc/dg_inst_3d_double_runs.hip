@@ -1,0 +1,9 @@
+// Instantiation of the DG cell kernels for dim = 3, storage type double: adaptive meshes.
+#define HPMG_TILE 3
+#include "dg_inst.hpp"
+
+namespace hpmg {
+bool dg_dispatch3_runs(int N, int op, const DGArgs<double>& a, int nrhs, int flag, hipStream_t s) {
+  return dgk_t3::dispatch<double, 3>(N, op, a, nrhs, flag, s);
+}
+}  // namespace hpmg

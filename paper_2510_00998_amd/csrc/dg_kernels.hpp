@@ -31,32 +31,72 @@
 
 namespace hpmg {
 
-// Cells per block: about 256 threads, unless a build overrides the 3D cell
-// count per block for one degree (HPMG_CPB3D_N / HPMG_CPB3D, tile tuning).
-#ifndef HPMG_CPB3D_N
-#define HPMG_CPB3D_N 0
-#define HPMG_CPB3D 0
-#endif
-__host__ __device__ constexpr int cells_per_block(int D, int N) {
-  return (D == 3 && N == HPMG_CPB3D_N) ? HPMG_CPB3D
-                                       : ((256 / (D == 2 ? N : N * N)) > 0 ? (256 / (D == 2 ? N : N * N)) : 1);
-}
-// Tile variants of a cell-block kernel (picked by the batched driver's
-// autotuner): V = 0 the cells of about 256 threads, V = 1 half as many
-// cells (about 128 threads, at least one cell).
+// Cells of a block (of shape V).  3D uniform meshes in FP64 and FP32: a brick
+// of BX x BY x BZ cells.  A traversal knows the traces of every facet inside a
+// brick from the u it holds, so only the facets between bricks go through the
+// trace buffers: of the 12 N^2 trace words that a cell writes and as many that
+// it reads per sweep beside its 3 N^3 of u and b, a share
+// 1 - (1/BX + 1/BY + 1/BZ)/3 stays on chip (0.75 at degree 1, 0.6 at degree 4).
+// 2D and adaptive meshes, and 16-bit storage (whose sweep is bound by
+// instruction issue, not by traffic: FP16 Q5 48^3 81 us in runs, 91 us in
+// bricks): runs of consecutive cells.
+//   V = 0  constant kappa (and 2D)
+//   V = 1  the same with about half the cells (tile variant of the batched
+//          driver's autotuner)
+//   V = 2  variable kappa, whose per-cell 1D matrices share the LDS
+//   V = 3  runs of cells in 3D
+// Bricks are chosen so that a workgroup has 4 or 8 nearly full waves: one of 5
+// waves is allocated as two waves on every SIMD (a 2 x 2 x 2 brick of degree 5,
+// 288 threads, held 20 of 32 waves per CU: FP64 48^3 sweep 283 us, against 197
+// us for 7 x 2 x 1).  Sweep, runs -> bricks: FP64 Q3 64^3 227 -> 146 us, Q4 48^3
+// 168 -> 121 us, Q5 48^3 252 -> 197 us, Q6 40^3 222 -> 189 us; FP32 Q3 64^3 110
+// -> 74 us, Q5 48^3 138 -> 106 us.
 constexpr int kTileVariants = 2;
-__host__ __device__ constexpr int cells_per_block_v(int D, int N, int V) {
-  return V == 0 ? cells_per_block(D, N) : (cells_per_block(D, N) / 2 > 0 ? cells_per_block(D, N) / 2 : 1);
+struct Brick {
+  int x, y, z;
+};
+__host__ __device__ constexpr Brick brick(int N, int V) {
+  switch (N) {
+    case 2: return V == 1 ? Brick{4, 4, 2} : Brick{4, 4, 4};
+    case 3: return V == 1 ? Brick{3, 2, 2} : Brick{3, 3, 3};
+    case 4: return V == 1 ? Brick{2, 2, 2} : Brick{4, 2, 2};
+    case 5: return V == 0 ? Brick{5, 2, 2} : Brick{5, 2, 1};
+    case 6: return V == 0 ? Brick{7, 2, 1} : Brick{3, 2, 1};
+    case 7: return V == 0 ? Brick{5, 2, 1} : Brick{5, 1, 1};
+    case 8: return V == 1 ? Brick{2, 1, 1} : Brick{2, 2, 1};
+    default: return V == 1 ? Brick{1, 1, 1} : Brick{3, 1, 1};
+  }
 }
+__host__ __device__ constexpr int cells_per_block_v(int D, int N, int V) {
+  if (D == 2) return 256 / N;
+  if (V == 3) return 256 / (N * N);
+  return brick(N, V).x * brick(N, V).y * brick(N, V).z;
+}
+// Blocks of a 3D uniform mesh with n cells per axis, and the facet records
+// (2 N^2 values each) that one trace buffer holds: for every axis the lower
+// and upper faces of the bricks, n^2 facets per layer of bricks.
+__host__ __device__ constexpr int brick_layers(int n, int b) { return (n + b - 1) / b; }
+inline long long brick_blocks(int n, int N, int V) {
+  const Brick b = brick(N, V);
+  return (long long)brick_layers(n, b.x) * brick_layers(n, b.y) * brick_layers(n, b.z);
+}
+inline long long brick_records(int n, int N, int V) {
+  const Brick b = brick(N, V);
+  return 2LL * n * n * (brick_layers(n, b.x) + brick_layers(n, b.y) + brick_layers(n, b.z));
+}
+// Block index of a brick (10 bits per axis; a 3D mesh has n <= 1023).
+__host__ __device__ constexpr int brick_id(int x, int y, int z) { return x | (y << 10) | (z << 20); }
 template <int D, int N, int V>
 struct DGShapeV {
   static constexpr int L = (D == 2) ? N : N * N;  // lines per cell = nodes per facet
   static constexpr int NV = L * N;                // nodes per cell
   static constexpr int NF = 2 * D;                // facets per cell
+  static constexpr int BX = brick(N, V).x, BY = brick(N, V).y, BZ = brick(N, V).z;  // 3D
   static constexpr int CPB = cells_per_block_v(D, N, V);
   static constexpr int NT = CPB * L;
   static constexpr int BLOCK = (NT + 63) / 64 * 64;  // launch bound: whole waves
-  static constexpr int EGS = 2 * N * N + N;       // S, Si, lambda of one direction
+  static constexpr int EGS = 2 * N * N + N;       // S, Si, lambda of one direction (class tables)
+  static constexpr int EGV = N * N + N;           // S, lambda of one direction (per cell, variable kappa)
 };
 template <int D, int N>
 using DGShape = DGShapeV<D, N, 0>;
@@ -120,7 +160,8 @@ struct DGArgs {
   const T* u_in;       // cell vector
   T* u_out;            // cell vector (may alias u_in)
   const T* b;          // cell vector
-  const T* tr_in;      // traces [2D][ncell][2][L] (adaptive meshes: then the hanging-facet slots)
+  const T* tr_in;      // traces, records of L pairs (value, derivative): 2D and adaptive meshes [2D][ncell] (then
+                       // the hanging-facet slots), 3D the faces of the bricks (Cells::own_rec)
   T* tr_out;
   C* out;              // apply: y; resid: r (NC=0) or coarse right-hand side (next level, compute type)
   const C* coarse;     // prolong: coarse cell vector (DG) or Q1 interior vertex vector (CG)
@@ -142,8 +183,8 @@ struct DGArgs {
   // the cell's own traces with the sign reversed, i.e. (D~ - A_{K<-K}) u
   // (the difference of the two 1D operators is the boundary-facet term,
   // kappa/2 (e ep^T + ep e^T) - sigma_hat kappa e e^T), so that the sweep
-  // computes u + omega D~^-1 (b - A u) and the apply A u.  Traces are then
-  // stored on boundary facets too.
+  // computes u + omega D~^-1 (b - A u) and the apply A u.  In 2D traces are
+  // then stored on boundary facets too.
   int ivar = 0;
   int ncd = 0;         // nodes per direction of the coarse DG level (transfers with a run-time degree)
   // 16-bit storage sweeps (3D): 1 runs the six volume contractions of the
@@ -174,10 +215,5 @@ struct DGArgs {
   double kmul = 1.0;
   double* kpartial = nullptr;
 };
-
-template <typename T, int D, int N> void launch_sweep(const DGArgs<T>& a, int nrhs, bool uzero, hipStream_t s);
-template <typename C, int D, int N> void launch_build_eig(const DGArgs<C>& a, hipStream_t s);
-template <typename T, int D, int N, int NC> void launch_apply(const DGArgs<T>& a, int nrhs, bool resid, hipStream_t s);
-template <typename T, int D, int N, int NC> void launch_prolong(const DGArgs<T>& a, int nrhs, hipStream_t s);
 
 }  // namespace hpmg

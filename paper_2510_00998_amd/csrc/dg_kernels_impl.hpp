@@ -17,16 +17,18 @@
 //   z  S, update, store of u and of the z-facet traces
 //   x, y facet traces from the updated cell in LDS
 // The facet traces are written by each cell for its own interior facets and
-// read once by the neighbour in the next sweep.
+// read once by the neighbour in the next sweep.  Where a block is a brick of
+// cells (see brick), only the facets on its faces go through the buffers: two
+// steps before the first one put u in LDS and hand the traces of the facets
+// inside the brick from cell to cell.
 #pragma once
 #include <type_traits>
 
 #include "dg_kernels.hpp"
 
-// A translation unit may compile the cell kernels for another tile variant
-// (cells per block, see DGShapeV) by defining HPMG_TILE first: they then
-// live in namespace dgk_t<HPMG_TILE>, the host launchers below are left
-// out, and unqualified DGShape<D, N> names the variant's shape.
+// A translation unit compiles the cell kernels for one block shape (DGShapeV)
+// by defining HPMG_TILE first: they live in namespace dgk (0) or
+// dgk_t<HPMG_TILE>, and unqualified DGShape<D, N> names that shape.
 #ifndef HPMG_TILE
 #define HPMG_TILE 0
 #endif
@@ -68,7 +70,12 @@ template <typename T>
 using cptr = const __attribute__((address_space(4))) T*;
 template <typename T>
 __device__ __forceinline__ cptr<T> as_const(const T* p) {
-  return (cptr<T>)(p);
+  // the same in every lane: without this the compiler keeps the pointer in
+  // vector registers once some lanes have used it, and loads the tables per
+  // lane (100 vector loads a wave in the FP64 degree-4 sweep)
+  const unsigned long long v = (unsigned long long)p;
+  const unsigned lo = __builtin_amdgcn_readfirstlane((int)v), hi = __builtin_amdgcn_readfirstlane((int)(v >> 32));
+  return (cptr<T>)(((unsigned long long)hi << 32) | lo);
 }
 
 // out = G in, G row-major N x N (TR: G^T)
@@ -224,12 +231,130 @@ __device__ __forceinline__ int cell_mask(const DGArgs<T>& a, int c) {
     return a.bmask[c];
 }
 
+// The cells of one block, by local index cl < CPB: a run of consecutive cells
+// (2D, HPMG_TILE 3; id the block's number) or a brick (3D; id from brick_id), whose cells past the end of the mesh are not valid.
+template <int D, int N, bool AD>
+struct Cells {
+  using Sh = DGShape<D, N>;
+  static constexpr bool BR = D == 3 && HPMG_TILE != 3;
+  static_assert(!BR || !AD, "adaptive meshes: runs of cells");
+  int n, c0 = 0, nc = 0;                  // run: first cell, count
+  int b[3], o[3], s[3];                   // brick: its place, first cell and cells per axis
+  template <typename T>
+  __device__ __forceinline__ Cells(const DGArgs<T>& a, int id) : n(a.n) {
+    if constexpr (BR) {
+      constexpr int B[3] = {Sh::BX, Sh::BY, Sh::BZ};
+#pragma unroll
+      for (int k = 0; k < 3; ++k) {
+        b[k] = (id >> (10 * k)) & 1023;
+        o[k] = b[k] * B[k];
+        s[k] = min(B[k], n - o[k]);
+      }
+    } else {
+      c0 = id * Sh::CPB;
+      nc = min(Sh::CPB, a.ncell - c0);
+    }
+  }
+  __device__ __forceinline__ void local(int cl, int (&l)[3]) const {
+    l[0] = cl % Sh::BX;
+    l[1] = cl / Sh::BX % Sh::BY;
+    l[2] = cl / (Sh::BX * Sh::BY);
+  }
+  // local indices the block's loops run over (a brick's may be not valid)
+  __device__ __forceinline__ int count() const { return BR ? Sh::CPB : nc; }
+  __device__ __forceinline__ bool valid(int cl) const {
+    if constexpr (BR) {
+      int l[3];
+      local(cl, l);
+      return cl < Sh::CPB && l[0] < s[0] && l[1] < s[1] && l[2] < s[2];
+    } else {
+      return cl < nc;
+    }
+  }
+  // its cell; for an index that is not valid another cell of the block
+  __device__ __forceinline__ int cell(int cl) const {
+    if constexpr (BR) {
+      int l[3];
+      local(min(cl, Sh::CPB - 1), l);
+      return o[0] + min(l[0], s[0] - 1) + n * (o[1] + min(l[1], s[1] - 1) + n * (o[2] + min(l[2], s[2] - 1)));
+    } else {
+      return c0 + min(cl, nc - 1);
+    }
+  }
+  // facet mask of cell c = cell(cl) (see axis_class, axis_cls)
+  template <typename T>
+  __device__ __forceinline__ int mask(const DGArgs<T>& a, int cl, int c) const {
+    if constexpr (BR) {
+      int l[3], m = 0;
+      local(cl, l);
+#pragma unroll
+      for (int k = 0; k < 3; ++k) {
+        const int x = o[k] + min(l[k], s[k] - 1);
+        m |= (x == 0 ? 1 : 0) << (2 * k) | (x == n - 1 ? 1 : 0) << (2 * k + 1);
+      }
+      return m;
+    } else {
+      return cell_mask<AD>(a, c);
+    }
+  }
+  // Brick: facet f of local cell l lies on the brick's face.
+  __device__ __forceinline__ bool face(int f, const int (&l)[3]) const {
+    const int k = f >> 1;
+    return (f & 1) ? l[k] == s[k] - 1 : l[k] == 0;
+  }
+  // Brick: trace record of facet f on the brick's face, written by the cell
+  // (own_rec) or by the neighbour across it (nb_rec).  Per axis the buffer
+  // holds the layers of lower faces, then of upper faces, and in a layer the
+  // facets of each brick's face one after another: a brick reads and writes
+  // six contiguous runs.
+  __device__ __forceinline__ unsigned face_rec(int k, int side, int layer, const int (&l)[3]) const {
+    const int i = k == 0 ? 1 : 0, j = k == 2 ? 1 : 2;  // tangential axes
+    const int nb[3] = {brick_layers(n, Sh::BX), brick_layers(n, Sh::BY), brick_layers(n, Sh::BZ)};
+    const int before = k == 0 ? 0 : (k == 1 ? 2 * nb[0] : 2 * nb[0] + 2 * nb[1]);
+    return (unsigned)(n * n) * (unsigned)(before + side * nb[k] + layer) +
+           (unsigned)(o[j] * n + s[j] * o[i] + l[i] + s[i] * l[j]);
+  }
+  __device__ __forceinline__ unsigned own_rec(int f, const int (&l)[3]) const {
+    return face_rec(f >> 1, f & 1, b[f >> 1], l);
+  }
+  __device__ __forceinline__ unsigned nb_rec(int f, const int (&l)[3]) const {
+    return face_rec(f >> 1, (f & 1) ^ 1, b[f >> 1] + ((f & 1) ? 1 : -1), l);
+  }
+  // number of the block among the blocks of one right-hand side
+  __device__ __forceinline__ int number(int id) const {
+    if constexpr (BR)
+      return b[0] + brick_layers(n, Sh::BX) * (b[1] + brick_layers(n, Sh::BY) * b[2]);
+    else
+      return id;
+  }
+};
+
+// Block and right-hand side of a launch (block_grid).
+template <int D, int N, bool AD, typename T>
+__device__ __forceinline__ void block_of_grid(const DGArgs<T>& a, int& id, int& rhs) {
+  if constexpr (Cells<D, N, AD>::BR) {
+    const int nbx = brick_layers(a.n, DGShape<D, N>::BX);
+    int x = blockIdx.x;
+    rhs = 0;
+    if (x >= nbx) {
+      rhs = x / nbx;
+      x -= rhs * nbx;
+    }
+    id = brick_id(x, blockIdx.y, blockIdx.z);
+  } else {
+    id = blockIdx.x;
+    rhs = blockIdx.y;
+  }
+}
+
 // LDS size of the staged eigendata: constant kappa shares the 4 (adaptive:
-// 16) class tables, variable kappa stages one set per cell and axis.
+// 16) class tables, variable kappa stages S | lambda per cell and axis (2D:
+// then the scratch of recompute_eig, which takes the trace slots in 3D).
 template <int D, int N, bool VARK, bool AD = false>
 struct EigLDS {
   static constexpr int SIZE =
-      VARK ? DGShape<D, N>::CPB * D * DGShape<D, N>::EGS : n_classes<AD>() * DGShape<D, N>::EGS;
+      VARK ? DGShape<D, N>::CPB * D * (DGShape<D, N>::EGV + (D == 2 ? N * N : 0))
+           : n_classes<AD>() * DGShape<D, N>::EGS;
 };
 
 // LDS after the staged eigendata: kappa_F per (cell, facet) (variable
@@ -255,8 +380,8 @@ __device__ __forceinline__ const int* mask_lds(const C* sKF) {
 
 // Stage the eigendata (and, per cell, kappa_F of every facet; 0 on the
 // boundary) of the block's cells.
-template <typename T, int D, int N, bool VARK, bool AD = false>
-__device__ __forceinline__ void load_eig(const DGArgs<T>& a, int c0, int nc, CT<T>* sE, CT<T>* sKF) {
+template <typename T, int D, int N, bool VARK, bool AD = false, typename CellsT>
+__device__ __forceinline__ void load_eig(const DGArgs<T>& a, const CellsT& B, CT<T>* sE, CT<T>* sKF) {
   using C = CT<T>;
   using Sh = DGShape<D, N>;
   constexpr int NN = N * N;
@@ -278,20 +403,21 @@ __device__ __forceinline__ void load_eig(const DGArgs<T>& a, int c0, int nc, CT<
     constexpr int IE = (NE + Sh::NT - 1) / Sh::NT;
     constexpr int NK = Sh::CPB * Sh::NF;
     constexpr int IK = (NK + Sh::NT - 1) / Sh::NT;
-    const int ne = nc * D * (NN + N), nk = nc * Sh::NF;
+    const int ne = B.count() * D * (NN + N), nk = B.count() * Sh::NF;
     C ev[IE], k0[IK], k1[IK];
     int msk[IK];
     const bool stored = a.rk == nullptr;  // else rebuilt by recompute_eig
 #pragma unroll
     for (int m = 0; m < IE; ++m) {
       const int i = tid + m * Sh::NT;
-      ev[m] = (stored && i < ne) ? a.eig[(size_t)c0 * D * (NN + N) + i] : C(0);
+      constexpr int R = D * (NN + N);  // words per cell
+      ev[m] = (stored && i < ne) ? a.eig[(size_t)B.cell(i / R) * R + i % R] : C(0);
     }
 #pragma unroll
     for (int m = 0; m < IK; ++m) {
       const int i = tid + m * Sh::NT;
       const int cl = i / Sh::NF, f = i % Sh::NF;
-      const int c = c0 + min(cl, nc - 1);
+      const int c = B.cell(cl);
       const int st = ipow<D>(a.n, f >> 1);
       const int nb = min(max((f & 1) ? c + st : c - st, 0), a.ncell - 1);
       msk[m] = a.bmask[c];
@@ -301,10 +427,7 @@ __device__ __forceinline__ void load_eig(const DGArgs<T>& a, int c0, int nc, CT<
 #pragma unroll
     for (int m = 0; m < IE; ++m) {
       const int i = tid + m * Sh::NT;
-      if (stored && i < ne) {
-        const int e = i % (NN + N), ck = i / (NN + N);
-        sE[ck * Sh::EGS + (e < NN ? e : NN + e)] = ev[m];
-      }
+      if (stored && i < ne) sE[i] = ev[m];
     }
 #pragma unroll
     for (int m = 0; m < IK; ++m) {
@@ -342,11 +465,12 @@ __host__ __device__ constexpr int jac_prev(int s) {
 
 // Fast-diagonalisation data of every staged (cell, axis), rebuilt from kappa
 // (block_recompute; the paper's variant that forms the block inverse anew in
-// each cell and traversal), in the cell's own S | Si | lambda record in LDS:
+// each cell and traversal), in the cell's own S | lambda record in LDS:
 //   L   = kappa_K Khat + sum_s [c1_s (e_s ep_s^T + ep_s e_s^T) + c2_s e_s e_s^T]
 //         (c1, c2) = (-kappa_F/2, sigma_hat kappa_F) interior, (-kappa_K,
 //         2 sigma_hat kappa_K) on the boundary (a boundary facet has kappa_F 0)
-//   A   = W L W^T with W = C^-1, Mhat = C C^T (symmetric), in the Si slot
+//   A   = W L W^T with W = C^-1, Mhat = C C^T (symmetric), in scratch (N^2
+//         words per cell and axis)
 //   parallel Jacobi rotations A <- J^T A J, V <- V J (V in the S slot) until A
 //   is diagonal to working precision (at most 8 sweeps in FP64, 6 in FP32)
 //   lambda = diag(A), S = W^T V, so that L S = Mhat S diag(lambda), S^T Mhat S = I.
@@ -356,7 +480,8 @@ __host__ __device__ constexpr int jac_prev(int s) {
 // a problem are in one wave, whose LDS accesses complete in program order,
 // so a wavefront-scope fence between the phases orders them.
 template <typename T, int D, int N>
-__device__ __forceinline__ void recompute_eig(const DGArgs<T>& a, int nc, CT<T>* sE, const CT<T>* sKF) {
+__device__ __forceinline__ void recompute_eig(const DGArgs<T>& a, int nc, CT<T>* sE, const CT<T>* sKF,
+                                              CT<T>* scratch) {
   using C = CT<T>;
   using Sh = DGShape<D, N>;
   constexpr int NN = N * N;
@@ -386,9 +511,9 @@ __device__ __forceinline__ void recompute_eig(const DGArgs<T>& a, int nc, CT<T>*
     if (__all(!act)) continue;  // nothing for this wave in this round
     const int tt = act ? t : R * CAP;  // idle lanes shadow a valid problem, writing nothing
     const int cl = tt / D, k = tt % D;
-    C* V = sE + tt * Sh::EGS;
-    C* A = V + NN;
-    C* lam = V + 2 * NN;
+    C* V = sE + tt * Sh::EGV;
+    C* A = scratch + tt * NN;
+    C* lam = V + NN;
     const C kK = sKK[cl];
     const C kF0 = sKF[cl * Sh::NF + 2 * k], kF1 = sKF[cl * Sh::NF + 2 * k + 1];
     const bool b0 = kF0 == C(0), b1 = kF1 == C(0);
@@ -571,24 +696,6 @@ __device__ __forceinline__ void recompute_eig(const DGArgs<T>& a, int nc, CT<T>*
   }
 }
 
-// Si = S^T M for every staged (cell, axis) when the data came per cell.
-template <typename T, int D, int N>
-__device__ __forceinline__ void make_si(const DGArgs<T>& a, int nc, CT<T>* sE) {
-  using C = CT<T>;
-  using Sh = DGShape<D, N>;
-  constexpr int NN = N * N;
-  const cptr<C> Mh = as_const(a.ref) + RefOff<N>::M;
-  for (int i = work_tid<D, N>(); i < nc * D * NN; i += Sh::NT) {
-    const int e = i % NN, ck = i / NN;
-    const int r = e / N, col = e % N;
-    const C* S = sE + ck * Sh::EGS;
-    C s = 0;
-#pragma unroll
-    for (int m = 0; m < N; ++m) s += S[m * N + r] * Mh[m * N + col];
-    sE[ck * Sh::EGS + NN + e] = s;
-  }
-}
-
 // Matrix of (cell, axis k) applied to a line: S^T (OP_ST), Si = S^T Mhat
 // (OP_SI), Si^T (OP_SIT) or S (OP_S) of its S | Si | lambda record.  Constant kappa: when
 // every lane of the wave needs the interior class, the even-odd form from
@@ -602,7 +709,20 @@ __device__ __forceinline__ void block_mv(const DGArgs<T>& a, const CT<T>* sE, in
   constexpr bool si = OP == OP_SI || OP == OP_SIT, tr = OP == OP_ST || OP == OP_SIT;
   constexpr int off = si ? N * N : 0;
   if constexpr (VARK) {
-    mv<N, tr>(sE + (cl * D + k) * Sh::EGS + off, in, out);
+    // the record holds S alone: Si = S^T Mhat as two products (Mhat in
+    // even-odd form from the compact table), which leaves LDS for more cells
+    const C* S = sE + (cl * D + k) * Sh::EGV;
+    const cptr<C> Mc = as_const(a.ref) + RefOff<N>::MC;
+    if constexpr (OP == OP_SI) {
+      C x[N];
+#pragma unroll
+      for (int j = 0; j < N; ++j) x[j] = in[j];
+      cs_mv<N>(Mc, x);
+      mv<N, true>(S, x, out);
+    } else {
+      mv<N, OP == OP_ST>(S, in, out);
+      if constexpr (OP == OP_SIT) cs_mv<N>(Mc, out);
+    }
   } else {
     const int cls = IVAR ? 0 : axis_cls<AD>(mask, k);
     // 2D degree 8 in FP32 keeps the plain product: the fixed point of its
@@ -627,7 +747,7 @@ __device__ __forceinline__ void eig_sums(const C* sE, int cl, int mask, int k, i
   using Sh = DGShape<D, N>;
   constexpr int NN = N * N;
   auto lam = [&](int m) -> const C* {
-    return sE + (VARK ? cl * D + m : (IVAR ? 0 : axis_cls<AD>(mask, m))) * Sh::EGS + 2 * NN;
+    return VARK ? sE + (cl * D + m) * Sh::EGV + NN : sE + (IVAR ? 0 : axis_cls<AD>(mask, m)) * Sh::EGS + 2 * NN;
   };
   C ls;
   if constexpr (D == 2)
@@ -747,16 +867,17 @@ __device__ __forceinline__ void nodal_lifts(const DGArgs<T>& a, int cl, int k, i
   }
 }
 
-// Traces (value, outward normal derivative) of a line along axis k, stored
-// straight to the trace buffer for the facets that are not on the boundary.
-template <typename T, int D, int N, bool IVAR = false>
-__device__ __forceinline__ void store_line_traces(const DGArgs<T>& a, T* trout, int c, int mask, int k, int ln,
-                                                  const CT<T> (&u)[N]) {
+// Traces (value g, outward normal derivative d) of a line at its two ends.
+template <typename T, int N>
+__device__ __forceinline__ void line_traces(const DGArgs<T>& a, const CT<T> (&u)[N], CT<T>& g0, CT<T>& d0, CT<T>& g1,
+                                            CT<T>& d1) {
   using C = CT<T>;
-  constexpr int L = DGShape<D, N>::L;
   const cptr<C> ep0 = as_const(a.ref) + RefOff<N>::EP0;
   const cptr<C> ep1 = as_const(a.ref) + RefOff<N>::EP1;
-  C d0 = 0, d1 = 0, g0 = u[0], g1 = u[N - 1];
+  d0 = 0;
+  d1 = 0;
+  g0 = u[0];
+  g1 = u[N - 1];
 #pragma unroll
   for (int j = 0; j < N; ++j) {
     d0 += ep0[j] * u[j];
@@ -773,16 +894,37 @@ __device__ __forceinline__ void store_line_traces(const DGArgs<T>& a, T* trout, 
       g1 += ev1[j] * u[j];
     }
   }
-  if (IVAR || !((mask >> (2 * k)) & 1))
-    *reinterpret_cast<TrPair<T>*>(trout + (((size_t)(2 * k) * a.ncell + c) * L + ln) * 2) = {(T)g0, (T)d0};
-  if (IVAR || !((mask >> (2 * k + 1)) & 1))
-    *reinterpret_cast<TrPair<T>*>(trout + (((size_t)(2 * k + 1) * a.ncell + c) * L + ln) * 2) = {(T)g1, (T)d1};
+}
+
+// The traces of a line along axis k, stored straight to the trace buffer
+// where a neighbour reads them there: on the facets that are not on the
+// boundary (bricks: on the faces of the brick).
+template <typename T, int D, int N, bool IVAR, bool AD>
+__device__ __forceinline__ void store_line_traces(const DGArgs<T>& a, T* trout, const Cells<D, N, AD>& B, int cl, int c,
+                                                  int mask, int k, int ln, const CT<T> (&u)[N]) {
+  using C = CT<T>;
+  constexpr int L = DGShape<D, N>::L;
+  C g0, d0, g1, d1;
+  line_traces<T, N>(a, u, g0, d0, g1, d1);
+  if constexpr (Cells<D, N, AD>::BR) {
+    int l[3];
+    B.local(cl, l);
+    if (B.face(2 * k, l) && !((mask >> (2 * k)) & 1))
+      *reinterpret_cast<TrPair<T>*>(trout + ((size_t)B.own_rec(2 * k, l) * L + ln) * 2) = {(T)g0, (T)d0};
+    if (B.face(2 * k + 1, l) && !((mask >> (2 * k + 1)) & 1))
+      *reinterpret_cast<TrPair<T>*>(trout + ((size_t)B.own_rec(2 * k + 1, l) * L + ln) * 2) = {(T)g1, (T)d1};
+  } else {
+    if (IVAR || !((mask >> (2 * k)) & 1))
+      *reinterpret_cast<TrPair<T>*>(trout + (((size_t)(2 * k) * a.ncell + c) * L + ln) * 2) = {(T)g0, (T)d0};
+    if (IVAR || !((mask >> (2 * k + 1)) & 1))
+      *reinterpret_cast<TrPair<T>*>(trout + (((size_t)(2 * k + 1) * a.ncell + c) * L + ln) * 2) = {(T)g1, (T)d1};
+  }
 }
 
 // Traces along every axis but F of the cell vector staged in sU.
-template <typename T, int D, int N, int F, bool IVAR = false>
-__device__ __forceinline__ void store_other_traces(const DGArgs<T>& a, T* trout, const CT<T>* sU, int cl, int c,
-                                                   int mask, int ln) {
+template <typename T, int D, int N, int F, bool IVAR, bool AD>
+__device__ __forceinline__ void store_other_traces(const DGArgs<T>& a, T* trout, const CT<T>* sU,
+                                                   const Cells<D, N, AD>& B, int cl, int c, int mask, int ln) {
   using C = CT<T>;
   using Sh = DGShape<D, N>;
 #pragma unroll
@@ -792,51 +934,108 @@ __device__ __forceinline__ void store_other_traces(const DGArgs<T>& a, T* trout,
     C u[N];
 #pragma unroll
     for (int j = 0; j < N; ++j) u[j] = sU[base + j * line_stride<N>(k)];
-    store_line_traces<T, D, N, IVAR>(a, trout, c, mask, k, ln, u);
+    store_line_traces<T, D, N, IVAR>(a, trout, B, cl, c, mask, k, ln, u);
+  }
+}
+
+// Staged trace of (local cell, facet) at facet node ln; SPLIT (dual form): the
+// record as [g | q] instead of pairs.
+template <int D, int N, bool SPLIT, typename C>
+__device__ __forceinline__ void put_pair(C* sNB, int cl, int f, int ln, const TrPair<C>& v) {
+  using Sh = DGShape<D, N>;
+  constexpr int L = Sh::L;
+  if constexpr (SPLIT) {
+    C* g = sNB + (cl * Sh::NF + f) * 2 * L + ln;
+    g[0] = v.g;
+    g[L] = v.q;
+  } else {
+    reinterpret_cast<TrPair<C>*>(sNB)[(cl * Sh::NF + f) * L + ln] = v;
   }
 }
 
 // Stages what a traversal of one block needs in LDS: the neighbour traces,
 // the eigendata and the lift coefficients (a barrier must follow before they
-// are read).  The class tables' and traces' loads of a thread are all issued
-// before the first LDS store.  SPLIT (dual form): the facet record as [g | q] instead
-// of pairs.
-template <typename T, int D, int N, bool VARK, bool IVAR, bool AD, bool TRACES, bool SPLIT = false>
-__device__ __forceinline__ void stage_block(const DGArgs<T>& a, const T* tr, int c0, int nc, int cl, int c, int ln,
-                                            bool act, int mask, CT<T>* sNB, CT<T>* sE, CT<T>* sKF) {
+// are read or sW is written).  The loads of a thread are all issued before
+// the first LDS store.  Bricks: the traces at the brick's faces come from the
+// buffer, those inside it from the block's own u (u: the thread's line along
+// axis F), in storage precision as if they had been stored; sW is used.
+template <typename T, int D, int N, bool VARK, bool IVAR, bool AD, bool TRACES, bool SPLIT, int F>
+__device__ __forceinline__ void stage_block(const DGArgs<T>& a, const T* tr, const Cells<D, N, AD>& B, int cl, int c,
+                                            int ln, bool act, int mask, const CT<T> (&u)[N], CT<T>* sNB, CT<T>* sW,
+                                            CT<T>* sE, CT<T>* sKF) {
   using C = CT<T>;
   using Sh = DGShape<D, N>;
   constexpr int L = Sh::L;
+  constexpr bool BR = Cells<D, N, AD>::BR;
   const int tid = work_tid<D, N>();
   TrPair<T> p[2 * D];
-  if constexpr (TRACES) load_pairs<T, D, N, IVAR, AD>(a, tr, c, mask, ln, p);
+  int l[3] = {0, 0, 0};
+  if constexpr (BR && TRACES) {
+    B.local(act ? cl : 0, l);
+#pragma unroll
+    for (int f = 0; f < 2 * D; ++f) {
+      p[f] = {T(0), T(0)};
+      if (act && B.face(f, l) && !((mask >> f) & 1))
+        p[f] = *reinterpret_cast<const TrPair<T>*>(tr + ((size_t)B.nb_rec(f, l) * L + ln) * 2);
+    }
+  } else if constexpr (TRACES) {
+    load_pairs<T, D, N, IVAR, AD>(a, tr, c, mask, ln, p);
+  }
   C* sAB = lift_lds<D, N, VARK>(sKF);
   const C ab = tid < 2 * N ? a.ref[RefOff<N>::AL0 + tid] : C(0);
   static_assert(2 * N <= Sh::NT, "the lift table is staged in one pass");
-  load_eig<T, D, N, VARK, AD>(a, c0, nc, sE, sKF);
+  load_eig<T, D, N, VARK, AD>(a, B, sE, sKF);
   if (tid < 2 * N) sAB[tid] = ab;
-  if constexpr (TRACES) {
-    if (act) {
-#pragma unroll
-      for (int f = 0; f < 2 * D; ++f) {
-        const TrPair<C> v = finish_pair<T, IVAR, AD>(a, p[f], mask, f);
-        if constexpr (SPLIT) {
-          C* g = sNB + (cl * Sh::NF + f) * 2 * L + ln;
-          g[0] = v.g;
-          g[L] = v.q;
-        } else {
-          reinterpret_cast<TrPair<C>*>(sNB)[(cl * Sh::NF + f) * L + ln] = v;
-        }
-      }
-    }
-  }
   if constexpr (VARK) {
-    __syncthreads();
     if (a.rk) {
-      recompute_eig<T, D, N>(a, nc, sE, sKF);
+      __syncthreads();
+      recompute_eig<T, D, N>(a, B.count(), sE, sKF, D == 2 ? sE + Sh::CPB * D * Sh::EGV : sNB);
       __syncthreads();
     }
-    make_si<T, D, N>(a, nc, sE);
+  }
+  if constexpr (BR && TRACES) {
+    if (act) {
+      const int base = cl * Sh::NV + line_base<D, N>(F, ln);
+#pragma unroll
+      for (int j = 0; j < N; ++j) sW[base + j * line_stride<N>(F)] = u[j];
+#pragma unroll
+      for (int f = 0; f < 2 * D; ++f)
+        if (B.face(f, l) && !(IVAR && ((mask >> f) & 1)))
+          put_pair<D, N, SPLIT>(sNB, cl, f, ln, TrPair<C>{(C)p[f].g, (C)p[f].q});
+    }
+  } else if constexpr (TRACES) {
+    if (act) {
+#pragma unroll
+      for (int f = 0; f < 2 * D; ++f) put_pair<D, N, SPLIT>(sNB, cl, f, ln, finish_pair<T, IVAR, AD>(a, p[f], mask, f));
+    }
+  }
+  if constexpr (BR && TRACES) {
+    __syncthreads();
+    if (act) {
+#pragma unroll
+      for (int k = 0; k < D; ++k) {
+        C x[N];
+        const int base = cl * Sh::NV + line_base<D, N>(k, ln);
+#pragma unroll
+        for (int j = 0; j < N; ++j) x[j] = k == F ? u[j] : sW[base + j * line_stride<N>(k)];
+        constexpr int step[3] = {1, Sh::BX, Sh::BX * Sh::BY};
+        C g0, d0, g1, d1;
+        line_traces<T, N>(a, x, g0, d0, g1, d1);
+        // rounded to the storage type, as a stored trace is
+        const TrPair<C> q0 = {(C)(T)g0, (C)(T)d0}, q1 = {(C)(T)g1, (C)(T)d1};
+        // the lower facet's trace is read by the cell below, and vice versa;
+        // the interior-block smoother reads the cell's own, negated, at the
+        // boundary
+        if (!B.face(2 * k, l))
+          put_pair<D, N, SPLIT>(sNB, cl - step[k], 2 * k + 1, ln, q0);
+        else if (IVAR && ((mask >> (2 * k)) & 1))
+          put_pair<D, N, SPLIT>(sNB, cl, 2 * k, ln, TrPair<C>{-q0.g, -q0.q});
+        if (!B.face(2 * k + 1, l))
+          put_pair<D, N, SPLIT>(sNB, cl + step[k], 2 * k, ln, q1);
+        else if (IVAR && ((mask >> (2 * k + 1)) & 1))
+          put_pair<D, N, SPLIT>(sNB, cl, 2 * k + 1, ln, TrPair<C>{-q1.g, -q1.q});
+      }
+    }
   }
 }
 
@@ -877,8 +1076,8 @@ __device__ __forceinline__ int tangential(int k, int pass) {
 // ordered (facet, cell, line) so that a wave mostly sees one facet
 // direction and therefore one matrix.
 template <typename T, int D, int N, bool VARK, bool IVAR, bool AD = false>
-__device__ __forceinline__ void facet_pass(const DGArgs<T>& a, int nc, int pass, CT<T>* sNB, const CT<T>* sE,
-                                           const CT<T>* sKF) {
+__device__ __forceinline__ void facet_pass(const DGArgs<T>& a, const Cells<D, N, AD>& B, int pass, CT<T>* sNB,
+                                           const CT<T>* sE, const CT<T>* sKF) {
   using C = CT<T>;
   using Sh = DGShape<D, N>;
   constexpr int L = Sh::L;
@@ -888,7 +1087,7 @@ __device__ __forceinline__ void facet_pass(const DGArgs<T>& a, int nc, int pass,
   for (int i = work_tid<D, N>(); i < Sh::CPB * Sh::NF * LINES; i += Sh::NT) {
     const int f = i / (Sh::CPB * LINES), rem = i % (Sh::CPB * LINES);
     const int cl = rem / LINES, li = rem % LINES;
-    if (cl >= nc) continue;
+    if (!B.valid(cl)) continue;
     const int k = f >> 1;
     const int t = tangential<D>(k, pass);
     const int st = pass == 0 ? 1 : N;  // node stride along t within the facet
@@ -1015,14 +1214,13 @@ __device__ __forceinline__ void sweep_body(const DGArgs<T>& a, int bx, int by, c
   C* sE = sW + Sh::CPB * Sh::NV;
   C* sKF = sE + EigLDS<D, N, VARK, AD>::SIZE;
 
-  const int c0 = bx * Sh::CPB;
-  const int nc = min(Sh::CPB, a.ncell - c0);
+  const Cells<D, N, AD> B(a, bx);
   const size_t rv = (size_t)by * a.vstride, rt = (size_t)by * a.tstride;
   const int tid = work_tid<D, N>();
   const int cl = tid / L, ln = tid % L;
-  const bool act = tid < Sh::NT && cl < nc;
-  const int c = c0 + (act ? cl : 0);
-  const int mask = cell_mask<AD>(a, c);
+  const bool act = tid < Sh::NT && B.valid(cl);
+  const int c = B.cell(act ? cl : 0);
+  const int mask = B.mask(a, act ? cl : 0, c);
   const int smask = IVAR ? 0 : mask;  // boundary classes of the block solve
   C hf = a.h_fwd;
   if constexpr (AD) {
@@ -1047,7 +1245,7 @@ __device__ __forceinline__ void sweep_body(const DGArgs<T>& a, int bx, int by, c
 #pragma unroll
     for (int j = 0; j < N; ++j) ul[j] = a.u_in[own + j * L];
   }
-  stage_block<T, D, N, VARK, IVAR, AD, !UZERO>(a, a.tr_in + rt, c0, nc, cl, c, ln, act, mask, sNB, sE, sKF);
+  stage_block<T, D, N, VARK, IVAR, AD, !UZERO, false, A>(a, a.tr_in + rt, B, cl, c, ln, act, mask, ul, sNB, sW, sE, sKF);
 #pragma unroll
   for (int j = 0; j < N; ++j) r[j] *= hf;
 
@@ -1084,6 +1282,7 @@ __device__ __forceinline__ void sweep_body(const DGArgs<T>& a, int bx, int by, c
     __syncthreads();
   } else {
     const cptr<C> Mi = as_const(a.ref) + RefOff<N>::MIC;
+    if constexpr (Cells<D, N, AD>::BR) __syncthreads();  // sW free
     if (act) {
       cs_mv<N>(Mi, r);
       put(A, r);
@@ -1136,10 +1335,10 @@ __device__ __forceinline__ void sweep_body(const DGArgs<T>& a, int bx, int by, c
       a.u_out[own + j * L] = t[j];
     }
     put(A, t);
-    store_line_traces<T, D, N, IVAR>(a, trout, c, mask, A, ln, t);
+    store_line_traces<T, D, N, IVAR>(a, trout, B, cl, c, mask, A, ln, t);
   }
   __syncthreads();
-  if (act) store_other_traces<T, D, N, A, IVAR>(a, trout, sW, cl, c, mask, ln);
+  if (act) store_other_traces<T, D, N, A, IVAR>(a, trout, sW, B, cl, c, mask, ln);
 }
 
 // The sweep in dual form (see dual_form): S^T along every axis with the
@@ -1155,15 +1354,14 @@ __device__ __forceinline__ void sweep_dual_body(const DGArgs<T>& a, int bx, int 
   C* sE = sW + Sh::CPB * Sh::NV;
   C* sKF = sE + EigLDS<D, N, VARK, AD>::SIZE;
 
-  const int c0 = bx * Sh::CPB;
-  const int nc = min(Sh::CPB, a.ncell - c0);
+  const Cells<D, N, AD> B(a, bx);
   const size_t rv = (size_t)by * a.vstride, rt = (size_t)by * a.tstride;
   const int tid = work_tid<D, N>();
   const int cl = tid / L, ln = tid % L;
-  const bool act = tid < Sh::NT && cl < nc;
-  const int c = c0 + (act ? cl : 0);
-  const int base0 = cl * Sh::NV + line_base<D, N>(0, ln);
-  const int mask = cell_mask<AD>(a, c);
+  const bool act = tid < Sh::NT && B.valid(cl);
+  const int c = B.cell(act ? cl : 0);
+  const int base0 = line_base<D, N>(0, ln);
+  const int mask = B.mask(a, act ? cl : 0, c);
   const int smask = IVAR ? 0 : mask;  // boundary classes of the block solve
   C hf = a.h_fwd;
   if constexpr (AD) {
@@ -1172,22 +1370,22 @@ __device__ __forceinline__ void sweep_dual_body(const DGArgs<T>& a, int bx, int 
 
   C ul[N], bl[N];
   if (act) {
-    const T* bs = a.b + rv + (size_t)c0 * Sh::NV + base0;
+    const T* bs = a.b + rv + (size_t)c * Sh::NV + base0;
 #pragma unroll
     for (int j = 0; j < N; ++j) bl[j] = bs[j];
     if (!UZERO) {
-      const T* us = a.u_in + rv + (size_t)c0 * Sh::NV + base0;
+      const T* us = a.u_in + rv + (size_t)c * Sh::NV + base0;
 #pragma unroll
       for (int j = 0; j < N; ++j) ul[j] = us[j];
     }
   }
-  stage_block<T, D, N, VARK, IVAR, AD, !UZERO, true>(a, a.tr_in + rt, c0, nc, cl, c, ln, act, mask, sNB, sE, sKF);
+  stage_block<T, D, N, VARK, IVAR, AD, !UZERO, true, 0>(a, a.tr_in + rt, B, cl, c, ln, act, mask, ul, sNB, sW, sE, sKF);
   if (act && ln == 0) mask_lds<D, N, VARK>(sKF)[cl] = mask;
   __syncthreads();
   if constexpr (!UZERO) {
 #pragma unroll
     for (int pass = 0; pass < D - 1; ++pass) {
-      facet_pass<T, D, N, VARK, IVAR, AD>(a, nc, pass, sNB, sE, sKF);
+      facet_pass<T, D, N, VARK, IVAR, AD>(a, B, pass, sNB, sE, sKF);
       __syncthreads();
     }
   }
@@ -1235,7 +1433,7 @@ __device__ __forceinline__ void sweep_dual_body(const DGArgs<T>& a, int bx, int 
       for (int j = 0; j < N; ++j) r[j] = sW[base + j * line_stride<N>(k)];
       block_mv<T, D, N, VARK, IVAR, AD, OP_S>(a, sE, cl, smask, k, r, t);
       if (k == 0) {
-        T* uo = a.u_out + rv + (size_t)c0 * Sh::NV + base0;
+        T* uo = a.u_out + rv + (size_t)c * Sh::NV + base0;
 #pragma unroll
         for (int j = 0; j < N; ++j) {
           const C uo0 = UZERO ? C(0) : ul[j];
@@ -1243,7 +1441,7 @@ __device__ __forceinline__ void sweep_dual_body(const DGArgs<T>& a, int bx, int 
           sW[base + j] = t[j];
           uo[j] = t[j];
         }
-        store_line_traces<T, D, N, IVAR>(a, trout, c, mask, 0, ln, t);
+        store_line_traces<T, D, N, IVAR>(a, trout, B, cl, c, mask, 0, ln, t);
       } else {
 #pragma unroll
         for (int j = 0; j < N; ++j) sW[base + j * line_stride<N>(k)] = t[j];
@@ -1251,7 +1449,7 @@ __device__ __forceinline__ void sweep_dual_body(const DGArgs<T>& a, int bx, int 
     }
     __syncthreads();
   }
-  if (act) store_other_traces<T, D, N, 0, IVAR>(a, trout, sW, cl, c, mask, ln);
+  if (act) store_other_traces<T, D, N, 0, IVAR>(a, trout, sW, B, cl, c, mask, ln);
 }
 
 // ---------------------------------------------------------------------------
@@ -1265,8 +1463,8 @@ __device__ __forceinline__ void sweep_dual_body(const DGArgs<T>& a, int bx, int 
 // definite).
 template <typename C, int D, int N>
 constexpr int build_eig_lds_bytes() {
-  return (int)sizeof(C) * (EigLDS<D, N, true>::SIZE + kappa_lds_entries<D, N, true>()) +
-         (int)sizeof(int) * DGShape<D, N>::CPB;
+  return (int)sizeof(C) *
+         (EigLDS<D, N, true>::SIZE + kappa_lds_entries<D, N, true>() + DGShape<D, N>::CPB * D * N * N);  // scratch
 }
 template <typename C, int D, int N>
 __global__ __launch_bounds__((DGShape<D, N>::BLOCK)) void k_build_eig(DGArgs<C> a) {
@@ -1275,19 +1473,20 @@ __global__ __launch_bounds__((DGShape<D, N>::BLOCK)) void k_build_eig(DGArgs<C> 
   __shared__ __attribute__((aligned(16))) char lds[build_eig_lds_bytes<C, D, N>()];
   C* sE = (C*)lds;
   C* sKF = sE + EigLDS<D, N, true>::SIZE;
-  const int c0 = blockIdx.x * Sh::CPB;
-  const int nc = min(Sh::CPB, a.ncell - c0);
-  load_eig<C, D, N, true>(a, c0, nc, sE, sKF);
+  int id, rhs;
+  block_of_grid<D, N, false>(a, id, rhs);
+  const Cells<D, N, false> B(a, id);
+  load_eig<C, D, N, true>(a, B, sE, sKF);
   __syncthreads();
-  recompute_eig<C, D, N>(a, nc, sE, sKF);
+  recompute_eig<C, D, N>(a, B.count(), sE, sKF, sKF + kappa_lds_entries<D, N, true>());
   __syncthreads();
-  C* out = a.out + (size_t)c0 * D * (NN + N);
+  constexpr int R = D * (NN + N);  // words per cell
   bool bad = false;
-  for (int i = work_tid<D, N>(); i < nc * D * (NN + N); i += Sh::NT) {
-    const int ck = i / (NN + N), e = i % (NN + N);
-    const C v = sE[ck * Sh::EGS + (e < NN ? e : NN + e)];
-    out[i] = v;
-    if (e >= NN && !(v > C(0) && v < C(1e30))) bad = true;
+  for (int i = work_tid<D, N>(); i < B.count() * R; i += Sh::NT) {
+    if (!B.valid(i / R)) continue;
+    const C v = sE[i];
+    a.out[(size_t)B.cell(i / R) * R + i % R] = v;
+    if (i % (NN + N) >= NN && !(v > C(0) && v < C(1e30))) bad = true;
   }
   if (bad && a.flag) atomicOr(a.flag, 1);
 }
@@ -1342,7 +1541,8 @@ struct Mfma16<__bf16> {
 };
 
 template <typename T, int D, int N, bool VARK, bool IVAR, bool TR, bool SCALE>
-__device__ __forceinline__ void mfma_stage(float* sW, const float* sE, const int* sMask, int nc, int k) {
+__device__ __forceinline__ void mfma_stage(float* sW, const float* sE, const int* sMask, int k) {
+  // sMask: boundary mask of each local cell, -1 where there is none
   using Sh = DGShape<D, N>;
   constexpr int NN = N * N;
   constexpr int L = Sh::L;
@@ -1356,7 +1556,7 @@ __device__ __forceinline__ void mfma_stage(float* sW, const float* sE, const int
   // cell record of block-diagonal block b (clamped to a staged cell)
   auto rec = [&](int cl) -> const float* {
     if constexpr (VARK)
-      return sE + (cl * D + k) * Sh::EGS;
+      return sE + (cl * D + k) * Sh::EGV;
     else
       return sE + (IVAR ? 0 : axis_class(sMask[cl], k)) * Sh::EGS;
   };
@@ -1371,14 +1571,15 @@ __device__ __forceinline__ void mfma_stage(float* sW, const float* sE, const int
       const int kk = 4 * kq + j;
       const int kb = kk / N, jj = kk % N;
       const int cl = g * NB + kb;
-      const bool okb = kb < NB && cl < nc && line < L;
-      const int clc = min(cl, nc - 1);
+      const int clc = min(cl, Sh::CPB - 1);
+      const bool okb = kb < NB && cl < Sh::CPB && sMask[clc] >= 0 && line < L;
       const float x = sW[clc * Sh::NV + lb + (jj < N ? jj : 0) * stride];
       bv[j] = okb ? x : 0.f;
       const int rb = c / N, ii = c % N;
       const int cla = g * NB + rb;
-      const bool oka = rb == kb && rb < NB && cla < nc;
-      const float* G = rec(min(cla, nc - 1));
+      const int clac = min(cla, Sh::CPB - 1);
+      const bool oka = rb == kb && rb < NB && cla < Sh::CPB && sMask[clac] >= 0;
+      const float* G = rec(clac);
       const float gv = TR ? G[jj * N + ii] : G[ii * N + jj];
       av[j] = oka ? gv : 0.f;
     }
@@ -1388,21 +1589,22 @@ __device__ __forceinline__ void mfma_stage(float* sW, const float* sE, const int
       const int i = 4 * kq + j;
       const int rb = i / N, ii = i % N;
       const int cl = g * NB + rb;
-      if (rb < NB && cl < nc && line < L) {
+      if (rb < NB && cl < Sh::CPB && line < L && sMask[cl] >= 0) {
         float v = d[j];
         if constexpr (SCALE) {
           // lambda sum of node (line, ii) along the last axis k = D - 1
           const int clc = cl;
+          constexpr int LO = VARK ? NN : 2 * NN;  // lambda within the record
           float ls;
           if constexpr (D == 2) {
-            const float* E0 = VARK ? sE + (clc * D + 0) * Sh::EGS : sE + (IVAR ? 0 : axis_class(sMask[clc], 0)) * Sh::EGS;
-            const float* E1 = VARK ? sE + (clc * D + 1) * Sh::EGS : sE + (IVAR ? 0 : axis_class(sMask[clc], 1)) * Sh::EGS;
-            ls = E0[2 * NN + line] + E1[2 * NN + ii];
+            const float* E0 = VARK ? sE + (clc * D + 0) * Sh::EGV : sE + (IVAR ? 0 : axis_class(sMask[clc], 0)) * Sh::EGS;
+            const float* E1 = VARK ? sE + (clc * D + 1) * Sh::EGV : sE + (IVAR ? 0 : axis_class(sMask[clc], 1)) * Sh::EGS;
+            ls = E0[LO + line] + E1[LO + ii];
           } else {
-            const float* E0 = VARK ? sE + (clc * D + 0) * Sh::EGS : sE + (IVAR ? 0 : axis_class(sMask[clc], 0)) * Sh::EGS;
-            const float* E1 = VARK ? sE + (clc * D + 1) * Sh::EGS : sE + (IVAR ? 0 : axis_class(sMask[clc], 1)) * Sh::EGS;
-            const float* E2 = VARK ? sE + (clc * D + 2) * Sh::EGS : sE + (IVAR ? 0 : axis_class(sMask[clc], 2)) * Sh::EGS;
-            ls = E0[2 * NN + line % N] + E1[2 * NN + line / N] + E2[2 * NN + ii];
+            const float* E0 = VARK ? sE + (clc * D + 0) * Sh::EGV : sE + (IVAR ? 0 : axis_class(sMask[clc], 0)) * Sh::EGS;
+            const float* E1 = VARK ? sE + (clc * D + 1) * Sh::EGV : sE + (IVAR ? 0 : axis_class(sMask[clc], 1)) * Sh::EGS;
+            const float* E2 = VARK ? sE + (clc * D + 2) * Sh::EGV : sE + (IVAR ? 0 : axis_class(sMask[clc], 2)) * Sh::EGS;
+            ls = E0[LO + line % N] + E1[LO + line / N] + E2[LO + ii];
           }
           v *= recip(ls);
         }
@@ -1427,34 +1629,33 @@ __device__ __forceinline__ void sweep_body_mfma(const DGArgs<T>& a, int bx, int 
   C* sKF = sE + EigLDS<D, N, VARK>::SIZE;
   int* sMask = mask_lds<D, N, VARK>(sKF);
 
-  const int c0 = bx * Sh::CPB;
-  const int nc = min(Sh::CPB, a.ncell - c0);
+  const Cells<D, N, false> B(a, bx);
   const size_t rv = (size_t)by * a.vstride, rt = (size_t)by * a.tstride;
   const int tid = work_tid<D, N>();
   const int cl = tid / L, ln = tid % L;
-  const bool act = tid < Sh::NT && cl < nc;
-  const int c = c0 + (act ? cl : 0);
-  const int base0 = cl * Sh::NV + line_base<D, N>(0, ln);
-  const int mask = a.bmask[c];
+  const bool act = tid < Sh::NT && B.valid(cl);
+  const int c = B.cell(act ? cl : 0);
+  const int base0 = line_base<D, N>(0, ln);
+  const int mask = B.mask(a, act ? cl : 0, c);
 
   C ul[N], bl[N];
   if (act) {
-    const T* bs = a.b + rv + (size_t)c0 * Sh::NV + base0;
+    const T* bs = a.b + rv + (size_t)c * Sh::NV + base0;
 #pragma unroll
     for (int j = 0; j < N; ++j) bl[j] = bs[j];
     if (!UZERO) {
-      const T* us = a.u_in + rv + (size_t)c0 * Sh::NV + base0;
+      const T* us = a.u_in + rv + (size_t)c * Sh::NV + base0;
 #pragma unroll
       for (int j = 0; j < N; ++j) ul[j] = us[j];
     }
   }
-  if (tid < nc) sMask[tid] = a.bmask[c0 + tid];
-  stage_block<T, D, N, VARK, IVAR, false, !UZERO, true>(a, a.tr_in + rt, c0, nc, cl, c, ln, act, mask, sNB, sE, sKF);
+  if (ln == 0 && cl < Sh::CPB) sMask[cl] = act ? mask : -1;
+  stage_block<T, D, N, VARK, IVAR, false, !UZERO, true, 0>(a, a.tr_in + rt, B, cl, c, ln, act, mask, ul, sNB, sW, sE, sKF);
   __syncthreads();
   if constexpr (!UZERO) {
 #pragma unroll
     for (int pass = 0; pass < D - 1; ++pass) {
-      facet_pass<T, D, N, VARK, IVAR>(a, nc, pass, sNB, sE, sKF);
+      facet_pass<T, D, N, VARK, IVAR>(a, B, pass, sNB, sE, sKF);
       __syncthreads();
     }
   }
@@ -1479,66 +1680,73 @@ __device__ __forceinline__ void sweep_body_mfma(const DGArgs<T>& a, int bx, int 
     }
     __syncthreads();
     if (k == D - 1)
-      mfma_stage<T, D, N, VARK, IVAR, true, true>(sW, sE, sMask, nc, k);
+      mfma_stage<T, D, N, VARK, IVAR, true, true>(sW, sE, sMask, k);
     else
-      mfma_stage<T, D, N, VARK, IVAR, true, false>(sW, sE, sMask, nc, k);
+      mfma_stage<T, D, N, VARK, IVAR, true, false>(sW, sE, sMask, k);
     __syncthreads();
   }
   // inverse: S along every axis, last axis first
 #pragma unroll
   for (int k = D - 1; k >= 0; --k) {
-    mfma_stage<T, D, N, VARK, IVAR, false, false>(sW, sE, sMask, nc, k);
+    mfma_stage<T, D, N, VARK, IVAR, false, false>(sW, sE, sMask, k);
     __syncthreads();
   }
   // update, store of u and of the traces
   T* trout = a.tr_out + rt;
   if (act) {
-    T* uo = a.u_out + rv + (size_t)c0 * Sh::NV + base0;
+    T* uo = a.u_out + rv + (size_t)c * Sh::NV + base0;
     C t[N];
 #pragma unroll
     for (int j = 0; j < N; ++j) {
       const C uo0 = UZERO ? C(0) : ul[j];
-      t[j] = (C(1) - a.omega) * uo0 + a.omega * sW[base0 + j];
-      sW[base0 + j] = t[j];
+      t[j] = (C(1) - a.omega) * uo0 + a.omega * sW[cl * Sh::NV + base0 + j];
+      sW[cl * Sh::NV + base0 + j] = t[j];
       uo[j] = t[j];
     }
-    store_line_traces<T, D, N, IVAR>(a, trout, c, mask, 0, ln, t);
+    store_line_traces<T, D, N, IVAR>(a, trout, B, cl, c, mask, 0, ln, t);
   }
   __syncthreads();
-  if (act) store_other_traces<T, D, N, 0, IVAR>(a, trout, sW, cl, c, mask, ln);
+  if (act) store_other_traces<T, D, N, 0, IVAR>(a, trout, sW, B, cl, c, mask, ln);
 }
 
-// At least two waves per SIMD for the 3D FP64 degree 7 and 8 sweeps: left to
-// itself the compiler keeps a whole 1D matrix (too large for scalar
-// registers) in vector registers and reaches 256 VGPRs (one wave per SIMD).
-template <typename T, int D, int N>
+// Waves per SIMD asked of the sweep: as many as its LDS allows (160 KB per
+// CU), so that the compiler does not spend registers on reading ahead past
+// that occupancy.  Variable kappa, two waves at degree 7 and 8 (left to itself
+// the compiler keeps whole 1D matrices in registers and reaches one wave).
+template <typename T, int D, int N, bool VARK>
 constexpr int sweep_waves_per_eu() {
-  // the FP64 degree-4 sweep fits 128 VGPRs (four waves per SIMD) without
-  // spills, which the compiler does not choose by itself
-  return (D == 3 && sizeof(CT<T>) == 8 && N >= 8) ? 2 : ((D == 3 && sizeof(CT<T>) == 8 && N == 5) ? 4 : 1);
+  if (D != 3 || sizeof(CT<T>) != 8) return 1;
+  if (VARK) return N >= 8 ? 2 : 1;
+  constexpr int blocks = 160 * 1024 / cell_lds_bytes<T, D, N, false>();
+  constexpr int waves = blocks * (DGShape<D, N>::BLOCK / 64) / 4;
+  return waves < 5 ? waves : 5;
 }
 template <typename T, int D, int N, bool UZERO, bool VARK, bool IVAR, bool MF = false, bool AD = false>
 __global__ __launch_bounds__((DGShape<D, N>::BLOCK))
-__attribute__((amdgpu_waves_per_eu(sweep_waves_per_eu<T, D, N>()))) void k_sweep(DGArgs<T> a) {
+__attribute__((amdgpu_waves_per_eu(sweep_waves_per_eu<T, D, N, VARK>()))) void k_sweep(DGArgs<T> a) {
   __shared__ __attribute__((aligned(16))) char lds[cell_lds_bytes<T, D, N, VARK, AD>()];
+  int id, rhs;
+  block_of_grid<D, N, AD>(a, id, rhs);
   if constexpr (MF)
-    sweep_body_mfma<T, D, N, UZERO, VARK, IVAR>(a, blockIdx.x, blockIdx.y, lds);
+    sweep_body_mfma<T, D, N, UZERO, VARK, IVAR>(a, id, rhs, lds);
   else if constexpr (dual_form<T, D, false>())
-    sweep_dual_body<T, D, N, UZERO, VARK, IVAR, AD>(a, blockIdx.x, blockIdx.y, lds);
+    sweep_dual_body<T, D, N, UZERO, VARK, IVAR, AD>(a, id, rhs, lds);
   else
-    sweep_body<T, D, N, UZERO, VARK, IVAR, AD>(a, blockIdx.x, blockIdx.y, lds);
+    sweep_body<T, D, N, UZERO, VARK, IVAR, AD>(a, id, rhs, lds);
 }
 
 // ---------------------------------------------------------------------------
 // Restriction (E^T)^(x d) of the cell residuals in sW, one axis per pass,
 // through sNB (every lift has been read) into a.out: a coarse DG cell
 // vector, or the 2^d Q1 corner contributions of each cell.
-template <typename T, int D, int N, int NC>
-__device__ __forceinline__ void restrict_body(const DGArgs<T>& a, int c0, int nc, int by, CT<T>* sNB, CT<T>* sW) {
+template <typename T, int D, int N, int NC, bool AD>
+__device__ __forceinline__ void restrict_body(const DGArgs<T>& a, const Cells<D, N, AD>& B, int by, CT<T>* sNB,
+                                              CT<T>* sW) {
   using C = CT<T>;
   using Sh = DGShape<D, N>;
   constexpr int L = Sh::L;
   const int tid = work_tid<D, N>();
+  const int nc = B.count();
   // NC < 0: the coarse node count ncr comes at run time (a.ncd <= N), loops
   // run to N.
   constexpr int NCB = NC > 0 ? NC : N;
@@ -1546,7 +1754,7 @@ __device__ __forceinline__ void restrict_body(const DGArgs<T>& a, int c0, int nc
   const cptr<C> E = as_const(a.ref) + RefOff<N>::E;
   const int NCD = (D == 2) ? ncr * ncr : ncr * ncr * ncr;
   constexpr int NBS = Sh::NF * 2 * L;  // per-cell stride of sNB
-  C* dst = a.out + (size_t)by * a.cstride + (size_t)c0 * NCD;
+  C* out = a.out + (size_t)by * a.cstride;
   // x: sW[cl][..][a] -> sNB[cl][ln][a'] (a' + ncr*ln)
   for (int i = tid; i < nc * L; i += Sh::NT) {
     const int c2 = i / L, l2 = i % L;
@@ -1568,6 +1776,7 @@ __device__ __forceinline__ void restrict_body(const DGArgs<T>& a, int c0, int nc
     // y: sNB[cl][b][a'] -> dst[a' + ncr b']
     for (int i = tid; i < nc * ncr; i += Sh::NT) {
       const int c2 = i / ncr, ac = i % ncr;
+      C* dst = out + (size_t)B.cell(c2) * NCD;
       C x[N];
 #pragma unroll
       for (int j = 0; j < N; ++j) x[j] = sNB[c2 * NBS + ac + ncr * j];
@@ -1577,7 +1786,7 @@ __device__ __forceinline__ void restrict_body(const DGArgs<T>& a, int c0, int nc
           C s = 0;
 #pragma unroll
           for (int j = 0; j < N; ++j) s += E[j * ncr + bc] * x[j];
-          dst[(size_t)c2 * NCD + ac + ncr * bc] = s;
+          dst[ac + ncr * bc] = s;
         }
       }
     }
@@ -1603,6 +1812,8 @@ __device__ __forceinline__ void restrict_body(const DGArgs<T>& a, int c0, int nc
     // z: sW[cl][c][b'][a'] -> dst[a' + ncr b' + ncr^2 c']
     for (int i = tid; i < nc * ncr * ncr; i += Sh::NT) {
       const int c2 = i / (ncr * ncr), rem = i % (ncr * ncr);
+      if (!B.valid(c2)) continue;
+      C* dst = out + (size_t)B.cell(c2) * NCD;
       C x[N];
 #pragma unroll
       for (int j = 0; j < N; ++j) x[j] = sW[c2 * Sh::NV + rem + ncr * ncr * j];
@@ -1612,7 +1823,7 @@ __device__ __forceinline__ void restrict_body(const DGArgs<T>& a, int c0, int nc
           C s = 0;
 #pragma unroll
           for (int j = 0; j < N; ++j) s += E[j * ncr + ccz] * x[j];
-          dst[(size_t)c2 * NCD + rem + ncr * ncr * ccz] = s;
+          dst[rem + ncr * ncr * ccz] = s;
         }
       }
     }
@@ -1621,11 +1832,11 @@ __device__ __forceinline__ void restrict_body(const DGArgs<T>& a, int c0, int nc
 
 // The block's share of p.(A p) in the outer FP64 iteration (kdot).
 template <typename T, int NC, bool RESID>
-__device__ __forceinline__ void apply_partial(const DGArgs<T>& a, double pdot, int bx) {
+__device__ __forceinline__ void apply_partial(const DGArgs<T>& a, double pdot, int block) {
   if constexpr (std::is_same<T, double>::value && NC == 0 && !RESID) {
     if (a.kdot) {
       __shared__ double sh[16];
-      block_partial(pdot, sh, a.kpartial + bx);
+      block_partial(pdot, sh, a.kpartial + block);
     }
   }
 }
@@ -1644,15 +1855,14 @@ __device__ __forceinline__ void apply_dual_body(const DGArgs<T>& a, int bx, int 
   C* sE = sW + Sh::CPB * Sh::NV;
   C* sKF = sE + EigLDS<D, N, VARK, AD>::SIZE;
 
-  const int c0 = bx * Sh::CPB;
-  const int nc = min(Sh::CPB, a.ncell - c0);
+  const Cells<D, N, AD> B(a, bx);
   const size_t rv = (size_t)by * a.vstride, rt = (size_t)by * a.tstride;
   const int tid = work_tid<D, N>();
   const int cl = tid / L, ln = tid % L;
-  const bool act = tid < Sh::NT && cl < nc;
-  const int c = c0 + (act ? cl : 0);
-  const int base0 = cl * Sh::NV + line_base<D, N>(0, ln);
-  const int mask = cell_mask<AD>(a, c);
+  const bool act = tid < Sh::NT && B.valid(cl);
+  const int c = B.cell(act ? cl : 0);
+  const int base0 = line_base<D, N>(0, ln);
+  const int mask = B.mask(a, act ? cl : 0, c);
   const int smask = IVAR ? 0 : mask;  // boundary classes of the block solve
   C ha = a.h_apply;
   if constexpr (AD) {
@@ -1661,22 +1871,22 @@ __device__ __forceinline__ void apply_dual_body(const DGArgs<T>& a, int bx, int 
 
   C ul[N], bl[N];
   if (act) {
-    const T* us = a.u_in + rv + (size_t)c0 * Sh::NV + base0;
+    const T* us = a.u_in + rv + (size_t)c * Sh::NV + base0;
 #pragma unroll
     for (int j = 0; j < N; ++j) ul[j] = us[j];
     if constexpr (RESID) {
-      const T* bs = a.b + rv + (size_t)c0 * Sh::NV + base0;
+      const T* bs = a.b + rv + (size_t)c * Sh::NV + base0;
 #pragma unroll
       for (int j = 0; j < N; ++j) bl[j] = bs[j];
     }
   }
   double pdot = 0.0;  // share of p.(A p) (kdot)
-  stage_block<T, D, N, VARK, IVAR, AD, true, true>(a, a.tr_in + rt, c0, nc, cl, c, ln, act, mask, sNB, sE, sKF);
+  stage_block<T, D, N, VARK, IVAR, AD, true, true, 0>(a, a.tr_in + rt, B, cl, c, ln, act, mask, ul, sNB, sW, sE, sKF);
   if (act && ln == 0) mask_lds<D, N, VARK>(sKF)[cl] = mask;
   __syncthreads();
 #pragma unroll
   for (int pass = 0; pass < D - 1; ++pass) {
-    facet_pass<T, D, N, VARK, IVAR, AD>(a, nc, pass, sNB, sE, sKF);
+    facet_pass<T, D, N, VARK, IVAR, AD>(a, B, pass, sNB, sE, sKF);
     __syncthreads();
   }
 
@@ -1725,7 +1935,7 @@ __device__ __forceinline__ void apply_dual_body(const DGArgs<T>& a, int bx, int 
           t[j] *= ha;
           if constexpr (RESID) t[j] = bl[j] - t[j];
           if constexpr (NC == 0)
-            a.out[rv + (size_t)c0 * Sh::NV + base0 + j] = t[j];
+            a.out[rv + (size_t)c * Sh::NV + base0 + j] = t[j];
           else
             sW[base + j] = t[j];
           if constexpr (std::is_same<T, double>::value && NC == 0 && !RESID) pdot += ul[j] * t[j];
@@ -1737,8 +1947,8 @@ __device__ __forceinline__ void apply_dual_body(const DGArgs<T>& a, int bx, int 
     }
     __syncthreads();
   }
-  apply_partial<T, NC, RESID>(a, pdot, bx);
-  if constexpr (NC != 0) restrict_body<T, D, N, NC>(a, c0, nc, by, sNB, sW);
+  apply_partial<T, NC, RESID>(a, pdot, B.number(bx));
+  if constexpr (NC != 0) restrict_body<T, D, N, NC>(a, B, by, sNB, sW);
 }
 
 // y = A u (RESID: r = b - A u), optionally restricted to the next coarser
@@ -1758,14 +1968,13 @@ __device__ __forceinline__ void apply_body(const DGArgs<T>& a, int bx, int by, c
   C* sE = sW + Sh::CPB * Sh::NV;
   C* sKF = sE + EigLDS<D, N, VARK, AD>::SIZE;
 
-  const int c0 = bx * Sh::CPB;
-  const int nc = min(Sh::CPB, a.ncell - c0);
+  const Cells<D, N, AD> B(a, bx);
   const size_t rv = (size_t)by * a.vstride, rt = (size_t)by * a.tstride;
   const int tid = work_tid<D, N>();
   const int cl = tid / L, ln = tid % L;
-  const bool act = tid < Sh::NT && cl < nc;
-  const int c = c0 + (act ? cl : 0);
-  const int mask = cell_mask<AD>(a, c);
+  const bool act = tid < Sh::NT && B.valid(cl);
+  const int c = B.cell(act ? cl : 0);
+  const int mask = B.mask(a, act ? cl : 0, c);
   const int smask = IVAR ? 0 : mask;  // boundary classes of the block solve
   C ha = a.h_apply;
   if constexpr (AD) {
@@ -1791,7 +2000,7 @@ __device__ __forceinline__ void apply_body(const DGArgs<T>& a, int bx, int by, c
 #pragma unroll
     for (int j = 0; j < N; ++j) bl[j] = a.b[own + j * L];
   }
-  stage_block<T, D, N, VARK, IVAR, AD, true>(a, a.tr_in + rt, c0, nc, cl, c, ln, act, mask, sNB, sE, sKF);
+  stage_block<T, D, N, VARK, IVAR, AD, true, false, A>(a, a.tr_in + rt, B, cl, c, ln, act, mask, ul, sNB, sW, sE, sKF);
   __syncthreads();
   double pdot = 0.0;  // share of p.(A p) (kdot)
 
@@ -1860,8 +2069,8 @@ __device__ __forceinline__ void apply_body(const DGArgs<T>& a, int bx, int by, c
     }
   }
   if constexpr (NC != 0) __syncthreads();
-  apply_partial<T, NC, RESID>(a, pdot, bx);
-  if constexpr (NC != 0) restrict_body<T, D, N, NC>(a, c0, nc, by, sNB, sW);
+  apply_partial<T, NC, RESID>(a, pdot, B.number(bx));
+  if constexpr (NC != 0) restrict_body<T, D, N, NC>(a, B, by, sNB, sW);
 }
 
 // Apply holds u, b and the neighbour traces in registers at once; for the
@@ -1874,10 +2083,12 @@ template <typename T, int D, int N, int NC, bool RESID, bool VARK, bool IVAR, bo
 __global__ __launch_bounds__((DGShape<D, N>::BLOCK))
 __attribute__((amdgpu_waves_per_eu(apply_waves_per_eu<T, N>()))) void k_apply(DGArgs<T> a) {
   __shared__ __attribute__((aligned(16))) char lds[cell_lds_bytes<T, D, N, VARK, AD>()];
+  int id, rhs;
+  block_of_grid<D, N, AD>(a, id, rhs);
   if constexpr (dual_form<T, D, RESID>())
-    apply_dual_body<T, D, N, NC, RESID, VARK, IVAR, AD>(a, blockIdx.x, blockIdx.y, lds);
+    apply_dual_body<T, D, N, NC, RESID, VARK, IVAR, AD>(a, id, rhs, lds);
   else
-    apply_body<T, D, N, NC, RESID, VARK, IVAR, AD>(a, blockIdx.x, blockIdx.y, lds);
+    apply_body<T, D, N, NC, RESID, VARK, IVAR, AD>(a, id, rhs, lds);
 }
 
 // ---------------------------------------------------------------------------
@@ -1901,14 +2112,14 @@ __device__ __forceinline__ void prolong_body(const DGArgs<T>& a, int bx, int by,
   C* sW = sU + Sh::CPB * Sh::NV;
   C* sNB = sW + Sh::CPB * Sh::NV;
 
-  const int c0 = bx * Sh::CPB;
-  const int nc = min(Sh::CPB, a.ncell - c0);
+  const Cells<D, N, AD> B(a, bx);
   const size_t rv = (size_t)by * a.vstride, rt = (size_t)by * a.tstride;
   const int tid = work_tid<D, N>();
   const int cl = tid / L, ln = tid % L;
-  const bool act = tid < Sh::NT && cl < nc;
-  const int c = c0 + (act ? cl : 0);
-  const int mask = cell_mask<AD>(a, c);
+  const bool act = tid < Sh::NT && B.valid(cl);
+  const int c = B.cell(act ? cl : 0);
+  const int mask = B.mask(a, act ? cl : 0, c);
+  const int nc = B.count();
   // NC < 0: coarse node count ncr at run time (a.ncd <= N); loops run to
   // NCB = N with the entries past ncr skipped
   constexpr int NCB = NC > 0 ? NC : (NC < 0 ? N : 1);
@@ -1940,13 +2151,14 @@ __device__ __forceinline__ void prolong_body(const DGArgs<T>& a, int bx, int by,
     const C* cs = a.coarse + (size_t)by * a.cstride;
     if (a.coarse_cg != 1) {
       // a coarse DG cell vector, or the Q1 corner values of every cell
-      for (int i = tid; i < nc * NCD; i += Sh::NT) sW[(i / NCD) * Sh::NV + i % NCD] = cs[(size_t)c0 * NCD + i];
+      for (int i = tid; i < nc * NCD; i += Sh::NT)
+        sW[(i / NCD) * Sh::NV + i % NCD] = cs[(size_t)B.cell(i / NCD) * NCD + i % NCD];
     } else {
       // Q1 corner values of each cell from the interior-vertex vector
       const int nv = a.n - 1;
       for (int i = tid; i < nc * NCD; i += Sh::NT) {
         const int c2 = i / NCD, corner = i % NCD;
-        const int cc = c0 + c2;
+        const int cc = B.cell(c2);
         int x[3];
         x[0] = cc % a.n;
         const int rr = cc / a.n;
@@ -2038,126 +2250,138 @@ __device__ __forceinline__ void prolong_body(const DGArgs<T>& a, int bx, int by,
     }
 #pragma unroll
     for (int j = 0; j < N; ++j) sU[cl * Sh::NV + lb + j * ST] = u[j];
-    store_line_traces<T, D, N, IVAR>(a, trout, c, mask, F, ln, u);
+    store_line_traces<T, D, N, IVAR>(a, trout, B, cl, c, mask, F, ln, u);
   }
   __syncthreads();
-  if (act) store_other_traces<T, D, N, F, IVAR>(a, trout, sU, cl, c, mask, ln);
+  if (act) store_other_traces<T, D, N, F, IVAR>(a, trout, sU, B, cl, c, mask, ln);
 }
 
 template <typename T, int D, int N, int NC, bool IVAR, bool AD = false>
 __global__ __launch_bounds__((DGShape<D, N>::BLOCK)) void k_prolong(DGArgs<T> a) {
   __shared__ __attribute__((aligned(16))) char lds[prolong_lds_bytes<T, D, N, NC>()];
-  prolong_body<T, D, N, NC, IVAR, AD>(a, blockIdx.x, blockIdx.y, lds);
+  int id, rhs;
+  block_of_grid<D, N, AD>(a, id, rhs);
+  prolong_body<T, D, N, NC, IVAR, AD>(a, id, rhs, lds);
+}
+
+
+// ---------------------------------------------------------------- launchers
+// Kinds of traversal that this shape serves (HPMG_TILE): constant kappa,
+// variable kappa, adaptive meshes.
+template <typename T, int D>
+constexpr bool serves_const() {
+  return D == 2 || HPMG_TILE == 0 || (HPMG_TILE == 3 && sizeof(T) == 2);
+}
+template <typename T, int D>
+constexpr bool serves_vark() {
+  return D == 2 || HPMG_TILE == 2 || (HPMG_TILE == 3 && sizeof(T) == 2);
+}
+template <typename T, int D>
+constexpr bool serves_adapt() {
+  return sizeof(T) >= 4 && (D == 2 || HPMG_TILE == 3);
+}
+
+// One block per brick (x layers times right-hand sides, y, z) or run of cells
+// (blocks, right-hand sides); see block_of_grid.
+template <int D, int N, typename T>
+dim3 block_grid(const DGArgs<T>& a, int nrhs) {
+  using Sh = DGShape<D, N>;
+  if (Cells<D, N, false>::BR)
+    return dim3(brick_layers(a.n, Sh::BX) * nrhs, brick_layers(a.n, Sh::BY), brick_layers(a.n, Sh::BZ));
+  return dim3((a.ncell + Sh::CPB - 1) / Sh::CPB, nrhs);
+}
+
+template <typename C, int D, int N>
+bool launch_build_eig(const DGArgs<C>& a, hipStream_t s) {
+  if constexpr (serves_vark<C, D>()) {
+    hipLaunchKernelGGL((k_build_eig<C, D, N>), (block_grid<D, N>(a, 1)), dim3(DGShape<D, N>::NT), 0, s, a);
+    return true;
+  }
+  return false;
+}
+
+template <typename T, int D, int N, bool UZERO>
+bool launch_sweep_u(const DGArgs<T>& a, int nrhs, hipStream_t s) {
+  using Sh = DGShape<D, N>;
+  const dim3 grid = block_grid<D, N>(a, nrhs);
+  // matrix cores (16-bit storage, 3D): whole waves per block
+  constexpr bool MF = sizeof(T) == 2 && D == 3;
+  const dim3 blk(MF && a.mfma ? Sh::BLOCK : Sh::NT);
+  if (a.adapt) {
+    if constexpr (serves_adapt<T, D>()) {
+      hipLaunchKernelGGL((k_sweep<T, D, N, UZERO, false, false, false, true>), grid, blk, 0, s, a);
+      return true;
+    }
+  } else if (a.vark) {
+    if constexpr (serves_vark<T, D>()) {
+      if (MF && a.mfma)
+        hipLaunchKernelGGL((k_sweep<T, D, N, UZERO, true, false, MF>), grid, blk, 0, s, a);
+      else
+        hipLaunchKernelGGL((k_sweep<T, D, N, UZERO, true, false>), grid, blk, 0, s, a);
+      return true;
+    }
+  } else if constexpr (serves_const<T, D>()) {
+    if (MF && a.mfma && a.ivar)
+      hipLaunchKernelGGL((k_sweep<T, D, N, UZERO, false, true, MF>), grid, blk, 0, s, a);
+    else if (MF && a.mfma)
+      hipLaunchKernelGGL((k_sweep<T, D, N, UZERO, false, false, MF>), grid, blk, 0, s, a);
+    else if (a.ivar)
+      hipLaunchKernelGGL((k_sweep<T, D, N, UZERO, false, true>), grid, blk, 0, s, a);
+    else
+      hipLaunchKernelGGL((k_sweep<T, D, N, UZERO, false, false>), grid, blk, 0, s, a);
+    return true;
+  }
+  return false;
+}
+template <typename T, int D, int N>
+bool launch_sweep(const DGArgs<T>& a, int nrhs, bool uzero, hipStream_t s) {
+  return uzero ? launch_sweep_u<T, D, N, true>(a, nrhs, s) : launch_sweep_u<T, D, N, false>(a, nrhs, s);
+}
+
+template <typename T, int D, int N, int NC, bool RESID>
+bool launch_apply_r(const DGArgs<T>& a, int nrhs, hipStream_t s) {
+  const dim3 grid = block_grid<D, N>(a, nrhs), blk(DGShape<D, N>::NT);
+  if (a.adapt) {
+    if constexpr (serves_adapt<T, D>()) {
+      hipLaunchKernelGGL((k_apply<T, D, N, NC, RESID, false, false, true>), grid, blk, 0, s, a);
+      return true;
+    }
+  } else if (a.vark) {
+    if constexpr (serves_vark<T, D>()) {
+      hipLaunchKernelGGL((k_apply<T, D, N, NC, RESID, true, false>), grid, blk, 0, s, a);
+      return true;
+    }
+  } else if constexpr (serves_const<T, D>()) {
+    if (a.ivar)
+      hipLaunchKernelGGL((k_apply<T, D, N, NC, RESID, false, true>), grid, blk, 0, s, a);
+    else
+      hipLaunchKernelGGL((k_apply<T, D, N, NC, RESID, false, false>), grid, blk, 0, s, a);
+    return true;
+  }
+  return false;
+}
+template <typename T, int D, int N, int NC>
+bool launch_apply(const DGArgs<T>& a, int nrhs, bool resid, hipStream_t s) {
+  return resid ? launch_apply_r<T, D, N, NC, true>(a, nrhs, s) : launch_apply_r<T, D, N, NC, false>(a, nrhs, s);
+}
+
+template <typename T, int D, int N, int NC>
+bool launch_prolong(const DGArgs<T>& a, int nrhs, hipStream_t s) {
+  const dim3 grid = block_grid<D, N>(a, nrhs), blk(DGShape<D, N>::NT);
+  if (a.adapt) {
+    if constexpr (serves_adapt<T, D>()) {
+      hipLaunchKernelGGL((k_prolong<T, D, N, NC, false, true>), grid, blk, 0, s, a);
+      return true;
+    }
+  } else if constexpr (serves_const<T, D>() || serves_vark<T, D>()) {
+    if (a.ivar)
+      hipLaunchKernelGGL((k_prolong<T, D, N, NC, true>), grid, blk, 0, s, a);
+    else
+      hipLaunchKernelGGL((k_prolong<T, D, N, NC, false>), grid, blk, 0, s, a);
+    return true;
+  }
+  return false;
 }
 
 }  // namespace HPMG_DGK
-
-#if HPMG_TILE == 0
-
-template <typename C, int D, int N>
-void launch_build_eig(const DGArgs<C>& a, hipStream_t s) {
-  using Sh = DGShape<D, N>;
-  hipLaunchKernelGGL((dgk::k_build_eig<C, D, N>), dim3((a.ncell + Sh::CPB - 1) / Sh::CPB), dim3(Sh::NT), 0, s, a);
-}
-
-// Matrix-core sweep (16-bit storage, 3D): whole waves per block.
-template <typename T, int D, int N>
-bool launch_sweep_mfma(const DGArgs<T>& a, dim3 grid, bool uzero, hipStream_t s) {
-  if constexpr (sizeof(T) == 2 && D == 3) {
-    using Sh = DGShape<D, N>;
-    const dim3 blk(Sh::BLOCK);
-    if (a.vark) {
-      if (uzero)
-        hipLaunchKernelGGL((dgk::k_sweep<T, D, N, true, true, false, true>), grid, blk, 0, s, a);
-      else
-        hipLaunchKernelGGL((dgk::k_sweep<T, D, N, false, true, false, true>), grid, blk, 0, s, a);
-    } else if (a.ivar) {
-      if (uzero)
-        hipLaunchKernelGGL((dgk::k_sweep<T, D, N, true, false, true, true>), grid, blk, 0, s, a);
-      else
-        hipLaunchKernelGGL((dgk::k_sweep<T, D, N, false, false, true, true>), grid, blk, 0, s, a);
-    } else {
-      if (uzero)
-        hipLaunchKernelGGL((dgk::k_sweep<T, D, N, true, false, false, true>), grid, blk, 0, s, a);
-      else
-        hipLaunchKernelGGL((dgk::k_sweep<T, D, N, false, false, false, true>), grid, blk, 0, s, a);
-    }
-    return true;
-  } else {
-    return false;
-  }
-}
-
-template <typename T, int D, int N>
-void launch_sweep(const DGArgs<T>& a, int nrhs, bool uzero, hipStream_t s) {
-  using Sh = DGShape<D, N>;
-  dim3 grid((a.ncell + Sh::CPB - 1) / Sh::CPB, nrhs);
-  if (a.mfma && launch_sweep_mfma<T, D, N>(a, grid, uzero, s)) return;
-  if (a.adapt) {  // adaptive meshes: FP64 and FP32 storage
-    if constexpr (sizeof(T) >= 4) {
-      if (uzero)
-        hipLaunchKernelGGL((dgk::k_sweep<T, D, N, true, false, false, false, true>), grid, dim3(Sh::NT), 0, s, a);
-      else
-        hipLaunchKernelGGL((dgk::k_sweep<T, D, N, false, false, false, false, true>), grid, dim3(Sh::NT), 0, s, a);
-    }
-  } else if (a.vark) {
-    if (uzero)
-      hipLaunchKernelGGL((dgk::k_sweep<T, D, N, true, true, false>), grid, dim3(Sh::NT), 0, s, a);
-    else
-      hipLaunchKernelGGL((dgk::k_sweep<T, D, N, false, true, false>), grid, dim3(Sh::NT), 0, s, a);
-  } else if (a.ivar) {
-    if (uzero)
-      hipLaunchKernelGGL((dgk::k_sweep<T, D, N, true, false, true>), grid, dim3(Sh::NT), 0, s, a);
-    else
-      hipLaunchKernelGGL((dgk::k_sweep<T, D, N, false, false, true>), grid, dim3(Sh::NT), 0, s, a);
-  } else {
-    if (uzero)
-      hipLaunchKernelGGL((dgk::k_sweep<T, D, N, true, false, false>), grid, dim3(Sh::NT), 0, s, a);
-    else
-      hipLaunchKernelGGL((dgk::k_sweep<T, D, N, false, false, false>), grid, dim3(Sh::NT), 0, s, a);
-  }
-}
-
-template <typename T, int D, int N, int NC>
-void launch_apply(const DGArgs<T>& a, int nrhs, bool resid, hipStream_t s) {
-  using Sh = DGShape<D, N>;
-  dim3 grid((a.ncell + Sh::CPB - 1) / Sh::CPB, nrhs);
-  if (a.adapt) {
-    if constexpr (sizeof(T) >= 4) {
-      if (resid)
-        hipLaunchKernelGGL((dgk::k_apply<T, D, N, NC, true, false, false, true>), grid, dim3(Sh::NT), 0, s, a);
-      else
-        hipLaunchKernelGGL((dgk::k_apply<T, D, N, NC, false, false, false, true>), grid, dim3(Sh::NT), 0, s, a);
-    }
-  } else if (a.vark) {
-    if (resid)
-      hipLaunchKernelGGL((dgk::k_apply<T, D, N, NC, true, true, false>), grid, dim3(Sh::NT), 0, s, a);
-    else
-      hipLaunchKernelGGL((dgk::k_apply<T, D, N, NC, false, true, false>), grid, dim3(Sh::NT), 0, s, a);
-  } else if (a.ivar) {
-    if (resid)
-      hipLaunchKernelGGL((dgk::k_apply<T, D, N, NC, true, false, true>), grid, dim3(Sh::NT), 0, s, a);
-    else
-      hipLaunchKernelGGL((dgk::k_apply<T, D, N, NC, false, false, true>), grid, dim3(Sh::NT), 0, s, a);
-  } else {
-    if (resid)
-      hipLaunchKernelGGL((dgk::k_apply<T, D, N, NC, true, false, false>), grid, dim3(Sh::NT), 0, s, a);
-    else
-      hipLaunchKernelGGL((dgk::k_apply<T, D, N, NC, false, false, false>), grid, dim3(Sh::NT), 0, s, a);
-  }
-}
-
-template <typename T, int D, int N, int NC>
-void launch_prolong(const DGArgs<T>& a, int nrhs, hipStream_t s) {
-  using Sh = DGShape<D, N>;
-  dim3 grid((a.ncell + Sh::CPB - 1) / Sh::CPB, nrhs);
-  if (a.adapt) {
-    if constexpr (sizeof(T) >= 4) hipLaunchKernelGGL((dgk::k_prolong<T, D, N, NC, false, true>), grid, dim3(Sh::NT), 0, s, a);
-  } else if (a.ivar)
-    hipLaunchKernelGGL((dgk::k_prolong<T, D, N, NC, true>), grid, dim3(Sh::NT), 0, s, a);
-  else
-    hipLaunchKernelGGL((dgk::k_prolong<T, D, N, NC, false>), grid, dim3(Sh::NT), 0, s, a);
-}
-
-#endif  // HPMG_TILE == 0
 }  // namespace hpmg

@@ -238,7 +238,17 @@ void build_dg_level(hpmg_ctx* h, DGLevel& L, const hpmg::Basis1D& B, const hpmg:
   const size_t ncell = h->adapt ? (size_t)h->amesh[L.am].ncell : (size_t)h->ncell;
   const size_t nif = h->adapt ? (size_t)h->amesh[L.am].nif : 0;
   L.ndof = ncell * ipow(N, D);
-  L.trsize = ((size_t)2 * D * ncell + nif * (h->mif + 1)) * 2 * ipow(N, D - 1);
+  // facet records of a trace buffer: one per cell and facet in runs of cells
+  // (2D, adaptive meshes with their hanging-facet slots, 16-bit storage), the
+  // faces of the bricks in 3D (the batched driver's tile variants share them)
+  size_t nrec = (size_t)2 * D * ncell + nif * (h->mif + 1);
+  L.trsize16 = nrec * 2 * ipow(N, D - 1);
+  if (D == 3 && !h->adapt) {
+    nrec = 0;
+    for (int V = h->vark ? 2 : 0; V < (h->vark ? 3 : hpmg::kTileVariants); ++V)
+      nrec = std::max(nrec, (size_t)hpmg::brick_records(h->n, N, V));
+  }
+  L.trsize = nrec * 2 * ipow(N, D - 1);
   // eigendata of the cell blocks
   const int EGS = 2 * NN + N;
   // compact even-odd tables of S and Si^T of the interior class (constant kappa)
@@ -1190,7 +1200,7 @@ void ensure_traces(hpmg_ctx* h) {
   DGData<T>& d = data<T>(L);
   if (d.tr[0]) return;
   const size_t R = h->opt.max_rhs;
-  for (int k = 0; k < 2; ++k) d.tr[k] = (T*)h->mem.alloc(L.trsize * R * sizeof(T));
+  for (int k = 0; k < 2; ++k) d.tr[k] = (T*)h->mem.alloc(L.trsize16 * R * sizeof(T));
 }
 
 // Calls f with a null T* for the storage type of dtype (16-bit traces
@@ -1356,8 +1366,10 @@ void fcg_iteration(hpmg_ctx* h, double rms, int restart, hipStream_t s) {
   aa.kdot = 1;
   aa.kpartial = h->kpartial;
   dg_run(h, hpmg::OP_APPLY, aa, L0.N, 1, 0, s);
-  const int cpb = hpmg::cells_per_block(h->dim, L0.N);
-  hpmg::krylov_alpha(h->kpartial, (h->ncell + cpb - 1) / cpb, h->scal, s);
+  const int cpb = hpmg::cells_per_block_v(h->dim, L0.N, 3);
+  const int nblk = h->dim == 3 && !h->adapt ? (int)hpmg::brick_blocks(h->n, L0.N, h->vark ? 2 : 0)
+                                            : (h->ncell + cpb - 1) / cpb;
+  hpmg::krylov_alpha(h->kpartial, nblk, h->scal, s);
   hpmg::krylov_update_ur(nd, h->ug, h->r, h->rold, h->pv, h->q, h->partial, h->scal, r32_next, s);
   HIPCHK(hipMemcpyAsync(h->host_scal, h->scal, 16 * sizeof(double), hipMemcpyDeviceToHost, s));
 }

@@ -27,8 +27,8 @@ enum DGOp {
 // NC = floor(p/2)+1 nodes while floor(p/2) >= 2, else Q1 (NC = 2).
 constexpr int nc_next(int N) { return ((N - 1) / 2 >= 2) ? (N - 1) / 2 + 1 : 2; }
 
-// Returns false if (dim, N) has no compiled kernel.  One definition per
-// (dimension, storage type) in dg_inst_<dim>d_<type>.hip.
+// Returns false if (dim, N) has no compiled kernel for the operation.  One
+// definition per (dimension, storage type) in dg_inst_<dim>d_<type>.hip.
 bool dg_dispatch2(int N, int op, const DGArgs<double>& a, int nrhs, int flag, hipStream_t s);
 bool dg_dispatch2(int N, int op, const DGArgs<float>& a, int nrhs, int flag, hipStream_t s);
 bool dg_dispatch2(int N, int op, const DGArgs<_Float16>& a, int nrhs, int flag, hipStream_t s);
@@ -37,6 +37,11 @@ bool dg_dispatch3(int N, int op, const DGArgs<double>& a, int nrhs, int flag, hi
 bool dg_dispatch3(int N, int op, const DGArgs<float>& a, int nrhs, int flag, hipStream_t s);
 bool dg_dispatch3(int N, int op, const DGArgs<_Float16>& a, int nrhs, int flag, hipStream_t s);
 bool dg_dispatch3(int N, int op, const DGArgs<__bf16>& a, int nrhs, int flag, hipStream_t s);
+// the parts of dg_dispatch3 with another block shape: variable kappa, adaptive meshes
+bool dg_dispatch3_vark(int N, int op, const DGArgs<double>& a, int nrhs, int flag, hipStream_t s);
+bool dg_dispatch3_vark(int N, int op, const DGArgs<float>& a, int nrhs, int flag, hipStream_t s);
+bool dg_dispatch3_runs(int N, int op, const DGArgs<double>& a, int nrhs, int flag, hipStream_t s);
+bool dg_dispatch3_runs(int N, int op, const DGArgs<float>& a, int nrhs, int flag, hipStream_t s);
 template <typename T>
 inline bool dg_dispatch(int dim, int N, int op, const DGArgs<T>& a, int nrhs, int flag, hipStream_t s) {
   return dim == 2 ? dg_dispatch2(N, op, a, nrhs, flag, s) : dg_dispatch3(N, op, a, nrhs, flag, s);

@@ -70,7 +70,9 @@ extern "C" hpmg_status hpmg_smooth_noalloc(hpmg_handle h, hpmg_dtype dtype, void
     h->trace_state[dtype] = -1;  // u changes; the handle's own traces no longer describe it
     DGLevel& L = h->dg[0];
     const size_t esz = dtype == HPMG_F64 ? 8 : (dtype == HPMG_F32 ? 4 : 2);
-    const size_t per = round_up_256(L.trsize * (size_t)nrhs * esz);
+    // one record per cell and facet (trsize16), the documented bound: the
+    // brick faces of FP64 and FP32 in 3D are fewer
+    const size_t per = round_up_256(L.trsize16 * (size_t)nrhs * esz);
     if (2 * per > kScratchBytes)
       throw HpmgError(HPMG_E_INVALID, "hpmg_smooth_noalloc: the two trace buffers need " + std::to_string(2 * per) +
                                           " bytes, more than the " + std::to_string(kScratchBytes) +
