@@ -91,10 +91,23 @@ struct DGShapeV {
   static constexpr int L = (D == 2) ? N : N * N;  // lines per cell = nodes per facet
   static constexpr int NV = L * N;                // nodes per cell
   static constexpr int NF = 2 * D;                // facets per cell
+  // LDS row of a cell along x, padded for N = 4 and 8 so that the lines of a
+  // wave along every axis fall into different banks (N = 8 in FP32: 8 lanes per
+  // bank without it; FP64 apply 32^3 169 -> 143 us, FP32 90 -> 71 us; N = 4,
+  // 64^3, 165 -> 147 and 90 -> 74 us; N = 6, two lanes per bank, 2% slower with
+  // it), and nodes of a cell with the padding
+  static constexpr int SY = N + (N % 4 == 0 ? 1 : 0), NVP = (D == 2 ? 1 : N) * N * SY;
   static constexpr int BX = brick(N, V).x, BY = brick(N, V).y, BZ = brick(N, V).z;  // 3D
   static constexpr int CPB = cells_per_block_v(D, N, V);
   static constexpr int NT = CPB * L;
-  static constexpr int BLOCK = (NT + 63) / 64 * 64;  // launch bound: whole waves
+  // 3D cells whose L lines fill (nearly) whole waves, CPW cells in each (degree
+  // 1, 2, 3 and 7: 16, 7, 4 and 1): no cell is split between waves, so the
+  // steps of a traversal that exchange lines within a cell need no barrier
+  // (cell_sync)
+  static constexpr int CPW = (D == 3 && L <= 64) ? 64 / L : 1;
+  static constexpr bool WAVE = D == 3 && L <= 64 && 64 - CPW * L <= 1;
+  static constexpr int BLOCK = WAVE ? (CPB + CPW - 1) / CPW * 64 : (NT + 63) / 64 * 64;  // whole waves
+  static constexpr int THREADS = WAVE ? BLOCK : NT;  // launched
   static constexpr int EGS = 2 * N * N + N;       // S, Si, lambda of one direction (class tables)
   static constexpr int EGV = N * N + N;           // S, lambda of one direction (per cell, variable kappa)
 };

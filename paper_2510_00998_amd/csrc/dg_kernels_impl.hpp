@@ -64,6 +64,22 @@ __device__ __forceinline__ constexpr int line_stride(int k) {
   return k == 0 ? 1 : (k == 1 ? N : N * N);
 }
 
+// The same for the cell data in LDS (padded rows, see DGShapeV::SY).
+template <int D, int N>
+__device__ __forceinline__ int lds_line(int cl, int k, int ln) {
+  using Sh = DGShape<D, N>;
+  if constexpr (D == 2) {
+    return cl * Sh::NVP + (k == 0 ? Sh::SY * ln : ln);
+  } else {
+    const int i0 = ln % N, i1 = ln / N;
+    return cl * Sh::NVP + (k == 0 ? Sh::SY * i0 + N * Sh::SY * i1 : (k == 1 ? i0 + N * Sh::SY * i1 : i0 + Sh::SY * i1));
+  }
+}
+template <int D, int N>
+__device__ __forceinline__ constexpr int lds_stride(int k) {
+  return k == 0 ? 1 : (k == 1 ? DGShape<D, N>::SY : N * DGShape<D, N>::SY);
+}
+
 // Read-only data addressed uniformly across a wave: the constant address
 // space lets the compiler fetch it with scalar loads into SGPRs.
 template <typename T>
@@ -203,6 +219,35 @@ __device__ __forceinline__ float recip(float d) {
 template <int D, int N>
 __device__ __forceinline__ int work_tid() {
   return threadIdx.x < DGShape<D, N>::NT ? (int)threadIdx.x : (1 << 28);
+}
+
+// Local cell and line of the thread (a cell index past the block's cells for
+// a thread without a line).
+template <int D, int N>
+__device__ __forceinline__ void cell_line(int& cl, int& ln) {
+  using Sh = DGShape<D, N>;
+  if constexpr (Sh::WAVE) {
+    const int lane = threadIdx.x & 63;
+    cl = lane < Sh::CPW * Sh::L ? (int)(threadIdx.x >> 6) * Sh::CPW + lane / Sh::L : (1 << 20);
+    ln = lane % Sh::L;
+  } else {
+    const int tid = work_tid<D, N>();
+    cl = tid / Sh::L;
+    ln = tid % Sh::L;
+  }
+}
+
+// Barrier between two steps that exchange lines within each cell: of the
+// block, or, where no cell is split between waves, of the wave, whose LDS
+// accesses complete in program order (the fence keeps the compiler's).
+template <int D, int N>
+__device__ __forceinline__ void cell_sync() {
+  if constexpr (DGShape<D, N>::WAVE) {
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  } else {
+    __syncthreads();
+  }
 }
 
 // Boundary mask of a cell (bit f = 2k + side set: facet f on the domain
@@ -930,10 +975,10 @@ __device__ __forceinline__ void store_other_traces(const DGArgs<T>& a, T* trout,
 #pragma unroll
   for (int k = 0; k < D; ++k) {
     if (k == F) continue;
-    const int base = cl * Sh::NV + line_base<D, N>(k, ln);
+    const int base = lds_line<D, N>(cl, k, ln);
     C u[N];
 #pragma unroll
-    for (int j = 0; j < N; ++j) u[j] = sU[base + j * line_stride<N>(k)];
+    for (int j = 0; j < N; ++j) u[j] = sU[base + j * lds_stride<D, N>(k)];
     store_line_traces<T, D, N, IVAR>(a, trout, B, cl, c, mask, k, ln, u);
   }
 }
@@ -995,9 +1040,9 @@ __device__ __forceinline__ void stage_block(const DGArgs<T>& a, const T* tr, con
   }
   if constexpr (BR && TRACES) {
     if (act) {
-      const int base = cl * Sh::NV + line_base<D, N>(F, ln);
+      const int base = lds_line<D, N>(cl, F, ln);
 #pragma unroll
-      for (int j = 0; j < N; ++j) sW[base + j * line_stride<N>(F)] = u[j];
+      for (int j = 0; j < N; ++j) sW[base + j * lds_stride<D, N>(F)] = u[j];
 #pragma unroll
       for (int f = 0; f < 2 * D; ++f)
         if (B.face(f, l) && !(IVAR && ((mask >> f) & 1)))
@@ -1015,9 +1060,9 @@ __device__ __forceinline__ void stage_block(const DGArgs<T>& a, const T* tr, con
 #pragma unroll
       for (int k = 0; k < D; ++k) {
         C x[N];
-        const int base = cl * Sh::NV + line_base<D, N>(k, ln);
+        const int base = lds_line<D, N>(cl, k, ln);
 #pragma unroll
-        for (int j = 0; j < N; ++j) x[j] = k == F ? u[j] : sW[base + j * line_stride<N>(k)];
+        for (int j = 0; j < N; ++j) x[j] = k == F ? u[j] : sW[base + j * lds_stride<D, N>(k)];
         constexpr int step[3] = {1, Sh::BX, Sh::BX * Sh::BY};
         C g0, d0, g1, d1;
         line_traces<T, N>(a, x, g0, d0, g1, d1);
@@ -1195,7 +1240,7 @@ template <typename T, int D, int N, bool VARK, bool AD = false>
 constexpr int cell_lds_bytes() {
   using C = CT<T>;
   using Sh = DGShape<D, N>;
-  return (int)sizeof(C) * (Sh::CPB * Sh::NV + Sh::CPB * Sh::NF * 2 * Sh::L + EigLDS<D, N, VARK, AD>::SIZE +
+  return (int)sizeof(C) * (Sh::CPB * Sh::NVP + Sh::CPB * Sh::NF * 2 * Sh::L + EigLDS<D, N, VARK, AD>::SIZE +
                            kappa_lds_entries<D, N, VARK>()) +
          (int)sizeof(int) * Sh::CPB;
 }
@@ -1211,14 +1256,14 @@ __device__ __forceinline__ void sweep_body(const DGArgs<T>& a, int bx, int by, c
   constexpr int A = D - 1;  // axis of the thread's own line
   C* sNB = (C*)lds;  // pairs: first, for their alignment
   C* sW = sNB + Sh::CPB * Sh::NF * 2 * L;
-  C* sE = sW + Sh::CPB * Sh::NV;
+  C* sE = sW + Sh::CPB * Sh::NVP;
   C* sKF = sE + EigLDS<D, N, VARK, AD>::SIZE;
 
   const Cells<D, N, AD> B(a, bx);
   const size_t rv = (size_t)by * a.vstride, rt = (size_t)by * a.tstride;
-  const int tid = work_tid<D, N>();
-  const int cl = tid / L, ln = tid % L;
-  const bool act = tid < Sh::NT && B.valid(cl);
+  int cl, ln;
+  cell_line<D, N>(cl, ln);
+  const bool act = B.valid(cl);
   const int c = B.cell(act ? cl : 0);
   const int mask = B.mask(a, act ? cl : 0, c);
   const int smask = IVAR ? 0 : mask;  // boundary classes of the block solve
@@ -1227,14 +1272,14 @@ __device__ __forceinline__ void sweep_body(const DGArgs<T>& a, int bx, int by, c
     if (a.hscale) hf *= a.hscale[c];
   }
   auto get = [&](int k, C(&r)[N]) {
-    const int base = cl * Sh::NV + line_base<D, N>(k, ln);
+    const int base = lds_line<D, N>(cl, k, ln);
 #pragma unroll
-    for (int j = 0; j < N; ++j) r[j] = sW[base + j * line_stride<N>(k)];
+    for (int j = 0; j < N; ++j) r[j] = sW[base + j * lds_stride<D, N>(k)];
   };
   auto put = [&](int k, const C(&r)[N]) {
-    const int base = cl * Sh::NV + line_base<D, N>(k, ln);
+    const int base = lds_line<D, N>(cl, k, ln);
 #pragma unroll
-    for (int j = 0; j < N; ++j) sW[base + j * line_stride<N>(k)] = r[j];
+    for (int j = 0; j < N; ++j) sW[base + j * lds_stride<D, N>(k)] = r[j];
   };
   const size_t own = rv + (size_t)c * Sh::NV + ln;  // first node of the thread's line, stride L
 
@@ -1272,28 +1317,31 @@ __device__ __forceinline__ void sweep_body(const DGArgs<T>& a, int bx, int by, c
           put(k, t);
         }
       }
-      __syncthreads();
+      cell_sync<D, N>();
     }
     if (act) {
       get(1, r);
       block_mv<T, D, N, VARK, IVAR, AD, OP_S>(a, sE, cl, smask, 1, r, t);
       put(1, t);
     }
-    __syncthreads();
+    cell_sync<D, N>();
   } else {
     const cptr<C> Mi = as_const(a.ref) + RefOff<N>::MIC;
-    if constexpr (Cells<D, N, AD>::BR) __syncthreads();  // sW free
+    if constexpr (Cells<D, N, AD>::BR) __syncthreads();  // traces staged, sW free
     if (act) {
       cs_mv<N>(Mi, r);
       put(A, r);
     }
-    __syncthreads();
+    if constexpr (Cells<D, N, AD>::BR)
+      cell_sync<D, N>();
+    else
+      __syncthreads();  // traces staged
     if (act) {
       get(1, r);
       cs_mv<N>(Mi, r);
       put(1, r);
     }
-    __syncthreads();
+    cell_sync<D, N>();
     // x: b in nodal values along every axis, minus the lifts
     if (act) {
       get(0, r);
@@ -1302,26 +1350,26 @@ __device__ __forceinline__ void sweep_body(const DGArgs<T>& a, int bx, int by, c
       block_mv<T, D, N, VARK, IVAR, AD, OP_SI>(a, sE, cl, smask, 0, r, t);
       put(0, t);
     }
-    __syncthreads();
+    cell_sync<D, N>();
     if (act) {
       get(A, r);
       block_mv<T, D, N, VARK, IVAR, AD, OP_SI>(a, sE, cl, smask, A, r, t);
       put(A, t);
     }
-    __syncthreads();
+    cell_sync<D, N>();
     if (act) {
       get(1, r);
       block_mv<T, D, N, VARK, IVAR, AD, OP_SI>(a, sE, cl, smask, 1, r, t);
       middle(1);
       put(1, r);
     }
-    __syncthreads();
+    cell_sync<D, N>();
     if (act) {
       get(0, r);
       block_mv<T, D, N, VARK, IVAR, AD, OP_S>(a, sE, cl, smask, 0, r, t);
       put(0, t);
     }
-    __syncthreads();
+    cell_sync<D, N>();
   }
   // last inverse transform, update, store of u and of the traces
   T* trout = a.tr_out + rt;
@@ -1337,7 +1385,7 @@ __device__ __forceinline__ void sweep_body(const DGArgs<T>& a, int bx, int by, c
     put(A, t);
     store_line_traces<T, D, N, IVAR>(a, trout, B, cl, c, mask, A, ln, t);
   }
-  __syncthreads();
+  cell_sync<D, N>();
   if (act) store_other_traces<T, D, N, A, IVAR>(a, trout, sW, B, cl, c, mask, ln);
 }
 
@@ -1351,14 +1399,14 @@ __device__ __forceinline__ void sweep_dual_body(const DGArgs<T>& a, int bx, int 
   constexpr int L = Sh::L;
   C* sNB = (C*)lds;
   C* sW = sNB + Sh::CPB * Sh::NF * 2 * L;
-  C* sE = sW + Sh::CPB * Sh::NV;
+  C* sE = sW + Sh::CPB * Sh::NVP;
   C* sKF = sE + EigLDS<D, N, VARK, AD>::SIZE;
 
   const Cells<D, N, AD> B(a, bx);
   const size_t rv = (size_t)by * a.vstride, rt = (size_t)by * a.tstride;
-  const int tid = work_tid<D, N>();
-  const int cl = tid / L, ln = tid % L;
-  const bool act = tid < Sh::NT && B.valid(cl);
+  int cl, ln;
+  cell_line<D, N>(cl, ln);
+  const bool act = B.valid(cl);
   const int c = B.cell(act ? cl : 0);
   const int base0 = line_base<D, N>(0, ln);
   const int mask = B.mask(a, act ? cl : 0, c);
@@ -1395,14 +1443,14 @@ __device__ __forceinline__ void sweep_dual_body(const DGArgs<T>& a, int bx, int 
 #pragma unroll
   for (int k = 0; k < D; ++k) {
     if (act) {
-      const int base = cl * Sh::NV + line_base<D, N>(k, ln);
+      const int base = lds_line<D, N>(cl, k, ln);
       C r[N], t[N];
       if (k == 0) {
 #pragma unroll
         for (int j = 0; j < N; ++j) r[j] = hf * bl[j];
       } else {
 #pragma unroll
-        for (int j = 0; j < N; ++j) r[j] = sW[base + j * line_stride<N>(k)];
+        for (int j = 0; j < N; ++j) r[j] = sW[base + j * lds_stride<D, N>(k)];
       }
       if (!UZERO) dual_lifts<T, D, N, -1>(a, cl, k, ln, sNB, r);
       block_mv<T, D, N, VARK, IVAR, AD, OP_ST>(a, sE, cl, smask, k, r, t);
@@ -1417,7 +1465,7 @@ __device__ __forceinline__ void sweep_dual_body(const DGArgs<T>& a, int bx, int 
         for (int j = 0; j < N; ++j) t[j] = r[j];
       }
 #pragma unroll
-      for (int j = 0; j < N; ++j) sW[base + j * line_stride<N>(k)] = t[j];
+      for (int j = 0; j < N; ++j) sW[base + j * lds_stride<D, N>(k)] = t[j];
     }
     __syncthreads();
   }
@@ -1427,10 +1475,10 @@ __device__ __forceinline__ void sweep_dual_body(const DGArgs<T>& a, int bx, int 
 #pragma unroll
   for (int k = D - 2; k >= 0; --k) {
     if (act) {
-      const int base = cl * Sh::NV + line_base<D, N>(k, ln);
+      const int base = lds_line<D, N>(cl, k, ln);
       C r[N], t[N];
 #pragma unroll
-      for (int j = 0; j < N; ++j) r[j] = sW[base + j * line_stride<N>(k)];
+      for (int j = 0; j < N; ++j) r[j] = sW[base + j * lds_stride<D, N>(k)];
       block_mv<T, D, N, VARK, IVAR, AD, OP_S>(a, sE, cl, smask, k, r, t);
       if (k == 0) {
         T* uo = a.u_out + rv + (size_t)c * Sh::NV + base0;
@@ -1444,7 +1492,7 @@ __device__ __forceinline__ void sweep_dual_body(const DGArgs<T>& a, int bx, int 
         store_line_traces<T, D, N, IVAR>(a, trout, B, cl, c, mask, 0, ln, t);
       } else {
 #pragma unroll
-        for (int j = 0; j < N; ++j) sW[base + j * line_stride<N>(k)] = t[j];
+        for (int j = 0; j < N; ++j) sW[base + j * lds_stride<D, N>(k)] = t[j];
       }
     }
     __syncthreads();
@@ -1552,7 +1600,7 @@ __device__ __forceinline__ void mfma_stage(float* sW, const float* sE, const int
   constexpr int NW = Sh::BLOCK / 64;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int c = lane & 15, kq = lane >> 4;
-  const int stride = line_stride<N>(k);
+  const int stride = lds_stride<D, N>(k);
   // cell record of block-diagonal block b (clamped to a staged cell)
   auto rec = [&](int cl) -> const float* {
     if constexpr (VARK)
@@ -1564,7 +1612,7 @@ __device__ __forceinline__ void mfma_stage(float* sW, const float* sE, const int
     const int g = t / CH, q = t % CH;
     const int line = 16 * q + c;
     const int lc = min(line, L - 1);
-    const int lb = line_base<D, N>(k, lc);
+    const int lb = lds_line<D, N>(0, k, lc);
     float av[4], bv[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
@@ -1573,7 +1621,7 @@ __device__ __forceinline__ void mfma_stage(float* sW, const float* sE, const int
       const int cl = g * NB + kb;
       const int clc = min(cl, Sh::CPB - 1);
       const bool okb = kb < NB && cl < Sh::CPB && sMask[clc] >= 0 && line < L;
-      const float x = sW[clc * Sh::NV + lb + (jj < N ? jj : 0) * stride];
+      const float x = sW[clc * Sh::NVP + lb + (jj < N ? jj : 0) * stride];
       bv[j] = okb ? x : 0.f;
       const int rb = c / N, ii = c % N;
       const int cla = g * NB + rb;
@@ -1608,7 +1656,7 @@ __device__ __forceinline__ void mfma_stage(float* sW, const float* sE, const int
           }
           v *= recip(ls);
         }
-        sW[cl * Sh::NV + lb + ii * stride] = v;
+        sW[cl * Sh::NVP + lb + ii * stride] = v;
       }
     }
   }
@@ -1625,15 +1673,15 @@ __device__ __forceinline__ void sweep_body_mfma(const DGArgs<T>& a, int bx, int 
   constexpr int L = Sh::L;
   C* sNB = (C*)lds;  // pairs: first, for their alignment
   C* sW = sNB + Sh::CPB * Sh::NF * 2 * L;
-  C* sE = sW + Sh::CPB * Sh::NV;
+  C* sE = sW + Sh::CPB * Sh::NVP;
   C* sKF = sE + EigLDS<D, N, VARK>::SIZE;
   int* sMask = mask_lds<D, N, VARK>(sKF);
 
   const Cells<D, N, false> B(a, bx);
   const size_t rv = (size_t)by * a.vstride, rt = (size_t)by * a.tstride;
-  const int tid = work_tid<D, N>();
-  const int cl = tid / L, ln = tid % L;
-  const bool act = tid < Sh::NT && B.valid(cl);
+  int cl, ln;
+  cell_line<D, N>(cl, ln);
+  const bool act = B.valid(cl);
   const int c = B.cell(act ? cl : 0);
   const int base0 = line_base<D, N>(0, ln);
   const int mask = B.mask(a, act ? cl : 0, c);
@@ -1665,18 +1713,18 @@ __device__ __forceinline__ void sweep_body_mfma(const DGArgs<T>& a, int bx, int 
 #pragma unroll
   for (int k = 0; k < D; ++k) {
     if (act && (k == 0 || !UZERO)) {
-      const int base = cl * Sh::NV + line_base<D, N>(k, ln);
+      const int base = lds_line<D, N>(cl, k, ln);
       C r[N];
       if (k == 0) {
 #pragma unroll
         for (int j = 0; j < N; ++j) r[j] = a.h_fwd * bl[j];
       } else {
 #pragma unroll
-        for (int j = 0; j < N; ++j) r[j] = sW[base + j * line_stride<N>(k)];
+        for (int j = 0; j < N; ++j) r[j] = sW[base + j * lds_stride<D, N>(k)];
       }
       if (!UZERO) dual_lifts<T, D, N, -1>(a, cl, k, ln, sNB, r);
 #pragma unroll
-      for (int j = 0; j < N; ++j) sW[base + j * line_stride<N>(k)] = r[j];
+      for (int j = 0; j < N; ++j) sW[base + j * lds_stride<D, N>(k)] = r[j];
     }
     __syncthreads();
     if (k == D - 1)
@@ -1699,8 +1747,8 @@ __device__ __forceinline__ void sweep_body_mfma(const DGArgs<T>& a, int bx, int 
 #pragma unroll
     for (int j = 0; j < N; ++j) {
       const C uo0 = UZERO ? C(0) : ul[j];
-      t[j] = (C(1) - a.omega) * uo0 + a.omega * sW[cl * Sh::NV + base0 + j];
-      sW[cl * Sh::NV + base0 + j] = t[j];
+      t[j] = (C(1) - a.omega) * uo0 + a.omega * sW[lds_line<D, N>(cl, 0, ln) + j];
+      sW[lds_line<D, N>(cl, 0, ln) + j] = t[j];
       uo[j] = t[j];
     }
     store_line_traces<T, D, N, IVAR>(a, trout, B, cl, c, mask, 0, ln, t);
@@ -1760,7 +1808,7 @@ __device__ __forceinline__ void restrict_body(const DGArgs<T>& a, const Cells<D,
     const int c2 = i / L, l2 = i % L;
     C x[N];
 #pragma unroll
-    for (int j = 0; j < N; ++j) x[j] = sW[c2 * Sh::NV + j + N * l2];
+    for (int j = 0; j < N; ++j) x[j] = sW[lds_line<D, N>(c2, 0, l2) + j];
 #pragma unroll
     for (int jc = 0; jc < NCB; ++jc) {
       if (jc < ncr) {
@@ -1852,14 +1900,14 @@ __device__ __forceinline__ void apply_dual_body(const DGArgs<T>& a, int bx, int 
   constexpr int L = Sh::L;
   C* sNB = (C*)lds;  // as in sweep_body
   C* sW = sNB + Sh::CPB * Sh::NF * 2 * L;
-  C* sE = sW + Sh::CPB * Sh::NV;
+  C* sE = sW + Sh::CPB * Sh::NVP;
   C* sKF = sE + EigLDS<D, N, VARK, AD>::SIZE;
 
   const Cells<D, N, AD> B(a, bx);
   const size_t rv = (size_t)by * a.vstride, rt = (size_t)by * a.tstride;
-  const int tid = work_tid<D, N>();
-  const int cl = tid / L, ln = tid % L;
-  const bool act = tid < Sh::NT && B.valid(cl);
+  int cl, ln;
+  cell_line<D, N>(cl, ln);
+  const bool act = B.valid(cl);
   const int c = B.cell(act ? cl : 0);
   const int base0 = line_base<D, N>(0, ln);
   const int mask = B.mask(a, act ? cl : 0, c);
@@ -1895,14 +1943,14 @@ __device__ __forceinline__ void apply_dual_body(const DGArgs<T>& a, int bx, int 
 #pragma unroll
   for (int k = 0; k < D; ++k) {
     if (act) {
-      const int base = cl * Sh::NV + line_base<D, N>(k, ln);
+      const int base = lds_line<D, N>(cl, k, ln);
       C r[N], t[N];
       if (k == 0) {
 #pragma unroll
         for (int j = 0; j < N; ++j) r[j] = ul[j];
       } else {
 #pragma unroll
-        for (int j = 0; j < N; ++j) r[j] = sW[base + j * line_stride<N>(k)];
+        for (int j = 0; j < N; ++j) r[j] = sW[base + j * lds_stride<D, N>(k)];
       }
       block_mv<T, D, N, VARK, IVAR, AD, OP_SI>(a, sE, cl, smask, k, r, t);
       if (k == D - 1) {
@@ -1916,17 +1964,17 @@ __device__ __forceinline__ void apply_dual_body(const DGArgs<T>& a, int bx, int 
         for (int j = 0; j < N; ++j) t[j] = r[j];
       }
 #pragma unroll
-      for (int j = 0; j < N; ++j) sW[base + j * line_stride<N>(k)] = t[j];
+      for (int j = 0; j < N; ++j) sW[base + j * lds_stride<D, N>(k)] = t[j];
     }
     __syncthreads();
   }
 #pragma unroll
   for (int k = D - 2; k >= 0; --k) {
     if (act) {
-      const int base = cl * Sh::NV + line_base<D, N>(k, ln);
+      const int base = lds_line<D, N>(cl, k, ln);
       C r[N], t[N];
 #pragma unroll
-      for (int j = 0; j < N; ++j) r[j] = sW[base + j * line_stride<N>(k)];
+      for (int j = 0; j < N; ++j) r[j] = sW[base + j * lds_stride<D, N>(k)];
       block_mv<T, D, N, VARK, IVAR, AD, OP_SIT>(a, sE, cl, smask, k, r, t);
       dual_lifts<T, D, N, 1>(a, cl, k, ln, sNB, t);
       if (k == 0) {
@@ -1942,7 +1990,7 @@ __device__ __forceinline__ void apply_dual_body(const DGArgs<T>& a, int bx, int 
         }
       } else {
 #pragma unroll
-        for (int j = 0; j < N; ++j) sW[base + j * line_stride<N>(k)] = t[j];
+        for (int j = 0; j < N; ++j) sW[base + j * lds_stride<D, N>(k)] = t[j];
       }
     }
     __syncthreads();
@@ -1965,14 +2013,14 @@ __device__ __forceinline__ void apply_body(const DGArgs<T>& a, int bx, int by, c
   constexpr int A = D - 1;  // axis of the thread's own line
   C* sNB = (C*)lds;  // pairs: first, for their alignment
   C* sW = sNB + Sh::CPB * Sh::NF * 2 * L;
-  C* sE = sW + Sh::CPB * Sh::NV;
+  C* sE = sW + Sh::CPB * Sh::NVP;
   C* sKF = sE + EigLDS<D, N, VARK, AD>::SIZE;
 
   const Cells<D, N, AD> B(a, bx);
   const size_t rv = (size_t)by * a.vstride, rt = (size_t)by * a.tstride;
-  const int tid = work_tid<D, N>();
-  const int cl = tid / L, ln = tid % L;
-  const bool act = tid < Sh::NT && B.valid(cl);
+  int cl, ln;
+  cell_line<D, N>(cl, ln);
+  const bool act = B.valid(cl);
   const int c = B.cell(act ? cl : 0);
   const int mask = B.mask(a, act ? cl : 0, c);
   const int smask = IVAR ? 0 : mask;  // boundary classes of the block solve
@@ -1982,14 +2030,14 @@ __device__ __forceinline__ void apply_body(const DGArgs<T>& a, int bx, int by, c
   }
 
   auto get = [&](int k, C(&r)[N]) {
-    const int base = cl * Sh::NV + line_base<D, N>(k, ln);
+    const int base = lds_line<D, N>(cl, k, ln);
 #pragma unroll
-    for (int j = 0; j < N; ++j) r[j] = sW[base + j * line_stride<N>(k)];
+    for (int j = 0; j < N; ++j) r[j] = sW[base + j * lds_stride<D, N>(k)];
   };
   auto put = [&](int k, const C(&r)[N]) {
-    const int base = cl * Sh::NV + line_base<D, N>(k, ln);
+    const int base = lds_line<D, N>(cl, k, ln);
 #pragma unroll
-    for (int j = 0; j < N; ++j) sW[base + j * line_stride<N>(k)] = r[j];
+    for (int j = 0; j < N; ++j) sW[base + j * lds_stride<D, N>(k)] = r[j];
   };
   const size_t own = rv + (size_t)c * Sh::NV + ln;  // first node of the thread's line, stride L
 
@@ -2025,14 +2073,14 @@ __device__ __forceinline__ void apply_body(const DGArgs<T>& a, int bx, int by, c
         put(k, t);
       }
     }
-    __syncthreads();
+    cell_sync<D, N>();
   }
   if (act) {
     get(A, r);
     block_mv<T, D, N, VARK, IVAR, AD, OP_S>(a, sE, cl, smask, A, r, t);
     put(A, t);
   }
-  __syncthreads();
+  cell_sync<D, N>();
   // plus the lifts (in the y-lines), times the mass along every axis
   const cptr<C> Mc = as_const(a.ref) + RefOff<N>::MC;
   if (act) {
@@ -2042,13 +2090,13 @@ __device__ __forceinline__ void apply_body(const DGArgs<T>& a, int bx, int by, c
     cs_mv<N>(Mc, t);
     put(1, t);
   }
-  __syncthreads();
+  cell_sync<D, N>();
   if (act) {
     get(0, r);
     cs_mv<N>(Mc, r);
     put(0, r);
   }
-  __syncthreads();
+  cell_sync<D, N>();
   if (act) {
     get(A, t);
     cs_mv<N>(Mc, t);
@@ -2100,7 +2148,7 @@ template <typename T, int D, int N, int NC>
 constexpr int prolong_lds_bytes() {
   using C = CT<T>;
   using Sh = DGShape<D, N>;
-  return (int)sizeof(C) * (Sh::CPB * Sh::NV + (NC != 0 ? Sh::CPB * Sh::NV + Sh::CPB * Sh::NF * 2 * Sh::L : 0));
+  return (int)sizeof(C) * (Sh::CPB * Sh::NVP + (NC != 0 ? Sh::CPB * Sh::NV + Sh::CPB * Sh::NF * 2 * Sh::L : 0));
 }
 
 template <typename T, int D, int N, int NC, bool IVAR = false, bool AD = false>
@@ -2109,14 +2157,15 @@ __device__ __forceinline__ void prolong_body(const DGArgs<T>& a, int bx, int by,
   using Sh = DGShape<D, N>;
   constexpr int L = Sh::L;
   C* sU = (C*)lds;
-  C* sW = sU + Sh::CPB * Sh::NV;
+  C* sW = sU + Sh::CPB * Sh::NVP;
   C* sNB = sW + Sh::CPB * Sh::NV;
 
   const Cells<D, N, AD> B(a, bx);
   const size_t rv = (size_t)by * a.vstride, rt = (size_t)by * a.tstride;
   const int tid = work_tid<D, N>();
-  const int cl = tid / L, ln = tid % L;
-  const bool act = tid < Sh::NT && B.valid(cl);
+  int cl, ln;
+  cell_line<D, N>(cl, ln);
+  const bool act = B.valid(cl);
   const int c = B.cell(act ? cl : 0);
   const int mask = B.mask(a, act ? cl : 0, c);
   const int nc = B.count();
@@ -2249,10 +2298,10 @@ __device__ __forceinline__ void prolong_body(const DGArgs<T>& a, int bx, int by,
       for (int j = 0; j < N; ++j) a.u_out[own + j * ST] = u[j];
     }
 #pragma unroll
-    for (int j = 0; j < N; ++j) sU[cl * Sh::NV + lb + j * ST] = u[j];
+    for (int j = 0; j < N; ++j) sU[lds_line<D, N>(cl, F, ln) + j * lds_stride<D, N>(F)] = u[j];
     store_line_traces<T, D, N, IVAR>(a, trout, B, cl, c, mask, F, ln, u);
   }
-  __syncthreads();
+  cell_sync<D, N>();
   if (act) store_other_traces<T, D, N, F, IVAR>(a, trout, sU, B, cl, c, mask, ln);
 }
 
@@ -2294,7 +2343,7 @@ dim3 block_grid(const DGArgs<T>& a, int nrhs) {
 template <typename C, int D, int N>
 bool launch_build_eig(const DGArgs<C>& a, hipStream_t s) {
   if constexpr (serves_vark<C, D>()) {
-    hipLaunchKernelGGL((k_build_eig<C, D, N>), (block_grid<D, N>(a, 1)), dim3(DGShape<D, N>::NT), 0, s, a);
+    hipLaunchKernelGGL((k_build_eig<C, D, N>), (block_grid<D, N>(a, 1)), dim3(DGShape<D, N>::THREADS), 0, s, a);
     return true;
   }
   return false;
@@ -2306,7 +2355,7 @@ bool launch_sweep_u(const DGArgs<T>& a, int nrhs, hipStream_t s) {
   const dim3 grid = block_grid<D, N>(a, nrhs);
   // matrix cores (16-bit storage, 3D): whole waves per block
   constexpr bool MF = sizeof(T) == 2 && D == 3;
-  const dim3 blk(MF && a.mfma ? Sh::BLOCK : Sh::NT);
+  const dim3 blk(MF && a.mfma ? Sh::BLOCK : Sh::THREADS);
   if (a.adapt) {
     if constexpr (serves_adapt<T, D>()) {
       hipLaunchKernelGGL((k_sweep<T, D, N, UZERO, false, false, false, true>), grid, blk, 0, s, a);
@@ -2340,7 +2389,7 @@ bool launch_sweep(const DGArgs<T>& a, int nrhs, bool uzero, hipStream_t s) {
 
 template <typename T, int D, int N, int NC, bool RESID>
 bool launch_apply_r(const DGArgs<T>& a, int nrhs, hipStream_t s) {
-  const dim3 grid = block_grid<D, N>(a, nrhs), blk(DGShape<D, N>::NT);
+  const dim3 grid = block_grid<D, N>(a, nrhs), blk(DGShape<D, N>::THREADS);
   if (a.adapt) {
     if constexpr (serves_adapt<T, D>()) {
       hipLaunchKernelGGL((k_apply<T, D, N, NC, RESID, false, false, true>), grid, blk, 0, s, a);
@@ -2367,7 +2416,7 @@ bool launch_apply(const DGArgs<T>& a, int nrhs, bool resid, hipStream_t s) {
 
 template <typename T, int D, int N, int NC>
 bool launch_prolong(const DGArgs<T>& a, int nrhs, hipStream_t s) {
-  const dim3 grid = block_grid<D, N>(a, nrhs), blk(DGShape<D, N>::NT);
+  const dim3 grid = block_grid<D, N>(a, nrhs), blk(DGShape<D, N>::THREADS);
   if (a.adapt) {
     if constexpr (serves_adapt<T, D>()) {
       hipLaunchKernelGGL((k_prolong<T, D, N, NC, false, true>), grid, blk, 0, s, a);
