@@ -4,6 +4,8 @@
 // operations of the outer Krylov iteration.
 #include <hip/hip_runtime.h>
 
+#include "cg_block.hpp"
+#include "cg_tiles.hpp"
 #include "kernels.hpp"
 
 namespace hpmg {
@@ -66,48 +68,6 @@ __global__ __launch_bounds__(256) void k_cg_stencil(int nv, const T* __restrict_
   out[v] = cg_stencil_at<T, D>(v, nv, total, st, dinv, u, b, omega, mode, uzero);
 }
 
-// Fine interior indices and weights of a coarse vertex along one axis
-// (RK slots; an empty slot, index < 0, becomes index 0 with weight 0).
-template <typename T, int RK>
-__device__ __forceinline__ void axis_parents(const int* __restrict__ idx, const T* __restrict__ w, int x, int (&i)[RK],
-                                             T (&wt)[RK]) {
-#pragma unroll
-  for (int a = 0; a < RK; ++a) {
-    const int k = idx[RK * x + a];
-    i[a] = k < 0 ? 0 : k;
-    wt[a] = k < 0 ? T(0) : w[RK * x + a];
-  }
-}
-
-// (P^T r_f)_v with the tensor-product 1D transfer: coarse interior index v
-// gathers up to RK = 2f - 1 fine interior indices ridx[RK I ..] per axis with
-// weights rw (f = 2 or 3: the coarsening factor).
-template <typename T, int D, int RK>
-__device__ __forceinline__ T cg_restrict_at(int v, int nvf, int nvc, const int* __restrict__ ridx,
-                                            const T* __restrict__ rw, const T* __restrict__ rf) {
-  int x[3];
-  vcoords<D>(v, nvc, x);
-  constexpr int RZ = (D == 3) ? RK : 1;
-  int ix[RK], iy[RK], iz[RK];
-  T wx[RK], wy[RK], wz[RK];
-  axis_parents<T, RK>(ridx, rw, x[0], ix, wx);
-  axis_parents<T, RK>(ridx, rw, x[1], iy, wy);
-  if constexpr (D == 3) {
-    axis_parents<T, RK>(ridx, rw, x[2], iz, wz);
-  } else {
-    iz[0] = 0;
-    wz[0] = T(1);
-  }
-  T s = 0;
-#pragma unroll
-  for (int c = 0; c < RZ; ++c)
-#pragma unroll
-    for (int b2 = 0; b2 < RK; ++b2)
-#pragma unroll
-      for (int a2 = 0; a2 < RK; ++a2) s += wz[c] * wy[b2] * wx[a2] * rf[ix[a2] + nvf * (iy[b2] + nvf * iz[c])];
-  return s;
-}
-
 template <typename T, int D, int RK>
 __global__ __launch_bounds__(256) void k_cg_restrict(int nvf, int nvc, const int* __restrict__ ridx,
                                                      const T* __restrict__ rw, const T* __restrict__ rf,
@@ -115,35 +75,9 @@ __global__ __launch_bounds__(256) void k_cg_restrict(int nvf, int nvc, const int
   const int total = (D == 2) ? nvc * nvc : nvc * nvc * nvc;
   const int v = blockIdx.x * blockDim.x + threadIdx.x;
   if (v >= total) return;
-  bc[v] = cg_restrict_at<T, D, RK>(v, nvf, nvc, ridx, rw, rf);
-}
-
-// (P e_c)_v: fine interior index v interpolates from up to two coarse
-// interior indices pidx[2v..2v+1] per axis with weights pw.
-template <typename T, int D>
-__device__ __forceinline__ T cg_prolong_at(int v, int nvf, int nvc, const int* __restrict__ pidx,
-                                           const T* __restrict__ pw, const T* __restrict__ ec) {
   int x[3];
-  vcoords<D>(v, nvf, x);
-  constexpr int RZ = (D == 3) ? 2 : 1;
-  int ix[2], iy[2], iz[2];
-  T wx[2], wy[2], wz[2];
-  axis_parents<T, 2>(pidx, pw, x[0], ix, wx);
-  axis_parents<T, 2>(pidx, pw, x[1], iy, wy);
-  if constexpr (D == 3) {
-    axis_parents<T, 2>(pidx, pw, x[2], iz, wz);
-  } else {
-    iz[0] = 0;
-    wz[0] = T(1);
-  }
-  T s = 0;
-#pragma unroll
-  for (int c = 0; c < RZ; ++c)
-#pragma unroll
-    for (int b2 = 0; b2 < 2; ++b2)
-#pragma unroll
-      for (int a2 = 0; a2 < 2; ++a2) s += wz[c] * wy[b2] * wx[a2] * ec[ix[a2] + nvc * (iy[b2] + nvc * iz[c])];
-  return s;
+  vcoords<D>(v, nvc, x);
+  bc[v] = cgt::restrict_box<T, D, RK>(cgt::Parents<T, D, RK>(ridx, rw, x, {0, 0, 0}), {0, 0, 0}, nvf, rf);
 }
 
 // u_f += P e_c
@@ -154,7 +88,9 @@ __global__ __launch_bounds__(256) void k_cg_prolong(int nvf, int nvc, const int*
   const int total = (D == 2) ? nvf * nvf : nvf * nvf * nvf;
   const int v = blockIdx.x * blockDim.x + threadIdx.x;
   if (v >= total) return;
-  uf[v] += cg_prolong_at<T, D>(v, nvf, nvc, pidx, pw, ec);
+  int x[3];
+  vcoords<D>(v, nvf, x);
+  uf[v] += cgt::prolong_xyz<T, D>(cgt::Parents<T, D, 2>(pidx, pw, x, {0, 0, 0}), nvc, ec);
 }
 
 // Q1 right-hand side from the per-cell corner contributions of the
@@ -167,17 +103,7 @@ __global__ __launch_bounds__(256) void k_gather_corners(int n, const T* __restri
   if (v >= total) return;
   int x[3];
   vcoords<D>(v, nv, x);
-  constexpr int NCOR = 1 << D;
-  T s = 0;
-#pragma unroll
-  for (int c = 0; c < NCOR; ++c) {
-    const int ix = c & 1, iy = (c >> 1) & 1, iz = (c >> 2) & 1;
-    const int cx = x[0] + ix, cy = x[1] + iy, cz = (D == 3) ? x[2] + iz : 0;  // vertex v+1 -> cell v+ix
-    const int cell = cx + n * (cy + n * cz);
-    const int corner = (1 - ix) + 2 * (1 - iy) + ((D == 3) ? 4 * (1 - iz) : 0);
-    s += contrib[(size_t)cell * NCOR + corner];
-  }
-  bcg[v] = s;
+  bcg[v] = cgt::gather_corners_at<T, D>(x, n, contrib);
 }
 
 // (Ainv b)_i on the coarsest level (dense FP64 inverse from a Cholesky
@@ -207,60 +133,21 @@ __global__ __launch_bounds__(256) void k_dense_solve(int m, const double* __rest
   x[i] = dense_at<T>(i, m, Ainv, b);
 }
 
-// The Q1 V-cycle below a level in one workgroup: every level from lv[0]
-// down is small (a few thousand vertices), so the workgroup's barriers
-// replace kernel boundaries between the Jacobi, residual, restriction,
-// coarsest-solve and prolongation steps.  Same steps, order and per-vertex
-// arithmetic as the level-by-level launches; every level is entered with a
-// zero initial guess, so after the pre-smoothing u[nu_pre & 1] holds the
-// iterate and after the post-smoothing u[(nu_pre + nu_post) & 1].
+template <typename T, int D, int RK, int NU>
+__global__ __launch_bounds__((cgt::Tile<D, RK>::THREADS)) void k_cg_down(CGTileArgs<T> a) {
+  __shared__ __attribute__((aligned(16))) char lds[cgt::Tile<D, RK>::template lds_bytes<T>()];
+  cgt::down_tile<T, D, RK, NU>(a, blockIdx.x, blockIdx.y, lds);
+}
+template <typename T, int D, int RK, int NU>
+__global__ __launch_bounds__((cgt::Tile<D, RK>::THREADS)) void k_cg_up(CGTileArgs<T> a) {
+  __shared__ __attribute__((aligned(16))) char lds[cgt::Tile<D, RK>::template lds_bytes<T>()];
+  cgt::up_tile<T, D, RK, NU>(a, blockIdx.x, blockIdx.y, lds);
+}
+
 template <typename T, int D, int RK>
-__global__ __launch_bounds__(1024) void k_cg_vcycle_block(CGBlockArgs<T> a) {
-  const int tid = threadIdx.x, nt = blockDim.x;
-  const int cpre = a.nu_pre & 1;
-  for (int l = 0; l + 1 < a.nlev; ++l) {
-    const CGBlockLevel<T>& L = a.lv[l];
-    const int total = (D == 2) ? L.nv * L.nv : L.nv * L.nv * L.nv;
-    int c = 0, zero = 1;
-    for (int i = 0; i < a.nu_pre; ++i) {
-      for (int v = tid; v < total; v += nt)
-        L.u[c ^ 1][v] = cg_stencil_at<T, D>(v, L.nv, total, L.st, L.dinv, L.u[c], L.b, a.omega, 0, zero);
-      __syncthreads();
-      c ^= 1;
-      zero = 0;
-    }
-    if (zero) {
-      for (int v = tid; v < total; v += nt) L.u[c][v] = T(0);
-      __syncthreads();
-    }
-    for (int v = tid; v < total; v += nt)
-      L.r[v] = cg_stencil_at<T, D>(v, L.nv, total, L.st, L.dinv, L.u[c], L.b, a.omega, 1, 0);
-    __syncthreads();
-    const CGBlockLevel<T>& C = a.lv[l + 1];
-    const int totc = (D == 2) ? C.nv * C.nv : C.nv * C.nv * C.nv;
-    for (int v = tid; v < totc; v += nt) C.b[v] = cg_restrict_at<T, D, RK>(v, L.nv, C.nv, L.ridx, L.rw, L.r);
-    __syncthreads();
-  }
-  {
-    const CGBlockLevel<T>& L = a.lv[a.nlev - 1];
-    for (int i = tid; i < a.m; i += nt) L.u[0][i] = dense_at<T>(i, a.m, a.Ainv, L.b);
-    __syncthreads();
-  }
-  for (int l = a.nlev - 2; l >= 0; --l) {
-    const CGBlockLevel<T>& L = a.lv[l];
-    const CGBlockLevel<T>& C = a.lv[l + 1];
-    const int total = (D == 2) ? L.nv * L.nv : L.nv * L.nv * L.nv;
-    const T* ec = C.u[l + 2 == a.nlev ? 0 : (a.nu_pre + a.nu_post) & 1];
-    int c = cpre;
-    for (int v = tid; v < total; v += nt) L.u[c][v] += cg_prolong_at<T, D>(v, L.nv, C.nv, L.pidx, L.pw, ec);
-    __syncthreads();
-    for (int i = 0; i < a.nu_post; ++i) {
-      for (int v = tid; v < total; v += nt)
-        L.u[c ^ 1][v] = cg_stencil_at<T, D>(v, L.nv, total, L.st, L.dinv, L.u[c], L.b, a.omega, 0, 0);
-      __syncthreads();
-      c ^= 1;
-    }
-  }
+__global__ __launch_bounds__(CG_BLOCK_MAX_VERTICES) void k_cg_vcycle_block(CGBlockArgs<T> a) {
+  __shared__ cgb::Lds<T> lds;
+  cgb::vcycle<T, D, RK>(a, blockIdx.x, lds);
 }
 
 template <typename T>
@@ -505,9 +392,42 @@ void dense_solve(int m, const double* Ainv, const T* b, T* x, hipStream_t s) {
   hipLaunchKernelGGL((k_dense_solve<T>), dim3(nblocks(m)), dim3(256), 0, s, m, Ainv, b, x);
 }
 
+template <typename T, int D, int RK>
+void cg_tile(bool down, int nu, const CGTileArgs<T>& a, int ncol, hipStream_t s) {
+  const dim3 t(cgt::Tile<D, RK>::THREADS);
+  const dim3 g(down ? cgt::down_tiles<D, RK>(a.nvc) : cgt::up_tiles<D, RK>(a.nv), ncol);
+  if (down && nu == 1)
+    hipLaunchKernelGGL((k_cg_down<T, D, RK, 1>), g, t, 0, s, a);
+  else if (down)
+    hipLaunchKernelGGL((k_cg_down<T, D, RK, 2>), g, t, 0, s, a);
+  else if (nu == 1)
+    hipLaunchKernelGGL((k_cg_up<T, D, RK, 1>), g, t, 0, s, a);
+  else
+    hipLaunchKernelGGL((k_cg_up<T, D, RK, 2>), g, t, 0, s, a);
+}
 template <typename T>
-void cg_vcycle_block(int D, int rk, const CGBlockArgs<T>& a, hipStream_t s) {
-  const dim3 g(1), t(1024);
+void cg_tile_rk(bool down, int D, int rk, int nu, const CGTileArgs<T>& a, int ncol, hipStream_t s) {
+  if (D == 2 && rk == 3)
+    cg_tile<T, 2, 3>(down, nu, a, ncol, s);
+  else if (D == 2)
+    cg_tile<T, 2, 5>(down, nu, a, ncol, s);
+  else if (rk == 3)
+    cg_tile<T, 3, 3>(down, nu, a, ncol, s);
+  else
+    cg_tile<T, 3, 5>(down, nu, a, ncol, s);
+}
+template <typename T>
+void cg_down(int D, int rk, int nu, const CGTileArgs<T>& a, int ncol, hipStream_t s) {
+  cg_tile_rk<T>(true, D, rk, nu, a, ncol, s);
+}
+template <typename T>
+void cg_up(int D, int rk, int nu, const CGTileArgs<T>& a, int ncol, hipStream_t s) {
+  cg_tile_rk<T>(false, D, rk, nu, a, ncol, s);
+}
+
+template <typename T>
+void cg_vcycle_block(int D, int rk, const CGBlockArgs<T>& a, int ncol, hipStream_t s) {
+  const dim3 g(ncol), t(CG_BLOCK_MAX_VERTICES);
   if (D == 2 && rk == 3)
     hipLaunchKernelGGL((k_cg_vcycle_block<T, 2, 3>), g, t, 0, s, a);
   else if (D == 2)
@@ -594,7 +514,9 @@ template void cast_up<__bf16>(size_t, const __bf16*, double*, const double*, dou
   template void cg_prolong<T>(int, int, int, const int*, const T*, const T*, T*, hipStream_t);                 \
   template void gather_corners<T>(int, int, const T*, T*, hipStream_t);                                        \
   template void dense_solve<T>(int, const double*, const T*, T*, hipStream_t);                                 \
-  template void cg_vcycle_block<T>(int, int, const CGBlockArgs<T>&, hipStream_t);                              \
+  template void cg_down<T>(int, int, int, const CGTileArgs<T>&, int, hipStream_t);                             \
+  template void cg_up<T>(int, int, int, const CGTileArgs<T>&, int, hipStream_t);                               \
+  template void cg_vcycle_block<T>(int, int, const CGBlockArgs<T>&, int, hipStream_t);                         \
   template void fill<T>(T*, size_t, T, hipStream_t);
 HPMG_INST(float)
 HPMG_INST(double)

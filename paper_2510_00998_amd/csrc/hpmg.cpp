@@ -968,29 +968,40 @@ void apply(hpmg_ctx* h, int l, const T* u, const T* tr, const T* b, T* out, int 
 int cg_nu_pre(const hpmg_ctx* h) { return h->opt.nu_pre_cg >= 0 ? h->opt.nu_pre_cg : h->opt.nu_pre; }
 int cg_nu_post(const hpmg_ctx* h) { return h->opt.nu_post_cg >= 0 ? h->opt.nu_post_cg : h->opt.nu_post; }
 
-// The Q1 part of a V-cycle for right-hand side `col` (the level vectors
-// hold max_rhs columns of L.size entries each).
+// The Q1 part of a V-cycle from level m, entered with a zero initial guess, for
+// ncol right-hand sides (the level vectors hold max_rhs columns of L.size
+// entries each).  contrib: the right-hand side of level m is the sum of these
+// corner contributions (else it is in the level's b); sets L.cur.
 template <typename T>
-void vcycle_cg(hpmg_ctx* h, int m, bool uzero, int col, hipStream_t s) {
+void vcycle_cg(hpmg_ctx* h, int m, const T* contrib, int ncol, hipStream_t s) {
   CGLevel& L = h->cg[m];
   CGData<T>& d = data<T>(L);
   const int D = h->dim;
-  const size_t o = (size_t)col * L.size;
-  T* u[2] = {d.u[0] + o, d.u[1] + o};
-  T* b = d.b + o;
-  T* r = d.r + o;
-  if (m + 1 == (int)h->cg.size()) {
-    hpmg::dense_solve<T>(h->coarse_m, h->coarse_inv, b, u[0], s);
+  const size_t nct = (size_t)h->ncell << D;
+  const T w = (T)h->opt.omega_cg;
+  const int npre = cg_nu_pre(h), npost = cg_nu_post(h);
+  const bool last = m + 1 == (int)h->cg.size();
+  // levels of at most CG_BLOCK_MAX_VERTICES: the rest of the cycle in one
+  // workgroup per column
+  const int nlev = (int)h->cg.size() - m;
+  size_t pool = 0;
+  for (int k = m; k < (int)h->cg.size(); ++k) pool += h->cg[k].size;
+  const bool block = !last && L.size <= (size_t)hpmg::CG_BLOCK_MAX_VERTICES &&
+                     nlev <= hpmg::CG_BLOCK_MAX_LEVELS && pool < (size_t)hpmg::CG_BLOCK_POOL;
+  // larger levels: one launch down, one up
+  const bool tiles = !last && !block && npre >= 1 && npre <= hpmg::CG_TILE_MAX_NU && npost >= 1 &&
+                     npost <= hpmg::CG_TILE_MAX_NU;
+  if (contrib && !tiles && !block)
+    for (int c = 0; c < ncol; ++c)
+      hpmg::gather_corners<T>(D, h->n, contrib + c * nct, d.b + (size_t)c * L.size, s);
+  if (last) {
+    for (int c = 0; c < ncol; ++c)
+      hpmg::dense_solve<T>(h->coarse_m, h->coarse_inv, d.b + (size_t)c * L.size, d.u[0] + (size_t)c * L.size, s);
     L.cur = 0;
     HIPCHK(hipGetLastError());
     return;
   }
-  const T w = (T)h->opt.omega_cg;
-  const int npre = cg_nu_pre(h), npost = cg_nu_post(h);
-  const int nlev = (int)h->cg.size() - m;
-  if (uzero && L.size <= (size_t)hpmg::CG_BLOCK_MAX_VERTICES && nlev <= hpmg::CG_BLOCK_MAX_LEVELS) {
-    // this level and all coarser ones are small: the rest of the cycle in
-    // one workgroup
+  if (block) {
     hpmg::CGBlockArgs<T> a{};
     a.nlev = nlev;
     a.nu_pre = npre;
@@ -998,39 +1009,75 @@ void vcycle_cg(hpmg_ctx* h, int m, bool uzero, int col, hipStream_t s) {
     a.m = h->coarse_m;
     a.omega = w;
     a.Ainv = h->coarse_inv;
+    a.contrib = contrib;
+    a.scon = (long long)nct;
     for (int k = 0; k < nlev; ++k) {
       CGLevel& Lk = h->cg[m + k];
       CGData<T>& dk = data<T>(Lk);
-      const size_t ok = (size_t)col * Lk.size;
-      a.lv[k] = {Lk.nv, dk.st, dk.dinv, {dk.u[0] + ok, dk.u[1] + ok}, dk.b + ok, dk.r + ok, Lk.ridx, dk.rw,
-                 Lk.pidx, dk.pw};
-      Lk.cur = k + 1 == nlev ? 0 : (npre + npost) & 1;
+      a.lv[k] = {Lk.nv, (int)Lk.size, dk.st, dk.dinv, dk.u[0], dk.b, Lk.ridx, dk.rw, Lk.pidx, dk.pw};
     }
-    hpmg::cg_vcycle_block<T>(D, L.rk, a, s);
+    L.cur = 0;
+    hpmg::cg_vcycle_block<T>(D, L.rk, a, ncol, s);
     HIPCHK(hipGetLastError());
     return;
   }
-  int cur = 0;
-  bool zero = uzero;
-  for (int i = 0; i < npre; ++i) {
-    hpmg::cg_stencil<T>(D, L.nv, d.st, d.dinv, u[cur], b, u[cur ^ 1], w, 0, zero ? 1 : 0, s);
-    cur ^= 1;
-    zero = false;
-  }
-  if (zero) {
-    hpmg::fill<T>(u[cur], L.size, T(0), s);
-    zero = false;
-  }
-  hpmg::cg_stencil<T>(D, L.nv, d.st, d.dinv, u[cur], b, r, w, 1, 0, s);
   CGLevel& C = h->cg[m + 1];
   CGData<T>& dc = data<T>(C);
-  const size_t oc = (size_t)col * C.size;
-  hpmg::cg_restrict<T>(D, L.nv, C.nv, L.rk, L.ridx, d.rw, r, dc.b + oc, s);
-  vcycle_cg<T>(h, m + 1, true, col, s);
-  hpmg::cg_prolong<T>(D, L.nv, C.nv, L.pidx, d.pw, dc.u[C.cur] + oc, u[cur], s);
-  for (int i = 0; i < npost; ++i) {
-    hpmg::cg_stencil<T>(D, L.nv, d.st, d.dinv, u[cur], b, u[cur ^ 1], w, 0, 0, s);
-    cur ^= 1;
+  if (tiles) {
+    hpmg::CGTileArgs<T> a{};
+    a.nv = L.nv;
+    a.nvc = C.nv;
+    a.n = h->n;
+    a.omega = w;
+    a.st = d.st;
+    a.dinv = d.dinv;
+    a.b = d.b;
+    a.u_in = d.u[0];
+    a.u_out = d.u[0];
+    a.contrib = contrib;
+    a.bc = dc.b;
+    a.ridx = L.ridx;
+    a.rw = d.rw;
+    a.pidx = L.pidx;
+    a.pw = d.pw;
+    a.sf = (long long)L.size;
+    a.sc = (long long)C.size;
+    a.scon = (long long)nct;
+    hpmg::cg_down<T>(D, L.rk, npre, a, ncol, s);
+    HIPCHK(hipGetLastError());
+    vcycle_cg<T>(h, m + 1, nullptr, ncol, s);
+    a.ec = dc.u[C.cur];
+    a.u_out = d.u[1];
+    hpmg::cg_up<T>(D, L.rk, npost, a, ncol, s);
+    L.cur = 1;
+    HIPCHK(hipGetLastError());
+    return;
+  }
+  // other smoothing counts: one launch per step and column
+  int cur = 0;
+  for (int c = 0; c < ncol; ++c) {
+    const size_t o = (size_t)c * L.size, oc = (size_t)c * C.size;
+    cur = 0;
+    bool zero = true;
+    for (int i = 0; i < npre; ++i) {
+      hpmg::cg_stencil<T>(D, L.nv, d.st, d.dinv, d.u[cur] + o, d.b + o, d.u[cur ^ 1] + o, w, 0, zero ? 1 : 0, s);
+      cur ^= 1;
+      zero = false;
+    }
+    if (zero) hpmg::fill<T>(d.u[cur] + o, L.size, T(0), s);
+    hpmg::cg_stencil<T>(D, L.nv, d.st, d.dinv, d.u[cur] + o, d.b + o, d.r + o, w, 1, 0, s);
+    hpmg::cg_restrict<T>(D, L.nv, C.nv, L.rk, L.ridx, d.rw, d.r + o, dc.b + oc, s);
+  }
+  vcycle_cg<T>(h, m + 1, nullptr, ncol, s);
+  const int pre = cur;
+  for (int c = 0; c < ncol; ++c) {
+    const size_t o = (size_t)c * L.size, oc = (size_t)c * C.size;
+    cur = pre;
+    hpmg::cg_prolong<T>(D, L.nv, C.nv, L.pidx, d.pw, dc.u[C.cur] + oc, d.u[cur] + o, s);
+    for (int i = 0; i < npost; ++i) {
+      hpmg::cg_stencil<T>(D, L.nv, d.st, d.dinv, d.u[cur] + o, d.b + o, d.u[cur ^ 1] + o, w, 0, 0, s);
+      cur ^= 1;
+    }
   }
   L.cur = cur;
   HIPCHK(hipGetLastError());
@@ -1123,14 +1170,11 @@ void vcycle_dg(hpmg_ctx* h, int l, T* u, const T* b, bool uzero, int nrhs, hipSt
     a.out = contrib;
     a.cstride = (long long)nct;
     dg_run(h, hpmg::OP_RESTRICT_Q1, a, L.N, nrhs, 1, s);
-    for (int c = 0; c < nrhs; ++c) {
-      if (h->adapt)  // base vertices <- corners of the leaves inside their cells
+    if (h->adapt)  // base vertices <- corners of the leaves inside their cells
+      for (int c = 0; c < nrhs; ++c)
         hpmg::csr_apply<C>(h->q1r_rows, h->q1r_ptr, h->q1r_col, q1_weights<C>(h, true), contrib + c * nct,
                            dc.b + c * Cg.size, s);
-      else
-        hpmg::gather_corners<C>(h->dim, h->n, contrib + c * nct, dc.b + c * Cg.size, s);
-      vcycle_cg<C>(h, 0, true, c, s);
-    }
+    vcycle_cg<C>(h, 0, h->adapt ? nullptr : contrib, nrhs, s);
     hpmg::DGArgs<T> pa = dg_args<T>(h, L);
     pa.u_in = u;
     pa.u_out = u;

@@ -79,19 +79,49 @@ void csr_apply(int nrow, const int* ptr, const int* col, const T* w, const T* x,
 template <typename T>
 void fill(T* x, size_t n, T v, hipStream_t s);
 
-// The Q1 V-cycle from level lv[0] (entered with a zero initial guess, its
-// right-hand side in lv[0].b) down to the coarsest level lv[nlev - 1]
-// (dense solve with Ainv, m unknowns), in one workgroup.
-constexpr int CG_BLOCK_MAX_LEVELS = 8;
-constexpr int CG_BLOCK_MAX_VERTICES = 512;  // largest level taken by the one-workgroup cycle
+// One Q1 level in tiles (cg_tiles.hpp), every column (right-hand side) in one
+// launch: on the way down nu Jacobi steps from zero into u_out, the residual,
+// its restriction into bc (b from the corner contributions contrib of n^d
+// cells when given, then stored); on the way up u_in + P ec and nu steps into
+// u_out.  1 <= nu <= CG_TILE_MAX_NU.
+constexpr int CG_TILE_MAX_NU = 2;
 template <typename T>
-struct CGBlockLevel {
-  int nv;
+struct CGTileArgs {
+  int nv, nvc, n;
+  T omega;
   const T* st;
   const T* dinv;
-  T* u[2];
-  T* b;
-  T* r;
+  const T* b;
+  const T* u_in;
+  T* u_out;
+  const T* contrib;
+  T* bc;
+  const T* ec;
+  const int* ridx;
+  const T* rw;
+  const int* pidx;
+  const T* pw;
+  long long sf, sc, scon;  // per column: this level, the coarser level, contrib
+};
+template <typename T>
+void cg_down(int D, int rk, int nu, const CGTileArgs<T>& a, int ncol, hipStream_t s);
+template <typename T>
+void cg_up(int D, int rk, int nu, const CGTileArgs<T>& a, int ncol, hipStream_t s);
+
+// The Q1 V-cycle from level lv[0] (entered with a zero initial guess, its
+// right-hand side in lv[0].b, or the sum of the corner contributions contrib
+// of the cells when given) down to the coarsest level lv[nlev - 1]
+// (dense solve with Ainv, m unknowns), in one workgroup per column.
+constexpr int CG_BLOCK_MAX_LEVELS = 8;
+constexpr int CG_BLOCK_MAX_VERTICES = 512;  // largest level taken by the one-workgroup cycle
+constexpr int CG_BLOCK_POOL = 1024;         // vertices of all its levels together
+template <typename T>
+struct CGBlockLevel {
+  int nv, size;
+  const T* st;
+  const T* dinv;
+  T* u;             // level 0: the result
+  const T* b;       // level 0: the right-hand side
   const int* ridx;  // restriction to the next level (RK slots per coarse vertex and axis)
   const T* rw;
   const int* pidx;  // prolongation from the next level (2 slots per vertex and axis)
@@ -102,10 +132,12 @@ struct CGBlockArgs {
   int nlev, nu_pre, nu_post, m;
   T omega;
   const double* Ainv;
+  const T* contrib;
+  long long scon;  // contrib per column
   CGBlockLevel<T> lv[CG_BLOCK_MAX_LEVELS];
 };
 template <typename T>
-void cg_vcycle_block(int D, int rk, const CGBlockArgs<T>& a, hipStream_t s);
+void cg_vcycle_block(int D, int rk, const CGBlockArgs<T>& a, int ncol, hipStream_t s);
 
 constexpr int KRYLOV_RED_BLOCKS = 1024;
 void krylov_dot(size_t n, const double* x, const double* y, const double* z, double* partial, double* scal, int op,
