@@ -24,7 +24,9 @@ using namespace hpmg::detail;
 namespace {
 
 struct Launch {
-  int kind = 0;  // 0: DG float, 1: DG double, 2: Q1 float
+  // 0: DG float, 1: DG double, 2: Q1 float (one step), 3: Q1 tiles down, 4: up
+  // (op: smoothing steps), 5: Q1 cycle of the small levels
+  int kind = 0;
   int op = 0;
   const void* args = nullptr;
   const hpmg::WorkItem* items = nullptr;  // DG: sorted by degree; cell blocks of tile variant 0
@@ -142,9 +144,11 @@ struct Builder {
     if (t.items.empty()) return Launch{};
     return dg_launch(b->mem, sizeof(T) == 4 ? 0 : 1, op, b->mem.upload(t.args, s), t.items, t.items1, s);
   }
-  Launch cg(Table<hpmg::CGArgs<float>>& t) {
+  template <typename T>
+  Launch cg(Table<T>& t, int kind = 2, int op = 0) {
     Launch L;
-    L.kind = 2;
+    L.kind = kind;
+    L.op = op;
     if (t.items.empty()) return L;
     L.args = b->mem.upload(t.args, s);
     L.items = b->mem.upload(t.items, s);
@@ -168,12 +172,16 @@ void add_dg_items(Table<hpmg::DGArgs<T>>& t, const hpmg::DGArgs<T>& a, int N, in
   }
 }
 
-void add_cg_items(Table<hpmg::CGArgs<float>>& t, const hpmg::CGArgs<float>& a, int count, int nrhs) {
+template <typename T>
+void add_block_items(Table<T>& t, const T& a, int nb, int nrhs) {
   const int idx = (int)t.args.size();
   t.args.push_back(a);
-  const int nb = (count + 255) / 256;
   for (int r = 0; r < nrhs; ++r)
     for (int blk = 0; blk < nb; ++blk) t.items.push_back(hpmg::WorkItem{idx, blk, r, 0});
+}
+
+void add_cg_items(Table<hpmg::CGArgs<float>>& t, const hpmg::CGArgs<float>& a, int count, int nrhs) {
+  add_block_items(t, a, (count + 255) / 256, nrhs);
 }
 
 // Per-problem cursor through the V-cycle schedule.
@@ -198,18 +206,61 @@ void build_vcycle(BatchPlan* B, const std::vector<hpmg_handle>& hs, const std::v
     lmax = std::max(lmax, ps[j].ndg + ps[j].ncg);
   }
   const hpmg_options& O = hs[0]->opt;
-  const int cg_pre = O.nu_pre_cg >= 0 ? O.nu_pre_cg : O.nu_pre;
-  const int cg_post = O.nu_post_cg >= 0 ? O.nu_post_cg : O.nu_post;
+  const int cg_pre = cg_nu_pre(hs[0]), cg_post = cg_nu_post(hs[0]);
   // level-l vectors of problem j
   auto dg_u = [&](int j, int l) -> float* { return l == 0 ? B->z32 + off0[j] : hs[j]->dg[l].f.u; };
   auto dg_b = [&](int j, int l) -> float* { return l == 0 ? B->r32 + off0[j] : hs[j]->dg[l].f.b; };
 
   std::vector<Launch>& out = B->vcycle;
+  // Q1 levels in tiles and one-workgroup cycles, after the last DG level of
+  // every problem: two launches per tiled level and one for the rest, where a
+  // launch per step takes 4.5 us whatever it does (16 problems of 8^3 to 24^3
+  // cells: 48 launches per cycle).  Needs every problem to reach levels of
+  // one workgroup by tiled ones.
+  std::vector<int> nt(np, 0);  // tiled levels of a problem
+  bool fused = true;
+  int ntmax = 0, ndgmax = 0;
+  for (int j = 0; j < np; ++j) {
+    while (nt[j] < ps[j].ncg && !cg_in_block(hs[j], nt[j])) ++nt[j];
+    fused = fused && nt[j] < ps[j].ncg && (nt[j] == 0 || cg_tiled(hs[j]));
+    ntmax = std::max(ntmax, nt[j]);
+    ndgmax = std::max(ndgmax, ps[j].ndg);
+  }
+  auto q1_fused = [&]() {
+    auto con = [&](int j, int m) -> const float* { return m == 0 ? hs[j]->dg.back().f.contrib : nullptr; };
+    auto tiles = [&](bool down, int m) {
+      Table<hpmg::CGTileArgs<float>> t;
+      for (int j = 0; j < np; ++j) {
+        if (m >= nt[j]) continue;
+        CGLevel& C = hs[j]->cg[m + 1];
+        hpmg::CGTileArgs<float> a = cg_tile_args<float>(hs[j], m, con(j, m));
+        a.omega = (float)O.omega_cg;
+        if (!down) {
+          a.u_out = hs[j]->cg[m].f.u[1];
+          a.ec = C.f.u[ps[j].cgcur[m + 1]];
+          ps[j].cgcur[m] = 1;
+        }
+        add_block_items(t, a, down ? hpmg::cg_down_tiles3(a.nvc) : hpmg::cg_up_tiles3(a.nv), R);
+      }
+      out.push_back(bld.cg(t, down ? 3 : 4, down ? cg_pre : cg_post));
+    };
+    for (int m = 0; m < ntmax; ++m) tiles(true, m);
+    Table<hpmg::CGBlockArgs<float>> t;
+    for (int j = 0; j < np; ++j) {
+      hpmg::CGBlockArgs<float> a = cg_block_args<float>(hs[j], nt[j], con(j, nt[j]));
+      a.omega = (float)O.omega_cg;
+      ps[j].cgcur[nt[j]] = 0;
+      add_block_items(t, a, 1, R);
+    }
+    out.push_back(bld.cg(t, 5));
+    for (int m = ntmax - 1; m >= 0; --m) tiles(false, m);
+  };
   // recursive descent over the level index
   std::function<void(int)> rec = [&](int l) {
+    if (fused && l == ndgmax) return q1_fused();
     std::vector<int> P;
     for (int j = 0; j < np; ++j)
-      if (l < ps[j].ndg + ps[j].ncg) P.push_back(j);
+      if (l < ps[j].ndg + (fused ? 0 : ps[j].ncg)) P.push_back(j);
     if (P.empty()) return;
     auto is_dg = [&](int j) { return l < ps[j].ndg; };
     auto cgl = [&](int j) { return l - ps[j].ndg; };
@@ -292,6 +343,8 @@ void build_vcycle(BatchPlan* B, const std::vector<hpmg_handle>& hs, const std::v
           } else {
             a.out = L.f.contrib;
             a.cstride = (long long)h->ncell << 3;
+          }
+          if (L.next_cg && !fused) {
             CGLevel& C = h->cg[0];
             hpmg::CGArgs<float> g{};
             g.op = hpmg::CGOP_GATHER;
@@ -442,6 +495,10 @@ void run_grid(const std::vector<Launch>& v, int grid, bool split, int tile, hipS
     if (L.nitems == 0) continue;
     if (L.kind == 2) {
       hpmg::batch_cg<float>((const hpmg::CGArgs<float>*)L.args, L.items, L.nitems, grid, s);
+    } else if (L.kind == 3 || L.kind == 4) {
+      hpmg::batch_cg_tile<float>(L.kind == 3, L.op, (const hpmg::CGTileArgs<float>*)L.args, L.items, L.nitems, s);
+    } else if (L.kind == 5) {
+      hpmg::batch_cg_block<float>((const hpmg::CGBlockArgs<float>*)L.args, L.items, L.nitems, s);
     } else if (split) {
       for (int V = 0; V < hpmg::kTileVariants; ++V)
         for (const int3& r : V == 0 ? L.runs : L.runs1) {

@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 
 #include "dg_kernels.hpp"
+#include "kernels.hpp"
 
 namespace hpmg {
 
@@ -76,6 +77,16 @@ template <typename T>
 void batch_dg_n_t1(int op, int N, const DGArgs<T>* args, const WorkItem* items, int nitems, int grid, hipStream_t s);
 template <typename T>
 void batch_cg(const CGArgs<T>* args, const WorkItem* items, int nitems, int grid, hipStream_t s);
+
+// The Q1 levels of 3D problems in tiles and in one workgroup each (CGTileArgs,
+// CGBlockArgs), one workgroup per item: y = tile of the level's way down or up
+// (cg_*_tiles3), not used by the cycle of the small levels.
+int cg_down_tiles3(int nvc);
+int cg_up_tiles3(int nv);
+template <typename T>
+void batch_cg_tile(bool down, int nu, const CGTileArgs<T>* args, const WorkItem* items, int nitems, hipStream_t s);
+template <typename T>
+void batch_cg_block(const CGBlockArgs<T>* args, const WorkItem* items, int nitems, hipStream_t s);
 
 // Segmented FP64 vector operations of the flexible CG (see batch_kernels.hip).
 void bk_dot(const SegTable& t, const double* x, const double* y, const double* z, double* partial, hipStream_t s);

@@ -2,6 +2,7 @@
 // problems of a batch, so one launch serves one multigrid phase of every
 // problem regardless of its mesh size and polynomial degree.
 #include "batch_dg_body.hpp"
+#include "cg_block.hpp"
 
 namespace hpmg {
 namespace {
@@ -161,6 +162,32 @@ __global__ __launch_bounds__(256) void k_cg_batch(const CGArgs<T>* __restrict__ 
     const CGArgs<T> a = args[w.x];
     cg_item<T>(a, w.y, w.z);
   }
+}
+
+// Coarse vertices per axis and tile.  Unlike one problem's levels (2 each way,
+// for the latency) a batch fills the chip, and the larger tile recomputes
+// less: 32 columns of up to 23^3 vertices take 20 us down with 4, 23 with 3 and
+// 26 with 2; up, where little is recomputed, 12.4 us with 2 and 17.2 with 4.
+constexpr int CT_DOWN = 4, CT_UP = 2;
+template <typename T, bool DOWN, int NU>
+__global__ __launch_bounds__((cgt::Tile<3, 3, DOWN ? CT_DOWN : CT_UP>::THREADS)) void k_cg_tile_batch(const CGTileArgs<T>* __restrict__ args,
+                                                                              const WorkItem* __restrict__ items) {
+  using Tile = cgt::Tile<3, 3, DOWN ? CT_DOWN : CT_UP>;
+  __shared__ __attribute__((aligned(16))) char lds[Tile::template lds_bytes<T>()];
+  const WorkItem w = items[blockIdx.x];
+  const CGTileArgs<T> a = args[w.x];
+  if constexpr (DOWN)
+    cgt::down_tile<T, 3, 3, CT_DOWN, NU>(a, w.y, w.z, lds);
+  else
+    cgt::up_tile<T, 3, 3, CT_UP, NU>(a, w.y, w.z, lds);
+}
+
+template <typename T>
+__global__ __launch_bounds__(CG_BLOCK_MAX_VERTICES) void k_cg_block_batch(const CGBlockArgs<T>* __restrict__ args,
+                                                                          const WorkItem* __restrict__ items) {
+  __shared__ cgb::Lds<T> lds;
+  const WorkItem w = items[blockIdx.x];
+  cgb::vcycle<T, 3, 3>(*dgk::as_const(args + w.x), w.z, lds);
 }
 
 // ----------------------------------------------------- segmented vectors
@@ -433,10 +460,34 @@ void batch_cg(const CGArgs<T>* args, const WorkItem* items, int nitems, int grid
   hipLaunchKernelGGL((k_cg_batch<T>), dim3(grid_for(nitems, grid)), dim3(256), 0, s, args, items, nitems);
 }
 
+int cg_down_tiles3(int nvc) { return cgt::down_tiles<3, CT_DOWN>(nvc); }
+int cg_up_tiles3(int nv) { return cgt::up_tiles<3, 3, CT_UP>(nv); }
+
+template <typename T, bool DOWN>
+void cg_tile_nu(int nu, const CGTileArgs<T>* args, const WorkItem* items, int nitems, hipStream_t s) {
+  const dim3 g(nitems), t(cgt::Tile<3, 3, DOWN ? CT_DOWN : CT_UP>::THREADS);
+  if (nu == 1)
+    hipLaunchKernelGGL((k_cg_tile_batch<T, DOWN, 1>), g, t, 0, s, args, items);
+  else
+    hipLaunchKernelGGL((k_cg_tile_batch<T, DOWN, 2>), g, t, 0, s, args, items);
+}
+template <typename T>
+void batch_cg_tile(bool down, int nu, const CGTileArgs<T>* args, const WorkItem* items, int nitems, hipStream_t s) {
+  if (down)
+    cg_tile_nu<T, true>(nu, args, items, nitems, s);
+  else
+    cg_tile_nu<T, false>(nu, args, items, nitems, s);
+}
+template <typename T>
+void batch_cg_block(const CGBlockArgs<T>* args, const WorkItem* items, int nitems, hipStream_t s) {
+  hipLaunchKernelGGL((k_cg_block_batch<T>), dim3(nitems), dim3(CG_BLOCK_MAX_VERTICES), 0, s, args, items);
+}
+template void batch_cg_tile<float>(bool, int, const CGTileArgs<float>*, const WorkItem*, int, hipStream_t);
+template void batch_cg_block<float>(const CGBlockArgs<float>*, const WorkItem*, int, hipStream_t);
+
 template void batch_dg<float>(int, const DGArgs<float>*, const WorkItem*, int, int, hipStream_t);
 template void batch_dg<double>(int, const DGArgs<double>*, const WorkItem*, int, int, hipStream_t);
 template void batch_cg<float>(const CGArgs<float>*, const WorkItem*, int, int, hipStream_t);
-template void batch_cg<double>(const CGArgs<double>*, const WorkItem*, int, int, hipStream_t);
 
 void bk_dot(const SegTable& t, const double* x, const double* y, const double* z, double* partial, hipStream_t s) {
   hipLaunchKernelGGL(k_bdot, dim3(grid_for(t.nchunks, 2048)), dim3(BV), 0, s, t, x, y, z, partial);

@@ -37,18 +37,19 @@ __device__ __forceinline__ T stencil_at(const T (&sv)[cgt::nst<D>()], const int 
   return au;
 }
 
-template <typename T, int D, int RK>
-__device__ __forceinline__ void vcycle(const CGBlockArgs<T>& a, int col, Lds<T>& S) {
+// Args: CGBlockArgs<T>, as a kernel argument or in constant memory.
+template <typename T, int D, int RK, typename Args>
+__device__ __forceinline__ void vcycle(Args& a, int col, Lds<T>& S) {
   constexpr int NS = cgt::nst<D>();
   const int v = threadIdx.x;
   T sv[NS], dv = 0;
   int x[3] = {0, 0, 0};
-  auto load = [&](const CGBlockLevel<T>& L) {  // the thread's vertex, stencil and inverse diagonal
+  auto load = [&](auto& L) {  // the thread's vertex, stencil and inverse diagonal
     const int w = v < L.size ? v : 0;
     x[0] = w % L.nv;
     x[1] = w / L.nv % L.nv;
     x[2] = D == 3 ? w / (L.nv * L.nv) : 0;
-    cgt::load_stencil<T, D>(L.st, L.size, w, sv);
+    cgt::load_stencil<T, D>(L.st, L.size, -1, w, sv);
     dv = L.dinv[w];
   };
   load(a.lv[0]);
@@ -60,8 +61,8 @@ __device__ __forceinline__ void vcycle(const CGBlockArgs<T>& a, int col, Lds<T>&
                        : a.lv[0].b[(size_t)col * a.lv[0].size + v];
   int off = 0;
   for (int l = 0; l + 1 < a.nlev; ++l) {
-    const CGBlockLevel<T>& L = a.lv[l];
-    const CGBlockLevel<T>& C = a.lv[l + 1];
+    auto& L = a.lv[l];
+    auto& C = a.lv[l + 1];
     if (l > 0) load(L);
     const bool in = v < L.size;
     __syncthreads();  // b of the level
@@ -96,11 +97,12 @@ __device__ __forceinline__ void vcycle(const CGBlockArgs<T>& a, int col, Lds<T>&
     double s = 0.0;
     for (int j = 0; j < a.m; ++j) s += row[j] * (double)S.b[off + j];
     S.u[off + v] = (T)s;
+    if (a.nlev == 1) a.lv[0].u[(size_t)col * a.lv[0].size + v] = (T)s;
   }
   if (a.m == 0 && v == 0) S.u[off] = T(0);  // a coarsest grid without interior vertices: e_c = 0
   for (int l = a.nlev - 2; l >= 0; --l) {
-    const CGBlockLevel<T>& L = a.lv[l];
-    const CGBlockLevel<T>& C = a.lv[l + 1];
+    auto& L = a.lv[l];
+    auto& C = a.lv[l + 1];
     if (a.nlev > 2) load(L);  // else level 0's are still there
     const bool in = v < L.size;
     const int offc = off;

@@ -133,15 +133,20 @@ __global__ __launch_bounds__(256) void k_dense_solve(int m, const double* __rest
   x[i] = dense_at<T>(i, m, Ainv, b);
 }
 
-template <typename T, int D, int RK, int NU>
-__global__ __launch_bounds__((cgt::Tile<D, RK>::THREADS)) void k_cg_down(CGTileArgs<T> a) {
-  __shared__ __attribute__((aligned(16))) char lds[cgt::Tile<D, RK>::template lds_bytes<T>()];
-  cgt::down_tile<T, D, RK, NU>(a, blockIdx.x, blockIdx.y, lds);
+// Coarse vertices per axis and tile.
+template <int D, int RK>
+constexpr int tile_ct() {
+  return D == 3 ? 2 : (RK == 3 ? 8 : 4);
 }
 template <typename T, int D, int RK, int NU>
-__global__ __launch_bounds__((cgt::Tile<D, RK>::THREADS)) void k_cg_up(CGTileArgs<T> a) {
-  __shared__ __attribute__((aligned(16))) char lds[cgt::Tile<D, RK>::template lds_bytes<T>()];
-  cgt::up_tile<T, D, RK, NU>(a, blockIdx.x, blockIdx.y, lds);
+__global__ __launch_bounds__((cgt::Tile<D, RK, tile_ct<D, RK>()>::THREADS)) void k_cg_down(CGTileArgs<T> a) {
+  __shared__ __attribute__((aligned(16))) char lds[cgt::Tile<D, RK, tile_ct<D, RK>()>::template lds_bytes<T>()];
+  cgt::down_tile<T, D, RK, tile_ct<D, RK>(), NU>(a, blockIdx.x, blockIdx.y, lds);
+}
+template <typename T, int D, int RK, int NU>
+__global__ __launch_bounds__((cgt::Tile<D, RK, tile_ct<D, RK>()>::THREADS)) void k_cg_up(CGTileArgs<T> a) {
+  __shared__ __attribute__((aligned(16))) char lds[cgt::Tile<D, RK, tile_ct<D, RK>()>::template lds_bytes<T>()];
+  cgt::up_tile<T, D, RK, tile_ct<D, RK>(), NU>(a, blockIdx.x, blockIdx.y, lds);
 }
 
 template <typename T, int D, int RK>
@@ -394,8 +399,8 @@ void dense_solve(int m, const double* Ainv, const T* b, T* x, hipStream_t s) {
 
 template <typename T, int D, int RK>
 void cg_tile(bool down, int nu, const CGTileArgs<T>& a, int ncol, hipStream_t s) {
-  const dim3 t(cgt::Tile<D, RK>::THREADS);
-  const dim3 g(down ? cgt::down_tiles<D, RK>(a.nvc) : cgt::up_tiles<D, RK>(a.nv), ncol);
+  const dim3 t(cgt::Tile<D, RK, tile_ct<D, RK>()>::THREADS);
+  const dim3 g(down ? cgt::down_tiles<D, tile_ct<D, RK>()>(a.nvc) : cgt::up_tiles<D, RK, tile_ct<D, RK>()>(a.nv), ncol);
   if (down && nu == 1)
     hipLaunchKernelGGL((k_cg_down<T, D, RK, 1>), g, t, 0, s, a);
   else if (down)

@@ -7,14 +7,15 @@
 // Bound: latency.  The levels hold at most some 10^5 vertices, a launch of
 // one step takes about 4 us whatever it does, and a cycle had 3 launches up
 // and 4 or 5 down per level.  The steps of a tile share one read of each
-// vertex's stencil, kept in registers.  31^3 and 15^3 vertices in FP32 with two
-// steps each way: 8 launches of 3.3 to 4.3 us down to one of 11 us on the way
-// down, and 3 launches to one of 7 us on the way up.  The tile is small (2
-// coarse vertices per axis in 3D): with 4 the recomputed share falls from 5.4
-// to 2.6 times the tile, but 64 workgroups leave most of the chip idle (15.4
-// and 10.8 us).  Per-vertex arithmetic and its order are
-// those of the single-step kernels (cg_stencil_at, restrict_box,
-// prolong_xyz), so the results are the same bit for bit.
+// vertex's stencil, kept in registers, or take it from scalar loads where all
+// vertices have the same.  31^3 and 15^3 vertices in FP32 with two steps each
+// way: 8 launches of 3.3 to 4.3 us down to one of 8.3 us on the way down (11.2
+// with a stencil per vertex), 3 to one of 5.6 us on the way up (7.2).  A small
+// tile, 2 coarse vertices per axis in 3D, suits one problem: with 4 the
+// recomputed share falls from 5.4 to 2.6 times the tile, but 64 workgroups
+// leave most of the chip idle (15.4 against 11.2 us).  Per-vertex arithmetic
+// and its order are those of the single-step kernels (cg_stencil_at,
+// restrict_box, prolong_xyz), so the results are the same bit for bit.
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -27,10 +28,10 @@ constexpr int cpow(int b, int e) { return e == 0 ? 1 : b * cpow(b, e - 1); }
 
 // Tile of a level: CT coarse vertices per axis on the way down, FT fine
 // vertices on the way up; RK = 2 factor - 1 fine vertices per coarse one.
-template <int D, int RK>
+template <int D, int RK, int CTILE>
 struct Tile {
   static constexpr int HF = (RK + 1) / 2;
-  static constexpr int CT = D == 3 ? 2 : (RK == 3 ? 8 : 4), FT = HF * CT;
+  static constexpr int CT = CTILE, FT = HF * CT;
   static constexpr int ER = HF * CT + HF - 1;  // extent of the residual's box
   static constexpr int EM = 2;                 // largest smoothing count
   static constexpr int EB = ER + 2 * EM, EU = ER + 2 * (EM - 1);
@@ -134,11 +135,19 @@ __device__ __forceinline__ void unpack(int i, int (&x)[3]) {
   x[2] = D == 3 ? i / (E * E) : 0;
 }
 
-// Stencil of vertex v into registers.
+// Stencil of vertex v into registers.  uni >= 0: every vertex has that
+// vertex's stencil (but for the neighbours outside the interior, whose values
+// in a box are zero), which comes by scalar loads.
 template <typename T, int D>
-__device__ __forceinline__ void load_stencil(const T* __restrict__ st, int total, int v, T (&sv)[nst<D>()]) {
+__device__ __forceinline__ void load_stencil(const T* __restrict__ st, int total, int uni, int v,
+                                             T (&sv)[nst<D>()]) {
+  if (uni >= 0) {
 #pragma unroll
-  for (int s = 0; s < nst<D>(); ++s) sv[s] = st[(size_t)s * total + v];
+    for (int s = 0; s < nst<D>(); ++s) sv[s] = st[(size_t)s * total + uni];
+  } else {
+#pragma unroll
+    for (int s = 0; s < nst<D>(); ++s) sv[s] = st[(size_t)s * total + v];
+  }
 }
 
 // (A u) at the box point with array index `at` (extent E).
@@ -155,9 +164,9 @@ __device__ __forceinline__ T stencil_box(const T (&sv)[nst<D>()], const T* u, in
 // cells' corner contributions and stored), NU Jacobi steps from zero, the
 // residual, its restriction to the CT^D coarse vertices of the tile.  u and b
 // are stored for the vertices the tile owns.
-template <typename T, int D, int RK, int NU>
+template <typename T, int D, int RK, int CT, int NU>
 __device__ __forceinline__ void down_tile(const CGTileArgs<T>& a, int tile, int rhs, char* lds) {
-  using Ti = Tile<D, RK>;
+  using Ti = Tile<D, RK, CT>;
   constexpr int NS = nst<D>(), HF = Ti::HF, EB = Ti::EB, EU = Ti::EU, ER = Ti::ER;
   T* sB = (T*)lds;          // right-hand side, box of the residual grown by NU
   T* sU = sB + Ti::NB;      // first iterate on the same box
@@ -201,8 +210,8 @@ __device__ __forceinline__ void down_tile(const CGTileArgs<T>& a, int tile, int 
       v = v * nv + g;
     }
     vv[m] = in ? v : -1;
-    load_stencil<T, D>(a.st, total, in ? v : 0, sv[m]);
-    if (NU == 2) dv[m] = a.dinv[in ? v : 0];
+    load_stencil<T, D>(a.st, total, a.uni, in ? v : 0, sv[m]);
+    if (NU == 2) dv[m] = a.uni >= 0 ? a.dinv[a.uni] : a.dinv[in ? v : 0];
   }
   // b and the first step from zero (indices clamped, not branched around, so
   // that every load of the tile is in flight at once)
@@ -228,7 +237,7 @@ __device__ __forceinline__ void down_tile(const CGTileArgs<T>& a, int tile, int 
     }
     vb[m] = in ? v : -1;
     bb[m] = con ? gather_corners_at<T, D>(g, a.n, con) : bin[v];
-    db[m] = a.dinv[v];
+    db[m] = a.uni >= 0 ? a.dinv[a.uni] : a.dinv[v];
   }
   const int nc0 = threadIdx.x < Ti::NC ? (int)threadIdx.x : 0;
   int I[3];
@@ -311,9 +320,9 @@ __device__ __forceinline__ void down_tile(const CGTileArgs<T>& a, int tile, int 
 
 // Up: u + P e of the tile's surroundings, NU Jacobi steps, stored (into the
 // other iterate: neighbouring tiles still read this one).
-template <typename T, int D, int RK, int NU>
+template <typename T, int D, int RK, int CT, int NU>
 __device__ __forceinline__ void up_tile(const CGTileArgs<T>& a, int tile, int rhs, char* lds) {
-  using Ti = Tile<D, RK>;
+  using Ti = Tile<D, RK, CT>;
   constexpr int NS = nst<D>(), FT = Ti::FT, EW = FT + 2 * NU, E1 = FT + 2 * (NU - 1);
   constexpr int NW = cpow(EW, D), N1 = cpow(E1, D);
   constexpr int RPT = (N1 + Ti::THREADS - 1) / Ti::THREADS;
@@ -343,9 +352,9 @@ __device__ __forceinline__ void up_tile(const CGTileArgs<T>& a, int tile, int rh
       v = v * nv + g;
     }
     vv[m] = in ? v : -1;
-    load_stencil<T, D>(a.st, total, in ? v : 0, sv[m]);
+    load_stencil<T, D>(a.st, total, a.uni, in ? v : 0, sv[m]);
     bv[m] = b[in ? v : 0];
-    dv[m] = a.dinv[in ? v : 0];
+    dv[m] = a.uni >= 0 ? a.dinv[a.uni] : a.dinv[in ? v : 0];
   }
 #pragma unroll
   for (int m = 0; m < (NW + Ti::THREADS - 1) / Ti::THREADS; ++m) {
@@ -399,13 +408,14 @@ __device__ __forceinline__ void up_tile(const CGTileArgs<T>& a, int tile, int rh
 }
 
 // Tiles of a level on the way down / up.
-template <int D, int RK>
+template <int D, int CT>
 inline int down_tiles(int nvc) {
-  return cpow((nvc + Tile<D, RK>::CT - 1) / Tile<D, RK>::CT, D);
+  return cpow((nvc + CT - 1) / CT, D);
 }
-template <int D, int RK>
+template <int D, int RK, int CT>
 inline int up_tiles(int nv) {
-  return cpow((nv + Tile<D, RK>::FT - 1) / Tile<D, RK>::FT, D);
+  constexpr int FT = Tile<D, RK, CT>::FT;
+  return cpow((nv + FT - 1) / FT, D);
 }
 
 }  // namespace cgt

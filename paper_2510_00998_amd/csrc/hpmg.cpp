@@ -539,6 +539,24 @@ void build_cg_levels(hpmg_ctx* h, hipStream_t s) {
     const int NS = nstencil(D);
     std::vector<double> dinv(L.size);
     for (size_t v = 0; v < L.size; ++v) dinv[v] = 1.0 / st[v * NS + NS / 2];
+    // one stencil for all vertices?  (constant kappa, no smaller last cell;
+    // neighbours outside the interior aside)
+    const size_t c = L.nv / 2, mid = c + L.nv * (c + (D == 3 ? L.nv * c : 0));
+    bool uniform = L.nv >= 3;
+    for (size_t v = 0; v < L.size && uniform; ++v) {
+      const int x[3] = {(int)(v % L.nv), (int)(v / L.nv % L.nv), D == 3 ? (int)(v / L.nv / L.nv) : 0};
+      bool inner = true;
+      for (int d = 0; d < D; ++d) inner = inner && x[d] > 0 && x[d] < L.nv - 1;
+      for (int k = 0; k < NS && uniform; ++k) {
+        bool in = true;
+        if (!inner) {
+          const int y[3] = {x[0] + k % 3 - 1, x[1] + (k / 3) % 3 - 1, D == 3 ? x[2] + k / 9 - 1 : 0};
+          for (int d = 0; d < D; ++d) in = in && y[d] >= 0 && y[d] < L.nv;
+        }
+        uniform = !in || st[v * NS + k] == st[mid * NS + k];
+      }
+    }
+    if (uniform) L.uni = (int)mid;
     // device copy point-major: st[s * size + v]
     std::vector<double> stp(st.size());
     for (size_t v = 0; v < L.size; ++v)
@@ -964,10 +982,6 @@ void apply(hpmg_ctx* h, int l, const T* u, const T* tr, const T* b, T* out, int 
   dg_run(h, hpmg::OP_APPLY, a, L.N, nrhs, b ? 1 : 0, s);
 }
 
-// Smoothing steps on the Q1 levels (their own counts, or the DG ones).
-int cg_nu_pre(const hpmg_ctx* h) { return h->opt.nu_pre_cg >= 0 ? h->opt.nu_pre_cg : h->opt.nu_pre; }
-int cg_nu_post(const hpmg_ctx* h) { return h->opt.nu_post_cg >= 0 ? h->opt.nu_post_cg : h->opt.nu_post; }
-
 // The Q1 part of a V-cycle from level m, entered with a zero initial guess, for
 // ncol right-hand sides (the level vectors hold max_rhs columns of L.size
 // entries each).  contrib: the right-hand side of level m is the sum of these
@@ -981,16 +995,7 @@ void vcycle_cg(hpmg_ctx* h, int m, const T* contrib, int ncol, hipStream_t s) {
   const T w = (T)h->opt.omega_cg;
   const int npre = cg_nu_pre(h), npost = cg_nu_post(h);
   const bool last = m + 1 == (int)h->cg.size();
-  // levels of at most CG_BLOCK_MAX_VERTICES: the rest of the cycle in one
-  // workgroup per column
-  const int nlev = (int)h->cg.size() - m;
-  size_t pool = 0;
-  for (int k = m; k < (int)h->cg.size(); ++k) pool += h->cg[k].size;
-  const bool block = !last && L.size <= (size_t)hpmg::CG_BLOCK_MAX_VERTICES &&
-                     nlev <= hpmg::CG_BLOCK_MAX_LEVELS && pool < (size_t)hpmg::CG_BLOCK_POOL;
-  // larger levels: one launch down, one up
-  const bool tiles = !last && !block && npre >= 1 && npre <= hpmg::CG_TILE_MAX_NU && npost >= 1 &&
-                     npost <= hpmg::CG_TILE_MAX_NU;
+  const bool block = !last && cg_in_block(h, m), tiles = !last && !block && cg_tiled(h);
   if (contrib && !tiles && !block)
     for (int c = 0; c < ncol; ++c)
       hpmg::gather_corners<T>(D, h->n, contrib + c * nct, d.b + (size_t)c * L.size, s);
@@ -1002,20 +1007,7 @@ void vcycle_cg(hpmg_ctx* h, int m, const T* contrib, int ncol, hipStream_t s) {
     return;
   }
   if (block) {
-    hpmg::CGBlockArgs<T> a{};
-    a.nlev = nlev;
-    a.nu_pre = npre;
-    a.nu_post = npost;
-    a.m = h->coarse_m;
-    a.omega = w;
-    a.Ainv = h->coarse_inv;
-    a.contrib = contrib;
-    a.scon = (long long)nct;
-    for (int k = 0; k < nlev; ++k) {
-      CGLevel& Lk = h->cg[m + k];
-      CGData<T>& dk = data<T>(Lk);
-      a.lv[k] = {Lk.nv, (int)Lk.size, dk.st, dk.dinv, dk.u[0], dk.b, Lk.ridx, dk.rw, Lk.pidx, dk.pw};
-    }
+    const hpmg::CGBlockArgs<T> a = cg_block_args<T>(h, m, contrib);
     L.cur = 0;
     hpmg::cg_vcycle_block<T>(D, L.rk, a, ncol, s);
     HIPCHK(hipGetLastError());
@@ -1024,25 +1016,7 @@ void vcycle_cg(hpmg_ctx* h, int m, const T* contrib, int ncol, hipStream_t s) {
   CGLevel& C = h->cg[m + 1];
   CGData<T>& dc = data<T>(C);
   if (tiles) {
-    hpmg::CGTileArgs<T> a{};
-    a.nv = L.nv;
-    a.nvc = C.nv;
-    a.n = h->n;
-    a.omega = w;
-    a.st = d.st;
-    a.dinv = d.dinv;
-    a.b = d.b;
-    a.u_in = d.u[0];
-    a.u_out = d.u[0];
-    a.contrib = contrib;
-    a.bc = dc.b;
-    a.ridx = L.ridx;
-    a.rw = d.rw;
-    a.pidx = L.pidx;
-    a.pw = d.pw;
-    a.sf = (long long)L.size;
-    a.sc = (long long)C.size;
-    a.scon = (long long)nct;
+    hpmg::CGTileArgs<T> a = cg_tile_args<T>(h, m, contrib);
     hpmg::cg_down<T>(D, L.rk, npre, a, ncol, s);
     HIPCHK(hipGetLastError());
     vcycle_cg<T>(h, m + 1, nullptr, ncol, s);

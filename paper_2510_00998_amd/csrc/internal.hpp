@@ -159,6 +159,7 @@ struct CGData {
 };
 
 struct CGLevel {
+  int uni = -1;  // a vertex whose stencil is that of every vertex, if there is one
   int n = 0, nv = 0;
   size_t size = 0;
   int cur = 0;                // which of u[0], u[1] holds the iterate
@@ -306,6 +307,73 @@ inline hpmg::DGArgs<T> dg_args(hpmg_ctx* h, DGLevel& L) {
     a.mif = h->mif;
     a.rfac = h->rfac;
   }
+  return a;
+}
+
+// Smoothing steps on the Q1 levels (their own counts, or the DG ones).
+inline int cg_nu_pre(const hpmg_ctx* h) { return h->opt.nu_pre_cg >= 0 ? h->opt.nu_pre_cg : h->opt.nu_pre; }
+inline int cg_nu_post(const hpmg_ctx* h) { return h->opt.nu_post_cg >= 0 ? h->opt.nu_post_cg : h->opt.nu_post; }
+
+// The Q1 cycle from level m down in one workgroup: one vertex per thread.
+inline bool cg_in_block(const hpmg_ctx* h, int m) {
+  size_t pool = 0;
+  for (size_t k = m; k < h->cg.size(); ++k) pool += h->cg[k].size;
+  return h->cg[m].size <= (size_t)hpmg::CG_BLOCK_MAX_VERTICES &&
+         (int)h->cg.size() - m <= hpmg::CG_BLOCK_MAX_LEVELS && pool < (size_t)hpmg::CG_BLOCK_POOL;
+}
+// Larger levels, down and up in one launch each: tiles grow by one vertex per
+// smoothing step on every side, which the box of two steps bounds.
+inline bool cg_tiled(const hpmg_ctx* h) {
+  const int a = cg_nu_pre(h), b = cg_nu_post(h);
+  return a >= 1 && a <= hpmg::CG_TILE_MAX_NU && b >= 1 && b <= hpmg::CG_TILE_MAX_NU;
+}
+
+// contrib: corner contributions that make up level m's right-hand side, or NULL
+template <typename T>
+inline hpmg::CGBlockArgs<T> cg_block_args(hpmg_ctx* h, int m, const T* contrib) {
+  hpmg::CGBlockArgs<T> a{};
+  a.nlev = (int)h->cg.size() - m;
+  a.nu_pre = cg_nu_pre(h);
+  a.nu_post = cg_nu_post(h);
+  a.m = h->coarse_m;
+  a.omega = (T)h->opt.omega_cg;
+  a.Ainv = h->coarse_inv;
+  a.contrib = contrib;
+  a.scon = (long long)h->ncell << h->dim;
+  for (int k = 0; k < a.nlev; ++k) {
+    CGLevel& L = h->cg[m + k];
+    CGData<T>& d = data<T>(L);
+    a.lv[k] = {L.nv, (int)L.size, d.st, d.dinv, d.u[0], d.b, L.ridx, d.rw, L.pidx, d.pw};
+  }
+  return a;
+}
+
+// Level m on the way down (u into u[0]); up: ec and u_out = u[1] are set by
+// the caller.
+template <typename T>
+inline hpmg::CGTileArgs<T> cg_tile_args(hpmg_ctx* h, int m, const T* contrib) {
+  CGLevel& L = h->cg[m];
+  CGLevel& C = h->cg[m + 1];
+  CGData<T>& d = data<T>(L);
+  hpmg::CGTileArgs<T> a{};
+  a.nv = L.nv;
+  a.nvc = C.nv;
+  a.n = h->n;
+  a.uni = L.uni;
+  a.omega = (T)h->opt.omega_cg;
+  a.st = d.st;
+  a.dinv = d.dinv;
+  a.b = d.b;
+  a.u_in = a.u_out = d.u[0];
+  a.contrib = contrib;
+  a.bc = data<T>(C).b;
+  a.ridx = L.ridx;
+  a.rw = d.rw;
+  a.pidx = L.pidx;
+  a.pw = d.pw;
+  a.sf = (long long)L.size;
+  a.sc = (long long)C.size;
+  a.scon = (long long)h->ncell << h->dim;
   return a;
 }
 

@@ -88,6 +88,7 @@ constexpr int CG_TILE_MAX_NU = 2;
 template <typename T>
 struct CGTileArgs {
   int nv, nvc, n;
+  int uni;  // >= 0: a vertex whose stencil is that of every vertex
   T omega;
   const T* st;
   const T* dinv;

@@ -41,3 +41,36 @@ def test_q1_levels(dim, n, hf, pre, post):
             err = rel_err(got[c * nd:(c + 1) * nd], ref[c])
             log(f"  {dt} column {c}: rel err {err:.3e}")
             assert err <= tol
+
+
+@pytest.mark.parametrize("pre,post", [(1, 2), (2, 2), (3, 1)])
+def test_q1_levels_of_a_batch(pre, post):
+    """maxit = 1 from u0 = 0: u1 = alpha z, z = V-cycle(r0), problems without,
+    with one and with two tiled Q1 levels and with one Q1 level in all."""
+    import paper_2510_00998_amd as hp
+    problems = [(2, 1), (4, 2), (9, 3), (10, 1), (13, 2), (19, 1)]
+    log(f"Q1 levels of a batch nu=({pre}, {post})")
+    kw = dict(nu_pre_cg=pre, nu_post_cg=post)
+    solvers = [hp.Solver(3, n, p, 1.7, max_rhs=2, **kw) for n, p in problems]
+    batch = hp.Batch(solvers)
+    us, bs, refs = [], [], []
+    for (n, p), s in zip(problems, solvers):
+        H = Hierarchy(3, n, p, 1.7, opts=HierarchyOptions(**kw))
+        A, nd = H.levels[0].A, s.ndof
+        b = synth.random_rhs(2 * nd, seed=64 + n)
+        ref = []
+        for r in range(2):
+            br = b[r * nd:(r + 1) * nd]
+            z = H.precondition(br)
+            ref.append((z @ br) / (z @ (A @ z)) * z)
+        refs.append(ref)
+        us.append(torch.zeros(2 * nd, dtype=torch.float64, device="cuda"))
+        bs.append(to_dev(b, torch.float64))
+    _, st = batch.solve(us, bs, rtol=1e-14, maxit=1, nrhs=2, check=False)
+    assert st == 4  # not converged after one iteration
+    for (n, p), s, u, ref in zip(problems, solvers, us, refs):
+        got, nd = to_host(u), s.ndof
+        for r in range(2):
+            err = rel_err(got[r * nd:(r + 1) * nd], ref[r])
+            log(f"  n={n} p={p} rhs={r}: rel err {err:.3e}")
+            assert err <= TOL[torch.float32]
