@@ -199,6 +199,12 @@ struct DGArgs {
   // computes u + omega D~^-1 (b - A u) and the apply A u.  In 2D traces are
   // then stored on boundary facets too.
   int ivar = 0;
+  // Variable kappa in 3D, FP64 and FP32, sweeps with u != 0 on entry: the
+  // right-hand side in nodal form, h_fwd b times Mhat^-1 along every axis, as
+  // [cell][node of the x line][line]; bp_mode 1 stores it, 2 reads it instead
+  // of forming it from b; vstride per right-hand side.
+  C* bp = nullptr;
+  int bp_mode = 0;
   int ncd = 0;         // nodes per direction of the coarse DG level (transfers with a run-time degree)
   // 16-bit storage sweeps (3D): 1 runs the six volume contractions of the
   // block solve on the matrix cores (16-bit operands, FP32 accumulation);

@@ -1284,13 +1284,27 @@ __device__ __forceinline__ void sweep_body(const DGArgs<T>& a, int bx, int by, c
   const size_t own = rv + (size_t)c * Sh::NV + ln;  // first node of the thread's line, stride L
 
   C ul[N], r[N], t[N];
+  // the right-hand side in nodal form, when an earlier sweep has left it
+  // (variable kappa, where the eigendata of the block solve fills the LDS pipe:
+  // degree 5, 48^3, FP64, a smoothing call 2153 -> 2029 us, degree
+  // 3, 64^3, FP32, 388 -> 377.  With constant kappa the vector it
+  // reads costs what the three contractions do: degree 4, 32^3, FP64 unchanged,
+  // degree 2, 63^3, FP32 165 -> 170 us)
+  constexpr bool BP = VARK && !UZERO && sizeof(T) == sizeof(C);
+  const bool have = BP && a.bp_mode == 2;
+  C* bp = a.bp + own;
+  {
+    const T* src = a.b + own;
+    if constexpr (BP) src = have ? bp : src;
 #pragma unroll
-  for (int j = 0; j < N; ++j) r[j] = a.b[own + j * L];
+    for (int j = 0; j < N; ++j) r[j] = src[j * L];
+  }
   if constexpr (!UZERO) {
 #pragma unroll
     for (int j = 0; j < N; ++j) ul[j] = a.u_in[own + j * L];
   }
   stage_block<T, D, N, VARK, IVAR, AD, !UZERO, false, A>(a, a.tr_in + rt, B, cl, c, ln, act, mask, ul, sNB, sW, sE, sKF);
+  if (have) hf = C(1);
 #pragma unroll
   for (int j = 0; j < N; ++j) r[j] *= hf;
 
@@ -1327,25 +1341,36 @@ __device__ __forceinline__ void sweep_body(const DGArgs<T>& a, int bx, int by, c
     cell_sync<D, N>();
   } else {
     const cptr<C> Mi = as_const(a.ref) + RefOff<N>::MIC;
-    if constexpr (Cells<D, N, AD>::BR) __syncthreads();  // traces staged, sW free
-    if (act) {
-      cs_mv<N>(Mi, r);
-      put(A, r);
-    }
-    if constexpr (Cells<D, N, AD>::BR)
+    if (have) {
+      __syncthreads();  // traces staged, sW free
+    } else {
+      if constexpr (Cells<D, N, AD>::BR) __syncthreads();
+      if (act) {
+        cs_mv<N>(Mi, r);
+        put(A, r);
+      }
+      if constexpr (Cells<D, N, AD>::BR)
+        cell_sync<D, N>();
+      else
+        __syncthreads();  // traces staged
+      if (act) {
+        get(1, r);
+        cs_mv<N>(Mi, r);
+        put(1, r);
+      }
       cell_sync<D, N>();
-    else
-      __syncthreads();  // traces staged
-    if (act) {
-      get(1, r);
-      cs_mv<N>(Mi, r);
-      put(1, r);
+      // x: b in nodal values along every axis
+      if (act) {
+        get(0, r);
+        cs_mv<N>(Mi, r);
+        if (BP && a.bp_mode == 1) {
+#pragma unroll
+          for (int j = 0; j < N; ++j) bp[j * L] = r[j];
+        }
+      }
     }
-    cell_sync<D, N>();
-    // x: b in nodal values along every axis, minus the lifts
+    // minus the lifts
     if (act) {
-      get(0, r);
-      cs_mv<N>(Mi, r);
       nodal_lifts<T, D, N, VARK, -1>(a, cl, 0, ln, sNB, sKF, r);
       block_mv<T, D, N, VARK, IVAR, AD, OP_SI>(a, sE, cl, smask, 0, r, t);
       put(0, t);

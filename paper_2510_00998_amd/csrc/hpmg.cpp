@@ -389,6 +389,12 @@ void build_dg_level(hpmg_ctx* h, DGLevel& L, const hpmg::Basis1D& B, const hpmg:
     L.d.tr[b] = (double*)h->mem.alloc(L.trsize * R * sizeof(double));
     L.f.tr[b] = (float*)h->mem.alloc(L.trsize * R * sizeof(float));
   }
+  // (up to degree 5 both types together take less than the bricks save of the
+  // traces of single cells; above, more)
+  if (h->dim == 3 && h->vark && L.N <= 6) {
+    L.d.bp = (double*)h->mem.alloc(L.ndof * R * sizeof(double));
+    L.f.bp = (float*)h->mem.alloc(L.ndof * R * sizeof(float));
+  }
 }
 
 // Q1 element stiffness on a cell of width h: h^(d-2) sum_k K1 (x) M1 ...
@@ -959,10 +965,16 @@ void project(hpmg_ctx* h, int l, const T* u, T* tr, int nrhs, hipStream_t s) {
   dg_run(h, hpmg::OP_PROJECT, a, L.N, nrhs, 0, s);
 }
 
+// DGArgs::bp_mode of the i-th of n sweeps on one right-hand side.
+int bp_step(int i, int n) { return n < 2 ? 0 : (i == 0 ? 1 : 2); }
+
 template <typename T>
-void sweep(hpmg_ctx* h, int l, T* u, const T* b, const T* trin, T* trout, bool uzero, int nrhs, hipStream_t s) {
+void sweep(hpmg_ctx* h, int l, T* u, const T* b, const T* trin, T* trout, bool uzero, int nrhs, hipStream_t s,
+           int bp_mode = 0) {
   DGLevel& L = h->dg[l];
   hpmg::DGArgs<T> a = dg_args<T>(h, L);
+  a.bp = data<hpmg::CT<T>>(L).bp;
+  a.bp_mode = a.bp ? bp_mode : 0;
   a.u_in = u;
   a.u_out = u;
   a.b = b;
@@ -1086,8 +1098,12 @@ void vcycle_dg(hpmg_ctx* h, int l, T* u, const T* b, bool uzero, int nrhs, hipSt
     zero = false;
   }
   if (!zero) project<T>(h, l, u, d.tr[0], nrhs, s);
+  // the first sweep with u != 0 leaves the right-hand side in nodal form for
+  // the others
+  const int nsweep = h->opt.nu_pre + h->opt.nu_post - (zero ? 1 : 0);
+  int isweep = 0;
   for (int i = 0; i < h->opt.nu_pre; ++i) {
-    sweep<T>(h, l, u, b, d.tr[cur], d.tr[cur ^ 1], zero, nrhs, s);
+    sweep<T>(h, l, u, b, d.tr[cur], d.tr[cur ^ 1], zero, nrhs, s, zero ? 0 : bp_step(isweep++, nsweep));
     cur ^= 1;
     zero = false;
   }
@@ -1171,7 +1187,7 @@ void vcycle_dg(hpmg_ctx* h, int l, T* u, const T* b, bool uzero, int nrhs, hipSt
     dg_run(h, hpmg::OP_PROLONG_Q1, pa, L.N, nrhs, 0, s);
   }
   for (int i = 0; i < h->opt.nu_post; ++i) {
-    sweep<T>(h, l, u, b, d.tr[cur], d.tr[cur ^ 1], false, nrhs, s);
+    sweep<T>(h, l, u, b, d.tr[cur], d.tr[cur ^ 1], false, nrhs, s, bp_step(isweep++, nsweep));
     cur ^= 1;
   }
 }
@@ -1811,7 +1827,8 @@ hpmg_status hpmg_smooth(hpmg_handle h, hpmg_dtype dtype, void* u, const void* b,
         if (h->opt.block_recompute == 2)
           sweep_split<T>(h, (T*)u, (const T*)b, d.tr[k & 1], d.tr[(k + 1) & 1], nrhs, stream);
         else
-          sweep<T>(h, 0, (T*)u, (const T*)b, d.tr[k & 1], d.tr[(k + 1) & 1], false, nrhs, stream);
+          sweep<T>(h, 0, (T*)u, (const T*)b, d.tr[k & 1], d.tr[(k + 1) & 1], false, nrhs, stream,
+                   bp_step(k, nsweeps));
       }
       if (h->opt.block_recompute == 2) split_join<T>(h, stream);
     });
@@ -1857,7 +1874,7 @@ hpmg_status hpmg_sweep(hpmg_handle h, hpmg_dtype dtype, void* u, const void* b, 
         if (h->opt.block_recompute == 2)
           sweep_split<T>(h, (T*)u, (const T*)b, d.tr[cur], d.tr[cur ^ 1], nrhs, stream);
         else
-          sweep<T>(h, 0, (T*)u, (const T*)b, d.tr[cur], d.tr[cur ^ 1], false, nrhs, stream);
+          sweep<T>(h, 0, (T*)u, (const T*)b, d.tr[cur], d.tr[cur ^ 1], false, nrhs, stream, bp_step(k, nsweeps));
         cur ^= 1;
       }
       if (h->opt.block_recompute == 2) split_join<T>(h, stream);
