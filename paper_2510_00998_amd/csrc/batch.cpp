@@ -34,8 +34,10 @@ struct Launch {
   // DG: runs of equal degree in `items` (degree, first item, count)
   std::vector<int3> runs;
   // DG: the same work in the cell blocks of tile variant 1 (half the cells
-  // per block), for the one-launch-per-degree kernels
+  // per block), for the one-launch-per-degree kernels and the launch over all
+  // degrees
   const hpmg::WorkItem* items1 = nullptr;
+  int nitems1 = 0;
   std::vector<int3> runs1;
 };
 
@@ -60,6 +62,7 @@ Launch dg_launch(DevMem& mem, int kind, int op, const void* args, std::vector<hp
   L.op = op;
   L.args = args;
   L.nitems = (int)items.size();
+  L.nitems1 = (int)items1.size();
   if (items.empty()) return L;
   L.items = sorted_runs(mem, std::move(items), L.runs, s);
   L.items1 = sorted_runs(mem, std::move(items1), L.runs1, s);
@@ -509,9 +512,9 @@ void run_grid(const std::vector<Launch>& v, int grid, bool split, int tile, hipS
             dg_run<double>(V, L.op, r, L.args, V == 0 ? L.items : L.items1, grid, s);
         }
     } else if (L.kind == 0) {
-      hpmg::batch_dg<float>(L.op, (const hpmg::DGArgs<float>*)L.args, L.items, L.nitems, grid, s);
+      hpmg::batch_dg<float>(L.op, (const hpmg::DGArgs<float>*)L.args, L.items1, L.nitems1, grid, s);
     } else {
-      hpmg::batch_dg<double>(L.op, (const hpmg::DGArgs<double>*)L.args, L.items, L.nitems, grid, s);
+      hpmg::batch_dg<double>(L.op, (const hpmg::DGArgs<double>*)L.args, L.items1, L.nitems1, grid, s);
     }
   }
   HIPCHK(hipGetLastError());

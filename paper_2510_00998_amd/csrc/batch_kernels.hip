@@ -7,38 +7,6 @@
 namespace hpmg {
 namespace {
 
-constexpr int cmax(int a, int b) { return a > b ? a : b; }
-
-template <typename T, int OP>
-constexpr int batch_lds() {
-  return cmax(cmax(cmax(item_lds<T, 2, OP>(), item_lds<T, 3, OP>()), cmax(item_lds<T, 4, OP>(), item_lds<T, 5, OP>())),
-              item_lds<T, 6, OP>());
-}
-
-// threads of a block that takes items of any degree
-constexpr int BATCH_BLOCK = cmax(cmax(cmax(DGShapeV<3, 2, 0>::BLOCK, DGShapeV<3, 3, 0>::BLOCK),
-                                      cmax(DGShapeV<3, 4, 0>::BLOCK, DGShapeV<3, 5, 0>::BLOCK)),
-                                 DGShapeV<3, 6, 0>::BLOCK);
-
-template <typename T, int OP>
-__global__ __launch_bounds__(BATCH_BLOCK) void k_dg_batch(const DGArgs<T>* __restrict__ args,
-                                                  const WorkItem* __restrict__ items, int nitems) {
-  __shared__ __attribute__((aligned(16))) char lds[batch_lds<T, OP>()];
-  for (int it = blockIdx.x; it < nitems; it += gridDim.x) {
-    const WorkItem w = items[it];
-    const DGArgs<T> a = args[w.x];
-    switch (w.w) {
-      case 2: dg_item<T, 2, OP>(a, w.y, w.z, lds); break;
-      case 3: dg_item<T, 3, OP>(a, w.y, w.z, lds); break;
-      case 4: dg_item<T, 4, OP>(a, w.y, w.z, lds); break;
-      case 5: dg_item<T, 5, OP>(a, w.y, w.z, lds); break;
-      case 6: dg_item<T, 6, OP>(a, w.y, w.z, lds); break;
-      default: break;
-    }
-    __syncthreads();  // the next item reuses the LDS
-  }
-}
-
 // ------------------------------------------------------------------ Q1
 __device__ __forceinline__ void vc3(int v, int nv, int& x, int& y, int& z) {
   x = v % nv;
@@ -442,20 +410,6 @@ inline unsigned grid_for(int n, int cap) { return (unsigned)(n < cap ? (n > 0 ? 
 }  // namespace
 
 template <typename T>
-void batch_dg(int op, const DGArgs<T>* args, const WorkItem* items, int nitems, int grid, hipStream_t s) {
-  const dim3 g(grid_for(nitems, grid)), b(BATCH_BLOCK);
-  switch (op) {
-    case BOP_SWEEP: hipLaunchKernelGGL((k_dg_batch<T, BOP_SWEEP>), g, b, 0, s, args, items, nitems); break;
-    case BOP_SWEEP0: hipLaunchKernelGGL((k_dg_batch<T, BOP_SWEEP0>), g, b, 0, s, args, items, nitems); break;
-    case BOP_RESTRICT: hipLaunchKernelGGL((k_dg_batch<T, BOP_RESTRICT>), g, b, 0, s, args, items, nitems); break;
-    case BOP_PROLONG: hipLaunchKernelGGL((k_dg_batch<T, BOP_PROLONG>), g, b, 0, s, args, items, nitems); break;
-    case BOP_PROJECT: hipLaunchKernelGGL((k_dg_batch<T, BOP_PROJECT>), g, b, 0, s, args, items, nitems); break;
-    case BOP_RESID: hipLaunchKernelGGL((k_dg_batch<T, BOP_RESID>), g, b, 0, s, args, items, nitems); break;
-    default: hipLaunchKernelGGL((k_dg_batch<T, BOP_APPLY>), g, b, 0, s, args, items, nitems); break;
-  }
-}
-
-template <typename T>
 void batch_cg(const CGArgs<T>* args, const WorkItem* items, int nitems, int grid, hipStream_t s) {
   hipLaunchKernelGGL((k_cg_batch<T>), dim3(grid_for(nitems, grid)), dim3(256), 0, s, args, items, nitems);
 }
@@ -485,8 +439,6 @@ void batch_cg_block(const CGBlockArgs<T>* args, const WorkItem* items, int nitem
 template void batch_cg_tile<float>(bool, int, const CGTileArgs<float>*, const WorkItem*, int, hipStream_t);
 template void batch_cg_block<float>(const CGBlockArgs<float>*, const WorkItem*, int, hipStream_t);
 
-template void batch_dg<float>(int, const DGArgs<float>*, const WorkItem*, int, int, hipStream_t);
-template void batch_dg<double>(int, const DGArgs<double>*, const WorkItem*, int, int, hipStream_t);
 template void batch_cg<float>(const CGArgs<float>*, const WorkItem*, int, int, hipStream_t);
 
 void bk_dot(const SegTable& t, const double* x, const double* y, const double* z, double* partial, hipStream_t s) {
