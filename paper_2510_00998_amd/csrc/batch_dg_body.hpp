@@ -13,22 +13,19 @@ template <typename T, int N, int OP>
 __device__ __forceinline__ void dg_item(const DGArgs<T>& a, int bx, int by, char* lds) {
   constexpr int NC = nc_next(N);
   if constexpr (OP == BOP_SWEEP)
-    HPMG_DGK::sweep_body<T, 3, N, false, false>(a, bx, by, lds);
+    HPMG_DGK::sweep_cells<T, 3, N, false, false>(a, bx, by, lds);
   else if constexpr (OP == BOP_SWEEP0)
-    HPMG_DGK::sweep_body<T, 3, N, true, false>(a, bx, by, lds);
-  else if constexpr (OP == BOP_RESTRICT) {
-    if constexpr (HPMG_DGK::dual_form<T, 3, true>())
-      HPMG_DGK::apply_dual_body<T, 3, N, NC, true, false>(a, bx, by, lds);
-    else
-      HPMG_DGK::apply_body<T, 3, N, NC, true, false>(a, bx, by, lds);
-  } else if constexpr (OP == BOP_PROLONG)
+    HPMG_DGK::sweep_cells<T, 3, N, true, false>(a, bx, by, lds);
+  else if constexpr (OP == BOP_RESTRICT)
+    HPMG_DGK::apply_cells<T, 3, N, NC, true, false>(a, bx, by, lds);
+  else if constexpr (OP == BOP_PROLONG)
     HPMG_DGK::prolong_body<T, 3, N, NC>(a, bx, by, lds);
   else if constexpr (OP == BOP_PROJECT)
     HPMG_DGK::prolong_body<T, 3, N, 0>(a, bx, by, lds);
   else if constexpr (OP == BOP_RESID)
-    HPMG_DGK::apply_body<T, 3, N, 0, true, false>(a, bx, by, lds);  // FP64 only
+    HPMG_DGK::apply_cells<T, 3, N, 0, true, false>(a, bx, by, lds);  // FP64 only
   else
-    HPMG_DGK::apply_body<T, 3, N, 0, false, false>(a, bx, by, lds);
+    HPMG_DGK::apply_cells<T, 3, N, 0, false, false>(a, bx, by, lds);
 }
 
 template <typename T, int N, int OP>

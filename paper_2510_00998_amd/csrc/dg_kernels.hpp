@@ -199,8 +199,8 @@ struct DGArgs {
   // computes u + omega D~^-1 (b - A u) and the apply A u.  In 2D traces are
   // then stored on boundary facets too.
   int ivar = 0;
-  // Variable kappa in 3D, FP64 and FP32, sweeps with u != 0 on entry: the
-  // right-hand side in nodal form, h_fwd b times Mhat^-1 along every axis, as
+  // Variable kappa in 3D, FP64, sweeps with u != 0 on entry: the right-hand
+  // side in nodal form, h_fwd b times Mhat^-1 along every axis, as
   // [cell][node of the x line][line]; bp_mode 1 stores it, 2 reads it instead
   // of forming it from b; vstride per right-hand side.
   C* bp = nullptr;

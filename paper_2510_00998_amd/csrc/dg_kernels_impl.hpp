@@ -3,7 +3,8 @@
 //
 // Every thread owns the line of a cell along the last axis (z in 3D): its
 // global loads and stores of u, b and the traces are consecutive across
-// lanes.  The lifts of all facets are added where the state holds nodal
+// lanes (dual form, see dual_sweep: x-lines).  In the nodal form, whose steps
+// follow, the lifts of all facets are added where the state holds nodal
 // values along every axis (b multiplied by Mhat^-1 along each axis), where a
 // facet field needs no tangential transform (see nodal_lifts).  Steps of the
 // fused sweep, one barrier after each (3D):
@@ -741,12 +742,46 @@ __device__ __forceinline__ void recompute_eig(const DGArgs<T>& a, int nc, CT<T>*
   }
 }
 
+// Variable kappa, apply (EV): S of every staged record becomes Si = S^T Mhat,
+// each entry rounded once as in the class tables (as two products an apply to
+// a smooth u has up to 1.25 times the error).  Follows a barrier that has
+// staged the records; one more must follow.
+template <typename T, int D, int N>
+__device__ __forceinline__ void make_si(const DGArgs<T>& a, int nc, CT<T>* sE) {
+  using C = CT<T>;
+  using Sh = DGShape<D, N>;
+  constexpr int R = (Sh::CPB * D * N + Sh::NT - 1) / Sh::NT;
+  const cptr<C> Mh = as_const(a.ref) + RefOff<N>::M;
+  const int tid = work_tid<D, N>();
+  C x[R][N];  // row i % N of Si from that column of S
+#pragma unroll
+  for (int m = 0; m < R; ++m) {
+    const int i = tid + m * Sh::NT;
+    if (i >= nc * D * N) continue;
+    const C* S = sE + i / N * Sh::EGV + i % N;
+    C y[N];
+#pragma unroll
+    for (int j = 0; j < N; ++j) y[j] = S[j * N];
+    mv<N, true>(Mh, y, x[m]);
+  }
+  __syncthreads();
+#pragma unroll
+  for (int m = 0; m < R; ++m) {
+    const int i = tid + m * Sh::NT;
+    if (i >= nc * D * N) continue;
+    C* E = sE + i / N * Sh::EGV + i % N * N;
+#pragma unroll
+    for (int j = 0; j < N; ++j) E[j] = x[m][j];
+  }
+}
+
 // Matrix of (cell, axis k) applied to a line: S^T (OP_ST), Si = S^T Mhat
-// (OP_SI), Si^T (OP_SIT) or S (OP_S) of its S | Si | lambda record.  Constant kappa: when
-// every lane of the wave needs the interior class, the even-odd form from
-// the compact tables; otherwise the record's LDS copy.
+// (OP_SI), Si^T (OP_SIT) or S (OP_S).  Constant kappa: when every lane of the
+// wave needs the interior class, the even-odd form from the compact tables;
+// otherwise the class record's LDS copy.  Variable kappa: the cell's record,
+// which holds S (then Si is two products, the first with Mhat) or, EV, Si.
 enum BlockOp { OP_ST = 0, OP_SI = 1, OP_S = 2, OP_SIT = 3 };
-template <typename T, int D, int N, bool VARK, bool IVAR, bool AD, int OP>
+template <typename T, int D, int N, bool VARK, bool IVAR, bool AD, int OP, bool EV = false>
 __device__ __forceinline__ void block_mv(const DGArgs<T>& a, const CT<T>* sE, int cl, int mask, int k,
                                          const CT<T> (&in)[N], CT<T> (&out)[N]) {
   using C = CT<T>;
@@ -754,24 +789,21 @@ __device__ __forceinline__ void block_mv(const DGArgs<T>& a, const CT<T>* sE, in
   constexpr bool si = OP == OP_SI || OP == OP_SIT, tr = OP == OP_ST || OP == OP_SIT;
   constexpr int off = si ? N * N : 0;
   if constexpr (VARK) {
-    // the record holds S alone: Si = S^T Mhat as two products (Mhat in
-    // even-odd form from the compact table), which leaves LDS for more cells
-    const C* S = sE + (cl * D + k) * Sh::EGV;
-    const cptr<C> Mc = as_const(a.ref) + RefOff<N>::MC;
-    if constexpr (OP == OP_SI) {
+    const C* G = sE + (cl * D + k) * Sh::EGV;
+    static_assert(EV ? si : OP != OP_SIT, "matrix of the record");
+    if constexpr (OP == OP_SI && !EV) {
       C x[N];
 #pragma unroll
       for (int j = 0; j < N; ++j) x[j] = in[j];
-      cs_mv<N>(Mc, x);
-      mv<N, true>(S, x, out);
+      cs_mv<N>(as_const(a.ref) + RefOff<N>::MC, x);
+      mv<N, true>(G, x, out);
     } else {
-      mv<N, OP == OP_ST>(S, in, out);
-      if constexpr (OP == OP_SIT) cs_mv<N>(Mc, out);
+      mv<N, tr>(G, in, out);
     }
   } else {
     const int cls = IVAR ? 0 : axis_cls<AD>(mask, k);
     // 2D degree 8 in FP32 keeps the plain product: the fixed point of its
-    // cycle is the rounded operator's (see dual_form)
+    // cycle is the rounded operator's (see dual_sweep)
     constexpr bool eo = D == 3 || sizeof(C) == 8 || N <= 8;
     if (eo && (IVAR || __all(cls == 0))) {
       const cptr<C> G = as_const(a.ref) + (si ? RefOff<N>::SIC : RefOff<N>::SC);
@@ -1003,8 +1035,9 @@ __device__ __forceinline__ void put_pair(C* sNB, int cl, int f, int ln, const Tr
 // are read or sW is written).  The loads of a thread are all issued before
 // the first LDS store.  Bricks: the traces at the brick's faces come from the
 // buffer, those inside it from the block's own u (u: the thread's line along
-// axis F), in storage precision as if they had been stored; sW is used.
-template <typename T, int D, int N, bool VARK, bool IVAR, bool AD, bool TRACES, bool SPLIT, int F>
+// axis F), in storage precision as if they had been stored; sW is used.  EV:
+// variable kappa's records as the apply reads them.
+template <typename T, int D, int N, bool VARK, bool IVAR, bool AD, bool TRACES, bool SPLIT, int F, bool EV = false>
 __device__ __forceinline__ void stage_block(const DGArgs<T>& a, const T* tr, const Cells<D, N, AD>& B, int cl, int c,
                                             int ln, bool act, int mask, const CT<T> (&u)[N], CT<T>* sNB, CT<T>* sW,
                                             CT<T>* sE, CT<T>* sKF) {
@@ -1082,23 +1115,45 @@ __device__ __forceinline__ void stage_block(const DGArgs<T>& a, const T* tr, con
       }
     }
   }
+  if constexpr (VARK && EV) {
+    if constexpr (!(BR && TRACES)) __syncthreads();  // records staged
+    make_si<T, D, N>(a, B.count(), sE);
+  }
 }
 
 // Form of a traversal: nodal (sweep_body, apply_body) or dual
-// (sweep_dual_body, apply_dual_body).
-// 2D is dual: its facets take one tangential transform of a single line, so
-// that the nodal form's extra products with Mhat^-1 buy nothing (Q2 16^2
-// V-cycle 41 us in both).
-// The FP32 residual is dual too: the fixed point of an FP32 cycle is that of
-// this operator as its rounded tables give it, and nothing after it corrects
-// it.  On Q4, 32^3 a cycle repeated to stagnation ends 4.9e-5 from the FP64
-// solution with the dual form's tables and 1.7e-4 with the nodal form's
-// (products with Mhat, S and Si each rounded), for 25 against 19 us per
-// residual.  The sweeps, whose rounding a cycle does correct, FP64 and the
-// 16-bit formats, whose stored u is coarser than either, are nodal.
-template <typename T, int D, bool RESID>
-constexpr bool dual_form() {
-  return D == 2 || (std::is_same<T, float>::value && RESID);
+// (sweep_dual_body, apply_dual_body).  The nodal form is the faster one in 3D
+// (see below), but the products with Mhat^-1 and Mhat add rounding, and with
+// the tables rounded once for all cells the error is systematic: its ratio to
+// the dual form's hardly depends on the mesh.  So a traversal is nodal where
+// its error against 64 bits is no larger than the dual form's (within 5%, as
+// far as the means below repeat).  Ratio at degree 1 to 8, four sweeps or one
+// apply on 4^3 to 32^3 cells, constant kappa, for a random | a smooth u:
+//   sweep FP64   .77  .96 1.04 1.01  .96 1.04 1.04 1.07 |  .58  .94 1.03 1.05  .96 1.77 1.21 2.01
+//   sweep FP32  1.40 1.03 1.26 1.04  .78  .96 1.17 1.01 | 1.02  .57 1.15  .94  .92 1.96 2.64 1.35
+//   apply FP64  1.11  .93 1.13  .98 1.00 1.02 1.02 1.02 | 2.39 1.03 1.23  .82  .93  .94  .74  .94
+//   apply FP32  1.33 1.71 1.38 1.55 1.20 1.10 1.34 1.31 |  .81  .84  .98 1.19  .80 1.13  .98 1.01
+// Variable kappa: sweeps .9 to 1.08 in FP64, 1.3 to 1.7 in FP32 at every degree;
+// apply 1.2 and more at half of the degrees.  16-bit storage, whose stored u is
+// coarser than either: 1.00 for sweeps; its residual, which steers the outer
+// iteration, is dual (Q5 96^3, log-normal kappa: 50 against 52 iterations in
+// FP16, 65 against 71 in BF16).  Gauss-Legendre nodes (DGArgs::gl; FP64 and FP32)
+// are dual throughout, by kernels of their own (GL): their ratios are others, up to
+// 1.44 in FP64 and 1.6 in FP32, both at degree 2.  2D: facets take one tangential transform of a
+// single line, so the nodal form's extra products buy nothing.
+// What the dual form costs, sweeps on more than 10^3 cells against the nodal
+// form's time: FP32 degree 1 1.37, 3 1.32, 6 1.15, 7 1.13, 8 1.22; FP64 degree 6
+// 1.16, 7 1.13, 8 1.22.
+template <typename T, int D, int N, bool VARK>
+constexpr bool dual_sweep() {
+  if (D == 2) return true;
+  if (sizeof(T) == 2) return false;
+  if (std::is_same<T, double>::value) return N > (VARK ? 8 : 6);
+  return VARK || !(N == 3 || N == 5 || N == 6);
+}
+template <typename T, int D, int N, bool VARK>
+constexpr bool dual_apply() {
+  return D == 2 || VARK || !std::is_same<T, double>::value || N == 2 || N == 4;
 }
 
 // ---- dual form: facet transforms and lifts (also of the matrix-core sweep)
@@ -1120,7 +1175,7 @@ __device__ __forceinline__ int tangential(int k, int pass) {
 // transforms along t1; pass 1 transforms along t2 (3D).  Work items are
 // ordered (facet, cell, line) so that a wave mostly sees one facet
 // direction and therefore one matrix.
-template <typename T, int D, int N, bool VARK, bool IVAR, bool AD = false>
+template <typename T, int D, int N, bool VARK, bool IVAR, bool AD = false, bool EV = false>
 __device__ __forceinline__ void facet_pass(const DGArgs<T>& a, const Cells<D, N, AD>& B, int pass, CT<T>* sNB,
                                            const CT<T>* sE, const CT<T>* sKF) {
   using C = CT<T>;
@@ -1156,8 +1211,8 @@ __device__ __forceinline__ void facet_pass(const DGArgs<T>& a, const Cells<D, N,
       }
     }
     if (t < k) {
-      block_mv<T, D, N, VARK, IVAR, AD, OP_SI>(a, sE, cl, smask, t, x1, o1);
-      block_mv<T, D, N, VARK, IVAR, AD, OP_SI>(a, sE, cl, smask, t, x2, o2);
+      block_mv<T, D, N, VARK, IVAR, AD, OP_SI, EV>(a, sE, cl, smask, t, x1, o1);
+      block_mv<T, D, N, VARK, IVAR, AD, OP_SI, EV>(a, sE, cl, smask, t, x2, o2);
     } else {
       mv<N, false>(Mh, x1, o1);
       mv<N, false>(Mh, x2, o2);
@@ -1228,8 +1283,8 @@ __device__ __forceinline__ void block_partial(double v, double* sh, double* out)
 // that in even-odd form) and a facet field enters with one multiply-add per
 // node, trace and facet.  Four instead of three waves per SIMD need no
 // register cap (74 VGPRs at degree 4 in FP64, 125 before).  Measured sweep,
-// dual -> nodal: FP64 Q4 32^3 57 -> 41.7 us, variable kappa Q3 64^3 FP32
-// 190 -> 135 us, FP16 Q5 48^3 99 -> 82 us; FP64 apply Q7 25^3 80 -> 55 us.
+// dual -> nodal: FP64 Q4 32^3 57 -> 41.7 us, FP16 Q5 48^3 99 -> 82 us; FP64
+// apply Q7 25^3 80 -> 55 us.
 //
 // Fused block-Jacobi sweep.  UZERO: u is identically zero on entry (first
 // sweep of a coarse-level smoothing with zero initial guess): u and the
@@ -1286,8 +1341,7 @@ __device__ __forceinline__ void sweep_body(const DGArgs<T>& a, int bx, int by, c
   C ul[N], r[N], t[N];
   // the right-hand side in nodal form, when an earlier sweep has left it
   // (variable kappa, where the eigendata of the block solve fills the LDS pipe:
-  // degree 5, 48^3, FP64, a smoothing call 2153 -> 2029 us, degree
-  // 3, 64^3, FP32, 388 -> 377.  With constant kappa the vector it
+  // degree 5, 48^3, FP64, a smoothing call 2153 -> 2029 us.  With constant kappa the vector it
   // reads costs what the three contractions do: degree 4, 32^3, FP64 unchanged,
   // degree 2, 63^3, FP32 165 -> 170 us)
   constexpr bool BP = VARK && !UZERO && sizeof(T) == sizeof(C);
@@ -1414,7 +1468,7 @@ __device__ __forceinline__ void sweep_body(const DGArgs<T>& a, int bx, int by, c
   if (act) store_other_traces<T, D, N, A, IVAR>(a, trout, sW, B, cl, c, mask, ln);
 }
 
-// The sweep in dual form (see dual_form): S^T along every axis with the
+// The sweep in dual form (see dual_sweep): S^T along every axis with the
 // facet lifts, transformed along their tangential axes, subtracted before
 // each; the x-lines of u and b stay in registers from load to update.
 template <typename T, int D, int N, bool UZERO, bool VARK, bool IVAR = false, bool AD = false>
@@ -1782,6 +1836,16 @@ __device__ __forceinline__ void sweep_body_mfma(const DGArgs<T>& a, int bx, int 
   if (act) store_other_traces<T, D, N, 0, IVAR>(a, trout, sW, B, cl, c, mask, ln);
 }
 
+// The sweep of a block in its form.  UZERO: the forms differ in the axes' order
+// alone.
+template <typename T, int D, int N, bool UZERO, bool VARK, bool IVAR = false, bool AD = false, bool GL = false>
+__device__ __forceinline__ void sweep_cells(const DGArgs<T>& a, int bx, int by, char* lds) {
+  if constexpr (D == 2 || (!UZERO && (GL || dual_sweep<T, D, N, VARK>())))
+    sweep_dual_body<T, D, N, UZERO, VARK, IVAR, AD>(a, bx, by, lds);
+  else
+    sweep_body<T, D, N, UZERO, VARK, IVAR, AD>(a, bx, by, lds);
+}
+
 // Waves per SIMD asked of the sweep: as many as its LDS allows (160 KB per
 // CU), so that the compiler does not spend registers on reading ahead past
 // that occupancy.  Variable kappa, two waves at degree 7 and 8 (left to itself
@@ -1794,7 +1858,7 @@ constexpr int sweep_waves_per_eu() {
   constexpr int waves = blocks * (DGShape<D, N>::BLOCK / 64) / 4;
   return waves < 5 ? waves : 5;
 }
-template <typename T, int D, int N, bool UZERO, bool VARK, bool IVAR, bool MF = false, bool AD = false>
+template <typename T, int D, int N, bool UZERO, bool VARK, bool IVAR, bool MF = false, bool AD = false, bool GL = false>
 __global__ __launch_bounds__((DGShape<D, N>::BLOCK))
 __attribute__((amdgpu_waves_per_eu(sweep_waves_per_eu<T, D, N, VARK>()))) void k_sweep(DGArgs<T> a) {
   __shared__ __attribute__((aligned(16))) char lds[cell_lds_bytes<T, D, N, VARK, AD>()];
@@ -1802,10 +1866,8 @@ __attribute__((amdgpu_waves_per_eu(sweep_waves_per_eu<T, D, N, VARK>()))) void k
   block_of_grid<D, N, AD>(a, id, rhs);
   if constexpr (MF)
     sweep_body_mfma<T, D, N, UZERO, VARK, IVAR>(a, id, rhs, lds);
-  else if constexpr (dual_form<T, D, false>())
-    sweep_dual_body<T, D, N, UZERO, VARK, IVAR, AD>(a, id, rhs, lds);
   else
-    sweep_body<T, D, N, UZERO, VARK, IVAR, AD>(a, id, rhs, lds);
+    sweep_cells<T, D, N, UZERO, VARK, IVAR, AD, GL>(a, id, rhs, lds);
 }
 
 // ---------------------------------------------------------------------------
@@ -1916,7 +1978,7 @@ __device__ __forceinline__ void apply_partial(const DGArgs<T>& a, double pdot, i
 
 // apply_body in dual form: Si along every axis, the eigenvalue sums, Si^T
 // back, with the facet lifts transformed along their tangential axes
-// (facet_pass) and added right after each axis.  See dual_form for where it
+// (facet_pass) and added right after each axis.  See dual_apply for where it
 // is used.
 template <typename T, int D, int N, int NC, bool RESID, bool VARK, bool IVAR = false, bool AD = false>
 __device__ __forceinline__ void apply_dual_body(const DGArgs<T>& a, int bx, int by, char* lds) {
@@ -1954,12 +2016,12 @@ __device__ __forceinline__ void apply_dual_body(const DGArgs<T>& a, int bx, int 
     }
   }
   double pdot = 0.0;  // share of p.(A p) (kdot)
-  stage_block<T, D, N, VARK, IVAR, AD, true, true, 0>(a, a.tr_in + rt, B, cl, c, ln, act, mask, ul, sNB, sW, sE, sKF);
+  stage_block<T, D, N, VARK, IVAR, AD, true, true, 0, true>(a, a.tr_in + rt, B, cl, c, ln, act, mask, ul, sNB, sW, sE, sKF);
   if (act && ln == 0) mask_lds<D, N, VARK>(sKF)[cl] = mask;
   __syncthreads();
 #pragma unroll
   for (int pass = 0; pass < D - 1; ++pass) {
-    facet_pass<T, D, N, VARK, IVAR, AD>(a, B, pass, sNB, sE, sKF);
+    facet_pass<T, D, N, VARK, IVAR, AD, true>(a, B, pass, sNB, sE, sKF);
     __syncthreads();
   }
 
@@ -1977,13 +2039,13 @@ __device__ __forceinline__ void apply_dual_body(const DGArgs<T>& a, int bx, int 
 #pragma unroll
         for (int j = 0; j < N; ++j) r[j] = sW[base + j * lds_stride<D, N>(k)];
       }
-      block_mv<T, D, N, VARK, IVAR, AD, OP_SI>(a, sE, cl, smask, k, r, t);
+      block_mv<T, D, N, VARK, IVAR, AD, OP_SI, true>(a, sE, cl, smask, k, r, t);
       if (k == D - 1) {
         C ls[N];
         eig_sums<D, N, VARK, IVAR, AD>(sE, cl, smask, k, ln, ls);
 #pragma unroll
         for (int j = 0; j < N; ++j) t[j] *= ls[j];
-        block_mv<T, D, N, VARK, IVAR, AD, OP_SIT>(a, sE, cl, smask, k, t, r);
+        block_mv<T, D, N, VARK, IVAR, AD, OP_SIT, true>(a, sE, cl, smask, k, t, r);
         dual_lifts<T, D, N, 1>(a, cl, k, ln, sNB, r);
 #pragma unroll
         for (int j = 0; j < N; ++j) t[j] = r[j];
@@ -2000,7 +2062,7 @@ __device__ __forceinline__ void apply_dual_body(const DGArgs<T>& a, int bx, int 
       C r[N], t[N];
 #pragma unroll
       for (int j = 0; j < N; ++j) r[j] = sW[base + j * lds_stride<D, N>(k)];
-      block_mv<T, D, N, VARK, IVAR, AD, OP_SIT>(a, sE, cl, smask, k, r, t);
+      block_mv<T, D, N, VARK, IVAR, AD, OP_SIT, true>(a, sE, cl, smask, k, r, t);
       dual_lifts<T, D, N, 1>(a, cl, k, ln, sNB, t);
       if (k == 0) {
 #pragma unroll
@@ -2146,22 +2208,27 @@ __device__ __forceinline__ void apply_body(const DGArgs<T>& a, int bx, int by, c
   if constexpr (NC != 0) restrict_body<T, D, N, NC>(a, B, by, sNB, sW);
 }
 
+template <typename T, int D, int N, int NC, bool RESID, bool VARK, bool IVAR = false, bool AD = false, bool GL = false>
+__device__ __forceinline__ void apply_cells(const DGArgs<T>& a, int bx, int by, char* lds) {
+  if constexpr (GL || dual_apply<T, D, N, VARK>())
+    apply_dual_body<T, D, N, NC, RESID, VARK, IVAR, AD>(a, bx, by, lds);
+  else
+    apply_body<T, D, N, NC, RESID, VARK, IVAR, AD>(a, bx, by, lds);
+}
+
 // Apply holds u, b and the neighbour traces in registers at once; for the
 // FP64 degree-4 instances at most 128 VGPRs (four waves per SIMD, no spills).
 template <typename T, int N>
 constexpr int apply_waves_per_eu() {
   return (sizeof(T) == 8 && N <= 5) ? 4 : 1;
 }
-template <typename T, int D, int N, int NC, bool RESID, bool VARK, bool IVAR, bool AD = false>
+template <typename T, int D, int N, int NC, bool RESID, bool VARK, bool IVAR, bool AD = false, bool GL = false>
 __global__ __launch_bounds__((DGShape<D, N>::BLOCK))
 __attribute__((amdgpu_waves_per_eu(apply_waves_per_eu<T, N>()))) void k_apply(DGArgs<T> a) {
   __shared__ __attribute__((aligned(16))) char lds[cell_lds_bytes<T, D, N, VARK, AD>()];
   int id, rhs;
   block_of_grid<D, N, AD>(a, id, rhs);
-  if constexpr (dual_form<T, D, RESID>())
-    apply_dual_body<T, D, N, NC, RESID, VARK, IVAR, AD>(a, id, rhs, lds);
-  else
-    apply_body<T, D, N, NC, RESID, VARK, IVAR, AD>(a, id, rhs, lds);
+  apply_cells<T, D, N, NC, RESID, VARK, IVAR, AD, GL>(a, id, rhs, lds);
 }
 
 // ---------------------------------------------------------------------------
@@ -2374,6 +2441,27 @@ bool launch_build_eig(const DGArgs<C>& a, hipStream_t s) {
   return false;
 }
 
+template <typename T, int D, int N, bool UZERO, bool VARK, bool IVAR, bool MF = false, bool AD = false>
+void start_sweep(const DGArgs<T>& a, dim3 grid, dim3 blk, hipStream_t s) {
+  if constexpr (!UZERO && sizeof(T) >= 4 && !dual_sweep<T, D, N, VARK>()) {
+    if (a.gl) {
+      hipLaunchKernelGGL((k_sweep<T, D, N, UZERO, VARK, IVAR, MF, AD, true>), grid, blk, 0, s, a);
+      return;
+    }
+  }
+  hipLaunchKernelGGL((k_sweep<T, D, N, UZERO, VARK, IVAR, MF, AD>), grid, blk, 0, s, a);
+}
+template <typename T, int D, int N, int NC, bool RESID, bool VARK, bool IVAR, bool AD = false>
+void start_apply(const DGArgs<T>& a, dim3 grid, dim3 blk, hipStream_t s) {
+  if constexpr (!dual_apply<T, D, N, VARK>()) {
+    if (a.gl) {
+      hipLaunchKernelGGL((k_apply<T, D, N, NC, RESID, VARK, IVAR, AD, true>), grid, blk, 0, s, a);
+      return;
+    }
+  }
+  hipLaunchKernelGGL((k_apply<T, D, N, NC, RESID, VARK, IVAR, AD>), grid, blk, 0, s, a);
+}
+
 template <typename T, int D, int N, bool UZERO>
 bool launch_sweep_u(const DGArgs<T>& a, int nrhs, hipStream_t s) {
   using Sh = DGShape<D, N>;
@@ -2383,26 +2471,26 @@ bool launch_sweep_u(const DGArgs<T>& a, int nrhs, hipStream_t s) {
   const dim3 blk(MF && a.mfma ? Sh::BLOCK : Sh::THREADS);
   if (a.adapt) {
     if constexpr (serves_adapt<T, D>()) {
-      hipLaunchKernelGGL((k_sweep<T, D, N, UZERO, false, false, false, true>), grid, blk, 0, s, a);
+      start_sweep<T, D, N, UZERO, false, false, false, true>(a, grid, blk, s);
       return true;
     }
   } else if (a.vark) {
     if constexpr (serves_vark<T, D>()) {
       if (MF && a.mfma)
-        hipLaunchKernelGGL((k_sweep<T, D, N, UZERO, true, false, MF>), grid, blk, 0, s, a);
+        start_sweep<T, D, N, UZERO, true, false, MF>(a, grid, blk, s);
       else
-        hipLaunchKernelGGL((k_sweep<T, D, N, UZERO, true, false>), grid, blk, 0, s, a);
+        start_sweep<T, D, N, UZERO, true, false>(a, grid, blk, s);
       return true;
     }
   } else if constexpr (serves_const<T, D>()) {
     if (MF && a.mfma && a.ivar)
-      hipLaunchKernelGGL((k_sweep<T, D, N, UZERO, false, true, MF>), grid, blk, 0, s, a);
+      start_sweep<T, D, N, UZERO, false, true, MF>(a, grid, blk, s);
     else if (MF && a.mfma)
-      hipLaunchKernelGGL((k_sweep<T, D, N, UZERO, false, false, MF>), grid, blk, 0, s, a);
+      start_sweep<T, D, N, UZERO, false, false, MF>(a, grid, blk, s);
     else if (a.ivar)
-      hipLaunchKernelGGL((k_sweep<T, D, N, UZERO, false, true>), grid, blk, 0, s, a);
+      start_sweep<T, D, N, UZERO, false, true>(a, grid, blk, s);
     else
-      hipLaunchKernelGGL((k_sweep<T, D, N, UZERO, false, false>), grid, blk, 0, s, a);
+      start_sweep<T, D, N, UZERO, false, false>(a, grid, blk, s);
     return true;
   }
   return false;
@@ -2417,19 +2505,19 @@ bool launch_apply_r(const DGArgs<T>& a, int nrhs, hipStream_t s) {
   const dim3 grid = block_grid<D, N>(a, nrhs), blk(DGShape<D, N>::THREADS);
   if (a.adapt) {
     if constexpr (serves_adapt<T, D>()) {
-      hipLaunchKernelGGL((k_apply<T, D, N, NC, RESID, false, false, true>), grid, blk, 0, s, a);
+      start_apply<T, D, N, NC, RESID, false, false, true>(a, grid, blk, s);
       return true;
     }
   } else if (a.vark) {
     if constexpr (serves_vark<T, D>()) {
-      hipLaunchKernelGGL((k_apply<T, D, N, NC, RESID, true, false>), grid, blk, 0, s, a);
+      start_apply<T, D, N, NC, RESID, true, false>(a, grid, blk, s);
       return true;
     }
   } else if constexpr (serves_const<T, D>()) {
     if (a.ivar)
-      hipLaunchKernelGGL((k_apply<T, D, N, NC, RESID, false, true>), grid, blk, 0, s, a);
+      start_apply<T, D, N, NC, RESID, false, true>(a, grid, blk, s);
     else
-      hipLaunchKernelGGL((k_apply<T, D, N, NC, RESID, false, false>), grid, blk, 0, s, a);
+      start_apply<T, D, N, NC, RESID, false, false>(a, grid, blk, s);
     return true;
   }
   return false;

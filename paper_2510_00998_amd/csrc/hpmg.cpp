@@ -389,12 +389,10 @@ void build_dg_level(hpmg_ctx* h, DGLevel& L, const hpmg::Basis1D& B, const hpmg:
     L.d.tr[b] = (double*)h->mem.alloc(L.trsize * R * sizeof(double));
     L.f.tr[b] = (float*)h->mem.alloc(L.trsize * R * sizeof(float));
   }
-  // (up to degree 5 both types together take less than the bricks save of the
-  // traces of single cells; above, more)
-  if (h->dim == 3 && h->vark && L.N <= 6) {
+  // (up to degree 5 it takes less than the bricks save of the traces of single
+  // cells; above, more; not where the sweeps are dual)
+  if (h->dim == 3 && h->vark && L.N <= 6 && h->opt.basis == 0)
     L.d.bp = (double*)h->mem.alloc(L.ndof * R * sizeof(double));
-    L.f.bp = (float*)h->mem.alloc(L.ndof * R * sizeof(float));
-  }
 }
 
 // Q1 element stiffness on a cell of width h: h^(d-2) sum_k K1 (x) M1 ...

@@ -102,7 +102,7 @@ struct DGData {
   int ecur = 0;
   T* rkb = nullptr;
   T* kappa = nullptr;
-  T* bp = nullptr;       // variable kappa in 3D: right-hand side in nodal form (DGArgs::bp)
+  T* bp = nullptr;       // variable kappa in 3D, FP64: right-hand side in nodal form (DGArgs::bp)
   T* u = nullptr;        // coarse levels only
   T* b = nullptr;        // coarse levels only
   T* tr[2] = {nullptr, nullptr};
