@@ -843,27 +843,29 @@ struct alignas(2 * sizeof(T)) TrPair {
   T g, q;
 };
 
-// Neighbour-side traces of the 2D facets of cell c at facet node ln.
-// Boundary facets have none: the caller zeroes them (finish_pair).  AD
-// (adaptive meshes): the slot table names the record.  IVAR (interior-block
-// smoother): a boundary facet takes the cell's own traces, negated.
+// Trace record (unit 2L values) that holds the neighbour-side traces of facet f
+// of cell c in runs of cells.  A boundary facet has none (finish_pair zeroes
+// what this names).  AD (adaptive meshes): the slot table names the record.
+// IVAR (interior-block smoother): a boundary facet takes the cell's own traces,
+// negated.
+template <typename T, int D, int N, bool IVAR, bool AD>
+__device__ __forceinline__ size_t nb_slot(const DGArgs<T>& a, int c, int mask, int f) {
+  if constexpr (AD) {
+    return (size_t)a.nbslot[(size_t)f * a.ncell + c];
+  } else {
+    const int st = ipow<D>(a.n, f >> 1);
+    const int nb = min(max((f & 1) ? c + st : c - st, 0), a.ncell - 1);
+    return IVAR && ((mask >> f) & 1) ? (size_t)f * a.ncell + c : (size_t)(f ^ 1) * a.ncell + nb;
+  }
+}
+// The traces of cell c at facet node ln of every facet.
 template <typename T, int D, int N, bool IVAR, bool AD>
 __device__ __forceinline__ void load_pairs(const DGArgs<T>& a, const T* tr, int c, int mask, int ln,
                                            TrPair<T> (&p)[2 * D]) {
   constexpr int L = DGShape<D, N>::L;
 #pragma unroll
-  for (int f = 0; f < 2 * D; ++f) {
-    size_t slot;
-    if constexpr (AD) {
-      slot = (size_t)a.nbslot[(size_t)f * a.ncell + c];
-    } else {
-      const int st = ipow<D>(a.n, f >> 1);
-      const int nb = min(max((f & 1) ? c + st : c - st, 0), a.ncell - 1);
-      slot = (size_t)(f ^ 1) * a.ncell + nb;
-      if (IVAR && ((mask >> f) & 1)) slot = (size_t)f * a.ncell + c;
-    }
-    p[f] = *reinterpret_cast<const TrPair<T>*>(tr + (slot * L + ln) * 2);
-  }
+  for (int f = 0; f < 2 * D; ++f)
+    p[f] = *reinterpret_cast<const TrPair<T>*>(tr + (nb_slot<T, D, N, IVAR, AD>(a, c, mask, f) * L + ln) * 2);
 }
 // The pair as the lifts read it: zero (IVAR: negated) on a boundary facet;
 // on the coarse side of a hanging facet, whose penalty is sig_hang,
@@ -1015,6 +1017,145 @@ __device__ __forceinline__ void store_other_traces(const DGArgs<T>& a, T* trout,
   }
 }
 
+// ---- dual form: facet transforms (also of the matrix-core sweep)
+
+// Tangential axis of pass `pass` of the facet transform of facets normal to k.
+template <int D>
+__device__ __forceinline__ int tangential(int k, int pass) {
+  if constexpr (D == 2)
+    return 1 - k;
+  else
+    return pass == 0 ? ((k == 0) ? 1 : 0) : ((k == 2) ? 1 : 2);
+}
+
+// Facet flux fields.  From the neighbour's traces (g', q') across facet f
+//   F1 = T_f (kappa_F (q'/2 - sigma_hat g')),  F2 = T_f (kappa_F g'/2),
+// T_f = G_t1 x G_t2 over the tangential axes with G_t = Si_t for t < k
+// (axes already transformed when facet k is processed) and Mhat otherwise.
+// sNB[cl][f][F1|F2][L].  Pass 0 takes the traces [as g | q] and transforms along
+// t1; pass 1 transforms along t2 (3D).  Work items are ordered (facet, cell,
+// line) so that a wave mostly sees one facet direction and therefore one
+// matrix.
+//
+// A line of facet f of local cell cl: pass 0's fluxes, then the matrix along t.
+template <typename T, int D, int N, bool VARK, bool IVAR, bool AD, bool EV>
+__device__ __forceinline__ void facet_line(const DGArgs<T>& a, int pass, const CT<T>* sE, const CT<T>* sKF, int cl,
+                                           int f, int smask, CT<T> (&x1)[N], CT<T> (&x2)[N], CT<T> (&o1)[N],
+                                           CT<T> (&o2)[N]) {
+  using C = CT<T>;
+  const int k = f >> 1, t = tangential<D>(k, pass);
+  if (pass == 0) {
+    const C kf = VARK ? sKF[cl * DGShape<D, N>::NF + f] : a.kappa_const;
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+      const C gv = x1[j], qv = x2[j];
+      // one rounding: sigma_hat g' and q'/2 cancel for a smooth u
+      x1[j] = kf * fma(-a.sigma_hat, gv, C(0.5) * qv);
+      x2[j] = C(0.5) * kf * gv;
+    }
+  }
+  if (t < k) {
+    block_mv<T, D, N, VARK, IVAR, AD, OP_SI, EV>(a, sE, cl, smask, t, x1, o1);
+    block_mv<T, D, N, VARK, IVAR, AD, OP_SI, EV>(a, sE, cl, smask, t, x2, o2);
+  } else {
+    const cptr<C> Mh = as_const(a.ref) + RefOff<N>::M;
+    mv<N, false>(Mh, x1, o1);
+    mv<N, false>(Mh, x2, o2);
+  }
+}
+template <typename T, int D, int N, bool VARK, bool IVAR, bool AD = false, bool EV = false>
+__device__ __forceinline__ void facet_pass(const DGArgs<T>& a, const Cells<D, N, AD>& B, int pass, CT<T>* sNB,
+                                           const CT<T>* sE, const CT<T>* sKF) {
+  using C = CT<T>;
+  using Sh = DGShape<D, N>;
+  constexpr int L = Sh::L;
+  constexpr int LINES = (D == 2) ? 1 : N;
+  for (int i = work_tid<D, N>(); i < Sh::CPB * Sh::NF * LINES; i += Sh::NT) {
+    const int f = i / (Sh::CPB * LINES), rem = i % (Sh::CPB * LINES);
+    const int cl = rem / LINES, li = rem % LINES;
+    if (!B.valid(cl)) continue;
+    const int st = pass == 0 ? 1 : N;  // node stride along t within the facet
+    C* g = sNB + (cl * Sh::NF + f) * 2 * L + (pass == 0 ? N * li : li);
+    const int smask = IVAR ? 0 : mask_lds<D, N, VARK>(sKF)[cl];  // boundary classes of the block solve
+    C x1[N], x2[N], o1[N], o2[N];
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+      x1[j] = g[st * j];
+      x2[j] = g[L + st * j];
+    }
+    facet_line<T, D, N, VARK, IVAR, AD, EV>(a, pass, sE, sKF, cl, f, smask, x1, x2, o1, o2);
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+      g[st * j] = o1[j];
+      g[L + st * j] = o2[j];
+    }
+  }
+}
+
+// Runs of cells with constant kappa take pass 0 straight from the trace buffer
+// (FacetLoad): a barrier and an LDS round trip less than through staged traces
+// (four matrix-core sweeps, FP16, Q4 32^3 237 -> 180 us, Q8 8^3 126 -> 83 us).  With variable kappa the pass needs the staged records.
+template <int D, int N, bool VARK, bool AD>
+constexpr bool pass0_on_load() {
+  return !VARK && !Cells<D, N, AD>::BR;
+}
+// A thread's items of pass 0: every load is issued by the constructor, run()
+// transforms them into sNB.
+template <typename T, int D, int N, bool IVAR, bool AD>
+struct FacetLoad {
+  using C = CT<T>;
+  using Sh = DGShape<D, N>;
+  static constexpr int L = Sh::L, LINES = (D == 2) ? 1 : N, ITEMS = Sh::CPB * Sh::NF * LINES;
+  static constexpr int IT = (ITEMS + Sh::NT - 1) / Sh::NT;
+  TrPair<T> p[IT][N];
+  int msk[IT];
+  static __device__ __forceinline__ void item(const Cells<D, N, AD>& B, int m, int& f, int& cl, int& li, bool& ok) {
+    const int i = work_tid<D, N>() + m * Sh::NT;
+    f = min(i / (Sh::CPB * LINES), Sh::NF - 1);
+    cl = i % (Sh::CPB * LINES) / LINES;
+    li = i % LINES;
+    ok = i < ITEMS && B.valid(cl);
+  }
+  __device__ __forceinline__ FacetLoad(const DGArgs<T>& a, const T* tr, const Cells<D, N, AD>& B) {
+#pragma unroll
+    for (int m = 0; m < IT; ++m) {
+      int f, cl, li;
+      bool ok;
+      item(B, m, f, cl, li, ok);
+      const int c = B.cell(ok ? cl : 0);
+      msk[m] = cell_mask<AD>(a, c);
+      const TrPair<T>* src =
+          reinterpret_cast<const TrPair<T>*>(tr) + nb_slot<T, D, N, IVAR, AD>(a, c, msk[m], f) * L + N * li;
+#pragma unroll
+      for (int j = 0; j < N; ++j) p[m][j] = src[j];
+    }
+  }
+  __device__ __forceinline__ void run(const DGArgs<T>& a, const Cells<D, N, AD>& B, C* sNB) const {
+#pragma unroll
+    for (int m = 0; m < IT; ++m) {
+      int f, cl, li;
+      bool ok;
+      item(B, m, f, cl, li, ok);
+      if (!ok) continue;
+      C x1[N], x2[N], o1[N], o2[N];
+#pragma unroll
+      for (int j = 0; j < N; ++j) {
+        const TrPair<C> v = finish_pair<T, IVAR, AD>(a, p[m][j], msk[m], f);
+        x1[j] = v.g;
+        x2[j] = v.q;
+      }
+      // the class tables in global memory: those in LDS are not staged yet
+      facet_line<T, D, N, false, IVAR, AD, false>(a, 0, a.eig, nullptr, cl, f, IVAR ? 0 : msk[m], x1, x2, o1, o2);
+      C* g = sNB + (cl * Sh::NF + f) * 2 * L + N * li;
+#pragma unroll
+      for (int j = 0; j < N; ++j) {
+        g[j] = o1[j];
+        g[L + j] = o2[j];
+      }
+    }
+  }
+};
+
 // Staged trace of (local cell, facet) at facet node ln; SPLIT (dual form): the
 // record as [g | q] instead of pairs.
 template <int D, int N, bool SPLIT, typename C>
@@ -1036,7 +1177,8 @@ __device__ __forceinline__ void put_pair(C* sNB, int cl, int f, int ln, const Tr
 // the first LDS store.  Bricks: the traces at the brick's faces come from the
 // buffer, those inside it from the block's own u (u: the thread's line along
 // axis F), in storage precision as if they had been stored; sW is used.  EV:
-// variable kappa's records as the apply reads them.
+// variable kappa's records as the apply reads them.  Where pass0_on_load, sNB
+// gets the fields after pass 0 of the dual form's transforms instead.
 template <typename T, int D, int N, bool VARK, bool IVAR, bool AD, bool TRACES, bool SPLIT, int F, bool EV = false>
 __device__ __forceinline__ void stage_block(const DGArgs<T>& a, const T* tr, const Cells<D, N, AD>& B, int cl, int c,
                                             int ln, bool act, int mask, const CT<T> (&u)[N], CT<T>* sNB, CT<T>* sW,
@@ -1046,6 +1188,12 @@ __device__ __forceinline__ void stage_block(const DGArgs<T>& a, const T* tr, con
   constexpr int L = Sh::L;
   constexpr bool BR = Cells<D, N, AD>::BR;
   const int tid = work_tid<D, N>();
+  if constexpr (TRACES && SPLIT && pass0_on_load<D, N, VARK, AD>()) {
+    const FacetLoad<T, D, N, IVAR, AD> fl(a, tr, B);
+    load_eig<T, D, N, VARK, AD>(a, B, sE, sKF);
+    fl.run(a, B, sNB);
+    return;
+  }
   TrPair<T> p[2 * D];
   int l[3] = {0, 0, 0};
   if constexpr (BR && TRACES) {
@@ -1156,74 +1304,7 @@ constexpr bool dual_apply() {
   return D == 2 || VARK || !std::is_same<T, double>::value || N == 2 || N == 4;
 }
 
-// ---- dual form: facet transforms and lifts (also of the matrix-core sweep)
-
-// Tangential axis of pass `pass` of the facet transform of facets normal to k.
-template <int D>
-__device__ __forceinline__ int tangential(int k, int pass) {
-  if constexpr (D == 2)
-    return 1 - k;
-  else
-    return pass == 0 ? ((k == 0) ? 1 : 0) : ((k == 2) ? 1 : 2);
-}
-
-// Facet flux fields.  From the neighbour's traces (g', q') across facet f
-//   F1 = T_f (kappa_F (q'/2 - sigma_hat g')),  F2 = T_f (kappa_F g'/2),
-// T_f = G_t1 x G_t2 over the tangential axes with G_t = Si_t for t < k
-// (axes already transformed when facet k is processed) and Mhat otherwise.
-// sNB[cl][f][F1|F2][L].  Pass 0 reads the traces staged as [g | q] and
-// transforms along t1; pass 1 transforms along t2 (3D).  Work items are
-// ordered (facet, cell, line) so that a wave mostly sees one facet
-// direction and therefore one matrix.
-template <typename T, int D, int N, bool VARK, bool IVAR, bool AD = false, bool EV = false>
-__device__ __forceinline__ void facet_pass(const DGArgs<T>& a, const Cells<D, N, AD>& B, int pass, CT<T>* sNB,
-                                           const CT<T>* sE, const CT<T>* sKF) {
-  using C = CT<T>;
-  using Sh = DGShape<D, N>;
-  constexpr int L = Sh::L;
-  constexpr int TL = 2 * L;
-  constexpr int LINES = (D == 2) ? 1 : N;
-  const cptr<C> Mh = as_const(a.ref) + RefOff<N>::M;
-  for (int i = work_tid<D, N>(); i < Sh::CPB * Sh::NF * LINES; i += Sh::NT) {
-    const int f = i / (Sh::CPB * LINES), rem = i % (Sh::CPB * LINES);
-    const int cl = rem / LINES, li = rem % LINES;
-    if (!B.valid(cl)) continue;
-    const int k = f >> 1;
-    const int t = tangential<D>(k, pass);
-    const int st = pass == 0 ? 1 : N;  // node stride along t within the facet
-    const int lo = pass == 0 ? N * li : li;
-    C* g = sNB + (cl * Sh::NF + f) * TL + lo;
-    const int smask = IVAR ? 0 : mask_lds<D, N, VARK>(sKF)[cl];  // boundary classes of the block solve
-    C x1[N], x2[N], o1[N], o2[N];
-#pragma unroll
-    for (int j = 0; j < N; ++j) {
-      x1[j] = g[st * j];
-      x2[j] = g[L + st * j];
-    }
-    if (pass == 0) {
-      const C kf = VARK ? sKF[cl * Sh::NF + f] : a.kappa_const;
-#pragma unroll
-      for (int j = 0; j < N; ++j) {
-        const C gv = x1[j], qv = x2[j];
-        // one rounding: sigma_hat g' and q'/2 cancel for a smooth u
-        x1[j] = kf * fma(-a.sigma_hat, gv, C(0.5) * qv);
-        x2[j] = C(0.5) * kf * gv;
-      }
-    }
-    if (t < k) {
-      block_mv<T, D, N, VARK, IVAR, AD, OP_SI, EV>(a, sE, cl, smask, t, x1, o1);
-      block_mv<T, D, N, VARK, IVAR, AD, OP_SI, EV>(a, sE, cl, smask, t, x2, o2);
-    } else {
-      mv<N, false>(Mh, x1, o1);
-      mv<N, false>(Mh, x2, o2);
-    }
-#pragma unroll
-    for (int j = 0; j < N; ++j) {
-      g[st * j] = o1[j];
-      g[L + st * j] = o2[j];
-    }
-  }
-}
+// ---- dual form: lifts (also of the matrix-core sweep)
 
 // r += SIGN x the dual lift of facets (k,0) and (k,1): value part at the
 // facet node, normal derivative part along the line.
@@ -1511,7 +1592,7 @@ __device__ __forceinline__ void sweep_dual_body(const DGArgs<T>& a, int bx, int 
   __syncthreads();
   if constexpr (!UZERO) {
 #pragma unroll
-    for (int pass = 0; pass < D - 1; ++pass) {
+    for (int pass = pass0_on_load<D, N, VARK, AD>() ? 1 : 0; pass < D - 1; ++pass) {
       facet_pass<T, D, N, VARK, IVAR, AD>(a, B, pass, sNB, sE, sKF);
       __syncthreads();
     }
@@ -1668,8 +1749,7 @@ struct Mfma16<__bf16> {
 };
 
 template <typename T, int D, int N, bool VARK, bool IVAR, bool TR, bool SCALE>
-__device__ __forceinline__ void mfma_stage(float* sW, const float* sE, const int* sMask, int k) {
-  // sMask: boundary mask of each local cell, -1 where there is none
+__device__ __forceinline__ void mfma_stage(float* sW, const float* sE, const int* sMask, int nc, int k) {
   using Sh = DGShape<D, N>;
   constexpr int NN = N * N;
   constexpr int L = Sh::L;
@@ -1698,15 +1778,13 @@ __device__ __forceinline__ void mfma_stage(float* sW, const float* sE, const int
       const int kk = 4 * kq + j;
       const int kb = kk / N, jj = kk % N;
       const int cl = g * NB + kb;
-      const int clc = min(cl, Sh::CPB - 1);
-      const bool okb = kb < NB && cl < Sh::CPB && sMask[clc] >= 0 && line < L;
-      const float x = sW[clc * Sh::NVP + lb + (jj < N ? jj : 0) * stride];
+      const bool okb = kb < NB && cl < nc && line < L;
+      const float x = sW[min(cl, nc - 1) * Sh::NVP + lb + (jj < N ? jj : 0) * stride];
       bv[j] = okb ? x : 0.f;
       const int rb = c / N, ii = c % N;
       const int cla = g * NB + rb;
-      const int clac = min(cla, Sh::CPB - 1);
-      const bool oka = rb == kb && rb < NB && cla < Sh::CPB && sMask[clac] >= 0;
-      const float* G = rec(clac);
+      const bool oka = rb == kb && rb < NB && cla < nc;
+      const float* G = rec(min(cla, nc - 1));
       const float gv = TR ? G[jj * N + ii] : G[ii * N + jj];
       av[j] = oka ? gv : 0.f;
     }
@@ -1716,7 +1794,7 @@ __device__ __forceinline__ void mfma_stage(float* sW, const float* sE, const int
       const int i = 4 * kq + j;
       const int rb = i / N, ii = i % N;
       const int cl = g * NB + rb;
-      if (rb < NB && cl < Sh::CPB && line < L && sMask[cl] >= 0) {
+      if (rb < NB && cl < nc && line < L) {
         float v = d[j];
         if constexpr (SCALE) {
           // lambda sum of node (line, ii) along the last axis k = D - 1
@@ -1776,12 +1854,13 @@ __device__ __forceinline__ void sweep_body_mfma(const DGArgs<T>& a, int bx, int 
       for (int j = 0; j < N; ++j) ul[j] = us[j];
     }
   }
-  if (ln == 0 && cl < Sh::CPB) sMask[cl] = act ? mask : -1;
+  static_assert(!Cells<D, N, false>::BR, "16-bit storage: runs of cells");
+  if (act && ln == 0) sMask[cl] = mask;
   stage_block<T, D, N, VARK, IVAR, false, !UZERO, true, 0>(a, a.tr_in + rt, B, cl, c, ln, act, mask, ul, sNB, sW, sE, sKF);
   __syncthreads();
   if constexpr (!UZERO) {
 #pragma unroll
-    for (int pass = 0; pass < D - 1; ++pass) {
+    for (int pass = pass0_on_load<D, N, VARK, false>() ? 1 : 0; pass < D - 1; ++pass) {
       facet_pass<T, D, N, VARK, IVAR>(a, B, pass, sNB, sE, sKF);
       __syncthreads();
     }
@@ -1807,15 +1886,15 @@ __device__ __forceinline__ void sweep_body_mfma(const DGArgs<T>& a, int bx, int 
     }
     __syncthreads();
     if (k == D - 1)
-      mfma_stage<T, D, N, VARK, IVAR, true, true>(sW, sE, sMask, k);
+      mfma_stage<T, D, N, VARK, IVAR, true, true>(sW, sE, sMask, B.nc, k);
     else
-      mfma_stage<T, D, N, VARK, IVAR, true, false>(sW, sE, sMask, k);
+      mfma_stage<T, D, N, VARK, IVAR, true, false>(sW, sE, sMask, B.nc, k);
     __syncthreads();
   }
   // inverse: S along every axis, last axis first
 #pragma unroll
   for (int k = D - 1; k >= 0; --k) {
-    mfma_stage<T, D, N, VARK, IVAR, false, false>(sW, sE, sMask, k);
+    mfma_stage<T, D, N, VARK, IVAR, false, false>(sW, sE, sMask, B.nc, k);
     __syncthreads();
   }
   // update, store of u and of the traces
@@ -2020,7 +2099,7 @@ __device__ __forceinline__ void apply_dual_body(const DGArgs<T>& a, int bx, int 
   if (act && ln == 0) mask_lds<D, N, VARK>(sKF)[cl] = mask;
   __syncthreads();
 #pragma unroll
-  for (int pass = 0; pass < D - 1; ++pass) {
+  for (int pass = pass0_on_load<D, N, VARK, AD>() ? 1 : 0; pass < D - 1; ++pass) {
     facet_pass<T, D, N, VARK, IVAR, AD, true>(a, B, pass, sNB, sE, sKF);
     __syncthreads();
   }
