@@ -29,6 +29,7 @@ SOURCES = [
     "adapt_kernels.hip",
     "dg_inst_2d_float.hip",
     "dg_inst_2d_double.hip",
+    "dg_inst_2d_double_plain.hip",
     "dg_inst_2d_f16.hip",
     "dg_inst_2d_bf16.hip",
     "dg_inst_3d_float.hip",

@@ -802,9 +802,11 @@ __device__ __forceinline__ void block_mv(const DGArgs<T>& a, const CT<T>* sE, in
     }
   } else {
     const int cls = IVAR ? 0 : axis_cls<AD>(mask, k);
-    // 2D degree 8 in FP32 keeps the plain product: the fixed point of its
-    // cycle is the rounded operator's (see dual_sweep)
-    constexpr bool eo = D == 3 || sizeof(C) == 8 || N <= 8;
+    // 2D: FP32 of degree 8 is faster with the plain product on all but large
+    // meshes (sweeps, even-odd against plain: 1.14 on 4^2 cells, 1.04 on 64^2,
+    // 0.87 on 150^2; the errors are alike), FP64 of degree 6 to 8 on meshes of few blocks
+    // (HPMG_TILE 4, see dg_inst_2d_double_plain.hip)
+    constexpr bool eo = D == 3 || (sizeof(C) == 8 ? HPMG_TILE != 4 : N <= 8);
     if (eo && (IVAR || __all(cls == 0))) {
       const cptr<C> G = as_const(a.ref) + (si ? RefOff<N>::SIC : RefOff<N>::SC);
       if constexpr (OP == OP_S || OP == OP_SIT)
