@@ -1,4 +1,5 @@
-// Instantiation of the DG cell kernels for dim = 3, storage type float: adaptive meshes.
+// Instantiation of the DG cell kernels for dim = 3, storage type float: adaptive and small
+// meshes (run_cells).
 #define HPMG_TILE 3
 #include "dg_inst.hpp"
 

@@ -37,9 +37,9 @@ namespace hpmg {
 // trace buffers: of the 12 N^2 trace words that a cell writes and as many that
 // it reads per sweep beside its 3 N^3 of u and b, a share
 // 1 - (1/BX + 1/BY + 1/BZ)/3 stays on chip (0.75 at degree 1, 0.6 at degree 4).
-// 2D and adaptive meshes, and 16-bit storage (whose sweep is bound by
-// instruction issue, not by traffic: FP16 Q5 48^3 81 us in runs, 91 us in
-// bricks): runs of consecutive cells.
+// 2D, adaptive and small meshes (run_cells), and 16-bit storage (whose sweep is
+// bound by instruction issue, not by traffic: FP16 Q5 48^3 81 us in runs, 91 us
+// in bricks): runs of consecutive cells.
 //   V = 0  constant kappa (and 2D)
 //   V = 1  the same with about half the cells (tile variant of the batched
 //          driver's autotuner)
@@ -49,8 +49,9 @@ namespace hpmg {
 // waves is allocated as two waves on every SIMD (a 2 x 2 x 2 brick of degree 5,
 // 288 threads, held 20 of 32 waves per CU: FP64 48^3 sweep 283 us, against 197
 // us for 7 x 2 x 1).  Sweep, runs -> bricks: FP64 Q3 64^3 227 -> 146 us, Q4 48^3
-// 168 -> 121 us, Q5 48^3 252 -> 197 us, Q6 40^3 222 -> 189 us; FP32 Q3 64^3 110
-// -> 74 us, Q5 48^3 138 -> 106 us.
+// 168 -> 121 us, Q5 48^3 252 -> 197 us; FP32 Q3 64^3 110 -> 74 us, Q5 48^3 138 -> 106 us.
+// Degree 6, whose sweeps are dual, takes 5 cells: with 10 they take 1.04 to 1.07
+// times as long on 15^3 to 28^3 cells.
 constexpr int kTileVariants = 2;
 struct Brick {
   int x, y, z;
@@ -62,7 +63,7 @@ __host__ __device__ constexpr Brick brick(int N, int V) {
     case 4: return V == 1 ? Brick{2, 2, 2} : Brick{4, 2, 2};
     case 5: return V == 0 ? Brick{5, 2, 2} : Brick{5, 2, 1};
     case 6: return V == 0 ? Brick{7, 2, 1} : Brick{3, 2, 1};
-    case 7: return V == 0 ? Brick{5, 2, 1} : Brick{5, 1, 1};
+    case 7: return Brick{5, 1, 1};
     case 8: return V == 1 ? Brick{2, 1, 1} : Brick{2, 2, 1};
     default: return V == 1 ? Brick{1, 1, 1} : Brick{3, 1, 1};
   }
@@ -83,6 +84,24 @@ inline long long brick_blocks(int n, int N, int V) {
 inline long long brick_records(int n, int N, int V) {
   const Brick b = brick(N, V);
   return 2LL * n * n * (brick_layers(n, b.x) + brick_layers(n, b.y) + brick_layers(n, b.z));
+}
+// Shape of the blocks of a 3D uniform mesh with constant kappa in FP64 or FP32,
+// the same for every operation on a level: runs of cells (V = 3) on meshes of at
+// most so many full bricks' cells, bricks (V = 0) above.  Small meshes leave
+// bricks, larger blocks than runs with a step more, few to a chip of 256 CUs, and
+// their ragged ones half empty: four sweeps in bricks | runs, FP64 degree 4, 8^3
+// cells 39 | 30 us, degree 6, 6^3 61 | 41, degree 1, 24^3 22.7 | 24.1; FP32 degree 1,
+// 16^3 26.7 | 24.4.  In FP32 the dual form (dual_sweep, dual_apply) gains so little
+// from bricks, whose passes it has beside one step more, that degree 4, 5 and 8
+// stay in runs up to 28^3, 30^3 and 13^3 cells (degree 5, 22^3, sweeps 72 | 62 us,
+// apply 24 | 20.5) and degree 6 always (27^3, sweeps 176 | 149).
+__host__ __device__ constexpr int run_cells(int N, bool fp64) {
+  constexpr int line[2][8] = {{400, 400, 160, 1400, 2000, 1 << 24, 160, 800}, {200, 200, 160, 160, 1000, 300, 160, 200}};
+  const long long c = (long long)line[fp64 ? 1 : 0][N - 2] * cells_per_block_v(3, N, 0);
+  return c < (1 << 30) ? (int)c : 1 << 30;
+}
+__host__ __device__ constexpr int mesh_variant(int n, int N, bool fp64) {
+  return (long long)n * n * n <= run_cells(N, fp64) ? 3 : 0;
 }
 // Block index of a brick (10 bits per axis; a 3D mesh has n <= 1023).
 __host__ __device__ constexpr int brick_id(int x, int y, int z) { return x | (y << 10) | (z << 20); }

@@ -806,7 +806,11 @@ __device__ __forceinline__ void block_mv(const DGArgs<T>& a, const CT<T>* sE, in
     // meshes (sweeps, even-odd against plain: 1.14 on 4^2 cells, 1.04 on 64^2,
     // 0.87 on 150^2; the errors are alike), FP64 of degree 6 to 8 on meshes of few blocks
     // (HPMG_TILE 4, see dg_inst_2d_double_plain.hip)
-    constexpr bool eo = D == 3 || (sizeof(C) == 8 ? HPMG_TILE != 4 : N <= 8);
+    // 3D runs of cells (HPMG_TILE 3: small and adaptive meshes) in FP64 and FP32: the
+    // same trade at degree 6 to 8 and 8 (even-odd | plain, FP64 degree 6, 6^3 48 | 41
+    // us, degree 7, 4^3 45 | 40, FP32 degree 8, 6^3 47 | 41)
+    constexpr bool big = N > (sizeof(C) == 8 ? 6 : 8);
+    constexpr bool eo = !big || (D == 3 ? HPMG_TILE != 3 || sizeof(T) == 2 : sizeof(C) == 8 && HPMG_TILE != 4);
     if (eo && (IVAR || __all(cls == 0))) {
       const cptr<C> G = as_const(a.ref) + (si ? RefOff<N>::SIC : RefOff<N>::SC);
       if constexpr (OP == OP_S || OP == OP_SIT)
@@ -1929,12 +1933,13 @@ __device__ __forceinline__ void sweep_cells(const DGArgs<T>& a, int bx, int by, 
 
 // Waves per SIMD asked of the sweep: as many as its LDS allows (160 KB per
 // CU), so that the compiler does not spend registers on reading ahead past
-// that occupancy.  Variable kappa, two waves at degree 7 and 8 (left to itself
-// the compiler keeps whole 1D matrices in registers and reaches one wave).
+// that occupancy.  Variable kappa and plain products (block_mv, eo) keep whole 1D
+// matrices in registers: two waves at degree 7 and 8 (left to itself the
+// compiler reaches one), no bound below.
 template <typename T, int D, int N, bool VARK>
 constexpr int sweep_waves_per_eu() {
   if (D != 3 || sizeof(CT<T>) != 8) return 1;
-  if (VARK) return N >= 8 ? 2 : 1;
+  if (VARK || (HPMG_TILE == 3 && N > 6)) return N >= 8 ? 2 : 1;
   constexpr int blocks = 160 * 1024 / cell_lds_bytes<T, D, N, false>();
   constexpr int waves = blocks * (DGShape<D, N>::BLOCK / 64) / 4;
   return waves < 5 ? waves : 5;
@@ -2492,7 +2497,7 @@ __global__ __launch_bounds__((DGShape<D, N>::BLOCK)) void k_prolong(DGArgs<T> a)
 // variable kappa, adaptive meshes.
 template <typename T, int D>
 constexpr bool serves_const() {
-  return D == 2 || HPMG_TILE == 0 || (HPMG_TILE == 3 && sizeof(T) == 2);
+  return D == 2 || HPMG_TILE == 0 || HPMG_TILE == 3;
 }
 template <typename T, int D>
 constexpr bool serves_vark() {

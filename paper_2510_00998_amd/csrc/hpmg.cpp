@@ -239,16 +239,18 @@ void build_dg_level(hpmg_ctx* h, DGLevel& L, const hpmg::Basis1D& B, const hpmg:
   const size_t nif = h->adapt ? (size_t)h->amesh[L.am].nif : 0;
   L.ndof = ncell * ipow(N, D);
   // facet records of a trace buffer: one per cell and facet in runs of cells
-  // (2D, adaptive meshes with their hanging-facet slots, 16-bit storage), the
-  // faces of the bricks in 3D (the batched driver's tile variants share them)
-  size_t nrec = (size_t)2 * D * ncell + nif * (h->mif + 1);
-  L.trsize16 = nrec * 2 * ipow(N, D - 1);
+  // (2D, adaptive meshes with their hanging-facet slots, 16-bit storage, small
+  // meshes), the faces of the bricks in 3D (the batched driver's tile variants
+  // share them; they are fewer than the runs' records)
+  const size_t rec = (size_t)2 * ipow(N, D - 1);
+  L.trsize = L.trsize32 = L.trsize16 = ((size_t)2 * D * ncell + nif * (h->mif + 1)) * rec;
   if (D == 3 && !h->adapt) {
-    nrec = 0;
+    size_t nrec = 0;
     for (int V = h->vark ? 2 : 0; V < (h->vark ? 3 : hpmg::kTileVariants); ++V)
       nrec = std::max(nrec, (size_t)hpmg::brick_records(h->n, N, V));
+    if (h->vark || hpmg::mesh_variant(h->n, N, true) != 3) L.trsize = nrec * rec;
+    if (h->vark || hpmg::mesh_variant(h->n, N, false) != 3) L.trsize32 = nrec * rec;
   }
-  L.trsize = nrec * 2 * ipow(N, D - 1);
   // eigendata of the cell blocks
   const int EGS = 2 * NN + N;
   // compact even-odd tables of S and Si^T of the interior class (constant kappa)
@@ -387,7 +389,7 @@ void build_dg_level(hpmg_ctx* h, DGLevel& L, const hpmg::Basis1D& B, const hpmg:
   const size_t R = (size_t)h->opt.max_rhs;
   for (int b = 0; b < 2; ++b) {
     L.d.tr[b] = (double*)h->mem.alloc(L.trsize * R * sizeof(double));
-    L.f.tr[b] = (float*)h->mem.alloc(L.trsize * R * sizeof(float));
+    L.f.tr[b] = (float*)h->mem.alloc(L.trsize32 * R * sizeof(float));
   }
   // (up to degree 5 it takes less than the bricks save of the traces of single
   // cells; above, more; not where the sweeps are dual)
@@ -1399,8 +1401,9 @@ void fcg_iteration(hpmg_ctx* h, double rms, int restart, hipStream_t s) {
   aa.kpartial = h->kpartial;
   dg_run(h, hpmg::OP_APPLY, aa, L0.N, 1, 0, s);
   const int cpb = hpmg::cells_per_block_v(h->dim, L0.N, 3);
-  const int nblk = h->dim == 3 && !h->adapt ? (int)hpmg::brick_blocks(h->n, L0.N, h->vark ? 2 : 0)
-                                            : (h->ncell + cpb - 1) / cpb;
+  const int V = h->vark ? 2 : hpmg::mesh_variant(h->n, L0.N, true);
+  const int nblk = h->dim == 3 && !h->adapt && V != 3 ? (int)hpmg::brick_blocks(h->n, L0.N, V)
+                                                      : (h->ncell + cpb - 1) / cpb;
   hpmg::krylov_alpha(h->kpartial, nblk, h->scal, s);
   hpmg::krylov_update_ur(nd, h->ug, h->r, h->rold, h->pv, h->q, h->partial, h->scal, r32_next, s);
   HIPCHK(hipMemcpyAsync(h->host_scal, h->scal, 16 * sizeof(double), hipMemcpyDeviceToHost, s));

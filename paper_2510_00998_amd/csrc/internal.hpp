@@ -137,9 +137,9 @@ struct DGLevel {
   bool next_h = false;       // adaptive meshes: the next level has the same degree on the next coarser leaf set
   bool dyn_nc = false;       // next DG level not the halved degree: run-time NC transfer kernels
   double sigma_hat = 0.0;
-  // per right-hand side: unknowns, values of a trace buffer in FP64 and FP32,
-  // and in 16-bit storage
-  size_t ndof = 0, trsize = 0, trsize16 = 0;
+  // per right-hand side: unknowns, values of a trace buffer in FP64, FP32 and
+  // 16-bit storage
+  size_t ndof = 0, trsize = 0, trsize32 = 0, trsize16 = 0;
   DGData<double> d;
   DGData<float> f;
   // 16-bit storage (finest level only, allocated on first use): traces; the
@@ -289,7 +289,7 @@ inline hpmg::DGArgs<T> dg_args(hpmg_ctx* h, DGLevel& L) {
   a.ivar = h->opt.block_variant;
   a.mfma = h->opt.mfma;
   a.vstride = (long long)L.ndof;
-  a.tstride = (long long)(sizeof(T) == 2 ? L.trsize16 : L.trsize);
+  a.tstride = (long long)(sizeof(T) == 8 ? L.trsize : sizeof(T) == 4 ? L.trsize32 : L.trsize16);
   if (h->adapt) {
     const AdaptMesh& M = h->amesh[L.am];
     a.ncell = M.ncell;

@@ -39,7 +39,7 @@ bool dg_dispatch3(int N, int op, const DGArgs<_Float16>& a, int nrhs, int flag, 
 bool dg_dispatch3(int N, int op, const DGArgs<__bf16>& a, int nrhs, int flag, hipStream_t s);
 // the part of dg_dispatch2 with plain products; false where it does not apply
 bool dg_dispatch2_plain(int N, int op, const DGArgs<double>& a, int nrhs, int flag, hipStream_t s);
-// the parts of dg_dispatch3 with another block shape: variable kappa, adaptive meshes
+// the parts of dg_dispatch3 with another block shape: variable kappa, adaptive and small meshes
 bool dg_dispatch3_vark(int N, int op, const DGArgs<double>& a, int nrhs, int flag, hipStream_t s);
 bool dg_dispatch3_vark(int N, int op, const DGArgs<float>& a, int nrhs, int flag, hipStream_t s);
 bool dg_dispatch3_runs(int N, int op, const DGArgs<double>& a, int nrhs, int flag, hipStream_t s);
