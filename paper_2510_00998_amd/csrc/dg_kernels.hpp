@@ -41,8 +41,8 @@ namespace hpmg {
 // bound by instruction issue, not by traffic: FP16 Q5 48^3 81 us in runs, 91 us
 // in bricks): runs of consecutive cells.
 //   V = 0  constant kappa (and 2D)
-//   V = 1  the same with about half the cells (tile variant of the batched
-//          driver's autotuner)
+//   V = 1  the same with about half the cells (degree 1 to 5: tile variant of the
+//          batched driver's autotuner)
 //   V = 2  variable kappa, whose per-cell 1D matrices share the LDS
 //   V = 3  runs of cells in 3D
 // Bricks are chosen so that a workgroup has 4 or 8 nearly full waves: one of 5
@@ -64,8 +64,8 @@ __host__ __device__ constexpr Brick brick(int N, int V) {
     case 5: return V == 0 ? Brick{5, 2, 2} : Brick{5, 2, 1};
     case 6: return V == 0 ? Brick{7, 2, 1} : Brick{3, 2, 1};
     case 7: return Brick{5, 1, 1};
-    case 8: return V == 1 ? Brick{2, 1, 1} : Brick{2, 2, 1};
-    default: return V == 1 ? Brick{1, 1, 1} : Brick{3, 1, 1};
+    case 8: return Brick{2, 2, 1};
+    default: return Brick{3, 1, 1};
   }
 }
 __host__ __device__ constexpr int cells_per_block_v(int D, int N, int V) {
