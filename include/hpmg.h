@@ -357,9 +357,8 @@ hpmg_status hpmg_batch_smooth(hpmg_batch b, hpmg_dtype dtype, void* const* u, co
 /* Launch configuration the autotuner chose for the batch's current number
  * of right-hand sides: out[0] grid cap (workgroups) of the V-cycle
  * launches: a persistent grid, or a cap at least the number of work items
- * of every launch (1 << 30 from the V-cycle tuner, the total item count
- * from the smoothing tuner): one workgroup per item, which runs loop-free
- * one-degree kernels; out[1] 1 if they run one launch per polynomial degree (else
+ * of every launch (1 << 30 from the tuner): one workgroup per item, which
+ * runs loop-free one-degree kernels; out[1] 1 if they run one launch per polynomial degree (else
  * one launch over all degrees), out[2..3] the same for FP32
  * hpmg_batch_smooth, out[4..5] for FP64, out[6..8] the tile masks of the
  * V-cycle, FP32 and FP64 smoothing launches: bit N (N = p + 1) set if the

@@ -652,9 +652,10 @@ std::unique_ptr<BatchPlan> make_plan(const std::vector<hpmg_handle>& hs, int nrh
 }
 
 // Autotuner over the launch configuration (grid, split, tile): first the
-// fastest (grid, split) among the candidates with tile variant 0, then,
-// degree by degree, tile variant 1 for that degree's one-degree launches
-// where it is faster.  Timed with events on s; work(grid, split, tile,
+// fastest (grid, split) among the candidates, the one-degree launches with tile
+// variant 0 (the launch over all degrees works in variant 1), then, degree by
+// degree, tile variant 1 for that degree's one-degree launches where it is
+// faster.  Timed with events on s; work(grid, split, tile,
 // reps) enqueues the timed work; `degrees` are the degrees N present.
 template <class F>
 void tune(const std::vector<int>& grids, const std::vector<int>& degrees, F work, hipStream_t s, int& grid,
@@ -803,7 +804,6 @@ void prepare_smooth(BatchPlan* B, const std::vector<hpmg_handle>& hs, hipStream_
     for (auto& w : v) w.x += by;
     return v;
   };
-  const int ni = (int)t.items.size();
   const int kind = sizeof(T) == 8 ? 1 : 0;
   S.proj = dg_launch(B->mem, kind, hpmg::BOP_PROJECT, S.args, shifted(t.items, 0), shifted(t.items1, 0), s);
   S.even = dg_launch(B->mem, kind, hpmg::BOP_SWEEP, S.args, shifted(t.items, np), shifted(t.items1, np), s);
@@ -818,7 +818,7 @@ void prepare_smooth(BatchPlan* B, const std::vector<hpmg_handle>& hs, hipStream_
   hpmg::fill<T>(ws_u<T>(B), B->total, T(0), s);
   hpmg::fill<T>(ws_b<T>(B), B->total, T(0), s);
   stage_smooth<T>(B, S, np, su.data(), sb.data(), s);
-  tune({1024, 2048, 4096, 8192, ni}, degrees_of({S.even}),
+  tune({1024, 2048, 4096, 8192, kOnePerItem}, degrees_of({S.even}),
        [&](int g, bool sp, int tl, int reps) { smooth_launches<T>(S, 2 * reps, g, sp, tl, s); }, s, S.grid, S.split,
        S.tile);
 }
