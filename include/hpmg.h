@@ -362,8 +362,8 @@ hpmg_status hpmg_batch_smooth(hpmg_batch b, hpmg_dtype dtype, void* const* u, co
  * one launch over all degrees), out[2..3] the same for FP32
  * hpmg_batch_smooth, out[4..5] for FP64, out[6..8] the tile masks of the
  * V-cycle, FP32 and FP64 smoothing launches: bit N (N = p + 1) set if the
- * degree-p launches use half the cells per workgroup (about 128 instead of
- * 256 threads).  0 where not tuned yet.  out: host array of 9 ints. */
+ * degree-p launches use half the cells per workgroup (where every mesh of
+ * the batch is small: runs of consecutive cells instead of bricks).  0 where not tuned yet.  out: host array of 9 ints. */
 hpmg_status hpmg_batch_tuning(hpmg_batch b, int* out);
 
 /* Replace the launch configuration of the batch's current plan (the one

@@ -33,9 +33,9 @@ struct Launch {
   int nitems = 0;
   // DG: runs of equal degree in `items` (degree, first item, count)
   std::vector<int3> runs;
-  // DG: the same work in the cell blocks of tile variant 1 (half the cells
-  // per block), for the one-launch-per-degree kernels and the launch over all
-  // degrees
+  // DG: the same work in the cell blocks of tile variant 1 (half bricks, or runs
+  // of cells where every mesh of the batch is small: BatchPlan::small), for the
+  // one-launch-per-degree kernels and the launch over all degrees
   const hpmg::WorkItem* items1 = nullptr;
   int nitems1 = 0;
   std::vector<int3> runs1;
@@ -75,6 +75,9 @@ Launch dg_launch(DevMem& mem, int kind, int op, const void* args, std::vector<hp
 // segment tables, launch lists and the captured iteration.
 struct BatchPlan {
   int nrhs = 0;
+  // FP32, FP64: on every DG level of every problem single-problem calls take
+  // runs of cells (the trace buffers are large enough for runs)
+  bool small[2] = {false, false};
   bool split = true;         // one launch per degree (tuned with the grid)
   int tile = 0;              // bit N: degree-N launches use tile variant 1 (tuned after the grid)
   std::vector<size_t> off0;  // offset of each problem in the workspace vectors
@@ -161,12 +164,18 @@ struct Builder {
 };
 
 template <typename T>
-void add_dg_items(Table<hpmg::DGArgs<T>>& t, const hpmg::DGArgs<T>& a, int N, int nrhs) {
+void add_dg_items(const BatchPlan* B, Table<hpmg::DGArgs<T>>& t, const hpmg::DGArgs<T>& a, int N, int nrhs) {
   const int idx = (int)t.args.size();
   t.args.push_back(a);
   for (int V = 0; V < hpmg::kTileVariants; ++V) {
     const hpmg::Brick b = hpmg::brick(N, V);
     std::vector<hpmg::WorkItem>& items = V == 0 ? t.items : t.items1;
+    if (V == 1 && B->small[sizeof(T) / 8]) {
+      const int cpb = hpmg::cells_per_block_v(3, N, 3);
+      for (int r = 0; r < nrhs; ++r)
+        for (int blk = 0; blk < (a.ncell + cpb - 1) / cpb; ++blk) items.push_back(hpmg::WorkItem{idx, blk, r, N});
+      continue;
+    }
     for (int r = 0; r < nrhs; ++r)
       for (int z = 0; z < hpmg::brick_layers(a.n, b.z); ++z)
         for (int y = 0; y < hpmg::brick_layers(a.n, b.y); ++y)
@@ -304,7 +313,7 @@ void build_vcycle(BatchPlan* B, const std::vector<hpmg_handle>& hs, const std::v
           a.tr_in = L.f.tr[cur];
           a.tr_out = L.f.tr[cur ^ 1];
           cur ^= 1;
-          add_dg_items(td, a, L.N, R);
+          add_dg_items(B, td, a, L.N, R);
         } else if (!coarsest(j)) {
           CGLevel& C = h->cg[cgl(j)];
           int& cur = ps[j].cgcur[cgl(j)];
@@ -358,7 +367,7 @@ void build_vcycle(BatchPlan* B, const std::vector<hpmg_handle>& hs, const std::v
             g.sout = (long long)C.size;
             add_cg_items(tg, g, (int)C.size, R);
           }
-          add_dg_items(td, a, L.N, R);
+          add_dg_items(B, td, a, L.N, R);
         } else if (!coarsest(j)) {
           CGLevel& C = h->cg[cgl(j)];
           CGLevel& Cc = h->cg[cgl(j) + 1];
@@ -415,7 +424,7 @@ void build_vcycle(BatchPlan* B, const std::vector<hpmg_handle>& hs, const std::v
             a.coarse_cg = 1;
             a.cstride = (long long)h->cg[0].size;
           }
-          add_dg_items(td, a, L.N, R);
+          add_dg_items(B, td, a, L.N, R);
         } else {
           CGLevel& C = h->cg[cgl(j)];
           CGLevel& Cc = h->cg[cgl(j) + 1];
@@ -454,7 +463,7 @@ void build_vcycle(BatchPlan* B, const std::vector<hpmg_handle>& hs, const std::v
           a.tr_in = L.f.tr[cur];
           a.tr_out = L.f.tr[cur ^ 1];
           cur ^= 1;
-          add_dg_items(td, a, L.N, R);
+          add_dg_items(B, td, a, L.N, R);
         } else {
           CGLevel& C = h->cg[cgl(j)];
           int& cur = ps[j].cgcur[cgl(j)];
@@ -482,18 +491,25 @@ void build_vcycle(BatchPlan* B, const std::vector<hpmg_handle>& hs, const std::v
   rec(0);
 }
 
-// One-degree launch of a degree run in tile variant V.
+// One-degree launch of a degree run in tile variant V (1: small, runs of cells).
 template <typename T>
-void dg_run(int V, int op, const int3& r, const void* args, const hpmg::WorkItem* items, int grid, hipStream_t s) {
+void dg_run(int V, bool small, int op, const int3& r, const void* args, const hpmg::WorkItem* items, int grid, hipStream_t s) {
   if (V == 0)
     hpmg::batch_dg_n_t0<T>(op, r.x, (const hpmg::DGArgs<T>*)args, items + r.y, r.z, grid, s);
+  else if (small)
+    hpmg::batch_dg_n_t3<T>(op, r.x, (const hpmg::DGArgs<T>*)args, items + r.y, r.z, grid, s);
   else
     hpmg::batch_dg_n_t1<T>(op, r.x, (const hpmg::DGArgs<T>*)args, items + r.y, r.z, grid, s);
 }
 
 // split: one launch per degree run (each with its own kernel; degree N in
 // tile variant (tile >> N) & 1), else one launch over all degrees
-void run_grid(const std::vector<Launch>& v, int grid, bool split, int tile, hipStream_t s) {
+template <typename T>
+void dg_all(bool small, const Launch& L, int grid, hipStream_t s) {
+  (small ? hpmg::batch_dg_t3<T> : hpmg::batch_dg_t1<T>)(L.op, (const hpmg::DGArgs<T>*)L.args, L.items1, L.nitems1, grid,
+                                                        s);
+}
+void run_grid(const BatchPlan* B, const std::vector<Launch>& v, int grid, bool split, int tile, hipStream_t s) {
   for (const Launch& L : v) {
     if (L.nitems == 0) continue;
     if (L.kind == 2) {
@@ -507,21 +523,21 @@ void run_grid(const std::vector<Launch>& v, int grid, bool split, int tile, hipS
         for (const int3& r : V == 0 ? L.runs : L.runs1) {
           if (((tile >> r.x) & 1) != V) continue;
           if (L.kind == 0)
-            dg_run<float>(V, L.op, r, L.args, V == 0 ? L.items : L.items1, grid, s);
+            dg_run<float>(V, B->small[0], L.op, r, L.args, V == 0 ? L.items : L.items1, grid, s);
           else
-            dg_run<double>(V, L.op, r, L.args, V == 0 ? L.items : L.items1, grid, s);
+            dg_run<double>(V, B->small[1], L.op, r, L.args, V == 0 ? L.items : L.items1, grid, s);
         }
     } else if (L.kind == 0) {
-      hpmg::batch_dg<float>(L.op, (const hpmg::DGArgs<float>*)L.args, L.items1, L.nitems1, grid, s);
+      dg_all<float>(B->small[0], L, grid, s);
     } else {
-      hpmg::batch_dg<double>(L.op, (const hpmg::DGArgs<double>*)L.args, L.items1, L.nitems1, grid, s);
+      dg_all<double>(B->small[1], L, grid, s);
     }
   }
   HIPCHK(hipGetLastError());
 }
 
 void run(BatchPlan* B, const std::vector<Launch>& v, hipStream_t s) {
-  run_grid(v, B->grid > 0 ? B->grid : 1024, B->split, B->tile, s);  // before tuning: a default
+  run_grid(B, v, B->grid > 0 ? B->grid : 1024, B->split, B->tile, s);  // before tuning: a default
 }
 
 // One iteration of the flexible CG for every segment; r32 holds r cast to
@@ -555,6 +571,11 @@ std::unique_ptr<BatchPlan> make_plan(const std::vector<hpmg_handle>& hs, int nrh
   B->mem.ctx = hs[0]->opt.alloc_ctx;
   B->nrhs = nrhs;
   const int np = (int)hs.size(), R = nrhs;
+  for (int f = 0; f < 2; ++f) {
+    B->small[f] = true;
+    for (hpmg_handle h : hs)
+      for (const DGLevel& L : h->dg) B->small[f] = B->small[f] && hpmg::mesh_variant(h->n, L.N, f == 1) == 3;
+  }
   // segments: one per (problem, right-hand side), [problem][rhs][dof] in
   // the workspace vectors
   std::vector<size_t> off0(np);
@@ -611,18 +632,18 @@ std::unique_ptr<BatchPlan> make_plan(const std::vector<hpmg_handle>& hs, int nrh
     hpmg::DGArgs<double> a = dg_args<double>(h, L);
     a.u_in = B->p + off0[j];
     a.tr_out = L.d.tr[0];
-    add_dg_items(tp, a, L.N, R);
+    add_dg_items(B.get(), tp, a, L.N, R);
     hpmg::DGArgs<double> c = dg_args<double>(h, L);
     c.u_in = B->p + off0[j];
     c.tr_in = L.d.tr[0];
     c.out = B->q + off0[j];
-    add_dg_items(ta, c, L.N, R);
+    add_dg_items(B.get(), ta, c, L.N, R);
     hpmg::DGArgs<double> pu = dg_args<double>(h, L);
     pu.tr_out = L.d.tr[0];
-    add_dg_items(tpu, pu, L.N, R);
+    add_dg_items(B.get(), tpu, pu, L.N, R);
     hpmg::DGArgs<double> rr = dg_args<double>(h, L);
     rr.tr_in = L.d.tr[0];
-    add_dg_items(tr, rr, L.N, R);
+    add_dg_items(B.get(), tr, rr, L.N, R);
   }
   B->applyp.push_back(bld.dg<double>(hpmg::BOP_PROJECT, tp));
   B->applyp.push_back(bld.dg<double>(hpmg::BOP_APPLY, ta));
@@ -726,7 +747,7 @@ void autotune_vcycle(BatchPlan* B, hipStream_t s) {
   bool split = true;
   tune({256, 512, 1024, 2048, 4096, kOnePerItem}, degrees_of(B->vcycle),
        [&](int g, bool sp, int tl, int reps) {
-         for (int i = 0; i < reps; ++i) run_grid(B->vcycle, g, sp, tl, s);
+         for (int i = 0; i < reps; ++i) run_grid(B, B->vcycle, g, sp, tl, s);
        },
        s, grid, split, tile);
   B->grid = grid;
@@ -763,10 +784,10 @@ void stage_smooth(BatchPlan* B, BatchPlan::Smooth& S, int np, T* const* u, const
 }
 
 template <typename T>
-void smooth_launches(BatchPlan::Smooth& S, int nsweeps, int grid, bool split, int tile, hipStream_t s) {
+void smooth_launches(const BatchPlan* B, BatchPlan::Smooth& S, int nsweeps, int grid, bool split, int tile, hipStream_t s) {
   std::vector<Launch> v = {S.proj};
   for (int i = 0; i < nsweeps; ++i) v.push_back((i & 1) ? S.odd : S.even);
-  run_grid(v, grid, split, tile, s);
+  run_grid(B, v, grid, split, tile, s);
 }
 
 // Tables of hpmg_batch_smooth for dtype T; the persistent grid is tuned on
@@ -783,7 +804,7 @@ void prepare_smooth(BatchPlan* B, const std::vector<hpmg_handle>& hs, hipStream_
     DGLevel& L = h->dg[0];
     DGData<T>& d = data<T>(L);
     hpmg::DGArgs<T> a = dg_args<T>(h, L);
-    add_dg_items(t, a, L.N, R);
+    add_dg_items(B, t, a, L.N, R);
     all[j] = a;
     all[j].tr_out = d.tr[0];
     all[np + j] = a;
@@ -819,7 +840,7 @@ void prepare_smooth(BatchPlan* B, const std::vector<hpmg_handle>& hs, hipStream_
   hpmg::fill<T>(ws_b<T>(B), B->total, T(0), s);
   stage_smooth<T>(B, S, np, su.data(), sb.data(), s);
   tune({1024, 2048, 4096, 8192, kOnePerItem}, degrees_of({S.even}),
-       [&](int g, bool sp, int tl, int reps) { smooth_launches<T>(S, 2 * reps, g, sp, tl, s); }, s, S.grid, S.split,
+       [&](int g, bool sp, int tl, int reps) { smooth_launches<T>(B, S, 2 * reps, g, sp, tl, s); }, s, S.grid, S.split,
        S.tile);
 }
 
@@ -940,12 +961,12 @@ hpmg_status hpmg_batch_smooth(hpmg_batch bt, hpmg_dtype dtype, void* const* u, c
       prepare_smooth<double>(B, hs, stream);
       BatchPlan::Smooth& S = B->sm[1];
       stage_smooth<double>(B, S, np, (double* const*)u, (const double* const*)b, stream);
-      smooth_launches<double>(S, nsweeps, S.grid, S.split, S.tile, stream);
+      smooth_launches<double>(B, S, nsweeps, S.grid, S.split, S.tile, stream);
     } else {
       prepare_smooth<float>(B, hs, stream);
       BatchPlan::Smooth& S = B->sm[0];
       stage_smooth<float>(B, S, np, (float* const*)u, (const float* const*)b, stream);
-      smooth_launches<float>(S, nsweeps, S.grid, S.split, S.tile, stream);
+      smooth_launches<float>(B, S, nsweeps, S.grid, S.split, S.tile, stream);
     }
     return HPMG_OK;
   } catch (const HpmgError& e) {

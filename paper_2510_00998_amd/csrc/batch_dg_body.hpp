@@ -1,6 +1,7 @@
 // Batched DG work items and the one-degree persistent kernels, compiled once
 // per tile variant (HPMG_TILE, cells per block; see DGShapeV): included by
-// batch_kernels.hip (variant 0) and batch_tile1.hip (variant 1).
+// batch_kernels.hip (variant 0), batch_tile1.hip (half bricks) and
+// batch_runs.hip (runs of cells).
 #pragma once
 #include "batch.hpp"
 #include "dg_kernels_impl.hpp"

@@ -24,6 +24,7 @@ SOURCES = [
     "cg_kernels.hip",
     "batch_kernels.hip",
     "batch_tile1.hip",
+    "batch_runs.hip",
     "batch.cpp",
     "noalloc.hip",
     "adapt_kernels.hip",
