@@ -254,7 +254,7 @@ def run_batched(args):
     # committed counter profile (so that roofline.traffic describes exactly
     # the timed kernels; the autotuner's choice among near-equal
     # configurations varies from run to run), else the autotuned one
-    srcs = ["dg_kernels_impl.hpp", "batch_dg_body.hpp", "batch_kernels.hip"]
+    srcs = ["dg_kernels.hpp", "dg_kernels_impl.hpp", "batch_dg_body.hpp", "batch_kernels.hip"]
     forced = [int(x) for x in args.smooth_tuning.split(",")] if args.smooth_tuning else None
     if forced is None and not args.profile_sweeps:
         forced = recorded_launch("batched_64x4_hbm_traffic.md", srcs)
@@ -283,9 +283,16 @@ def run_batched(args):
             out[name] = (e[1].elapsed_time(e[2]) - e[0].elapsed_time(e[1])) * 1e-3 / S
         return out
 
-    by64 = R * sum(traffic.sweep_bytes(3, n, p, 8) for n, p in probs)
-    by32 = R * sum(traffic.sweep_bytes(3, n, p, 4) for n, p in probs)
     degs = sorted({p for _, p in probs})
+
+    def shapes(kind, cfg):  # block shapes that a launch configuration takes
+        half = degs if not cfg[kind + "_split_by_degree"] else cfg[kind + "_half_tile_degrees"]
+        return {p: int(p in half) for p in range(1, max(degs) + 1)}
+    # bytes that the launches move, and with the traces of every facet in memory
+    by64 = R * sum(traffic.sweep_bytes(3, n, p, 8, moved=True, shapes=shapes("smooth_f64", tuning)) for n, p in probs)
+    by32 = R * sum(traffic.sweep_bytes(3, n, p, 4, moved=True, shapes=shapes("smooth_f32", tuning)) for n, p in probs)
+    facet64 = R * sum(traffic.sweep_bytes(3, n, p, 8) for n, p in probs)
+    facet32 = R * sum(traffic.sweep_bytes(3, n, p, 4) for n, p in probs)
     if args.profile_sweeps:
         t = smooth_timed()
         if args.copy_calibration:
@@ -382,7 +389,8 @@ def run_batched(args):
         else "k_dg_batch<double,0> (one launch per sweep)"
     # time-to-solution roofline: bytes of one FCG iteration of every segment
     # (the captured graph iterates all segments until the last converges)
-    iter_bytes = R * sum(traffic.fcg_iteration_bytes(3, n, p, 4) for n, p in probs)
+    cyc_shapes = shapes("vcycle", batch.tuning)
+    iter_bytes = R * sum(traffic.fcg_iteration_bytes(3, n, p, 4, moved=True, shapes=cyc_shapes) for n, p in probs)
     tts = None
     if t_batch:
         a = iter_bytes * its_batch / t_batch / 1e9
@@ -410,11 +418,13 @@ def run_batched(args):
                      "traffic": counter_traffic("batched_64x4_hbm_traffic.md", srcs, "traffic_bytes_per_sweep_f64",
                                                 {"launch_smooth_f64": launch_cfg["launch_smooth_f64"]}),
                      "kernel": kern64 + " (batched fused sweep of all problems and RHS, FP64)",
-                     "algorithmic_bytes_per_launch": by64, "mean_launch_s": t64,
+                     "algorithmic_bytes_per_launch": by64, "facet_model_bytes_per_launch": facet64,
+                     "mean_launch_s": t64,
                      "measured_copy_GBs": copy_gbs, "frac_of_measured_copy": ach / copy_gbs},
         "sweep_dofs_per_s": {"f64": total / t64, "f32": total / t32},
         "sweep_roofline_f32": {"achieved": by32 / t32 / 1e9, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                                "frac": by32 / t32 / 1e9 / HBM_PEAK_GBS, "algorithmic_bytes_per_launch": by32,
+                               "facet_model_bytes_per_launch": facet32,
                                "traffic": counter_traffic("batched_64x4_hbm_traffic.md", srcs,
                                                           "traffic_bytes_per_sweep_f32",
                                                           {"launch_smooth_f32": launch_cfg["launch_smooth_f32"]}),
@@ -659,7 +669,9 @@ def run_single(args):
 
     tsw = {name: _median([r["sw_" + name] for r in res]) for name in sweep_in}
     isz = {"f64": 8, "f32": 4, "f16": 2, "bf16": 2}
-    bysw = {name: traffic.sweep_bytes(dim, n, p, isz[name], per_cell_kappa=vark) for name in sweep_in}
+    # bytes that the launches move, and with the traces of every facet in memory
+    bysw = {name: traffic.sweep_bytes(dim, n, p, isz[name], per_cell_kappa=vark, moved=True) for name in sweep_in}
+    facet = {name: traffic.sweep_bytes(dim, n, p, isz[name], per_cell_kappa=vark) for name in sweep_in}
     t64, t32 = tsw["f64"], tsw["f32"]
     by64, by32 = bysw["f64"], bysw["f32"]
     conv = {k: all(r[k][2] == 0 for r in res) for k in solves}
@@ -675,13 +687,13 @@ def run_single(args):
     tts = {}
     for k, isz_c in cyc.items():
         if k in solves and tt.get(k):
-            by = traffic.fcg_iteration_bytes(dim, n, p, isz_c) * its[k]
-            tts[k] = {"achieved": by / tt[k] / 1e9, "frac": by / tt[k] / 1e9 / HBM_PEAK_GBS,
-                      "bytes_per_iteration": traffic.fcg_iteration_bytes(dim, n, p, isz_c)}
+            by = traffic.fcg_iteration_bytes(dim, n, p, isz_c, per_cell_kappa=vark, moved=True)
+            a = by * its[k] / tt[k] / 1e9
+            tts[k] = {"achieved": a, "frac": a / HBM_PEAK_GBS, "bytes_per_iteration": by}
 
     copy_gbs = measured_copy_bandwidth(torch, dev, stream)
     ach64 = by64 / t64 / 1e9
-    srcs = ["dg_kernels_impl.hpp"]
+    srcs = ["dg_kernels.hpp", "dg_kernels_impl.hpp"]
     tsum = {2: "sweep_q4_32cube_hbm_traffic.md", 3: "variable_kappa_q3_64cube_hbm_traffic.md",
             5: "sweep_q5_96cube_hbm_traffic.md"}[args.config]
     line = {
@@ -704,12 +716,14 @@ def run_single(args):
         "roofline": {"bound": "hbm", "achieved": ach64, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": ach64 / HBM_PEAK_GBS,
                      "traffic": counter_traffic(tsum, srcs, "traffic_bytes_per_launch_f64"),
-                     "kernel": f"k_sweep<double,3,{p + 1},false,{str(vark).lower()},false,false,false> (fused sweep, FP64)",
-                     "algorithmic_bytes_per_launch": by64, "mean_launch_s": t64,
+                     "kernel": f"k_sweep<double,3,{p + 1},false,{str(vark).lower()},false,false,false,false> (fused sweep, FP64)",
+                     "algorithmic_bytes_per_launch": by64, "facet_model_bytes_per_launch": facet["f64"],
+                     "mean_launch_s": t64,
                      "measured_copy_GBs": copy_gbs, "frac_of_measured_copy": ach64 / copy_gbs},
         "sweep_dofs_per_s": {name: nd / t for name, t in tsw.items()},
         "sweep_roofline": {name: {"achieved": bysw[name] / tsw[name] / 1e9, "frac": bysw[name] / tsw[name] / 1e9 /
                                   HBM_PEAK_GBS, "algorithmic_bytes_per_launch": bysw[name],
+                                  "facet_model_bytes_per_launch": facet[name],
                                   "mean_launch_s": tsw[name],
                                   "traffic": counter_traffic(tsum, srcs, f"traffic_bytes_per_launch_{name}")}
                            for name in sweep_in},
@@ -729,7 +743,7 @@ def run_single(args):
         trc = {name: _median([r["swrc_" + name] for r in res]) for name in rc_in}
         rsum = {3: "variable_kappa_q3_64cube_recompute_hbm_traffic.md", 5: "sweep_q5_96cube_recompute_hbm_traffic.md"}[
             args.config]
-        byrc = {name: traffic.sweep_bytes(dim, n, p, isz[name], per_cell_kappa=True, block_recompute=True)
+        byrc = {name: traffic.sweep_bytes(dim, n, p, isz[name], per_cell_kappa=True, block_recompute=True, moved=True)
                 for name in rc_in}
         line["block_recompute"] = {
             "setup_s": t_setup_rc,
@@ -854,7 +868,7 @@ def run_adaptive(args):
     bysw = {name: traffic.adaptive_sweep_bytes(dim, n, r, leaves, p, isz[name], counts) for name in sweep_in}
     conv = {k: all(rr[k][2] == 0 for rr in res) for k in solves}
     tt = {k: (_median([rr[k][0] for rr in res]) if conv[k] else None) for k in solves}
-    srcs = ["dg_kernels_impl.hpp", "adapt_kernels.hip"]
+    srcs = ["dg_kernels.hpp", "dg_kernels_impl.hpp", "adapt_kernels.hip"]
     tsum = "adaptive_q4_16cube_hbm_traffic.md"
     ach = {name: bysw[name] / tsw[name] / 1e9 for name in sweep_in}
     levels = {int(l): int(c) for l, c in zip(*__import__("numpy").unique(leaves[:, 0], return_counts=True))}

@@ -1,9 +1,12 @@
 """Algorithmic memory traffic of the smoother (host-side bookkeeping).
 
 The paper's per-cell access counts (Section 4.1, "Reduction in memory
-traffic", Table tab:memory_references) and the exact byte counts of one
-launch of each kernel of this library, used as the numerator of the HBM
-roofline.
+traffic", Table tab:memory_references) and the byte counts of one launch of
+each kernel of this library in two models: with the traces of every interior
+facet in memory (the default, the paper's facet variables), and with
+moved=True the facets that the kernels do exchange through memory, those
+between the blocks of cells of a level (exchanged_facets).  The second is the
+numerator of the HBM roofline.
 """
 from __future__ import annotations
 
@@ -34,33 +37,78 @@ def interior_facets(d: int, n: int) -> int:
     return d * n ** (d - 1) * (n - 1)
 
 
+# Blocks of cells in 3D by degree, brick() of csrc/dg_kernels.hpp: shape 0
+# (constant kappa), 1 (half the cells, batches), 2 (variable kappa); degree 8
+# and above share the last row.  Shape 3 is a run of consecutive cells, which
+# exchanges every facet.
+BRICKS = {
+    1: ((4, 4, 4), (4, 4, 2), (4, 4, 4)),
+    2: ((3, 3, 3), (3, 2, 2), (3, 3, 3)),
+    3: ((4, 2, 2), (2, 2, 2), (4, 2, 2)),
+    4: ((5, 2, 2), (5, 2, 1), (5, 2, 1)),
+    5: ((7, 2, 1), (3, 2, 1), (3, 2, 1)),
+    6: ((5, 1, 1), (5, 1, 1), (5, 1, 1)),
+    7: ((2, 2, 1), (2, 2, 1), (2, 2, 1)),
+    8: ((3, 1, 1), (3, 1, 1), (3, 1, 1)),
+}
+# Degree 1 to 8: meshes with constant kappa of at most so many full bricks'
+# cells take runs of cells, run_cells() of the same file.
+RUN_BRICKS = {4: (400, 400, 160, 1400, 2000, 1 << 24, 160, 800), 8: (200, 200, 160, 160, 1000, 300, 160, 200)}
+
+
+def block_shape(d: int, n: int, p: int, itemsize: int, per_cell_kappa: bool = False) -> int:
+    """Shape of the blocks of cells of a uniform mesh (a key of a BRICKS row, or 3)."""
+    if d == 2 or itemsize == 2:
+        return 3
+    if per_cell_kappa:
+        return 2
+    x, y, z = BRICKS[min(p, 8)][0]
+    return 3 if n ** 3 <= RUN_BRICKS[itemsize][min(p, 8) - 1] * x * y * z else 0
+
+
+def exchanged_facets(d: int, n: int, p: int, shape: int) -> int:
+    """Interior facets whose traces go through memory: all of them in runs of
+    cells, in bricks those between two bricks."""
+    if shape == 3:
+        return interior_facets(d, n)
+    return n * n * sum((n + b - 1) // b - 1 for b in BRICKS[min(p, 8)][shape])
+
+
+def _facets(d: int, n: int, p: int, itemsize: int, per_cell_kappa: bool, moved: bool, shapes: dict | None) -> int:
+    if not moved:
+        return interior_facets(d, n)
+    shape = shapes[p] if shapes and itemsize > 2 else block_shape(d, n, p, itemsize, per_cell_kappa)
+    return exchanged_facets(d, n, p, shape)
+
+
 def sweep_bytes(d: int, n: int, p: int, itemsize: int, per_cell_kappa: bool = False,
-                block_recompute: bool = False) -> int:
-    """Exact algorithmic bytes of one fused sweep launch on the n^d mesh:
-    3 cell vectors, plus 2 sides x 2 fields x (p+1)^(d-1) trace values per
-    interior facet read once and written once (boundary facets carry no
-    traces), plus per-cell eigendata d((p+1)^2 + (p+1)) and kappa when the
-    coefficient varies per cell (kappa alone when the kernels rebuild the
-    eigendata in each traversal)."""
+                block_recompute: bool = False, moved: bool = False, shapes: dict | None = None) -> int:
+    """Bytes of one fused sweep launch on the n^d mesh: 3 cell vectors, plus
+    2 sides x 2 fields x (p+1)^(d-1) trace values per facet read once and
+    written once (boundary facets carry no traces), plus per-cell eigendata
+    d((p+1)^2 + (p+1)) and kappa when the coefficient varies per cell (kappa
+    alone when the kernels rebuild the eigendata in each traversal).  The
+    facets are all interior ones, or with moved those between blocks of cells;
+    shapes (degree -> shape) replaces block_shape where a batch chooses."""
     N = p + 1
     ncell = n ** d
-    words = 3 * ncell * N ** d + interior_facets(d, n) * 2 * 2 * N ** (d - 1) * 2
+    words = 3 * ncell * N ** d + _facets(d, n, p, itemsize, per_cell_kappa, moved, shapes) * 2 * 2 * N ** (d - 1) * 2
     if per_cell_kappa:
         words += ncell * (1 if block_recompute else d * (N * N + N) + 1)
     return words * itemsize
 
 
-def project_bytes(d: int, n: int, p: int, itemsize: int) -> int:
-    """Read u, write both sides' traces of every interior facet."""
+def project_bytes(d: int, n: int, p: int, itemsize: int, per_cell_kappa: bool = False, moved: bool = False) -> int:
+    """Read u, write both sides' traces of every (exchanged) facet."""
     N = p + 1
-    return (n ** d * N ** d + interior_facets(d, n) * 2 * 2 * N ** (d - 1)) * itemsize
+    return (n ** d * N ** d + _facets(d, n, p, itemsize, per_cell_kappa, moved, None) * 2 * 2 * N ** (d - 1)) * itemsize
 
 
-def apply_bytes(d: int, n: int, p: int, itemsize: int, per_cell_kappa: bool = False) -> int:
+def apply_bytes(d: int, n: int, p: int, itemsize: int, per_cell_kappa: bool = False, moved: bool = False) -> int:
     """Read u, read the neighbour traces, write y."""
     N = p + 1
     ncell = n ** d
-    words = 2 * ncell * N ** d + interior_facets(d, n) * 2 * 2 * N ** (d - 1)
+    words = 2 * ncell * N ** d + _facets(d, n, p, itemsize, per_cell_kappa, moved, None) * 2 * 2 * N ** (d - 1)
     if per_cell_kappa:
         words += ncell * (d * (N * N + N) + 1)
     return words * itemsize
@@ -69,11 +117,6 @@ def apply_bytes(d: int, n: int, p: int, itemsize: int, per_cell_kappa: bool = Fa
 # ---------------------------------------------------------------------------
 # Bytes of a whole V-cycle and of one outer iteration, kernel by kernel as
 # the library runs them (the numerator of the time-to-solution roofline).
-
-def _trace_words(d: int, n: int, N: int) -> int:
-    """Trace values of every interior facet, both sides, both fields."""
-    return interior_facets(d, n) * 2 * 2 * N ** (d - 1)
-
 
 def _p_levels(p: int) -> list:
     out, q = [p], p // 2
@@ -120,14 +163,16 @@ def q1_cycle_bytes(d: int, n: int, itemsize: int, nu_pre: int = 2, nu_post: int 
 
 
 def vcycle_bytes(d: int, n: int, p: int, itemsize: int, nu_pre: int = 2, nu_post: int = 2,
-                 coarsest_n: int = 4) -> int:
+                 coarsest_n: int = 4, per_cell_kappa: bool = False, moved: bool = False,
+                 shapes: dict | None = None) -> int:
     """One V-cycle from a zero guess (the preconditioner application): on
     each DG level (p halved while >= 2) the first sweep reads b and writes u
     and traces, the next ones are full sweeps, then residual + restriction
     (u, b, neighbour traces in; coarse right-hand side out), the coarser
     levels, prolongation + projection (u and the coarse vector in; u and
     traces out) and the post-smoothing sweeps; then the Q1 levels.  The
-    coarser levels run in the compute type (FP32 for 16-bit storage)."""
+    coarser levels run in the compute type (FP32 for 16-bit storage).
+    Per-cell eigendata is not counted: per_cell_kappa names the block shape."""
     degs = _p_levels(p)
     total = 0
     ncell = n ** d
@@ -135,7 +180,8 @@ def vcycle_bytes(d: int, n: int, p: int, itemsize: int, nu_pre: int = 2, nu_post
         isz = itemsize if li == 0 else max(itemsize, 4)
         N = q + 1
         nd = ncell * N ** d
-        tw = _trace_words(d, n, N)
+        tw = _facets(d, n, q, isz, per_cell_kappa, moved, shapes) * 2 * 2 * N ** (d - 1)
+        sweep = (3 * nd + 2 * tw) * isz
         if li + 1 < len(degs):
             ndc = ncell * (degs[li + 1] + 1) ** d
             csz = max(itemsize, 4)
@@ -148,16 +194,17 @@ def vcycle_bytes(d: int, n: int, p: int, itemsize: int, nu_pre: int = 2, nu_post
             prol_in = nct * csz
         b = 0
         for k in range(nu_pre):
-            b += (2 * nd + tw) * isz if k == 0 else sweep_bytes(d, n, q, isz)
+            b += (2 * nd + tw) * isz if k == 0 else sweep
         b += (2 * nd + tw) * isz + rest_out
         b += (2 * nd + tw) * isz + prol_in
-        b += nu_post * sweep_bytes(d, n, q, isz)
+        b += nu_post * sweep
         total += b
     return total + q1_cycle_bytes(d, n, max(itemsize, 4), nu_pre, nu_post, coarsest_n)
 
 
 def fcg_iteration_bytes(d: int, n: int, p: int, cycle_itemsize: int, nu_pre: int = 2, nu_post: int = 2,
-                        coarsest_n: int = 4) -> int:
+                        coarsest_n: int = 4, per_cell_kappa: bool = False, moved: bool = False,
+                        shapes: dict | None = None) -> int:
     """One flexible-CG iteration of hpmg_solve: the V-cycle z = M r in the
     cycle's storage type, the dots z.r and z.(r - r_old) (z, r, r_old), the
     projection of p = z + beta p (z, p in; p and its FP64 traces out), q = A p
@@ -165,9 +212,9 @@ def fcg_iteration_bytes(d: int, n: int, p: int, cycle_itemsize: int, nu_pre: int
     r_old and the FP32 copy of r out)."""
     N = p + 1
     nd = n ** d * N ** d
-    tw = _trace_words(d, n, N)
+    tw = _facets(d, n, p, 8, per_cell_kappa, moved, shapes) * 2 * 2 * N ** (d - 1)
     zs = cycle_itemsize
-    b = vcycle_bytes(d, n, p, cycle_itemsize, nu_pre, nu_post, coarsest_n)
+    b = vcycle_bytes(d, n, p, cycle_itemsize, nu_pre, nu_post, coarsest_n, per_cell_kappa, moved, shapes)
     b += nd * (zs + 16)                      # dots
     b += nd * (zs + 16) + tw * 8             # p = z + beta p, traces of p
     b += (2 * nd + tw) * 8                   # q = A p
