@@ -224,7 +224,8 @@ hpmg_status hpmg_sweep(hpmg_handle h, hpmg_dtype dtype, void* u, const void* b, 
  * levels, nu_pre_cg / nu_post_cg point-Jacobi steps on the Q1 levels,
  * p-coarsening, Q1, h-coarsening, dense coarsest solve) for each of the nrhs
  * stacked right-hand sides (1 <= nrhs <= max_rhs): the DG levels run every
- * column in one launch per traversal, the Q1 levels column after column. */
+ * column in one launch per traversal, and so do the Q1 levels (smoothing counts
+ * that no fused kernel takes: a launch per step and column). */
 hpmg_status hpmg_vcycle(hpmg_handle h, hpmg_dtype dtype, void* u, const void* b, int nrhs,
                         hipStream_t stream);
 

@@ -44,8 +44,9 @@ inline unsigned grid_for_n(int n, int cap) { return (unsigned)(n < cap ? (n > 0 
 // One degree per launch: the kernel takes only that degree's registers and
 // LDS (items of other degrees are not expected in its list).  ONE: the grid
 // covers the list, one item per block and no item loop (the loop alone
-// takes the sweeps of degree 4 from 70 to 97 VGPRs in FP64 and from 47 to 92 in
-// FP32, five waves per SIMD instead of eight).
+// takes the FP32 sweeps of degree 4 from 47 to 92 VGPRs, five waves per SIMD
+// instead of eight; those in FP64, from 70 to 97 VGPRs, have four either way:
+// their LDS allows no more).
 template <typename T, int OP, int N, int V, bool ONE>
 __global__ __launch_bounds__((HPMG_DGK::DGShape<3, N>::BLOCK)) void k_dg_batch_n(const DGArgs<T>* __restrict__ args,
                                                                           const WorkItem* __restrict__ items,

@@ -1,10 +1,11 @@
 // Matrix-free SIPG kernels on DG levels (gfx950).
 //
 // One thread per 1D line of a cell ("pencil"): a cell of N^d nodes owns
-// N^(d-1) threads; a block holds CPB whole cells (about 256 threads).  The
-// block stages the cell data of its cells, which are consecutive in memory,
-// through LDS with coalesced loads, applies sum-factorised 1D contractions
-// along x, y, z with the line in registers, and writes back coalesced.
+// N^(d-1) threads; a block holds CPB whole cells (up to 512 threads), a run of
+// cells that follow one another in memory or a brick of them (brick()).  The
+// threads load and store lines of their cells so that a wave's accesses are
+// consecutive, and apply sum-factorised 1D contractions along x, y, z with the
+// line in registers, exchanging lines through LDS.
 //
 // Operator (paper Section 2.3.1 eq. weak_form_IP with theta = -1 and the
 // facet form eq. weak_form_IP_facet_spaces): in reference units the cell

@@ -278,7 +278,8 @@ __device__ __forceinline__ int cell_mask(const DGArgs<T>& a, int c) {
 }
 
 // The cells of one block, by local index cl < CPB: a run of consecutive cells
-// (2D, HPMG_TILE 3; id the block's number) or a brick (3D; id from brick_id), whose cells past the end of the mesh are not valid.
+// (2D, HPMG_TILE 3; id the block's number) or a brick (3D; id from brick_id),
+// whose cells past the end of the mesh are not valid.
 template <int D, int N, bool AD>
 struct Cells {
   using Sh = DGShape<D, N>;

@@ -1083,7 +1083,7 @@ const C* q1_weights(const hpmg_ctx* h, bool restr) {
 // level's vectors (for l = 0 the caller's).  Traversals on the level:
 // [projection], nu_pre sweeps, residual + restriction, prolongation +
 // projection, nu_post sweeps (each one launch over all columns); the Q1
-// levels run column after column.
+// levels as vcycle_cg says.
 template <typename T>
 void vcycle_dg(hpmg_ctx* h, int l, T* u, const T* b, bool uzero, int nrhs, hipStream_t s) {
   // 16-bit storage applies to this level only: the coarser levels run in
