@@ -331,6 +331,8 @@ def run_batched(args):
     t_batch = _median([r["solve"][0] for r in res]) if ok_batch else None
     its_batch = res[-1]["solve"][1]
 
+    cyc_shapes = shapes("vcycle", batch.tuning)
+
     # worst true relative residual of the batched solutions (FP64 apply)
     worst = 0.0
     for s, u, b in zip(solvers, us, bs):
@@ -389,7 +391,6 @@ def run_batched(args):
         else "k_dg_batch<double,0> (one launch per sweep)"
     # time-to-solution roofline: bytes of one FCG iteration of every segment
     # (the captured graph iterates all segments until the last converges)
-    cyc_shapes = shapes("vcycle", batch.tuning)
     iter_bytes = R * sum(traffic.fcg_iteration_bytes(3, n, p, 4, moved=True, shapes=cyc_shapes) for n, p in probs)
     tts = None
     if t_batch:
