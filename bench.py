@@ -896,7 +896,7 @@ def run_adaptive(args):
         "roofline": {"bound": "hbm", "achieved": ach["f64"], "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": ach["f64"] / HBM_PEAK_GBS,
                      "traffic": counter_traffic(tsum, srcs, "traffic_bytes_per_launch_f64"),
-                     "kernel": f"k_sweep<double,3,{p + 1},false,false,false,false,true> + k_remap<double> "
+                     "kernel": f"k_sweep<double,3,{p + 1},false,false,false,false,true,false> + k_remap<double> "
                                "(fused sweep and hanging-facet remap, FP64)",
                      "algorithmic_bytes_per_launch": bysw["f64"], "mean_launch_s": tsw["f64"]},
         "sweep_dofs_per_s": {name: nd / t for name, t in tsw.items()},
