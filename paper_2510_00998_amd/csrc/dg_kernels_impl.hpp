@@ -1291,8 +1291,9 @@ __device__ __forceinline__ void stage_block(const DGArgs<T>& a, const T* tr, con
 // Variable kappa: sweeps .9 to 1.08 in FP64, 1.3 to 1.7 in FP32 at every degree;
 // apply 1.2 and more at half of the degrees.  16-bit storage, whose stored u is
 // coarser than either: 1.00 for sweeps; its residual, which steers the outer
-// iteration, is dual (Q5 96^3, log-normal kappa: 50 against 52 iterations in
-// FP16, 65 against 71 in BF16).  Gauss-Legendre nodes (DGArgs::gl; FP64 and FP32)
+// iteration, is dual (Q5 96^3, log-normal kappa, to 1e-9, with the outer
+// residual in the same form: 40 iterations in FP16, 49 in BF16; nodal 42, and
+// 56 without getting there).  Gauss-Legendre nodes (DGArgs::gl; FP64 and FP32)
 // are dual throughout, by kernels of their own (GL): their ratios are others, up to
 // 1.44 in FP64 and 1.6 in FP32, both at degree 2.  2D: facets take one tangential transform of a
 // single line, so the nodal form's extra products buy nothing.
